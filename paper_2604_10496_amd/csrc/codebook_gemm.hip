@@ -31,6 +31,12 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restri
   }
 }
 
+// Whether a K range of ksteps steps runs the streaming kernel's pipelined unit loop: 8 or 7 steps for every wavefront,
+// or (one table per row) up to 4 with empty ones in between.
+bool pipelined(int ksteps, bool blockwise) {
+  return ksteps == 8 * kWaves || (!blockwise && (ksteps == 7 * kWaves || ksteps <= 4 * kWaves));
+}
+
 }  // namespace
 
 
@@ -39,7 +45,7 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restri
 // into ranges of at most 4096 that different workgroups stream, and their partial sums are added in a
 // fixed order afterwards.  Plain products only (a nonlinear epilogue needs the whole sum).
 // Block-wise tables on the streaming kernel's pipelined loop: tables of 1024 weights (two K steps per wavefront
-// and table), groups of at most 32 rows (the loop's limit: two passes of 16), and K ranges of whole tables that give every wavefront
+// and table), groups of at most 32 rows (the loop's limit), and K ranges of whole tables that give every wavefront
 // exactly 8 steps (4096 weights) or 4 (2048); a nonlinear epilogue needs all of K in one range.
 bool cq_gemm_blockwise_streams(const cq_codebook_weights* W, int M_total, int epilogue, int max_group_rows) {
   if (kWaves != 8 || cq_is_w2(W) || W->group_k != 1024 || W->K % 2048 != 0) return false;
@@ -88,7 +94,7 @@ size_t cq_gemm_partials_bytes(const cq_codebook_weights* W, int M_total, int epi
 }
 
 // The grouping by expert can be folded into a launch when every workgroup of it runs the pipelined unit loop
-// (at most 32 rows per group, a K range of exactly 8 or 7 steps per wavefront) and one lane per assignment
+// (at most 32 rows per group, a K range that it takes) and one lane per assignment
 // suffices: at most 32 tokens (a group has at most one row per token), at most 64 assignments and experts.
 bool cq_gemm_can_fuse_route(const cq_codebook_weights* W, int T, int E, int S, int top_k, int epilogue) {
   if (kWaves != 8) return false;
@@ -100,7 +106,7 @@ bool cq_gemm_can_fuse_route(const cq_codebook_weights* W, int T, int E, int S, i
   if (cq_gemm_uses_large_tiles(W, M_total, epilogue, T)) return false;
   int ksplit, ksteps;
   cq_gemm_split_plan(W, M_total, epilogue, &ksplit, &ksteps, T);
-  return ksplit == 1 && (ksteps == 8 * kWaves || (ksteps == 7 * kWaves && cq_tables_per_row(W) == 1));
+  return ksplit == 1 && pipelined(ksteps, cq_tables_per_row(W) > 1);
 }
 
 cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, int a_kind, const float* row_scale,
@@ -132,24 +138,21 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
     cq_gemm_split_plan(W, M_total, epilogue, &a.ksplit, &a.ksteps, max_group_rows);
     a.partials = (float*)workspace;  // partial sums first, then the large-tile kernel's lists
     a.part_stride = (size_t)M_total * W->N;
-    // (a whole number of workgroups per (group, K range), at most 256 in all: 56 pairs take 4 each, not 5 --
-    // 280 workgroups would run as a full round and a nearly empty one)
-    // The pipelined unit loop takes 16 rows at a time: when groups of 17..32 rows are possible the launch gets a
-    // second set of workgroups for rows 16.. of such groups (they return at once for the other groups).
-    const int row_bound = max_group_rows > 0 && max_group_rows < M_total ? max_group_rows : M_total;
-    a.halves = row_bound > 16 ? 2 : 1;
-    // (when groups above 16 rows are likely -- 8 rows per group on average -- the workgroups are half as long, so
-    // that the second halves, which start when a compute unit comes free, do not add a whole round)
+    // The kernel itself divides these workgroups among the groups that have rows (cq_route::pick_group).  Up to 32
+    // such groups share one round of them evenly enough; with more, the whole number of workgroups per group can
+    // leave a good part of the chip idle (129 groups: one workgroup each on 256 compute units), so the grid has room
+    // for two or four rounds of which the kernel uses what is cheapest.
+    const bool large_too = cq_gemm_uses_large_tiles(W, M_total, epilogue, max_group_rows);
+    const int n_max = W->G < M_total ? W->G : M_total;   // groups that can have rows
     // Where the pipelined loop is not available (other K), a group of 17..32 rows runs the plain loop on one
     // set of workgroups, several times slower per unit than the small groups around it: many short workgroups
     // then, so that the compute units the small groups leave early take the rest of the big ones.
-    const bool piped = a.ksteps == 8 * kWaves || (a.ksteps == 7 * kWaves && cq_tables_per_row(W) == 1);
-    const long target = a.halves == 1 ? 256 : !piped ? 1024 : (long)M_total >= 8L * W->G ? 512 : 256;
-    const long pairs = (long)W->G * a.ksplit;
-    const long per_pair = pairs < target ? target / pairs : 1;
-    long upw = (W->N / 64 + per_pair - 1) / per_pair;
-    if (upw < 1) upw = 1;
-    a.upw = (int)upw;
+    const int row_bound = max_group_rows > 0 && max_group_rows < M_total ? max_group_rows : M_total;
+    const int target = row_bound > 16 && !pipelined(a.ksteps, cq_tables_per_row(W) > 1) ? 1024 : 256;
+    a.G = W->G;
+    a.slots = target / a.ksplit > 1 ? target / a.ksplit : 1;
+    a.rounds = target != 256 || (n_max <= 32 && !large_too) ? 1 : n_max <= 256 ? 2 : 4;
+    a.grid = a.slots * a.rounds > n_max ? a.slots * a.rounds : n_max;
   }
   // Groups of up to 32 rows go to the streaming kernel above; larger ones to the large-tile kernel (when
   // the row count allows its 256-row tiles), which runs off a device-built tile list.  Block-wise tables
@@ -162,17 +165,10 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
   const int small_max = blockwise ? 0 : kSmallMaxRows;
   const int qt = bw_streams ? W->group_k / 512 : 0;
   a.max_rows = large ? small_max : 0x7fffffff;
-  a.small_hdr = nullptr;
-  a.small_ids = nullptr;
   void* large_ws = (char*)workspace + cq_gemm_partials_bytes(W, M_total, epilogue, max_group_rows);
   cq_status st;
   if (large) {
-    // the host does not know which groups are small: a device-built list spreads exactly those over
-    // the grid (a grid over all groups would leave most workgroups without work)
-    // (the listed workgroups exist once per K range: a K-split launch lists fewer per range)
-    const int listed = kListedWorkgroups / a.ksplit;
-    st = cq_gemm_build_lists(W, group_offsets, M_total, small_max, W->G > listed ? W->G : listed, large_ws, &a.small_hdr,
-                             &a.small_ids, s, cq_gemm_large_tail_split(W, epilogue, out_kind));
+    st = cq_gemm_build_lists(W, group_offsets, M_total, small_max, large_ws, s, cq_gemm_large_tail_split(W, epilogue, out_kind));
     if (st != CQ_OK) return st;
   }
   if (blockwise) {
@@ -194,10 +190,10 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
     return cq_check_launch();
   }
   switch (a_kind) {
-    case CQ_A_INT8_CODES: st = cq_gemm_small_dispatch_int8(a, W->G, qt, epilogue, out_kind, s); break;
-    case CQ_A_F16: st = cq_gemm_small_dispatch_f16(a, W->G, qt, epilogue, out_kind, s); break;
-    case CQ_A_BF16: st = cq_gemm_small_dispatch_bf16(a, W->G, qt, epilogue, out_kind, s); break;
-    default: st = cq_gemm_small_dispatch_f32(a, W->G, qt, epilogue, out_kind, s); break;
+    case CQ_A_INT8_CODES: st = cq_gemm_small_dispatch_int8(a, qt, epilogue, out_kind, s); break;
+    case CQ_A_F16: st = cq_gemm_small_dispatch_f16(a, qt, epilogue, out_kind, s); break;
+    case CQ_A_BF16: st = cq_gemm_small_dispatch_bf16(a, qt, epilogue, out_kind, s); break;
+    default: st = cq_gemm_small_dispatch_f32(a, qt, epilogue, out_kind, s); break;
   }
   if (st != CQ_OK) return st;
   if (a.ksplit > 1) {

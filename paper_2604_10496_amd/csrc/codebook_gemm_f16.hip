@@ -1,6 +1,6 @@
 // The streaming kernel's instantiations for one operand kind (CQ_A_F16); see codebook_gemm_small.h.
 #include "codebook_gemm_small.h"
 
-cq_status cq_gemm_small_dispatch_f16(const GemmArgs& a, int G, int qt, int epilogue, int out_kind, hipStream_t s) {
-  return dispatch_epi<CQ_A_F16>(a, G, qt, epilogue, out_kind, s);
+cq_status cq_gemm_small_dispatch_f16(const GemmArgs& a, int qt, int epilogue, int out_kind, hipStream_t s) {
+  return dispatch_epi<CQ_A_F16>(a, qt, epilogue, out_kind, s);
 }

@@ -551,25 +551,22 @@ __global__ __launch_bounds__(256) void convert_rows_kernel(const void* __restric
 }
 
 // One workgroup: cut every group with more than `small_max` rows into token tiles of 256 (while more
-// than 128 rows remain), then one of 128 or (up to 64 rows left) 64, in group order (deterministic), and list the non-empty groups with up
-// to `small_max` rows for the streaming kernel, together with a split of their 64-row units over
-// `small_wgs` workgroups.  counts: [0] 256-wide tiles, [1] 128-wide tiles, [2] small groups,
-// [3] units per workgroup, [4] workgroups per small group, [5] 64-wide tiles, [6] K parts of the narrow tiles,
-// [7] K parts of the 256-wide tiles.
+// than 128 rows remain), then one of 128 or (up to 64 rows left) 64, in group order (deterministic); the streaming
+// kernel takes the other groups.  counts: [0] 256-wide tiles, [1] 128-wide tiles, [5] 64-wide tiles, [6] K parts of
+// the narrow tiles, [7] K parts of the 256-wide tiles.
 __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __restrict__ offsets, int G, int small_max,
-                                                           int n_units, int small_wgs,
+                                                           int n_units,
                                                            int32_t* __restrict__ tiles256, int32_t* __restrict__ tiles128,
                                                            int32_t* __restrict__ tiles64,
-                                                           int32_t* __restrict__ small_groups,
                                                            int32_t* __restrict__ counts, int split_max, int split_all) {
-  __shared__ int n256[1024], n128[1024], n64[1024], nsm[1024];
-  __shared__ int base256, base128, base64, basesm;
+  __shared__ int n256[1024], n128[1024], n64[1024];
+  __shared__ int base256, base128, base64;
   const int tid = threadIdx.x;
-  if (tid == 0) { base256 = 0; base128 = 0; base64 = 0; basesm = 0; }
+  if (tid == 0) { base256 = 0; base128 = 0; base64 = 0; }
   __syncthreads();
   for (int g0 = 0; g0 < G; g0 += 1024) {
     const int g = g0 + tid;
-    int a = 0, b = 0, b64 = 0, c = 0, m0 = 0, me = 0;
+    int a = 0, b = 0, b64 = 0, m0 = 0, me = 0;
     if (g < G) {
       m0 = offsets[g];
       me = offsets[g + 1] - m0;
@@ -577,24 +574,21 @@ __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __rest
         a = me / 256;
         const int rem = me - a * 256;
         if (rem > 128) ++a; else if (rem > 64) b = 1; else if (rem > 0) b64 = 1;
-      } else if (me > 0) {
-        c = 1;
       }
     }
     n256[tid] = a;
     n128[tid] = b;
     n64[tid] = b64;
-    nsm[tid] = c;
     __syncthreads();
     if (tid == 0) {  // exclusive prefix in group order
-      int s256 = base256, s128 = base128, s64 = base64, ssm = basesm;
+      int s256 = base256, s128 = base128, s64 = base64;
       const int n = min(1024, G - g0);
       for (int i = 0; i < n; ++i) {
-        const int x = n256[i], y = n128[i], y2 = n64[i], z = nsm[i];
-        n256[i] = s256; n128[i] = s128; n64[i] = s64; nsm[i] = ssm;
-        s256 += x; s128 += y; s64 += y2; ssm += z;
+        const int x = n256[i], y = n128[i], y2 = n64[i];
+        n256[i] = s256; n128[i] = s128; n64[i] = s64;
+        s256 += x; s128 += y; s64 += y2;
       }
-      base256 = s256; base128 = s128; base64 = s64; basesm = ssm;
+      base256 = s256; base128 = s128; base64 = s64;
     }
     __syncthreads();
     if (g < G && me > small_max) {
@@ -613,13 +607,11 @@ __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __rest
         t[3] = 0;
       }
     }
-    if (c) small_groups[nsm[tid]] = g;
     __syncthreads();
   }
   if (tid == 0) {
     counts[0] = base256;
     counts[1] = base128;
-    counts[2] = basesm;
     counts[5] = base64;
     // [6] K parts of the narrow tiles (split_max > 1: a plain fp32 product with a long K).  The narrow tiles
     // come last; when there are fewer of them than compute units, the tail of the launch runs on a part of the
@@ -636,15 +628,6 @@ __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __rest
       while (split_all && parts < split_max && base256 > 0 && all * parts * 2 <= 256) parts *= 2;
       counts[7] = parts;
     }
-    // fewest units per workgroup such that all small groups fit into small_wgs workgroups
-    int upw = 1, chunks = n_units;
-    if (basesm > 0) {
-      const int per_group = max(1, small_wgs / basesm);       // workgroups a group may take
-      upw = (n_units + per_group - 1) / per_group;
-      chunks = (n_units + upw - 1) / upw;
-    }
-    counts[3] = upw;
-    counts[4] = chunks;
   }
 }
 
@@ -727,7 +710,7 @@ cq_status dispatch_large(const LargeArgs& a, int epilogue, int out_kind, const i
 size_t tile_list_bytes(int G, int M_total) {
   int c256, c128;
   cq_large_tile_caps(G, M_total, &c256, &c128);
-  return cq_align_up(256 + ((size_t)(c256 + 2 * c128) * 4 + (size_t)G) * sizeof(int32_t), 256);
+  return cq_align_up(256 + ((size_t)(c256 + 2 * c128) * 4) * sizeof(int32_t), 256);
 }
 
 }  // namespace
@@ -779,12 +762,9 @@ bool cq_gemm_large_supported(const cq_codebook_weights* W) {
   return nblk == 1 || (W->group_k % (8 * kStepK) == 0 && (long)W->N * nblk * (CQ_N_CENTROIDS * 2) < (1L << 31));
 }
 
-// Builds the work lists of both kernels in `workspace` (first step of a mixed launch).  Returns the list
-// of small groups for the streaming kernel: header {count, units per workgroup, workgroups per group,
-// unused} followed by the group ids... as two pointers: *small_hdr -> counts + 2, *small_ids -> ids.
+// Builds the work lists in `workspace` (first step of a launch that uses the large-tile kernel).
 cq_status cq_gemm_build_lists(const cq_codebook_weights* W, const int32_t* group_offsets, int M_total, int small_max,
-                              int small_wgs, void* workspace, const int32_t** small_hdr, const int32_t** small_ids,
-                              hipStream_t s, bool tail_split) {
+                              void* workspace, hipStream_t s, bool tail_split) {
   int cap256, cap128;
   cq_large_tile_caps(W->G, M_total, &cap256, &cap128);
   bool split_all = false;
@@ -793,11 +773,8 @@ cq_status cq_gemm_build_lists(const cq_codebook_weights* W, const int32_t* group
   int32_t* t256 = counts + 64;
   int32_t* t128 = t256 + (size_t)cap256 * 4;
   int32_t* t64 = t128 + (size_t)cap128 * 4;
-  int32_t* small = t64 + (size_t)cap128 * 4;
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(1024), 0, s, group_offsets, W->G, small_max, W->N / 64, small_wgs,
-                     t256, t128, t64, small, counts, tail_split ? kTailSplitMax : 1, split_all ? 1 : 0);
-  *small_hdr = counts + 2;
-  *small_ids = small;
+  hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(1024), 0, s, group_offsets, W->G, small_max, W->N / 64,
+                     t256, t128, t64, counts, tail_split ? kTailSplitMax : 1, split_all ? 1 : 0);
   return cq_check_launch();
 }
 

@@ -23,11 +23,16 @@
 //     v_mfma_f32_32x32x16 with the decoded weights as A.  Integer codes and bf16 centroids are exact bf16
 //     operands; f16 activations (the down projection) use f16 MFMA with centroids converted to f16.  Both
 //     operands number K identically, so the sum over K is the plain dot product.
-//   * Two unit loops.  Pipelined (groups of up to 16 tokens whose wavefronts have exactly 8 or 7 K steps
-//     per unit -- run_units_pipe): activations of a wavefront's own K steps in registers, two tables and
-//     the K partials in LDS, the next unit's table written and the previous unit finished inside the K
-//     loop, one barrier per unit.  Plain (everything else): activations staged in a 64 KiB LDS slab one K
+//   * Two unit loops.  Pipelined (groups of up to 32 tokens whose wavefronts have exactly 8 or 7 K steps
+//     per unit, or up to 4 -- run_units_pipe): activations of a wavefront's own K steps in registers, two tables
+//     and the K partials in LDS, the next unit's table written and the previous unit finished inside the K
+//     loop, one barrier per unit.  (K = 2048 and 1408 at 41 active groups, 16 tokens: 39 and 27 us in the plain loop,
+//     35 and 24 us in this one.)  Plain (everything else): activations staged in a 64 KiB LDS slab one K
 //     slab at a time, already in fragment order, one table rebuilt between units.
+//   * Workgroups.  About one per compute unit in all, divided in the kernel among the groups that have rows
+//     (cq_route::pick_group): 2 active experts of 8 (one token of the Mixtral shape) gate/up 66 -> 27 us and down
+//     36 -> 16 us against a grid over all groups; 41 of 66 active groups (DeepSeek-V2-Lite's shape, 16 tokens)
+//     54 -> 39 and 36 -> 27 us.
 //   * Epilogue.  The wavefronts' partial accumulators are summed through LDS in a fixed order
 //     (deterministic), scaled per token, optionally passed through SiLU(gate)*up (gate/up rows interleaved
 //     so both sit in one lane), and stored.
@@ -53,27 +58,25 @@ struct cq_small_gemm_args {
   const int32_t* group_offsets;
   void* out;
   int out_ld;
-  int upw;                  // 64-row units per workgroup (consecutive, same expert)
+  int G;                    // groups
+  int slots;                // workgroups per K range that the chip runs at a time
+  int rounds;               // rounds of them in the grid (1, 2 or 4)
+  int grid;                 // gridDim.x: slots * rounds, and no less than the number of groups that can have rows
   int max_rows;             // groups with more rows are left to the large-tile kernel
   int ksteps;               // K steps (of 64) per K split; blockIdx.z selects the split
   int ksplit;               // number of K splits; > 1: scaled fp32 partial sums go to `partials`
-  int halves;               // 1, or 2: gridDim.z = ksplit * 2 (see the kernel)
   float* partials;          // [ksplit][M_total][N]
   size_t part_stride;       // M_total * N
-  // device-built work list (launches that also use the large-tile kernel), else NULL: blockIdx.y is
-  // the group and blockIdx.x * upw the first unit
-  const int32_t* small_hdr; // {number of listed groups, units per workgroup, workgroups per group}
-  const int32_t* small_ids; // the listed groups
   // grouping by expert folded into the launch (pipelined unit loop only), else route.ids == NULL
   cq_route_fuse route;
 };
 using GemmArgs = cq_small_gemm_args;
 
 // one per operand kind, each in its own translation unit; qt: 0, or block-wise tables of 512 * qt weights
-cq_status cq_gemm_small_dispatch_int8(const GemmArgs& a, int G, int qt, int epilogue, int out_kind, hipStream_t s);
-cq_status cq_gemm_small_dispatch_f16(const GemmArgs& a, int G, int qt, int epilogue, int out_kind, hipStream_t s);
-cq_status cq_gemm_small_dispatch_bf16(const GemmArgs& a, int G, int qt, int epilogue, int out_kind, hipStream_t s);
-cq_status cq_gemm_small_dispatch_f32(const GemmArgs& a, int G, int qt, int epilogue, int out_kind, hipStream_t s);
+cq_status cq_gemm_small_dispatch_int8(const GemmArgs& a, int qt, int epilogue, int out_kind, hipStream_t s);
+cq_status cq_gemm_small_dispatch_f16(const GemmArgs& a, int qt, int epilogue, int out_kind, hipStream_t s);
+cq_status cq_gemm_small_dispatch_bf16(const GemmArgs& a, int qt, int epilogue, int out_kind, hipStream_t s);
+cq_status cq_gemm_small_dispatch_f32(const GemmArgs& a, int qt, int epilogue, int out_kind, hipStream_t s);
 
 namespace {
 
@@ -83,10 +86,6 @@ namespace {
 constexpr int kSmallMaxRows = CQ_SMALL_MAX_ROWS;  // groups with more rows go to the large-tile kernel
 constexpr int kTableBytes = 65536;   // 256 entries x 64 row slots x 4 bytes
 constexpr int kSlabBytes = 65536;    // activation slab
-#ifndef CQ_LISTED_WGS
-#define CQ_LISTED_WGS 512
-#endif
-constexpr int kListedWorkgroups = CQ_LISTED_WGS;  // grid of a launch that runs off the device-built group list
 constexpr int kRedBytes = 32768;     // K partials of up to 16 token columns: 8 wavefronts x 16 registers x 64 lanes
 #ifndef CQ_GEMM_WAVES
 #define CQ_GEMM_WAVES 8
@@ -96,17 +95,9 @@ constexpr int kWaves = CQ_GEMM_WAVES;  // wavefronts per workgroup: they split K
 // 8 (the per-unit phases in which nothing is consumed then find more data already on its way)
 // Ring depth of the pipelined unit loop in HALF steps (one 16-byte load per lane: 32 rows x 64 k) for a
 // wavefront with Q steps per unit.  It must divide 2Q so that a slot always meets the same half step of
-// every unit: 8 for even Q (4 steps = 64 KiB in flight per compute unit; 16 was measured 5 % slower), Q for
-// odd Q.
-#ifndef CQ_PIPE_HD_EVEN
-#define CQ_PIPE_HD_EVEN 8
-#endif
-#ifndef CQ_PIPE_HD_ODD
-#define CQ_PIPE_HD_ODD 1
-#endif
-constexpr int pipe_ring_depth(int Q) {
-  return (2 * Q) % CQ_PIPE_HD_EVEN == 0 ? CQ_PIPE_HD_EVEN : (Q % 2 ? CQ_PIPE_HD_ODD * Q : 2);
-}
+// every unit: 8 where that divides 2Q (4 steps = 64 KiB in flight per compute unit; 16 was measured 5 % slower at
+// Q = 8), Q for 7 steps (14 was measured 4 % slower), else all half steps of a unit.
+constexpr int pipe_ring_depth(int Q) { return (2 * Q) % 8 == 0 ? 8 : Q == 7 ? 7 : 2 * Q; }
 constexpr int kSlabCheck = 16 / kWaves;  // smallest number of wavefront steps in a slab (Mpad = 32)
 
 
@@ -123,8 +114,9 @@ __device__ __forceinline__ cq_v16f mfma32(const cq_v4u a, const uint4 b, cq_v16f
 }
 
 
-// QS > 0: a workgroup whose group has at most 32 rows and whose wavefronts have exactly QS K steps per unit
-// runs the pipelined unit loop (run_units_pipe below); 0: that path is left out of the instantiation.
+// QS > 0: a workgroup whose group has at most 32 rows and whose wavefronts have QS K steps per unit (8 and 7: each of
+// them exactly; fewer: at most) runs the pipelined unit loop (run_units_pipe below); 0: that path is left out of the
+// instantiation.
 // QT > 0: block-wise centroid tables, one per 512 * QT weights of a row (QT K steps per wavefront and table; QT
 // divides QS); the instantiation then holds nothing but the pipelined loop.  0: one table per row.
 template <int AK, int EPI, int OUTK, int kRing, int QS, int QT = 0>
@@ -143,39 +135,26 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: what depends on it stays scalar
   const int N = p.N, K = p.K;
   const int nUnits = N >> 6;
-  int grp, u0, upw;
-  if (p.small_hdr) {
-    const int chunks = p.small_hdr[2];
-    if ((int)blockIdx.x >= p.small_hdr[0] * chunks) return;
-    const int gi = blockIdx.x / chunks;
-    grp = p.small_ids[gi];
-    upw = p.small_hdr[1];
-    u0 = (blockIdx.x - gi * chunks) * upw;
-  } else {
-    grp = blockIdx.y;
-    upw = p.upw;
-    u0 = blockIdx.x * upw;
-  }
-  // Rows of this group: from the grouped layout, or -- a5 folded into this launch -- from the selected expert
-  // ids themselves (cq_route::group_rows_from_ids).
-  // blockIdx.z = K range + ksplit * half: half 1 exists in launches in which groups of 17..32 rows are possible and
-  // takes rows 16.. of such a group in the pipelined unit loop
-  const int kz = p.halves > 1 ? (int)blockIdx.z % p.ksplit : (int)blockIdx.z;
-  const int half = p.halves > 1 ? (int)blockIdx.z / p.ksplit : 0;
-  int m0, Me, row_token = 0;
+  // This workgroup's group and its share of the group's units (cq_route::pick_group: only groups with rows get
+  // workgroups).  Rows of the group: from the grouped layout, or -- a5 folded into this launch -- from the selected
+  // expert ids themselves (cq_route::group_rows_from_ids).
+  const int kz = blockIdx.z;   // K range
+  cq_route::group_share share;
+  int row_token = 0;
   bool fused = false;
   if constexpr (QS > 0) fused = p.route.ids != nullptr;
   if (fused) {
-    cq_route::group_rows_from_ids(p.route, grp, lane,
-                                  blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && wave == 0, m0, Me, row_token);
+    if (!cq_route::pick_group_from_ids(p.route, nUnits, p.slots, p.rounds, blockIdx.x, lane, share)) return;
+    cq_route::group_rows_from_ids(p.route, share.grp, lane, blockIdx.x == 0 && blockIdx.z == 0 && wave == 0, share.m0,
+                                  share.Me, row_token);
   } else {
-    m0 = p.group_offsets[grp];
-    Me = p.group_offsets[grp + 1] - m0;
+    if (!cq_route::pick_group(p.group_offsets, p.G, p.max_rows, nUnits, p.slots, p.rounds, blockIdx.x, lane, share))
+      return;
   }
-  if (Me <= 0 || Me > p.max_rows) return;
-  if (half > 0 && (Me <= 16 || Me > 32)) return;   // (second halves exist for groups of 17..32 rows only)
-  const int u1 = min(nUnits, u0 + upw);
-  if (u0 >= u1) return;
+  const int grp = share.grp, m0 = share.m0, Me = share.Me;
+  // units of this workgroup: a contiguous run in the plain loop, every chunks-th unit in the pipelined one
+  const int u0 = (int)((long)nUnits * share.chunk / share.chunks);
+  const int u1 = (int)((long)nUnits * (share.chunk + 1) / share.chunks);
   const size_t rowbytes = (size_t)K >> 1;
   const uint8_t* gbase = p.idx + (size_t)grp * N * rowbytes;
   const int r32 = lane & 31, g2 = lane >> 5;
@@ -201,10 +180,33 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
   const uint32_t lanebase0 = (uint32_t)(r32 * 4);
   const uint32_t lanebase1 = (uint32_t)((32 + r32) * 4);
   const int n_tb = (Me + 31) >> 5;
-  if (half > 0 && !(QS > 0 && nS == QS * NW)) return;   // (no pipelined loop here: the first half's workgroup takes all rows)
 
-  // ---- up to 16 tokens, K range of exactly QS steps per wavefront: the unit loop as a pipeline ----
-  // (described for up to 8 tokens; the form for 9..16 differs where WIDE says so)
+  // four scaled sums of token row m for the weight rows row .. row + 3, through the epilogue
+  auto store_quad = [&](const int m, const int row, const float (&x)[4]) {
+    if (p.ksplit > 1) {  // partial sum of this K range (the launcher allows this for CQ_EPI_NONE only)
+      float* dst = p.partials + (size_t)kz * p.part_stride + (size_t)m * N + row;
+      *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
+    } else if constexpr (EPI == CQ_EPI_SWIGLU) {
+      const float h0 = x[0] / (1.f + __expf(-x[0])) * x[1];
+      const float h1 = x[2] / (1.f + __expf(-x[2])) * x[3];
+      const size_t o = (size_t)m * p.out_ld + (row >> 1);
+      if constexpr (OUTK == CQ_OUT_F16)
+        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(p.out) + o) =
+            f32_to_f16_bits_sat(h0) | (f32_to_f16_bits_sat(h1) << 16);
+      else
+        *reinterpret_cast<float2*>(reinterpret_cast<float*>(p.out) + o) = make_float2(h0, h1);
+    } else {
+      const size_t o = (size_t)m * p.out_ld + row;
+      if constexpr (OUTK == CQ_OUT_F16)
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p.out) + o) =
+            make_uint2(f32_to_f16_bits_sat(x[0]) | (f32_to_f16_bits_sat(x[1]) << 16),
+                       f32_to_f16_bits_sat(x[2]) | (f32_to_f16_bits_sat(x[3]) << 16));
+      else
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.out) + o) = make_float4(x[0], x[1], x[2], x[3]);
+    }
+  };
+
+  // ---- up to 32 tokens, K range of QS steps per wavefront: the unit loop as a pipeline ----
   // With few tokens the activations of a wavefront's own K steps fit in registers (its K steps are the same
   // in every unit), so no slab is needed and LDS holds TWO pair tables and two buffers of K partials.  While
   // unit u is looked up in one table, the table of unit u+1 is written into the other, a few entries per K
@@ -214,13 +216,20 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
   // before the barrier that ends unit u-1.
   // Ring slot hs % HD serves half step hs = 2q + row block (one 16-byte load per lane) and is refilled with
   // half step hs + HD, of this unit or of the next one, as soon as step q's lookups are issued.
-  // (a group of 17..32 rows is shared by two workgroups per run of units, 16 rows and the rest -- `half` above: it
-  // streams its indices twice, which is still faster than the plain loop below, whose 32-token slab holds a quarter
-  // of K and is restaged four times per unit)
-  const int pass_row0 = 16 * half;
-  const int pass_rows = min(16, Me - pass_row0);   // this workgroup's rows: m0 + pass_row0 .. + pass_rows - 1
-  auto run_units_pipe = [&](auto wide_tag) {
-    constexpr bool WIDE = decltype(wide_tag)::value;   // 9..16 tokens: see below
+  // Three forms by the group's rows.  FORM 0, up to 8: described so far.  FORM 1, 9..16: every column of the 16x16x32
+  // shape is real, so there is one B register set per K half, and the 32 KiB of partials are one buffer (a second
+  // barrier per unit).  FORM 2, 17..32: the 32x32x16 shape, whose A operand is the looked-up row as it is loaded (no
+  // lane swaps) and whose B operand takes four register sets per step (128 registers at 8 steps); the 64 KiB of
+  // partials go over the table that the unit has just been looked up in, which is free until
+  // half into the next unit: three barriers per unit.  Every form streams the indices once and looks every weight up once.
+  // (Two workgroups of 16 rows each, which was the form for 17..32 rows before, streamed the indices twice: gate/up of
+  // the Mixtral shape at 77 tokens 160 us, with FORM 2 102 us.)
+  // Where the K range is not a whole number of rounds of the wavefronts (PAD; K = 1408: 22 steps), a step that does
+  // not exist loads the wavefront's first one again (the number of loads in flight stays the same) and is left out of
+  // the sum.
+  auto run_units_pipe = [&](auto form_tag) {
+    constexpr int FORM = decltype(form_tag)::value;
+    constexpr bool WIDE = FORM == 1, QUAD = FORM == 2;
     constexpr int Q = QS > 0 ? QS : 1;
     constexpr int HD = pipe_ring_depth(Q);
     // A unit's K loop is a run of NSUB sub-units of QL steps, one per centroid table of the K range (one
@@ -231,9 +240,13 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
     static_assert(Q % QL == 0, "whole tables per K range");
     constexpr int TB0 = QL / 2;
     const int i16 = lane & 15, g4 = lane >> 4;
-    const int tcol = WIDE ? i16 : (i16 & 7);   // token column whose activations this lane holds
-    const bool tok = tcol < pass_rows;      // ... a real token (of this pass's block of up to 16 rows)
+    const int tcol = QUAD ? r32 : WIDE ? i16 : (i16 & 7);   // token column whose activations this lane holds
+    const bool tok = tcol < Me;             // ... a real token
     const bool grouped = p.prepacked != 0;
+    constexpr bool PAD = QS < 7 && QT == 0;            // steps past the end of the K range are possible
+    auto real = [&](int q) { return !PAD || wave + NW * q < nS; };
+    // byte offset of this wavefront's step q in the K range (uniform)
+    auto step_off = [&](int q) { return (size_t)(real(q) ? wave + NW * q : real(0) ? wave : 0) * sstride; };
     constexpr uint32_t kRed = 2 * kTableBytes;   // partial buffers: [2][wave][16 registers][32 columns] floats
     const uint32_t slot = WIDE ? (uint32_t)lane : (uint32_t)(g4 * 8 + (i16 & 7));
     constexpr uint32_t kRegStride = WIDE ? 256u : 128u;    // bytes between two accumulator registers' partials
@@ -247,8 +260,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
     // units of this workgroup: its index among the group's workgroups + i * (workgroups of the group), so
     // that the workgroups of a group read one contiguous window of the index stream at any time (measured
     // 1-2 % faster than a contiguous run of units per workgroup)
-    const int ustep = (nUnits + upw - 1) / upw;
-    const int ufirst = u0 / upw;
+    const int ustep = share.chunks;
+    const int ufirst = share.chunk;
     const int ucnt = (nUnits - ufirst + ustep - 1) / ustep;
 
     // centroid rows of a unit (raw bf16 pairs; chp: the two entries this wavefront uses as high halves)
@@ -289,14 +302,14 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
       const uint8_t* wb = kbase + (size_t)ufirst * ubytes;
 #pragma unroll
       for (int j = 0; j < HD; ++j)
-        ring[j] = load_stream(wb + (size_t)(wave + NW * (j >> 1)) * sstride + ((j & 1) ? rb1 : 0) + loff);
+        ring[j] = load_stream(wb + step_off(j >> 1) + ((j & 1) ? rb1 : 0) + loff);
     }
     __builtin_amdgcn_sched_barrier(0);
     float sc16 = 1.f;
     size_t arow = 0;
-    const int col_token = __shfl(row_token, pass_row0 + tcol);   // (folded grouping: the token of this lane's column)
+    const int col_token = __shfl(row_token, tcol);   // (folded grouping: the token of this lane's column)
     if (tok) {
-      const int m = m0 + pass_row0 + tcol;
+      const int m = m0 + tcol;
       const size_t src = fused ? (size_t)col_token : p.row_gather ? (size_t)p.row_gather[m] : (size_t)m;
       arow = src * K;
       if (p.row_scale) sc16 = p.row_scale[src];
@@ -305,33 +318,57 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
     // fragment of their token, lanes of columns 8..15 the second half's fragment of token column - 8 (the
     // matrix cores' output columns 8..15 are never stored, so what their B columns hold does not matter);
     // a rotation by 8 inside each row of 16 lanes brings the second half into place.
-    // With 9..16 tokens every column is real: one register set per K half, no rotation.
-    constexpr int NB = WIDE ? 2 : 1;
+    // With 9..16 tokens every column is real: one register set per K half, no rotation; with 17..32 one per 16 k.
+    constexpr int NB = QUAD ? 4 : WIDE ? 2 : 1;
+    // steps whose rows are requested together: all, or (FORM 2, 32-bit rows) what the registers hold
+    constexpr int QB = AK == CQ_A_F32 ? (QUAD ? 1 : WIDE ? (Q + 1) / 2 : Q) : QUAD ? (Q + 1) / 2 : Q;
     cq_v4u breg[Q][NB];
-    {
-      ActRaw raw[Q][NB];
 #pragma unroll
-      for (int q = 0; q < Q; ++q)
+    for (int q0 = 0; q0 < Q; q0 += QB) {
+      ActRaw raw[QB][NB];
+#pragma unroll
+      for (int q = q0; q < q0 + QB && q < Q; ++q)
 #pragma unroll
         for (int c = 0; c < NB; ++c) {
-          const int chunk = (wave + NW * q) * 8 + (g4 & 1) + 4 * (g4 >> 1) + 2 * (WIDE ? c : (i16 >> 3));
-          raw[q][c] = act_load8<AK>(p.A, arow + (size_t)sb * 64 + (size_t)chunk * 8);
+          const int sub = QUAD ? 4 * g2 + c : (g4 & 1) + 4 * (g4 >> 1) + 2 * (WIDE ? c : (i16 >> 3));
+          const int chunk = (real(q) ? wave + NW * q : 0) * 8 + sub;
+          raw[q - q0][c] = act_load8<AK>(p.A, arow + (size_t)sb * 64 + (size_t)chunk * 8);
         }
 #pragma unroll
-      for (int q = 0; q < Q; ++q)
+      for (int q = q0; q < q0 + QB && q < Q; ++q)
 #pragma unroll
         for (int c = 0; c < NB; ++c) {
-          const uint4 v = tok ? act_pack8<AK>(raw[q][c], grouped) : make_uint4(0u, 0u, 0u, 0u);
+          const uint4 v = tok && real(q) ? act_pack8<AK>(raw[q - q0][c], grouped) : make_uint4(0u, 0u, 0u, 0u);
           breg[q][c] = cq_v4u{v.x, v.y, v.z, v.w};
         }
+      if constexpr (QB < Q) __builtin_amdgcn_sched_barrier(0);
     }
     cent_f16();
     table_part((uint32_t)(wave * 8192 + lane * 4), 0, 32);
     __syncthreads();
 
     // finish of a unit: this wavefront adds up accumulator registers 2*wave and 2*wave+1 (a gate/up pair of
-    // rows) of all wavefronts' partials in buffer pb, in wavefront order
+    // rows) of all wavefronts' partials in buffer pb, in wavefront order (FORM 2: registers 4*wave .. 4*wave+3, two
+    // pairs of rows, and pb is the table that holds the partials)
     auto finish = [&](const int uu, const uint32_t pb) {
+      if constexpr (QUAD) {
+        const uint32_t rb0 = (pb << 16) + (uint32_t)(4 * wave) * 256u + (uint32_t)lane * 4u;
+        float x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float sum = __uint_as_float(lds_read_u32(rb0 + (uint32_t)i * 256u));
+#pragma unroll
+          for (int w = 1; w < NW; ++w) sum += __uint_as_float(lds_read_u32(rb0 + (uint32_t)(w * 32 + i) * 256u));
+          x[i] = sc16 * sum;
+        }
+        if (tok) {
+          // MFMA 32x32 output: register v of a lane holds row 8*(v/4) + 4*(lane/32) + v%4, column lane%32
+          const int r = 4 * wave;
+          const int row = uu * 64 + (r >> 4) * 32 + ((r >> 2) & 3) * 8 + g2 * 4;
+          store_quad(m0 + r32, row, x);
+        }
+        return;
+      }
       if (pcol) {
         const uint32_t rb0 = kRed + pb * 16384u + (uint32_t)(2 * wave) * kRegStride + slot * 4u;
         float val[2];
@@ -343,8 +380,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
             sum += __uint_as_float(lds_read_u32(rb0 + (uint32_t)w * kWaveStride + (uint32_t)i * kRegStride));
           val[i] = sum;
         }
-        if (i16 < pass_rows) {
-          const int m = m0 + pass_row0 + i16;
+        if (i16 < Me) {
+          const int m = m0 + i16;
           const int r = 2 * wave;
           const int row = uu * 64 + (r >> 3) * 32 + ((r >> 2) & 1) * 16 + g4 * 4 + (r & 3);
           const float x0 = sc16 * val[0], x1 = sc16 * val[1];
@@ -390,6 +427,9 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
       for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
         for (int h = 0; h < 2; ++h) acc[rb][h] = cq_v4f{0.f, 0.f, 0.f, 0.f};
+      cq_v16f acc32[2];   // (FORM 2)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) { acc32[0][i] = 0.f; acc32[1][i] = 0.f; }
 
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
@@ -411,40 +451,57 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
         // step: left alone, the older one always wins and the younger one finishes each unit late.
         if ((q ^ (wave >> 2)) & 1) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
+        if (!real(q)) {   // (no such step: nothing is added)
+        } else if constexpr (QUAD) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          cq_v4u bv = breg[q][WIDE ? c : 0];
-          if (!WIDE && c == 1) {
+          for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)   // row_ror:8 -- lane l of a row of 16 takes lane (l + 8) % 16
-              bv[i] = (uint32_t)__builtin_amdgcn_update_dpp((int)bv[i], (int)bv[i], 0x128, 0xf, 0xf, false);
-          }
+            for (int rb = 0; rb < 2; ++rb) {
+              const uint4 w = ring[(2 * q + rb) % HD];
+              const uint32_t wd = c == 0 ? w.x : c == 1 ? w.y : c == 2 ? w.z : w.w;
+              cq_v4u a0;
 #pragma unroll
-          for (int rb = 0; rb < 2; ++rb) {
-            const uint4 w = ring[(2 * q + rb) % HD];
-            const uint32_t wd[4] = {w.x, w.y, w.z, w.w};
-            cq_v4u a0, a1;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              // pair index byte -> table entry, row slot -> bank, byte 2 of the lane base -> table
-              const uint32_t ox = __builtin_amdgcn_perm(wd[2 * c], lbase[rb], 0x0c020400u + (i << 8));
-              const uint32_t oy = __builtin_amdgcn_perm(wd[2 * c + 1], lbase[rb], 0x0c020400u + (i << 8));
-              const uint32_t x = lds_read_u32(ox);
-              const uint32_t y = lds_read_u32(oy);
-              const pair_u32 sw = __builtin_amdgcn_permlane16_swap(x, y, false, false);
-              a0[i] = sw[0];
-              a1[i] = sw[1];
+              for (int i = 0; i < 4; ++i)
+                a0[i] = lds_read_u32(__builtin_amdgcn_perm(wd, lbase[rb], 0x0c020400u + (i << 8)));
+              const cq_v4u b = breg[q][c];
+              acc32[rb] = mfma32<F16>(a0, make_uint4(b[0], b[1], b[2], b[3]), acc32[rb]);
             }
-            if constexpr (F16) {
-              acc[rb][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                  __builtin_bit_cast(cq_v8f16, a0), __builtin_bit_cast(cq_v8f16, bv), acc[rb][0], 0, 0, 0);
-              acc[rb][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                  __builtin_bit_cast(cq_v8f16, a1), __builtin_bit_cast(cq_v8f16, bv), acc[rb][1], 0, 0, 0);
-            } else {
-              acc[rb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  __builtin_bit_cast(cq_v8bf16, a0), __builtin_bit_cast(cq_v8bf16, bv), acc[rb][0], 0, 0, 0);
-              acc[rb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  __builtin_bit_cast(cq_v8bf16, a1), __builtin_bit_cast(cq_v8bf16, bv), acc[rb][1], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            cq_v4u bv = breg[q][WIDE ? c : 0];
+            if (!WIDE && c == 1) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i)   // row_ror:8 -- lane l of a row of 16 takes lane (l + 8) % 16
+                bv[i] = (uint32_t)__builtin_amdgcn_update_dpp((int)bv[i], (int)bv[i], 0x128, 0xf, 0xf, false);
+            }
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) {
+              const uint4 w = ring[(2 * q + rb) % HD];
+              const uint32_t wd[4] = {w.x, w.y, w.z, w.w};
+              cq_v4u a0, a1;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                // pair index byte -> table entry, row slot -> bank, byte 2 of the lane base -> table
+                const uint32_t ox = __builtin_amdgcn_perm(wd[2 * c], lbase[rb], 0x0c020400u + (i << 8));
+                const uint32_t oy = __builtin_amdgcn_perm(wd[2 * c + 1], lbase[rb], 0x0c020400u + (i << 8));
+                const uint32_t x = lds_read_u32(ox);
+                const uint32_t y = lds_read_u32(oy);
+                const pair_u32 sw = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+                a0[i] = sw[0];
+                a1[i] = sw[1];
+              }
+              if constexpr (F16) {
+                acc[rb][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(cq_v8f16, a0), __builtin_bit_cast(cq_v8f16, bv), acc[rb][0], 0, 0, 0);
+                acc[rb][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(cq_v8f16, a1), __builtin_bit_cast(cq_v8f16, bv), acc[rb][1], 0, 0, 0);
+              } else {
+                acc[rb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(cq_v8bf16, a0), __builtin_bit_cast(cq_v8bf16, bv), acc[rb][0], 0, 0, 0);
+                acc[rb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(cq_v8bf16, a1), __builtin_bit_cast(cq_v8bf16, bv), acc[rb][1], 0, 0, 0);
+              }
             }
           }
         }
@@ -454,12 +511,12 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
           const int hn = 2 * q + rb + HD;    // the half step that reuses this slot
           const bool same = hn < 2 * Q;
           const int h2 = same ? hn : hn - 2 * Q;
-          const uint8_t* sp = (same ? wb : wb_next) + ((same || has_next) ? (size_t)(wave + NW * (h2 >> 1)) * sstride : 0) +
-                              ((h2 & 1) ? rb1 : 0);
+          const uint8_t* sp = (same ? wb : wb_next) + ((same || has_next) ? step_off(h2 >> 1) : 0) + ((h2 & 1) ? rb1 : 0);
           ring[(2 * q + rb) % HD] = load_stream(sp + loff);
         }
         // the previous unit's results (once), and this step's share of the next unit's table
-        if (q == 0 && ui > 0) finish(u - ustep, WIDE ? 0u : upar ^ 1u);
+        if (q == 0 && ui > 0) finish(u - ustep, QUAD ? par ^ 1u : WIDE ? 0u : upar ^ 1u);
+        if (QUAD && q == TB0) __syncthreads();   // (the partials lie where the next table goes)
         if (ql == TB0) cent_f16();
         if (ql >= TB0) table_part(tnext, ((ql - TB0) * 32) / (QL - TB0), ((ql - TB0 + 1) * 32) / (QL - TB0));
       }
@@ -467,8 +524,16 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
       // (9..16 tokens: the 32 KiB hold ONE buffer, so a barrier separates these writes from the reads of the
       // previous unit's partials at the top of this loop; it comes right before the unit's own barrier and
       // costs little)
-      if constexpr (WIDE) __syncthreads();
-      if (pcol) {
+      if constexpr (WIDE || QUAD) __syncthreads();
+      if constexpr (QUAD) {
+        const uint32_t wbase = (par << 16) + (uint32_t)wave * 8192u + (uint32_t)lane * 4u;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            *reinterpret_cast<__attribute__((address_space(3))) float*>(
+                (uintptr_t)(wbase + (uint32_t)(rb * 16 + v) * 256u)) = acc32[rb][v];
+      } else if (pcol) {
         const uint32_t wbase = kRed + (WIDE ? 0u : upar * 16384u) + (uint32_t)wave * kWaveStride + slot * 4u;
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb)
@@ -484,13 +549,14 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
       upar ^= 1u;
     }
     __builtin_amdgcn_s_setprio(0);
-    finish(ufirst + (ucnt - 1) * ustep, WIDE ? 0u : upar ^ 1u);
+    finish(ufirst + (ucnt - 1) * ustep, QUAD ? par ^ 1u : WIDE ? 0u : upar ^ 1u);
   };
 #ifndef CQ_NO_PIPE
   if constexpr (QS > 0) {
-    if (Me <= 16 * p.halves && nS == QS * NW) {   // every wavefront has exactly QS real steps
-      if (pass_rows <= 8) run_units_pipe(std::false_type{});
-      else run_units_pipe(std::true_type{});
+    if (Me <= 32 && (QS < 7 && QT == 0 ? nS <= QS * NW : nS == QS * NW)) {
+      if (Me <= 8) run_units_pipe(std::integral_constant<int, 0>{});
+      else if (Me <= 16) run_units_pipe(std::integral_constant<int, 1>{});
+      else run_units_pipe(std::integral_constant<int, 2>{});
       return;
     }
   }
@@ -732,31 +798,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
             const int row = u * 64 + (r >> 4) * 32 + ((r >> 2) & 3) * 8 + g2 * 4;
             const float x0 = sc * val[4 * h], x1 = sc * val[4 * h + 1], x2 = sc * val[4 * h + 2],
                         x3 = sc * val[4 * h + 3];
-            if (p.ksplit > 1) {  // partial sum of this K range (the launcher allows this for CQ_EPI_NONE only)
-              float* dst = p.partials + (size_t)kz * p.part_stride + (size_t)m * N + row;
-              *reinterpret_cast<float4*>(dst) = make_float4(x0, x1, x2, x3);
-              continue;
-            }
-            if constexpr (EPI == CQ_EPI_SWIGLU) {
-              const float h0 = x0 / (1.f + __expf(-x0)) * x1;
-              const float h1 = x2 / (1.f + __expf(-x2)) * x3;
-              const size_t o = (size_t)m * p.out_ld + (row >> 1);
-              if constexpr (OUTK == CQ_OUT_F16) {
-                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(p.out) + o) =
-                    f32_to_f16_bits_sat(h0) | (f32_to_f16_bits_sat(h1) << 16);
-              } else {
-                *reinterpret_cast<float2*>(reinterpret_cast<float*>(p.out) + o) = make_float2(h0, h1);
-              }
-            } else {
-              const size_t o = (size_t)m * p.out_ld + row;
-              if constexpr (OUTK == CQ_OUT_F16) {
-                *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p.out) + o) =
-                    make_uint2(f32_to_f16_bits_sat(x0) | (f32_to_f16_bits_sat(x1) << 16),
-                               f32_to_f16_bits_sat(x2) | (f32_to_f16_bits_sat(x3) << 16));
-              } else {
-                *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.out) + o) = make_float4(x0, x1, x2, x3);
-              }
-            }
+              const float x4[4] = {x0, x1, x2, x3};
+            store_quad(m, row, x4);
           }
         }
       }
@@ -957,41 +1000,44 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
 }
 
 template <int AK, int EPI, int OUTK, int RING, int QS, int QT = 0>
-cq_status launch_small_ring(const GemmArgs& a, int G, hipStream_t s) {
+cq_status launch_small_ring(const GemmArgs& a, hipStream_t s) {
   auto kern = gemm_small_kernel<AK, EPI, OUTK, RING, QS, QT>;
   static std::atomic<bool> configured{false};
   const cq_status cst = cq_configure_lds(kern, kTableBytes + kSlabBytes + kRedBytes, configured, true);
   if (cst != CQ_OK) return cst;
-  const int n_units = a.N / 64;
-  const dim3 grid = a.small_hdr ? dim3(G > kListedWorkgroups ? G : kListedWorkgroups, 1, a.ksplit * a.halves)
-                                : dim3((n_units + a.upw - 1) / a.upw, G, a.ksplit * a.halves);
+  const dim3 grid((unsigned)a.grid, 1, a.ksplit);
   hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), kTableBytes + kSlabBytes + kRedBytes, s, a);
   return cq_check_launch();
 }
 
 // qt: 0, or block-wise tables of 512 * qt weights (every K range then gives each wavefront exactly 8 or 4 steps)
 template <int AK, int EPI, int OUTK>
-cq_status launch_small(const GemmArgs& a, int G, int qt, hipStream_t s) {
+cq_status launch_small(const GemmArgs& a, int qt, hipStream_t s) {
   const int per_wave = (a.ksteps + kWaves - 1) / kWaves;  // steps of a wavefront in the (first) K range
   if (qt != 0) {
-    if (kWaves == 8 && qt == 2 && a.ksteps == 8 * kWaves) return launch_small_ring<AK, EPI, OUTK, 8, 8, 2>(a, G, s);
-    if (kWaves == 8 && qt == 2 && a.ksteps == 4 * kWaves) return launch_small_ring<AK, EPI, OUTK, 8, 4, 2>(a, G, s);
+    if (kWaves == 8 && qt == 2 && a.ksteps == 8 * kWaves) return launch_small_ring<AK, EPI, OUTK, 8, 8, 2>(a, s);
+    if (kWaves == 8 && qt == 2 && a.ksteps == 4 * kWaves) return launch_small_ring<AK, EPI, OUTK, 8, 4, 2>(a, s);
     return CQ_ERR_UNSUPPORTED;
   }
-  if (kWaves == 8 && per_wave == 8) return launch_small_ring<AK, EPI, OUTK, 8, 8>(a, G, s);
-  if (kWaves == 8 && per_wave == 7) return launch_small_ring<AK, EPI, OUTK, 4, 7>(a, G, s);
-  return per_wave % 8 == 0 ? launch_small_ring<AK, EPI, OUTK, 8, 0>(a, G, s)
-                           : launch_small_ring<AK, EPI, OUTK, 4, 0>(a, G, s);
+  if (kWaves == 8 && per_wave == 8) return launch_small_ring<AK, EPI, OUTK, 8, 8>(a, s);
+  if (kWaves == 8 && per_wave == 7) return launch_small_ring<AK, EPI, OUTK, 4, 7>(a, s);
+  // short K (2048 and less): up to four steps per wavefront, padded with empty ones
+  if (kWaves == 8 && per_wave == 4) return launch_small_ring<AK, EPI, OUTK, 4, 4>(a, s);
+  if (kWaves == 8 && per_wave == 3) return launch_small_ring<AK, EPI, OUTK, 4, 3>(a, s);
+  if (kWaves == 8 && per_wave == 2) return launch_small_ring<AK, EPI, OUTK, 4, 2>(a, s);
+  if (kWaves == 8 && per_wave == 1) return launch_small_ring<AK, EPI, OUTK, 4, 1>(a, s);
+  return per_wave % 8 == 0 ? launch_small_ring<AK, EPI, OUTK, 8, 0>(a, s)
+                           : launch_small_ring<AK, EPI, OUTK, 4, 0>(a, s);
 }
 
 template <int AK>
-cq_status dispatch_epi(const GemmArgs& a, int G, int qt, int epilogue, int out_kind, hipStream_t s) {
+cq_status dispatch_epi(const GemmArgs& a, int qt, int epilogue, int out_kind, hipStream_t s) {
   if (epilogue == CQ_EPI_SWIGLU) {
-    return out_kind == CQ_OUT_F16 ? launch_small<AK, CQ_EPI_SWIGLU, CQ_OUT_F16>(a, G, qt, s)
-                                  : launch_small<AK, CQ_EPI_SWIGLU, CQ_OUT_F32>(a, G, qt, s);
+    return out_kind == CQ_OUT_F16 ? launch_small<AK, CQ_EPI_SWIGLU, CQ_OUT_F16>(a, qt, s)
+                                  : launch_small<AK, CQ_EPI_SWIGLU, CQ_OUT_F32>(a, qt, s);
   }
-  return out_kind == CQ_OUT_F16 ? launch_small<AK, CQ_EPI_NONE, CQ_OUT_F16>(a, G, qt, s)
-                                : launch_small<AK, CQ_EPI_NONE, CQ_OUT_F32>(a, G, qt, s);
+  return out_kind == CQ_OUT_F16 ? launch_small<AK, CQ_EPI_NONE, CQ_OUT_F16>(a, qt, s)
+                                : launch_small<AK, CQ_EPI_NONE, CQ_OUT_F32>(a, qt, s);
 }
 
 }  // namespace

@@ -43,7 +43,8 @@ struct W2Args {
   void* out;
   int out_ld;
   cq_route_fuse route;      // grouping by expert folded into the launch (cq_route::group_rows_from_ids), else ids == NULL
-  int upw;                  // 32-row units per workgroup
+  int G;                    // groups
+  int slots, rounds, grid;  // workgroups per K range at a time, rounds of them in the grid, gridDim.x (as in codebook_gemm_small.h)
   int ksplit;               // K ranges (blockIdx.z); > 1: scaled fp32 partial sums go to `partials`
   float* partials;          // [ksplit][M_total][N]
   size_t part_stride;
@@ -72,20 +73,20 @@ __global__ __launch_bounds__(64 * kW2Waves, 1) void gemm_w2_kernel(const W2Args 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r32 = lane & 31, g2 = lane >> 5, i16 = lane & 15, g4 = lane >> 4;
   const int N = p.N, K = p.K;
-  const int grp = blockIdx.y;
-  int m0, Me, row_token = 0;
+  const int nUnits = N >> 5;
+  cq_route::group_share share;   // this workgroup's group and its share of the units (only groups with rows get any)
+  int row_token = 0;
   const bool fused = p.route.ids != nullptr;
   if (fused) {
-    cq_route::group_rows_from_ids(p.route, grp, lane,
-                                  blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && wave == 0, m0, Me, row_token);
+    if (!cq_route::pick_group_from_ids(p.route, nUnits, p.slots, p.rounds, blockIdx.x, lane, share)) return;
+    cq_route::group_rows_from_ids(p.route, share.grp, lane, blockIdx.x == 0 && blockIdx.z == 0 && wave == 0, share.m0,
+                                  share.Me, row_token);
   } else {
-    m0 = p.group_offsets[grp];
-    Me = p.group_offsets[grp + 1] - m0;
+    if (!cq_route::pick_group(p.group_offsets, p.G, 0x7fffffff, nUnits, p.slots, p.rounds, blockIdx.x, lane, share))
+      return;
   }
-  if (Me <= 0) return;
-  const int nUnits = N >> 5;
-  const int ustep = gridDim.x, ufirst = blockIdx.x;   // a group's workgroups interleave its units
-  if (ufirst >= nUnits) return;
+  const int grp = share.grp, m0 = share.m0, Me = share.Me;
+  const int ustep = share.chunks, ufirst = share.chunk;   // a group's workgroups interleave its units
   const int ucnt = (nUnits - ufirst + ustep - 1) / ustep;
   const size_t rowbytes = (size_t)K >> 2;
   const size_t ubytes = 32 * rowbytes;                // index bytes of one unit
@@ -303,24 +304,23 @@ __global__ __launch_bounds__(64 * kW2Waves, 1) void gemm_w2_kernel(const W2Args 
 }
 
 template <int AK, int EPI, int OUTK, int Q>
-cq_status launch_w2(const W2Args& a, int G, hipStream_t s) {
+cq_status launch_w2(const W2Args& a, hipStream_t s) {
   auto kern = gemm_w2_kernel<AK, EPI, OUTK, Q>;
   static std::atomic<bool> configured{false};
   const cq_status cst = cq_configure_lds(kern, kW2Lds, configured, true);
   if (cst != CQ_OK) return cst;
-  const int n_units = a.N / 32;
-  const dim3 grid((n_units + a.upw - 1) / a.upw, G, a.ksplit);
+  const dim3 grid((unsigned)a.grid, 1, a.ksplit);
   hipLaunchKernelGGL(kern, grid, dim3(64 * kW2Waves), kW2Lds, s, a);
   return cq_check_launch();
 }
 
 template <int AK, int Q>
-cq_status dispatch_w2(const W2Args& a, int G, int epilogue, int out_kind, hipStream_t s) {
+cq_status dispatch_w2(const W2Args& a, int epilogue, int out_kind, hipStream_t s) {
   if (epilogue == CQ_EPI_SWIGLU)
-    return out_kind == CQ_OUT_F16 ? launch_w2<AK, CQ_EPI_SWIGLU, CQ_OUT_F16, Q>(a, G, s)
-                                  : launch_w2<AK, CQ_EPI_SWIGLU, CQ_OUT_F32, Q>(a, G, s);
-  return out_kind == CQ_OUT_F16 ? launch_w2<AK, CQ_EPI_NONE, CQ_OUT_F16, Q>(a, G, s)
-                                : launch_w2<AK, CQ_EPI_NONE, CQ_OUT_F32, Q>(a, G, s);
+    return out_kind == CQ_OUT_F16 ? launch_w2<AK, CQ_EPI_SWIGLU, CQ_OUT_F16, Q>(a, s)
+                                  : launch_w2<AK, CQ_EPI_SWIGLU, CQ_OUT_F32, Q>(a, s);
+  return out_kind == CQ_OUT_F16 ? launch_w2<AK, CQ_EPI_NONE, CQ_OUT_F16, Q>(a, s)
+                                : launch_w2<AK, CQ_EPI_NONE, CQ_OUT_F32, Q>(a, s);
 }
 
 template <int OUTK>
@@ -384,21 +384,23 @@ cq_status cq_gemm_w2_launch(const cq_codebook_weights* W, const void* A, int a_k
   a.partials = (float*)workspace;
   a.part_stride = (size_t)M_total * W->N;
   {
-    const long units = (long)(W->N / 32) * W->G * a.ksplit;   // about one workgroup per compute unit
-    long upw = (units + 255) / 256;
-    if (upw < 1) upw = 1;
-    if (upw > W->N / 32) upw = W->N / 32;
-    a.upw = (int)upw;
+    // about one workgroup per compute unit, divided by the kernel among the groups that have rows (see the rule for
+    // the rounds at the 4-bit kernel's launcher)
+    const int n_max = W->G < M_total ? W->G : M_total;
+    a.G = W->G;
+    a.slots = 256 / a.ksplit > 1 ? 256 / a.ksplit : 1;
+    a.rounds = n_max <= 32 ? 1 : n_max <= 256 ? 2 : 4;
+    a.grid = a.slots * a.rounds > n_max ? a.slots * a.rounds : n_max;
   }
   cq_status st;
   if (steps == 32) {
-    st = a_kind == CQ_A_INT8_CODES ? dispatch_w2<CQ_A_INT8_CODES, 4>(a, W->G, epilogue, out_kind, s)
-         : a_kind == CQ_A_F16      ? dispatch_w2<CQ_A_F16, 4>(a, W->G, epilogue, out_kind, s)
-                                   : dispatch_w2<CQ_A_BF16, 4>(a, W->G, epilogue, out_kind, s);
+    st = a_kind == CQ_A_INT8_CODES ? dispatch_w2<CQ_A_INT8_CODES, 4>(a, epilogue, out_kind, s)
+         : a_kind == CQ_A_F16      ? dispatch_w2<CQ_A_F16, 4>(a, epilogue, out_kind, s)
+                                   : dispatch_w2<CQ_A_BF16, 4>(a, epilogue, out_kind, s);
   } else {
-    st = a_kind == CQ_A_INT8_CODES ? dispatch_w2<CQ_A_INT8_CODES, 7>(a, W->G, epilogue, out_kind, s)
-         : a_kind == CQ_A_F16      ? dispatch_w2<CQ_A_F16, 7>(a, W->G, epilogue, out_kind, s)
-                                   : dispatch_w2<CQ_A_BF16, 7>(a, W->G, epilogue, out_kind, s);
+    st = a_kind == CQ_A_INT8_CODES ? dispatch_w2<CQ_A_INT8_CODES, 7>(a, epilogue, out_kind, s)
+         : a_kind == CQ_A_F16      ? dispatch_w2<CQ_A_F16, 7>(a, epilogue, out_kind, s)
+                                   : dispatch_w2<CQ_A_BF16, 7>(a, epilogue, out_kind, s);
   }
   if (st != CQ_OK || a.ksplit == 1) return st;
   if (ksplit_left) {

@@ -128,6 +128,70 @@ __device__ __forceinline__ void wave_topk_regs(float val, int E, int k, int lane
   }
 }
 
+// lane that holds the n-th (from 0) set bit of a ballot mask; n < popcount(mask)
+__device__ __forceinline__ int nth_set_lane(uint64_t mask, int n, int lane) {
+  const bool hit = ((mask >> lane) & 1ull) && __popcll(mask & lanemask_lt(lane)) == n;
+  return __ffsll((long long)__ballot(hit)) - 1;
+}
+
+// Workgroups per group of a streaming launch.  n_act groups have rows, each of n_units units of work; the chip runs
+// `slots` workgroups of the launch at a time and its grid holds rmax rounds of them.  With r rounds a group gets
+// c = r * slots / n_act workgroups; a workgroup costs its units plus about one unit of prologue (first table, ring
+// fill, activation rows), so the launch costs about r * (1 + ceil(n_units / c)): lane r - 1 prices r rounds and the
+// cheapest (the fewest rounds among equals) wins.  Called by all 64 lanes; rmax is 1, 2 or 4.
+__device__ __forceinline__ int workgroups_per_group(int n_act, int n_units, int slots, int rmax, int lane) {
+  const int r = min(lane, 3) + 1;
+  const int c = min(n_units, (r * slots) / n_act);
+  // (price and choice in one number: a unit of price is 2^12; prices stay below 2^19 / 4)
+  uint32_t price = c >= 1 && r <= rmax ? (uint32_t)r * (1u + (uint32_t)(n_units + c - 1) / (uint32_t)c) : 0x3ffffu;
+  uint32_t best = (min(price, 0x3ffffu) << 12) | ((uint32_t)r << 8);
+#pragma unroll
+  for (int off = 1; off < 4; off <<= 1) best = min(best, (uint32_t)__shfl_xor((int)best, off));
+  best = (uint32_t)__builtin_amdgcn_readfirstlane((int)best);
+  return max(1, min(n_units, (int)((best >> 8) & 15u) * slots / n_act));
+}
+
+// The group that workgroup `b` of a streaming launch works on, chosen among the groups that have between 1 and
+// max_rows rows (the others cost the launch nothing: with one workgroup set per group of the layer, a batch of one
+// token left three quarters of the chip without work).  Sets the group, its first row and row count, this
+// workgroup's number among the group's workgroups and their count; false: no work for this workgroup.  All values are
+// uniform over the wavefront.  Called by all 64 lanes.
+struct group_share {
+  int grp, m0, Me, chunk, chunks;
+};
+__device__ __forceinline__ bool pick_group(const int32_t* __restrict__ offsets, int G, int max_rows, int n_units,
+                                           int slots, int rmax, int b, int lane, group_share& o) {
+  int base = 0, first, rows;
+  auto load = [&]() {
+    const int g = base + lane;
+    first = g < G ? offsets[g] : 0;
+    rows = g < G ? offsets[g + 1] - first : 0;
+    return (uint64_t)__ballot(rows > 0 && rows <= max_rows);
+  };
+  uint64_t mask = load();
+  int n_act = __popcll(mask);
+  for (int g0 = 64; g0 < G; g0 += 64) {   // (more than 64 groups: the further rounds are loaded again below)
+    const int g = g0 + lane;
+    const int me = g < G ? offsets[g + 1] - offsets[g] : 0;
+    n_act += __popcll(__ballot(me > 0 && me <= max_rows));
+  }
+  if (n_act == 0) return false;
+  o.chunks = workgroups_per_group(n_act, n_units, slots, rmax, lane);
+  int n = b / o.chunks;
+  if (n >= n_act) return false;
+  o.chunk = b - n * o.chunks;
+  while (n >= __popcll(mask)) {
+    n -= __popcll(mask);
+    base += 64;
+    mask = load();
+  }
+  const int src = nth_set_lane(mask, n, lane);
+  o.grp = base + src;
+  o.m0 = __builtin_amdgcn_readlane(first, src);
+  o.Me = __builtin_amdgcn_readlane(rows, src);
+  return true;
+}
+
 // a5 folded into a product launch for decode-sized batches (cq_route_fuse): the rows of group `grp`, derived by
 // one wavefront from the selected expert ids.  There are at most 64 assignments (token, choice), one per lane,
 // numbered a = token * top_k + choice; the rows of expert e are the assignments that chose e, in ascending a, and
@@ -173,6 +237,28 @@ __device__ __forceinline__ void group_rows_from_ids(const cq_route_fuse& rt, int
     }
     for (int i = lane; i < rt.S * rt.T; i += 64) rt.src_token[n_assign + i] = i % rt.T;
   }
+}
+
+// pick_group for a launch with the grouping folded in: the active experts are those among the selected ids (at most
+// 64 experts: one bit each), and every shared expert is active.  m0 and Me come from group_rows_from_ids.
+__device__ __forceinline__ bool pick_group_from_ids(const cq_route_fuse& rt, int n_units, int slots, int rmax, int b,
+                                                    int lane, group_share& o) {
+  const int n_assign = rt.T * rt.top_k;
+  const int id = lane < n_assign ? rt.ids[lane] : 0x7fffffff;
+  uint64_t mask = 0;
+  if (rt.E <= n_assign) {
+    for (int e = 0; e < rt.E; ++e)
+      if (__ballot(id == e)) mask |= 1ull << e;
+  } else {
+    for (int a = 0; a < n_assign; ++a) mask |= 1ull << __builtin_amdgcn_readlane(id, a);
+  }
+  const int n_exp = __popcll(mask);
+  o.chunks = workgroups_per_group(n_exp + rt.S, n_units, slots, rmax, lane);
+  const int n = b / o.chunks;
+  if (n >= n_exp + rt.S) return false;
+  o.chunk = b - n * o.chunks;
+  o.grp = n < n_exp ? nth_set_lane(mask, n, lane) : rt.E + n - n_exp;
+  return true;
 }
 
 }  // namespace cq_route

@@ -474,10 +474,42 @@ def test_gemm_instantiation_matrix(B, a_kind, epi, out_kind, blockwise, prepacke
         assert err.max() < (1e-3 if out_kind == "f16" else 2e-5), f"row {int(err.argmax())}: {err.max():.3e}"
 
 
+@pytest.mark.parametrize("prepacked", [True, False])
+@pytest.mark.parametrize("G,N,K,rows", [
+    (3, 320, 64, {1: 8}),                                  # one K step: seven of eight wavefronts have none
+    (5, 64, 512, {0: 1, 4: 32}), (70, 128, 576, {69: 17, 2: 9, 64: 31}),
+    (66, 192, 768, {g: 1 + g % 17 for g in range(0, 66, 2)}),
+    (130, 64, 1408, {g: 1 + g % 3 for g in range(130)}),   # more groups than half the compute units: two rounds
+    (300, 64, 512, {g: 1 + g % 2 for g in range(300)}),    # more groups than one round holds
+    (66, 256, 2048, {g: 16 + g % 19 for g in range(3, 60, 7)}),   # ... next to large tiles (33 and 34 rows)
+    (9, 448, 2048, {8: 32}), (200, 64, 4096, {199: 20, 100: 3}), (4, 128, 3584, {2: 32, 3: 24}),
+])
+def test_gemm_streaming_workgroups_by_active_groups(B, G, N, K, rows, prepacked):
+    """The streaming launch gives workgroups to the groups that have rows only: few active groups among many (also
+    past one wavefront of them), more groups than a round of workgroups, and K ranges that leave wavefronts without a
+    step.  Exact integers, as above."""
+    rng = np.random.default_rng(G + N + K)
+    counts = [rows.get(g, 0) for g in range(G)]
+    M = sum(counts)
+    table = synth.f32_to_bf16_bits(np.arange(16, dtype=np.float32) - 8.0)
+    idx, cent = _rand_weights(rng, G, N, K, cent=np.broadcast_to(table, (G, N, 16)).copy())
+    codes = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
+    off = _group_offsets(counts)
+    W = B.DeviceCodebook(idx, cent, prepack=True)
+    for a_kind, acts in ((B.CQ_A_INT8_CODES, codes), (B.CQ_A_F16, (codes // 4).astype(np.float16))):
+        out = B.cq_codebook_grouped_gemm(W, _dev(acts), a_kind, None, None, _dev(off), M, B.CQ_EPI_NONE, B.CQ_OUT_F32,
+                                         use_prepacked=prepacked).cpu().numpy()
+        for g in range(G):
+            at = slice(off[g], off[g + 1])
+            if counts[g]:
+                ref = O.codebook_matmul(acts[at].astype(np.float64), idx[g], cent[g])
+                assert np.array_equal(out[at].astype(np.float64), ref), f"group {g}"
+
+
 @pytest.mark.parametrize("counts,n_extra", [
     ([8, 12, 0, 5, 16, 1, 9, 7], 0),         # up to 8 tokens and 9..16 tokens: the two forms of the pipelined loop
-    ([17, 32, 3, 20, 0, 25, 16, 9], 0),      # 17..32 rows: two workgroups per run of units (device-built group list)
-    ([24, 2, 31, 16, 17, 0, 8, 32], 64),     # ... with a launch grid over all groups (no 256-row tiles for N + 64)
+    ([17, 32, 3, 20, 0, 25, 16, 9], 0),      # 17..32 rows: the third form
+    ([24, 2, 31, 16, 17, 0, 8, 32], 64),     # ... in a launch without large tiles (N + 64 has no 256-row tiles)
 ])
 @pytest.mark.parametrize("shape", ["gate_up", "down"])
 def test_gemm_streaming_pipeline_many_units(B, shape, counts, n_extra):
