@@ -112,7 +112,7 @@ bool cq_gemm_can_fuse_route(const cq_codebook_weights* W, int T, int E, int S, i
 cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, int a_kind, const float* row_scale,
                                   const int32_t* row_gather, const int32_t* group_offsets, int M_total,
                                   int epilogue, void* out, int out_kind, void* workspace, hipStream_t s,
-                                  int* ksplit_left, const cq_route_fuse* route, int max_group_rows) {
+                                  int* ksplit_left, const cq_route_fuse* route, int max_group_rows, long a_rows) {
   if (route && !cq_gemm_can_fuse_route(W, route->T, route->E, route->S, route->top_k, epilogue))
     return CQ_ERR_UNSUPPORTED;
   if (cq_is_w2(W))
@@ -162,19 +162,28 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
   const bool blockwise = cq_tables_per_row(W) > 1 && !bw_streams;
   const bool large = cq_gemm_uses_large_tiles(W, M_total, epilogue, max_group_rows);
   if (blockwise && !large) return CQ_ERR_UNSUPPORTED;
-  const int small_max = blockwise ? 0 : kSmallMaxRows;
+  // (the converted copy of A, and rows that are not gathered, are M_total)
+  const bool converts = a_kind == CQ_A_INT8_CODES || a_kind == CQ_A_F32;
+  const bool half = large && cq_gemm_uses_half_tiles(W, M_total, converts || !row_gather ? M_total : a_rows);
+  // Where large tiles run anyway, they take the small groups as well and the streaming launch falls away if that is the
+  // cheaper: with a short K always (DeepSeek-V2-Lite shape, gate/up + down at 40 tokens: 92 us against 105 us in two
+  // launches, Qwen3 shape 46 against 78), with a long one from 28 rows per group on (Mixtral shape at 64 tokens 245
+  // against 172 us, at 96 tokens 241 against 246, at 128 tokens the whole layer 290 against 302).
+  const bool no_small = blockwise || (half && (W->K <= 2048 || (long)M_total >= 28L * W->G)) ||
+                        (large && !half && (long)M_total >= 384L * W->G);
+  const int small_max = no_small ? 0 : kSmallMaxRows;
   const int qt = bw_streams ? W->group_k / 512 : 0;
   a.max_rows = large ? small_max : 0x7fffffff;
   void* large_ws = (char*)workspace + cq_gemm_partials_bytes(W, M_total, epilogue, max_group_rows);
   cq_status st;
   if (large) {
-    st = cq_gemm_build_lists(W, group_offsets, M_total, small_max, large_ws, s, cq_gemm_large_tail_split(W, epilogue, out_kind));
+    st = cq_gemm_build_lists(W, group_offsets, M_total, small_max, large_ws, s, cq_gemm_large_tail_split(W, epilogue, out_kind), half);
     if (st != CQ_OK) return st;
   }
   if (blockwise) {
     // (with a K split the kernel stores fp32 partial sums, per split, where the streaming kernel would)
     st = cq_gemm_large_launch(W, A, a_kind, row_scale, row_gather, group_offsets, M_total, small_max, epilogue,
-                              a.ksplit > 1 ? (void*)a.partials : out, a.ksplit > 1 ? CQ_OUT_F32 : out_kind, large_ws, s);
+                              a.ksplit > 1 ? (void*)a.partials : out, a.ksplit > 1 ? CQ_OUT_F32 : out_kind, large_ws, s, false);
     if (st != CQ_OK || a.ksplit == 1) return st;
     if (ksplit_left) {
       *ksplit_left = a.ksplit;  // the caller adds the partial sums itself
@@ -189,6 +198,9 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
                          group_offsets, 0x7fffffff, W->N, out);
     return cq_check_launch();
   }
+  if (no_small)
+    return cq_gemm_large_launch(W, A, a_kind, row_scale, row_gather, group_offsets, M_total, 0, epilogue, out, out_kind,
+                                large_ws, s, half);
   switch (a_kind) {
     case CQ_A_INT8_CODES: st = cq_gemm_small_dispatch_int8(a, qt, epilogue, out_kind, s); break;
     case CQ_A_F16: st = cq_gemm_small_dispatch_f16(a, qt, epilogue, out_kind, s); break;
@@ -213,7 +225,7 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
   }
   if (!large) return st;
   return cq_gemm_large_launch(W, A, a_kind, row_scale, row_gather, group_offsets, M_total, kSmallMaxRows, epilogue,
-                              out, out_kind, large_ws, s);
+                              out, out_kind, large_ws, s, half);
 }
 
 

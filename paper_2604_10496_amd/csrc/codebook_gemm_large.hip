@@ -1,6 +1,6 @@
 // a6 / a7 for groups with many tokens (prefill regime, bound by the matrix cores).
 //
-// Workgroup tile: 256 weight rows x CT tokens (CT = 256, 128, 64 or 32), four wavefronts, each owning 64 rows
+// Workgroup tile: 256 weight rows x CT tokens (CT = 256, 128, 96, 64 or 32), four wavefronts, each owning 64 rows
 // and ALL the tile's tokens (accumulators 2 x CT/32 MFMA blocks of 32x32).  Consequences:
 //   * every wavefront decodes only its own rows, straight into MFMA A-operand registers: the decoded
 //     weights never touch LDS, and no weight is decoded twice;
@@ -9,7 +9,8 @@
 //     nibbles become byte selectors, v_perm_b32 picks the low and the high bytes of the centroids out
 //     of register-resident byte tables (two 8-entry halves; a third perm, steered by bit 3 of the
 //     index, picks between them), one or two more perm levels interleave the bytes into bf16/f16 pairs.
-//     About 1.4 ALU operations per MFMA, all full rate, mostly hidden behind the matrix pipe.
+//     About 1.4 ALU operations per MFMA at 256 tokens, mostly hidden behind the matrix pipe (with two wavefronts on a
+//     SIMD v_perm_b32 was measured at 4.8 clocks, plain logic and shifts at 2.6: 21 weights per clock and compute unit);
 //     With block-wise tables (one per group of g weights along K, g a multiple of 512) the two tables are
 //     replaced every g/64 steps; the raw tables of the next group are requested one group ahead;
 //   * LDS holds only the activation tiles.  They arrive by direct global->LDS loads (no staging
@@ -24,14 +25,19 @@
 #include "cq_async.h"
 #include "cq_decode.h"
 
-void cq_large_tile_caps(int G, int M_total, int* cap256, int* cap128);
+void cq_large_tile_caps(int G, int M_total, int* cap0, int* cap1);
 
 namespace {
 
 constexpr int kLargeRows = 256;  // weight rows per workgroup
 constexpr int kStepK = 64;       // K per pipeline step
 constexpr int kStepBytes = kStepK * 2;  // one token's share of a step in LDS and in global memory
-constexpr int kLdsTileBytes = 4 * 256 * kStepBytes;  // activation tile rings: 4 x 256, 8 x 128 or 8 x 64 tokens
+// tokens of the tiles of the three work lists: whole tiles (one workgroup per compute unit), half tiles (two)
+template <bool HALF>
+struct tile_widths {
+  static constexpr int w0 = HALF ? 128 : 256, w1 = HALF ? 96 : 128, w2 = 64;
+};
+constexpr int kAtOnce[2] = {256, 512};   // workgroups that the chip runs at a time
 constexpr int kNextTableBytes = 2048;  // block-wise tables: raw next tables of a wavefront's 64 rows (x 4 wavefronts x 2)
 
 struct LargeArgs {
@@ -45,10 +51,10 @@ struct LargeArgs {
   const int32_t* scale_gather; // sorted row -> entry of row_scale, or NULL
   void* out;
   int out_ld;
-  const int32_t* tiles;    // 256-token tiles [cap][4]: group, first row (absolute sorted row), row count, unused
-  const int32_t* tiles128; // 128-token tiles, same layout
-  const int32_t* tiles64;  // 64-token tiles, same layout
-  const int32_t* n_tiles;  // the builder's counts: [0] entries in tiles, [1] in tiles128, [5] in tiles64
+  const int32_t* tiles;   // widest tiles [cap][4]: group, first row (absolute sorted row), row count, unused
+  const int32_t* tiles1;  // the next width (tile_widths), same layout
+  const int32_t* tiles2;  // 64-token tiles, same layout
+  const int32_t* n_tiles; // the builder's counts: [0] entries in tiles, [1] in tiles1, [5] in tiles2
   int row_tiles;          // N / 256
   int nblk;               // centroid tables per weight row (1: one table over all of K)
   int gsteps;             // K steps per table (block-wise tables: group size / 64, a multiple of 8)
@@ -57,13 +63,15 @@ struct LargeArgs {
   // out + z * part_stride elements; ksteps covers all of K when there is no split
   int ksteps;
   size_t part_stride;
-  // K split of the narrow tiles of a plain fp32 product with a long K (tail_part != NULL): the builder chooses
-  // S = n_tiles[6] in {1, 2, 4}; split z > 0 of the j-th 128-token (64-token) tile stores its partial sums at
-  // rows j*128 (tail_rows128 + j*64) of slice z-1 of tail_part, [S-1][tail_rows][N] fp32 -- or, when the launch
-  // has fewer rows than such slots (tail_abs), at the tile's own sorted rows -- and tail_sum_kernel adds them to
-  // `out` in the order z = 1, 2, ...
+  // K split of the tiles of a plain fp32 product with a long K (tail_part != NULL): the builder chooses S = n_tiles[6]
+  // parts in {1, 2, 4} for the tiles of the two narrow widths w1 and w2, which come last; split z > 0 of the j-th
+  // w1-token (w2-token) tile stores its partial sums at rows j*w1 (tail_rows1 + j*w2) of slice z-1 of tail_part,
+  // [S-1][tail_rows][N] fp32 -- or, when the launch has fewer rows than such slots (tail_abs), at the tile's own sorted
+  // rows; the widest tiles then come in n_tiles[7] parts.  tail_sum_kernel adds the slices to `out` in the order z = 1,
+  // 2, ...
   float* tail_part;
-  int tail_rows128;   // rows reserved for the 128-token tiles (capacity of that list * 128)
+  int w1, w2;         // the two narrow widths of the launch
+  int tail_rows1;     // rows reserved for the w1-token tiles (capacity of that list * w1)
   int tail_rows;      // rows per slice
   int tail_abs;       // 1: a slice has M_total rows and a tile stores at its own sorted rows (fewer rows than slots)
 };
@@ -108,30 +116,28 @@ constexpr int epilogue_row_stride(int epi, int outk) {
 // prepacked copy (whose nibble arrangement decodes with four operations fewer per 8 weights).
 // kz / kS: this workgroup takes part kz of kS equal parts of K (narrow tiles of a plain fp32 product; 0 / 1
 // otherwise) and, for kz > 0, stores at row tail_row0 of slice kz-1 of p.tail_part instead of p.out.
-template <bool F16, int EPI, int OUTK, int C, int D, bool BLK, bool PRE>
-__device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp, const int mrow0, const int mcnt,
-                                           const int rt, const int kz = 0, const int kS = 1, const int tail_row0 = 0) {
+template <bool F16, int EPI, int OUTK, int C, int D, bool BLK, bool PRE, bool A32 = false>
+__device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, const int mrow0_, const int mcnt_,
+                                           const int rt_, const int kz_ = 0, const int kS_ = 1, const int tail_row0 = 0) {
+  // (uniform, but read through the work lists: kept in scalar registers from here on)
+  const int grp = __builtin_amdgcn_readfirstlane(grp_), mrow0 = __builtin_amdgcn_readfirstlane(mrow0_);
+  const int mcnt = __builtin_amdgcn_readfirstlane(mcnt_), rt = __builtin_amdgcn_readfirstlane(rt_);
+  const int kz = __builtin_amdgcn_readfirstlane(kz_), kS = __builtin_amdgcn_readfirstlane(kS_);
   constexpr bool kTail = !BLK && EPI == CQ_EPI_NONE && OUTK == CQ_OUT_F32;
   constexpr int CT = 32 * C;
   constexpr uint32_t kBufBytes = CT * kStepBytes;  // one activation tile: CT tokens x 128 bytes
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: what depends on it stays scalar
   const int r32 = lane & 31, g2 = lane >> 5;
   const int N = p.N, K = p.K;
   const size_t rowbytes = (size_t)K >> 1;
   const int n0 = rt * kLargeRows + wave * 64;  // this wavefront's 64 rows
-  const uint8_t* wbase = p.idx + ((size_t)grp * N + n0) * rowbytes;
-  const uint8_t *wp0, *wp1;  // this lane's 16 bytes of step 0, for each of its two rows
-  int sstride;
-  if constexpr (PRE) {
-    wp0 = wbase + (size_t)lane * 16;
-    wp1 = wbase + 32 * rowbytes + (size_t)lane * 16;
-    sstride = 1024;
-  } else {
-    wp0 = wbase + (size_t)r32 * rowbytes + g2 * 16;
-    wp1 = wbase + (size_t)(32 + r32) * rowbytes + g2 * 16;
-    sstride = 32;
-  }
+  // index loads: a uniform base per row block and step, plus this lane's offset of its 16 bytes (of row r32 of the block)
+  const uint8_t* wp0 = p.idx + ((size_t)grp * N + n0) * rowbytes;
+  const uint8_t* wp1 = wp0 + 32 * rowbytes;
+  const uint32_t woff = PRE ? (uint32_t)lane * 16u : (uint32_t)r32 * (uint32_t)rowbytes + (uint32_t)g2 * 16u;
+  constexpr int sstride = PRE ? 1024 : 32;
   // this workgroup's K range: steps [sb, sb + nS) (all of K unless the launch splits K)
   int sb = BLK ? (int)blockIdx.y * p.ksteps : 0;
   int nS = BLK ? min(p.ksteps, K / kStepK - sb) : K / kStepK;
@@ -181,14 +187,18 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp, co
   // tokens [w*CT/4, (w+1)*CT/4) of every step: C loads.
   // Tokens past the end of the tile load the tile's last row instead (no branches in the pipeline);
   // a token is one output column, and those columns are never stored.
-  const uint8_t* ap[C];
+  // (A32: the launcher knows that every row's byte offset fits 32 bits; the address arithmetic is then scalar)
+  const uint8_t* ap[A32 ? 1 : C];
+  uint32_t aoff[A32 ? C : 1];
+  const uint8_t* const abase = reinterpret_cast<const uint8_t*>(p.A) + (size_t)sb * kStepK * 2;
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     const int tok = wave * (CT / 4) + i * 8 + (lane >> 3);
     const int m = mrow0 + min(tok, mcnt - 1);
     const size_t row = (size_t)(p.a_gather ? p.a_gather[m] : m);
     const int chunk = (lane & 7) ^ ((tok >> 1) & 7);
-    ap[i] = reinterpret_cast<const uint8_t*>(p.A) + (row * (size_t)K + (size_t)sb * kStepK + chunk * 8) * 2;
+    if constexpr (A32) aoff[i] = (uint32_t)((row * (size_t)K + chunk * 8) * 2);
+    else ap[i] = abase + (row * (size_t)K + chunk * 8) * 2;
   }
   const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(wave * (CT / 4) * kStepBytes);
   // this wavefront's loads i0 .. i0+n-1 of the activations of step s into tile `buf`
@@ -196,17 +206,32 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp, co
     const size_t o = (size_t)s * kStepBytes;
 #pragma unroll
     for (int i = 0; i < C; ++i)
-      if (i >= i0 && i < i0 + n) load_global_to_lds(buf * kBufBytes + lds_wave + i * 1024, ap[i] + o);
+      if (i >= i0 && i < i0 + n) {
+        if constexpr (A32) load_global_to_lds_s<0>(buf * kBufBytes + lds_wave + i * 1024, abase + o, aoff[i]);
+        else load_global_to_lds(buf * kBufBytes + lds_wave + i * 1024, ap[i] + o);
+      }
   };
   auto fetch_weights = [&](cq_v4u (&w)[2], int s) {
     const size_t o = (size_t)s * sstride;
-    load_global_async(w[0], wp0 + o);
-    load_global_async(w[1], wp1 + o);
+    load_global_async_s<0>(w[0], wp0 + o, woff);
+    load_global_async_s<0>(w[1], wp1 + o, woff);
   };
   // fragment read: lane (token r32 of block cb, k group g2) wants chunk g2*4 + jj of sub-step jj
   const uint32_t boff = (uint32_t)r32 * kStepBytes + ((uint32_t)((g2 * 4) ^ ((r32 >> 1) & 7)) << 4);
+  // One address register per sub-step (and per 64 KiB of tiles), opaque to the compiler; buffer and token block go into
+  // the instruction's offset field.  (Left to itself the compiler keeps up to 48 loop-invariant addresses in registers,
+  // which half tiles do not have: 13 to 28 spilled.)
+  constexpr int kBufSets = (int)((D * kBufBytes + 65535) / 65536), kSetBufs = D / kBufSets;
+  uint32_t bx[kBufSets][4];
+#pragma unroll
+  for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+    for (int i = 0; i < kBufSets; ++i) {
+      bx[i][jj] = (boff ^ ((uint32_t)jj << 4)) + i * kSetBufs * kBufBytes;
+      asm volatile("" : "+v"(bx[i][jj]));
+    }
   auto read_b = [&](int buf, int jj, int cb) {
-    return lds_read_u128((boff ^ ((uint32_t)jj << 4)) + buf * kBufBytes + cb * 32 * kStepBytes);
+    return lds_read_u128(bx[buf / kSetBufs][jj] + (uint32_t)(buf % kSetBufs) * kBufBytes + cb * 32 * kStepBytes);
   };
 
   cq_v16f acc[2][C];
@@ -249,6 +274,8 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp, co
   // the group barriers below ask the scheduler for exactly that).
   // The B fragments live in one register set: as soon as the two MFMAs of a token block are issued,
   // its registers take the block's fragment of the next sub-step (a full sub-step of slack).
+  // vector ALU operations per MFMA that the scheduler is asked for: two decode8 calls per 2 C MFMAs
+  constexpr int kValu = C >= 8 ? 4 : C == 4 ? 6 : 12;
   cq_v4u af[2][2];
   cq_v4u bfr[C];
   uint32_t ident = 0x03020100u;   // kept in a vector register (see decode8)
@@ -311,7 +338,7 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp, co
 #pragma unroll
         for (int i = 0; i < 2 * C; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                   // one MFMA
-          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);                   // four vector ALU operations
+          __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);               // vector ALU operations
           if (i % 2 == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -353,8 +380,9 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp, co
   for (int pass = 0; pass < (C + 1) / 2; ++pass) {
     __syncthreads();  // the tile buffers (first pass) or the previous pass's rows are no longer read
 #pragma unroll
-    for (int half = 0; half < (C >= 2 ? 2 : 1); ++half) {
+    for (int half = 0; half < 2; ++half) {
       const int cb = pass * 2 + half;
+      if (cb >= C) break;
       const int tl = half * 32 + r32;  // token within the pass
       float sc = 1.f;
       if (p.row_scale) {
@@ -413,64 +441,76 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp, co
   }
 }
 
-// Work items = (token tile, row tile); tiles of 256, 128 and 64 tokens in ONE launch so that the
-// short lists do not leave most of the chip idle.  XCD-aware remap of the linear workgroup id (ids go
-// round-robin over the 8 XCDs): XCD x takes a contiguous share of the 256-token work and then a
-// contiguous share of the 128-token and of the 64-token work (neighbours share activations in its L2;
-// equal mix on every XCD).  The grid is sized for the worst case; the lists are usually much shorter.
-template <bool F16, int EPI, int OUTK, bool BLK, bool PRE>
-__global__ __launch_bounds__(256, 1) void gemm_large_kernel(const LargeArgs p) {
-  const int kS = p.tail_part ? p.n_tiles[6] : 1;   // K parts of a narrow tile
-  const int kS256 = p.tail_part && p.tail_abs ? p.n_tiles[7] : 1;   // ... of a 256-token tile (launches of few tiles)
-  const int n256 = p.n_tiles[0] * p.row_tiles * kS256, n128 = p.n_tiles[1] * p.row_tiles * kS,
-            n64 = p.n_tiles[5] * p.row_tiles * kS;
-  const int per256 = (n256 + 7) >> 3, per128 = (n128 + 7) >> 3, per64 = (n64 + 7) >> 3;
+// Work items = (token tile, row tile, K part); tiles of the three widths in ONE launch so that the short lists do not
+// leave most of the chip idle.  Two forms:
+//   * whole tiles, 256 / 128 / 64 tokens, one workgroup per compute unit (all 512 registers of a lane, four or eight
+//     activation tiles in LDS): a decoded weight serves up to 256 tokens.  Bound by the matrix cores and by power;
+//   * half tiles, 128 / 96 / 64 tokens (HALF), 256 registers and at most half the LDS, so that TWO workgroups share a
+//     compute unit and one's barriers, waits, decoding and epilogue run under the other's matrix work.  (A tile of 32
+//     would cost what one of 64 does: decoding its weights takes longer than either's products.)
+//     gate/up + down of the Mixtral shape at 128 rows per group 314 + 172 -> 275 + 148 us, of DeepSeek-V2-Lite's at
+//     48 rows per group (two launches before, of the streaming kernel and of whole tiles) 203 -> 134 us.
+// cq_gemm_uses_half_tiles has the rule between the two.
+// XCD-aware remap of the linear workgroup id (ids go round-robin over the 8 XCDs): XCD x takes a contiguous share of
+// each list (neighbours share activations in its L2; equal mix on every XCD), the widest tiles first.  The grid is
+// sized for the worst case; the lists are usually much shorter.
+template <bool F16, int EPI, int OUTK, bool BLK, bool PRE, bool HALF>
+__global__ __launch_bounds__(256, HALF ? 2 : 1) void gemm_large_kernel(const LargeArgs p) {
+  using W = tile_widths<HALF>;
+  constexpr int kDeep = HALF ? 4 : 8;   // pipeline depth of the narrower tiles: less matrix time per step, needs more
+  const int kS1 = p.tail_part ? p.n_tiles[6] : 1;                  // K parts of a tile of the two narrow widths
+  const int kS0 = p.tail_part && p.tail_abs ? p.n_tiles[7] : 1;    // ... of a wide one (launches of few tiles)
   const int xcd = blockIdx.x & 7;
   int slot = blockIdx.x >> 3;
-  if (slot < per256) {
-    const int work = xcd * per256 + slot;
-    if (work >= n256) return;
-    const int item = work / kS256, kz = work - item * kS256;
-    const int tile = item / p.row_tiles, rt = item - tile * p.row_tiles;
+  // work item `slot` of this XCD's share of a list of n items of kS parts each
+  auto item = [&](int n, int kS, int& tile, int& rt, int& kz) {
+    const int work = xcd * ((n + 7) >> 3) + slot;
+    const int per_tile = p.row_tiles * kS;
+    tile = work / per_tile;
+    const int rest = work - tile * per_tile;
+    rt = rest / kS;
+    kz = rest - rt * kS;
+    return work < n;
+  };
+  int tile, rt, kz;
+  const int n0 = p.n_tiles[0] * p.row_tiles * kS0, n1 = p.n_tiles[1] * p.row_tiles * kS1,
+            n2 = p.n_tiles[5] * p.row_tiles * kS1;
+  if (slot < (n0 + 7) >> 3) {
+    if (!item(n0, kS0, tile, rt, kz)) return;
     const int32_t* t = p.tiles + tile * 4;
-    large_tile<F16, EPI, OUTK, 8, 4, BLK, PRE>(p, t[0], t[1], t[2], rt, kz, kS256, t[1]);
+    large_tile<F16, EPI, OUTK, W::w0 / 32, 4, BLK, PRE, HALF>(p, t[0], t[1], t[2], rt, kz, kS0, t[1]);
     return;
   }
-  slot -= per256;
-  if (slot < per128) {
-    const int work = xcd * per128 + slot;
-    if (work >= n128) return;
-    const int item = work / kS, kz = work - item * kS;
-    const int tile = item / p.row_tiles, rt = item - tile * p.row_tiles;
-    const int32_t* t = p.tiles128 + tile * 4;
-    large_tile<F16, EPI, OUTK, 4, 8, BLK, PRE>(p, t[0], t[1], t[2], rt, kz, kS, p.tail_abs ? t[1] : tile * 128);
+  slot -= (n0 + 7) >> 3;
+  if (slot < (n1 + 7) >> 3) {
+    if (!item(n1, kS1, tile, rt, kz)) return;
+    const int32_t* t = p.tiles1 + tile * 4;
+    large_tile<F16, EPI, OUTK, W::w1 / 32, kDeep, BLK, PRE, HALF>(p, t[0], t[1], t[2], rt, kz, kS1,
+                                                                  p.tail_abs ? t[1] : tile * W::w1);
     return;
   }
-  slot -= per128;
-  if (slot < per64) {
-    const int work = xcd * per64 + slot;
-    if (work >= n64) return;
-    const int item = work / kS, kz = work - item * kS;
-    const int tile = item / p.row_tiles, rt = item - tile * p.row_tiles;
-    const int32_t* t = p.tiles64 + tile * 4;
-    large_tile<F16, EPI, OUTK, 2, 8, BLK, PRE>(p, t[0], t[1], t[2], rt, kz, kS,
-                                               p.tail_abs ? t[1] : p.tail_rows128 + tile * 64);
+  slot -= (n1 + 7) >> 3;
+  if (slot < (n2 + 7) >> 3) {
+    if (!item(n2, kS1, tile, rt, kz)) return;
+    const int32_t* t = p.tiles2 + tile * 4;
+    large_tile<F16, EPI, OUTK, W::w2 / 32, kDeep, BLK, PRE, HALF>(p, t[0], t[1], t[2], rt, kz, kS1,
+                                                                  p.tail_abs ? t[1] : p.tail_rows1 + tile * W::w2);
   }
 }
 
-// out[row] += slice 0 + slice 1 + ... of the narrow tiles' K parts, in that order (see LargeArgs::tail_part).
-// blockIdx.y: entry of the 128-token list, then of the 64-token list; blockIdx.x: 1024 columns; blockIdx.z: 8 rows.
+// out[row] += slice 0 + slice 1 + ... of the tiles' K parts, in that order (see LargeArgs::tail_part).
+// blockIdx.y: entry of the w1-token list, of the w2-token list, then (launches of few tiles) of the widest list;
+// blockIdx.x: 1024 columns; blockIdx.z: 8 rows.
 constexpr int kTailSumRows = 8;
-__global__ __launch_bounds__(256) void tail_sum_kernel(const LargeArgs p, int cap128) {
-  // blockIdx.y: entries of the 128-token list, of the 64-token list, then (launches of few tiles) of the 256-token list
-  const int list = (int)blockIdx.y < cap128 ? 0 : (int)blockIdx.y < 2 * cap128 ? 1 : 2;
-  const int j = (int)blockIdx.y - list * cap128;
-  const int kS = list == 2 ? p.n_tiles[7] : p.n_tiles[6];
+__global__ __launch_bounds__(256) void tail_sum_kernel(const LargeArgs p, int cap1) {
+  const int list = (int)blockIdx.y < cap1 ? 1 : (int)blockIdx.y < 2 * cap1 ? 2 : 0;
+  const int j = (int)blockIdx.y - (list == 0 ? 2 : list - 1) * cap1;
+  const int kS = list == 0 ? p.n_tiles[7] : p.n_tiles[6];
   if (kS <= 1) return;
-  if (j >= (list == 0 ? p.n_tiles[1] : list == 1 ? p.n_tiles[5] : p.n_tiles[0])) return;
-  const int32_t* t = (list == 0 ? p.tiles128 : list == 1 ? p.tiles64 : p.tiles) + j * 4;
+  if (j >= p.n_tiles[list == 2 ? 5 : list]) return;
+  const int32_t* t = (list == 0 ? p.tiles : list == 1 ? p.tiles1 : p.tiles2) + j * 4;
   const int mrow0 = t[1], mcnt = t[2];
-  const int row0 = p.tail_abs ? mrow0 : list == 1 ? p.tail_rows128 + j * 64 : j * 128;
+  const int row0 = p.tail_abs ? mrow0 : list == 2 ? p.tail_rows1 + j * p.w2 : j * p.w1;
   const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
   const int r0 = blockIdx.z * kTailSumRows;
   if (c >= p.N || r0 >= mcnt) return;
@@ -507,14 +547,14 @@ __global__ __launch_bounds__(256) void tail_sum_kernel(const LargeArgs p, int ca
 constexpr int narrow_depth(int C) { return C >= 2 ? 4 : 8; }
 template <bool F16, int EPI, int OUTK, bool BLK, bool PRE, int C>
 __global__ __launch_bounds__(256, 2) void gemm_narrow_kernel(const LargeArgs p) {
-  const int n64 = p.n_tiles[5] * p.row_tiles;
-  const int per64 = (n64 + 7) >> 3;
+  const int n_2 = p.n_tiles[5] * p.row_tiles;
+  const int per64 = (n_2 + 7) >> 3;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   if (slot >= per64) return;
   const int work = xcd * per64 + slot;
-  if (work >= n64) return;
+  if (work >= n_2) return;
   const int tile = work / p.row_tiles, rt = work - tile * p.row_tiles;
-  const int32_t* t = p.tiles64 + tile * 4;
+  const int32_t* t = p.tiles2 + tile * 4;
   large_tile<F16, EPI, OUTK, C, narrow_depth(C), BLK, PRE>(p, t[0], t[1], t[2], rt);
 }
 
@@ -550,19 +590,20 @@ __global__ __launch_bounds__(256) void convert_rows_kernel(const void* __restric
   *reinterpret_cast<uint4*>(out + (size_t)m * K + (size_t)c * 8) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-// One workgroup: cut every group with more than `small_max` rows into token tiles of 256 (while more
-// than 128 rows remain), then one of 128 or (up to 64 rows left) 64, in group order (deterministic); the streaming
-// kernel takes the other groups.  counts: [0] 256-wide tiles, [1] 128-wide tiles, [5] 64-wide tiles, [6] K parts of
-// the narrow tiles, [7] K parts of the 256-wide tiles.
+// One workgroup: cut every group with more than `small_max` rows into token tiles of w0 (while more than w1 rows
+// remain), then one of w1 or (up to w2 rows left) w2, in group order (deterministic); the streaming kernel takes the
+// other groups.  counts: [0] w0-wide tiles, [1] w1-wide tiles, [5] w2-wide tiles, [6] K parts of the two narrow
+// widths, [7] K parts of the w0-wide tiles.  at_once: workgroups of the launch that the chip runs at a time.
 __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __restrict__ offsets, int G, int small_max,
                                                            int n_units,
-                                                           int32_t* __restrict__ tiles256, int32_t* __restrict__ tiles128,
-                                                           int32_t* __restrict__ tiles64,
-                                                           int32_t* __restrict__ counts, int split_max, int split_all) {
-  __shared__ int n256[1024], n128[1024], n64[1024];
-  __shared__ int base256, base128, base64;
+                                                           int32_t* __restrict__ tiles0, int32_t* __restrict__ tiles1,
+                                                           int32_t* __restrict__ tiles2,
+                                                           int32_t* __restrict__ counts, int split_max, int split_all,
+                                                           int w0, int w1, int w2, int at_once) {
+  __shared__ int n_0[1024], n_1[1024], n_2[1024];
+  __shared__ int base_0, base_1, base_2;
   const int tid = threadIdx.x;
-  if (tid == 0) { base256 = 0; base128 = 0; base64 = 0; }
+  if (tid == 0) { base_0 = 0; base_1 = 0; base_2 = 0; }
   __syncthreads();
   for (int g0 = 0; g0 < G; g0 += 1024) {
     const int g = g0 + tid;
@@ -571,68 +612,68 @@ __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __rest
       m0 = offsets[g];
       me = offsets[g + 1] - m0;
       if (me > small_max) {
-        a = me / 256;
-        const int rem = me - a * 256;
-        if (rem > 128) ++a; else if (rem > 64) b = 1; else if (rem > 0) b64 = 1;
+        a = me / w0;
+        const int rem = me - a * w0;
+        if (rem > w1) ++a; else if (rem > w2) b = 1; else if (rem > 0) b64 = 1;
       }
     }
-    n256[tid] = a;
-    n128[tid] = b;
-    n64[tid] = b64;
+    n_0[tid] = a;
+    n_1[tid] = b;
+    n_2[tid] = b64;
     __syncthreads();
     if (tid == 0) {  // exclusive prefix in group order
-      int s256 = base256, s128 = base128, s64 = base64;
+      int s_0 = base_0, s_1 = base_1, s_2 = base_2;
       const int n = min(1024, G - g0);
       for (int i = 0; i < n; ++i) {
-        const int x = n256[i], y = n128[i], y2 = n64[i];
-        n256[i] = s256; n128[i] = s128; n64[i] = s64;
-        s256 += x; s128 += y; s64 += y2;
+        const int x = n_0[i], y = n_1[i], y2 = n_2[i];
+        n_0[i] = s_0; n_1[i] = s_1; n_2[i] = s_2;
+        s_0 += x; s_1 += y; s_2 += y2;
       }
-      base256 = s256; base128 = s128; base64 = s64;
+      base_0 = s_0; base_1 = s_1; base_2 = s_2;
     }
     __syncthreads();
     if (g < G && me > small_max) {
-      int at = n256[tid];
+      int at = n_0[tid];
       for (int i = 0; i < a; ++i) {
-        tiles256[(at + i) * 4 + 0] = g;
-        tiles256[(at + i) * 4 + 1] = m0 + i * 256;
-        tiles256[(at + i) * 4 + 2] = min(256, me - i * 256);
-        tiles256[(at + i) * 4 + 3] = 0;
+        tiles0[(at + i) * 4 + 0] = g;
+        tiles0[(at + i) * 4 + 1] = m0 + i * w0;
+        tiles0[(at + i) * 4 + 2] = min(w0, me - i * w0);
+        tiles0[(at + i) * 4 + 3] = 0;
       }
       if (b || b64) {
-        int32_t* t = b ? tiles128 + n128[tid] * 4 : tiles64 + n64[tid] * 4;
+        int32_t* t = b ? tiles1 + n_1[tid] * 4 : tiles2 + n_2[tid] * 4;
         t[0] = g;
-        t[1] = m0 + a * 256;
-        t[2] = me - a * 256;
+        t[1] = m0 + a * w0;
+        t[2] = me - a * w0;
         t[3] = 0;
       }
     }
     __syncthreads();
   }
   if (tid == 0) {
-    counts[0] = base256;
-    counts[1] = base128;
-    counts[5] = base64;
+    counts[0] = base_0;
+    counts[1] = base_1;
+    counts[5] = base_2;
     // [6] K parts of the narrow tiles (split_max > 1: a plain fp32 product with a long K).  The narrow tiles
-    // come last; when there are fewer of them than compute units, the tail of the launch runs on a part of the
+    // come last; when there are fewer of them than the chip runs at a time, the tail of the launch runs on a part of the
     // chip for the length of a whole K loop -- parts of K on more workgroups shorten it.
     {
-      const int narrow = (base128 + base64) * (n_units / 4);
+      const int narrow = (base_1 + base_2) * (n_units / 4);
       int parts = 1;
-      while (parts < split_max && narrow > 0 && narrow * parts * 2 <= 256) parts *= 2;
+      while (parts < split_max && narrow > 0 && narrow * parts * 2 <= at_once) parts *= 2;
       counts[6] = parts;
-      // [7] K parts of the 256-token tiles: a launch of few tiles in all (split_all: its partial sums are kept by
+      // [7] K parts of the widest tiles: a launch of few tiles in all (split_all: its partial sums are kept by
       // sorted row, so any tile can have them) leaves most of the chip idle for a whole K loop otherwise
-      const int all = narrow + base256 * (n_units / 4);
+      const int all = narrow + base_0 * (n_units / 4);
       parts = 1;
-      while (split_all && parts < split_max && base256 > 0 && all * parts * 2 <= 256) parts *= 2;
+      while (split_all && parts < split_max && base_0 > 0 && all * parts * 2 <= at_once) parts *= 2;
       counts[7] = parts;
     }
   }
 }
 
 template <bool F16, int EPI, int OUTK, bool BLK, bool PRE, int C>
-cq_status launch_narrow(const LargeArgs& a, int max128, hipStream_t s) {
+cq_status launch_narrow(const LargeArgs& a, int max1, hipStream_t s) {
   auto kern = gemm_narrow_kernel<F16, EPI, OUTK, BLK, PRE, C>;
   constexpr int lds_epi = 64 * epilogue_row_stride(EPI, OUTK);
   constexpr int lds_loop = narrow_depth(C) * 32 * C * kStepBytes + (BLK ? 8 * kNextTableBytes : 0);
@@ -641,115 +682,138 @@ cq_status launch_narrow(const LargeArgs& a, int max128, hipStream_t s) {
   static std::atomic<bool> configured{false};
   const cq_status st = cq_configure_lds(kern, lds, configured, true);
   if (st != CQ_OK) return st;
-  const long grid = (((long)max128 * a.row_tiles + 7) / 8) * 8;
+  const long grid = (((long)max1 * a.row_tiles + 7) / 8) * 8;
   if (grid <= 0) return CQ_OK;
   const int total = a.K / kStepK;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)((total + a.ksteps - 1) / a.ksteps)), dim3(256), lds, s, a);
   return cq_check_launch();
 }
 
-// narrow: 64 or 32 when the caller knows that no group has more rows than that, else 0
-template <bool F16, int EPI, int OUTK, bool BLK, bool PRE>
-cq_status launch_both(LargeArgs a, const int32_t* t256, const int32_t* t128, const int32_t* counts, int max256,
-                      int max128, int narrow, hipStream_t s) {
-  a.tiles = t256;
-  a.tiles128 = t128;
-  a.tiles64 = t128 + (size_t)max128 * 4;
-  a.n_tiles = counts;
+// narrow: 64 or 32 when the caller knows that no group has more rows than that (block-wise tables), kHalf: half tiles,
+// else 0
+constexpr int kHalf = -1;
+template <bool F16, int EPI, int OUTK, bool BLK, bool PRE, bool HALF>
+cq_status launch_tiles(LargeArgs a, int max0, int max1, hipStream_t s) {
+  auto kern = gemm_large_kernel<F16, EPI, OUTK, BLK, PRE, HALF>;
   constexpr int lds_epi = 64 * epilogue_row_stride(EPI, OUTK);
-  if constexpr (BLK) {
-    if (narrow == 32) return launch_narrow<F16, EPI, OUTK, BLK, PRE, 1>(a, max128, s);
-    if (narrow == 64) return launch_narrow<F16, EPI, OUTK, BLK, PRE, 2>(a, max128, s);
-  }
-  auto kern = gemm_large_kernel<F16, EPI, OUTK, BLK, PRE>;
-  constexpr int lds_loop = kLdsTileBytes + (BLK ? 8 * kNextTableBytes : 0);
+  constexpr int lds_loop = 4 * tile_widths<HALF>::w0 * kStepBytes + (BLK ? 8 * kNextTableBytes : 0);
   constexpr int lds = lds_loop > lds_epi ? lds_loop : lds_epi;
+  static_assert((HALF ? 2 : 1) * lds <= 160 * 1024, "workgroups per compute unit");
+  static_assert(HALF || 8 * tile_widths<HALF>::w1 * kStepBytes <= 4 * tile_widths<HALF>::w0 * kStepBytes, "deep rings fit");
   static std::atomic<bool> configured{false};
   const cq_status st = cq_configure_lds(kern, lds, configured, true);
   if (st != CQ_OK) return st;
-  // worst case of the kernel's per-XCD shares (a group ends in at most one 128- or 64-token tile, but the
-  // two lists round up separately): ceil(n256/8) + ceil(n128/8) + ceil(n64/8) slots on each of 8 XCDs
-  const long w256 = (long)max256 * a.row_tiles * (a.tail_part && a.tail_abs ? kTailSplitMax : 1),
-             w128 = (long)max128 * a.row_tiles * (a.tail_part ? kTailSplitMax : 1);   // (narrow tiles may come in K parts)
-  const long grid = ((w256 + 7) / 8 + (w128 + 7) / 8 + 1) * 8;
+  // worst case of the kernel's per-XCD shares (a group ends in at most one tile of a narrow width, but the
+  // two lists round up separately): ceil(n0/8) + ceil(n1/8) + ceil(n2/8) slots on each of 8 XCDs
+  const long w0 = (long)max0 * a.row_tiles * (a.tail_part && a.tail_abs ? kTailSplitMax : 1),
+             w1 = (long)max1 * a.row_tiles * (a.tail_part ? kTailSplitMax : 1);   // (narrow tiles may come in K parts)
+  const long grid = ((w0 + 7) / 8 + (w1 + 7) / 8 + 1) * 8;
   if (grid <= 0) return CQ_OK;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, s, a);
   return cq_check_launch();
 }
 
+template <bool F16, int EPI, int OUTK, bool BLK, bool PRE>
+cq_status launch_both(LargeArgs a, const int32_t* t0, const int32_t* t1, const int32_t* counts, int max0,
+                      int max1, int narrow, hipStream_t s) {
+  a.tiles = t0;
+  a.tiles1 = t1;
+  a.tiles2 = t1 + (size_t)max1 * 4;
+  a.n_tiles = counts;
+  if constexpr (BLK) {
+    if (narrow == 32) return launch_narrow<F16, EPI, OUTK, BLK, PRE, 1>(a, max1, s);
+    if (narrow == 64) return launch_narrow<F16, EPI, OUTK, BLK, PRE, 2>(a, max1, s);
+  } else {
+    if (narrow == kHalf) return launch_tiles<F16, EPI, OUTK, BLK, PRE, true>(a, max0, max1, s);
+  }
+  return launch_tiles<F16, EPI, OUTK, BLK, PRE, false>(a, max0, max1, s);
+}
+
 template <bool F16, bool BLK, bool PRE>
-cq_status dispatch_large_pre(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t256, const int32_t* t128,
-                             const int32_t* counts, int max256, int max128, int narrow, hipStream_t s) {
+cq_status dispatch_large_pre(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t0, const int32_t* t1,
+                             const int32_t* counts, int max0, int max1, int narrow, hipStream_t s) {
   if (epilogue == CQ_EPI_SWIGLU)
     return out_kind == CQ_OUT_F16
-               ? launch_both<F16, CQ_EPI_SWIGLU, CQ_OUT_F16, BLK, PRE>(a, t256, t128, counts, max256, max128, narrow, s)
-               : launch_both<F16, CQ_EPI_SWIGLU, CQ_OUT_F32, BLK, PRE>(a, t256, t128, counts, max256, max128, narrow, s);
+               ? launch_both<F16, CQ_EPI_SWIGLU, CQ_OUT_F16, BLK, PRE>(a, t0, t1, counts, max0, max1, narrow, s)
+               : launch_both<F16, CQ_EPI_SWIGLU, CQ_OUT_F32, BLK, PRE>(a, t0, t1, counts, max0, max1, narrow, s);
   return out_kind == CQ_OUT_F16
-             ? launch_both<F16, CQ_EPI_NONE, CQ_OUT_F16, BLK, PRE>(a, t256, t128, counts, max256, max128, narrow, s)
-             : launch_both<F16, CQ_EPI_NONE, CQ_OUT_F32, BLK, PRE>(a, t256, t128, counts, max256, max128, narrow, s);
+             ? launch_both<F16, CQ_EPI_NONE, CQ_OUT_F16, BLK, PRE>(a, t0, t1, counts, max0, max1, narrow, s)
+             : launch_both<F16, CQ_EPI_NONE, CQ_OUT_F32, BLK, PRE>(a, t0, t1, counts, max0, max1, narrow, s);
 }
 
 template <bool F16, bool BLK>
-cq_status dispatch_large_blk(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t256, const int32_t* t128,
-                             const int32_t* counts, int max256, int max128, int narrow, hipStream_t s) {
+cq_status dispatch_large_blk(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t0, const int32_t* t1,
+                             const int32_t* counts, int max0, int max1, int narrow, hipStream_t s) {
   return a.prepacked
-             ? dispatch_large_pre<F16, BLK, true>(a, epilogue, out_kind, t256, t128, counts, max256, max128, narrow, s)
-             : dispatch_large_pre<F16, BLK, false>(a, epilogue, out_kind, t256, t128, counts, max256, max128, narrow, s);
+             ? dispatch_large_pre<F16, BLK, true>(a, epilogue, out_kind, t0, t1, counts, max0, max1, narrow, s)
+             : dispatch_large_pre<F16, BLK, false>(a, epilogue, out_kind, t0, t1, counts, max0, max1, narrow, s);
 }
 
 // The two-workgroup kernel for 64-token tiles exists for block-wise tables only (the streaming kernel takes
 // the small groups otherwise).
 template <bool F16>
-cq_status dispatch_large(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t256, const int32_t* t128,
-                         const int32_t* counts, int max256, int max128, int narrow, hipStream_t s) {
+cq_status dispatch_large(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t0, const int32_t* t1,
+                         const int32_t* counts, int max0, int max1, int narrow, hipStream_t s) {
   return a.nblk > 1
-             ? dispatch_large_blk<F16, true>(a, epilogue, out_kind, t256, t128, counts, max256, max128, narrow, s)
-             : dispatch_large_blk<F16, false>(a, epilogue, out_kind, t256, t128, counts, max256, max128, 0, s);
+             ? dispatch_large_blk<F16, true>(a, epilogue, out_kind, t0, t1, counts, max0, max1, narrow, s)
+             : dispatch_large_blk<F16, false>(a, epilogue, out_kind, t0, t1, counts, max0, max1, narrow == kHalf ? kHalf : 0, s);
 }
 
 size_t tile_list_bytes(int G, int M_total) {
-  int c256, c128;
-  cq_large_tile_caps(G, M_total, &c256, &c128);
-  return cq_align_up(256 + ((size_t)(c256 + 2 * c128) * 4) * sizeof(int32_t), 256);
+  int c0, c1;
+  cq_large_tile_caps(G, M_total, &c0, &c1);
+  return cq_align_up(256 + ((size_t)(c0 + 2 * c1) * 4) * sizeof(int32_t), 256);
 }
 
 }  // namespace
 
 // Upper bounds on the tile counts for M_total rows in G groups (host side; sizes on the device vary).
-void cq_large_tile_caps(int G, int M_total, int* cap256, int* cap128) {
-  *cap256 = M_total / 129 + 1;   // every 256-wide tile covers more than 128 rows
-  *cap128 = G < M_total ? G : M_total;  // at most one per group
-  if (*cap128 < 1) *cap128 = 1;
+void cq_large_tile_caps(int G, int M_total, int* cap0, int* cap1) {
+  *cap0 = M_total / (tile_widths<true>::w1 + 1) + 1;   // every widest tile covers more than w1 rows (96, or 128)
+  *cap1 = G < M_total ? G : M_total;  // at most one per group
+  if (*cap1 < 1) *cap1 = 1;
 }
 
-// Narrow tiles of a plain fp32 product with a long K may be cut into K parts (LargeArgs::tail_part).
+// The tiles of a plain fp32 product with a long K may be cut into K parts (LargeArgs::tail_part).
 bool cq_gemm_large_tail_split(const cq_codebook_weights* W, int epilogue, int out_kind) {
   return epilogue == CQ_EPI_NONE && out_kind == CQ_OUT_F32 && cq_tables_per_row(W) == 1 &&
          W->K / kStepK >= kTailMinSteps;
 }
 
+// Whole or half tiles.  The weights are decoded once per tile of tokens: with a long K (prologue and epilogue do not
+// count) and several 256-token tiles per group, whole tiles save more than two workgroups per compute unit gain
+// (Mixtral shape, K = 4096 and 14336: 1645 us per layer on half tiles against 1604 at 512 rows per group, 961 against
+// 983 at 256, 622 against 691 at 128; K = 2048 / 1408 and 2048 / 768: 823 against 888 at 496 rows per group, 618 against
+// 674 at 256).  Half tiles address the rows of A with 32-bit byte offsets.
+// a_rows: number of rows of A, 0 if unknown.
+bool cq_gemm_uses_half_tiles(const cq_codebook_weights* W, int M_total, long a_rows) {
+  if (cq_tables_per_row(W) > 1 || a_rows <= 0 || a_rows * W->K * 2 >= (1L << 32)) return false;
+  return W->K <= 2048 || M_total < 384L * W->G;
+}
+
 namespace {
-// rows of a slice of partial sums: a slot per possible narrow tile (128 + 64 rows per group), or the launch's own
+// rows of a slice of partial sums: a slot per possible narrow tile (w1 + w2 rows per group), or the launch's own
 // rows when those are fewer
-int tail_slice_rows(int G, int M_total, bool* absolute) {
-  int c256, c128;
-  cq_large_tile_caps(G, M_total, &c256, &c128);
-  *absolute = M_total < c128 * 192;
-  return *absolute ? M_total : c128 * 192;
+int tail_slice_rows(int G, int M_total, bool half, bool* absolute) {
+  int c0, c1;
+  cq_large_tile_caps(G, M_total, &c0, &c1);
+  const int slots = c1 * (half ? tile_widths<true>::w1 + tile_widths<true>::w2 : tile_widths<false>::w1 + tile_widths<false>::w2);
+  *absolute = M_total < slots;
+  return *absolute ? M_total : slots;
 }
 // partial sums of those K parts: [kTailSplitMax - 1][rows of a slice][N] fp32
-size_t tail_part_bytes(int G, int M_total, int N) {
+size_t tail_part_bytes(int G, int M_total, int N, bool half) {
   bool absolute;
-  const int rows = tail_slice_rows(G, M_total, &absolute);
+  const int rows = tail_slice_rows(G, M_total, half, &absolute);
   return cq_align_up((size_t)(kTailSplitMax - 1) * rows * N * sizeof(float), 256);
 }
 }  // namespace
 
 // tile lists, plus (tail_N > 0: a plain fp32 product of N columns whose K is long enough) the partial sums of
-// the narrow tiles' K parts, plus (with_conversion) room for the activations as 16-bit rows [M_total, K]
+// the tiles' K parts, plus (with_conversion) room for the activations as 16-bit rows [M_total, K]
 size_t cq_gemm_large_workspace_bytes(int G, int M_total, int K, bool with_conversion, int tail_N) {
   size_t n = tile_list_bytes(G, M_total);
-  if (tail_N > 0 && K / kStepK >= kTailMinSteps) n += tail_part_bytes(G, M_total, tail_N);
+  if (tail_N > 0 && K / kStepK >= kTailMinSteps) n += tail_part_bytes(G, M_total, tail_N, false);   // (whole tiles have the more slots)
   if (with_conversion) n += cq_align_up((size_t)M_total * K * sizeof(uint16_t), 256);
   return n;
 }
@@ -764,29 +828,31 @@ bool cq_gemm_large_supported(const cq_codebook_weights* W) {
 
 // Builds the work lists in `workspace` (first step of a launch that uses the large-tile kernel).
 cq_status cq_gemm_build_lists(const cq_codebook_weights* W, const int32_t* group_offsets, int M_total, int small_max,
-                              void* workspace, hipStream_t s, bool tail_split) {
-  int cap256, cap128;
-  cq_large_tile_caps(W->G, M_total, &cap256, &cap128);
+                              void* workspace, hipStream_t s, bool tail_split, bool half) {
+  int cap0, cap1;
+  cq_large_tile_caps(W->G, M_total, &cap0, &cap1);
   bool split_all = false;
-  if (tail_split) (void)tail_slice_rows(W->G, M_total, &split_all);   // partial sums by sorted row: any tile may split
+  if (tail_split) (void)tail_slice_rows(W->G, M_total, half, &split_all);   // partial sums by sorted row: any tile may split
   int32_t* counts = (int32_t*)workspace;
-  int32_t* t256 = counts + 64;
-  int32_t* t128 = t256 + (size_t)cap256 * 4;
-  int32_t* t64 = t128 + (size_t)cap128 * 4;
+  int32_t* t0 = counts + 64;
+  int32_t* t1 = t0 + (size_t)cap0 * 4;
+  int32_t* t2 = t1 + (size_t)cap1 * 4;
   hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(1024), 0, s, group_offsets, W->G, small_max, W->N / 64,
-                     t256, t128, t64, counts, tail_split ? kTailSplitMax : 1, split_all ? 1 : 0);
+                     t0, t1, t2, counts, tail_split ? kTailSplitMax : 1, split_all ? 1 : 0,
+                     half ? tile_widths<true>::w0 : tile_widths<false>::w0, half ? tile_widths<true>::w1 : tile_widths<false>::w1,
+                     tile_widths<true>::w2, kAtOnce[half]);
   return cq_check_launch();
 }
 
 // the lists must have been built by cq_gemm_build_lists in the same workspace
 cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int a_kind, const float* row_scale,
                                const int32_t* row_gather, const int32_t* group_offsets, int M_total, int small_max,
-                               int epilogue, void* out, int out_kind, void* workspace, hipStream_t s) {
-  int cap256, cap128;
-  cq_large_tile_caps(W->G, M_total, &cap256, &cap128);
+                               int epilogue, void* out, int out_kind, void* workspace, hipStream_t s, bool half) {
+  int cap0, cap1;
+  cq_large_tile_caps(W->G, M_total, &cap0, &cap1);
   int32_t* counts = (int32_t*)workspace;
-  int32_t* t256 = counts + 64;
-  int32_t* t128 = t256 + (size_t)cap256 * 4;
+  int32_t* t0 = counts + 64;
+  int32_t* t1 = t0 + (size_t)cap0 * 4;
   LargeArgs a;
   a.idx = W->prepacked ? (const uint8_t*)W->prepacked : W->idx;
   a.cent = W->cent;
@@ -800,8 +866,8 @@ cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int 
   a.out = out;
   a.out_ld = epilogue == CQ_EPI_SWIGLU ? W->N / 2 : W->N;
   a.tiles = nullptr;
-  a.tiles128 = nullptr;
-  a.tiles64 = nullptr;
+  a.tiles1 = nullptr;
+  a.tiles2 = nullptr;
   a.n_tiles = nullptr;
   a.row_tiles = W->N / kLargeRows;
   a.nblk = cq_tables_per_row(W);
@@ -816,15 +882,17 @@ cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int 
   size_t ws_off = tile_list_bytes(W->G, M_total);
   const bool tail = cq_gemm_large_tail_split(W, epilogue, out_kind);
   a.tail_part = nullptr;
-  a.tail_rows128 = cap128 * 128;
+  a.w1 = half ? tile_widths<true>::w1 : tile_widths<false>::w1;
+  a.w2 = tile_widths<true>::w2;
+  a.tail_rows1 = cap1 * a.w1;
   {
     bool absolute;
-    a.tail_rows = tail_slice_rows(W->G, M_total, &absolute);
+    a.tail_rows = tail_slice_rows(W->G, M_total, half, &absolute);
     a.tail_abs = absolute ? 1 : 0;
   }
   if (tail) {
     a.tail_part = (float*)((char*)workspace + ws_off);
-    ws_off += tail_part_bytes(W->G, M_total, W->N);
+    ws_off += tail_part_bytes(W->G, M_total, W->N, half);
   }
   if (a_kind == CQ_A_INT8_CODES || a_kind == CQ_A_F32) {
     // 16-bit copy of the rows in sorted order (the gather is applied here)
@@ -842,16 +910,18 @@ cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int 
   }
   const bool f16 = a_kind == CQ_A_F16 || a_kind == CQ_A_F32;
   // with so few rows in all, every group has at most that many: one narrow tile each
-  const int narrow = M_total <= 32 ? 32 : M_total <= 64 ? 64 : 0;
-  const cq_status st = f16 ? dispatch_large<true>(a, epilogue, out_kind, t256, t128, counts, cap256, cap128, narrow, s)
-                           : dispatch_large<false>(a, epilogue, out_kind, t256, t128, counts, cap256, cap128, narrow, s);
+  const int narrow = half ? kHalf : M_total <= 32 ? 32 : M_total <= 64 ? 64 : 0;
+  // (for the grid: every widest tile of a launch of whole tiles covers more than 128 rows)
+  const int max0 = half ? cap0 : M_total / (tile_widths<false>::w1 + 1) + 1;
+  const cq_status st = f16 ? dispatch_large<true>(a, epilogue, out_kind, t0, t1, counts, max0, cap1, narrow, s)
+                           : dispatch_large<false>(a, epilogue, out_kind, t0, t1, counts, max0, cap1, narrow, s);
   if (st != CQ_OK || !tail) return st;
   // (a launch of a few dozen workgroups that return at once when the builder chose not to split)
-  a.tiles = t256;
-  a.tiles128 = t128;
-  a.tiles64 = t128 + (size_t)cap128 * 4;
+  a.tiles = t0;
+  a.tiles1 = t1;
+  a.tiles2 = t1 + (size_t)cap1 * 4;
   a.n_tiles = counts;
-  hipLaunchKernelGGL(tail_sum_kernel, dim3((W->N / 4 + 255) / 256, 2 * cap128 + (a.tail_abs ? cap256 : 0), (a.tail_abs ? 256 : 128) / kTailSumRows),
-                     dim3(256), 0, s, a, cap128);
+  hipLaunchKernelGGL(tail_sum_kernel, dim3((W->N / 4 + 255) / 256, 2 * cap1 + (a.tail_abs ? cap0 : 0), (half ? tile_widths<true>::w0 : tile_widths<false>::w0) / kTailSumRows),
+                     dim3(256), 0, s, a, cap1);
   return cq_check_launch();
 }

@@ -117,7 +117,8 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
                                   const float* row_scale, const int32_t* row_gather,
                                   const int32_t* group_offsets, int M_total, int epilogue,
                                   void* out, int out_kind, void* workspace, hipStream_t s, int* ksplit_left,
-                                  const cq_route_fuse* route = nullptr, int max_group_rows = 0);
+                                  const cq_route_fuse* route = nullptr, int max_group_rows = 0, long a_rows = 0);
+// a_rows: number of rows of A where row_gather is given and the caller knows it, else 0.
 // max_group_rows (here and below): an upper bound on the rows of any one group if the caller has one (the
 // layer: a group has at most one row per token), else 0 = M_total.
 size_t cq_gemm_partials_bytes(const cq_codebook_weights* W, int M_total, int epilogue, int max_group_rows = 0);
@@ -153,9 +154,11 @@ bool cq_gemm_large_tail_split(const cq_codebook_weights* W, int epilogue, int ou
 // work lists of the large-tile kernel (device-built: group sizes are device data), of the groups with more than
 // small_max rows
 cq_status cq_gemm_build_lists(const cq_codebook_weights* W, const int32_t* group_offsets, int M_total, int small_max,
-                              void* workspace, hipStream_t s, bool tail_split = false);
+                              void* workspace, hipStream_t s, bool tail_split, bool half);
 cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int a_kind, const float* row_scale,
                                const int32_t* row_gather, const int32_t* group_offsets, int M_total, int small_max,
-                               int epilogue, void* out, int out_kind, void* workspace, hipStream_t s);
+                               int epilogue, void* out, int out_kind, void* workspace, hipStream_t s, bool half);
+// whether a launch of it runs half tiles (lists and product alike); a_rows: rows of A, 0 if unknown
+bool cq_gemm_uses_half_tiles(const cq_codebook_weights* W, int M_total, long a_rows);
 
 #endif  // CQ_INTERNAL_H_

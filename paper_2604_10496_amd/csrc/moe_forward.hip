@@ -213,7 +213,7 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
   st = cq_gemm_codebook_launch(&L->gate_up, bf16_codes ? (const void*)Q16 : (const void*)Q,
                                bf16_codes ? CQ_A_BF16 : CQ_A_INT8_CODES, scale, src_token, offsets, M, CQ_EPI_SWIGLU,
                                Hbuf, L->h_bits ? CQ_OUT_F32 : CQ_OUT_F16, scratch, hs, nullptr,
-                               fuse_route ? &route : nullptr, T);
+                               fuse_route ? &route : nullptr, T, T);
   if (st != CQ_OK) return st;
   if (!mark(3)) return CQ_ERR_HIP;
   int down_splits = 1;  // > 1: the down projection left K-split partial sums in the scratch area

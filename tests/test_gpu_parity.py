@@ -506,6 +506,37 @@ def test_gemm_streaming_workgroups_by_active_groups(B, G, N, K, rows, prepacked)
                 assert np.array_equal(out[at].astype(np.float64), ref), f"group {g}"
 
 
+@pytest.mark.parametrize("gathered", [False, True])
+@pytest.mark.parametrize("N,K,counts", [
+    (512, 256, [1, 32, 33, 64, 65, 96, 97, 128, 129, 0, 192, 193, 225, 257]),   # half tiles: edges of the three widths
+    (256, 4096, [96, 65, 0, 130, 31, 1]),        # long K, 28 rows per group and more: no streaming launch
+    (256, 4096, [27, 40, 5, 33]),                # ... fewer: both launches
+    (256, 8192, [128, 97, 64, 200, 1]),          # K parts of all three widths
+    (256, 4096, [385, 513, 300]),                # 384 rows per group and more: whole tiles, small groups included
+    (256, 4096, [1200, 1, 20]),
+])
+def test_gemm_tile_widths(B, N, K, counts, gathered):
+    """Rows of a group around every tile width of the large-tile kernel, in both of its forms (half tiles need to know
+    the number of rows of a gathered operand: a gathered f16 operand of a stand-alone call takes whole tiles).  Exact
+    integers: codes of up to 15 and centroids of up to 8 over K <= 8192 stay below 2^24."""
+    rng = np.random.default_rng(N + K + len(counts))
+    G, M = len(counts), sum(counts)
+    table = synth.f32_to_bf16_bits(np.arange(16, dtype=np.float32) - 8.0)
+    idx, cent = _rand_weights(rng, G, N, K, cent=np.broadcast_to(table, (G, N, 16)).copy())
+    codes = rng.integers(-15, 16, size=(M, K)).astype(np.int8)
+    gather = rng.permutation(M).astype(np.int32) if gathered else np.arange(M, dtype=np.int32)
+    off = _group_offsets(counts)
+    W = B.DeviceCodebook(idx, cent)
+    for a_kind, acts in ((B.CQ_A_INT8_CODES, codes), (B.CQ_A_F16, codes.astype(np.float16))):
+        out = B.cq_codebook_grouped_gemm(W, _dev(acts), a_kind, None, _dev(gather) if gathered else None, _dev(off), M,
+                                         B.CQ_EPI_NONE, B.CQ_OUT_F32).cpu().numpy()
+        for g in range(G):
+            at = slice(off[g], off[g + 1])
+            if counts[g]:
+                ref = O.codebook_matmul(codes[gather[at]].astype(np.float64), idx[g], cent[g])
+                assert np.array_equal(out[at].astype(np.float64), ref), f"group {g} ({counts[g]} rows)"
+
+
 @pytest.mark.parametrize("counts,n_extra", [
     ([8, 12, 0, 5, 16, 1, 9, 7], 0),         # up to 8 tokens and 9..16 tokens: the two forms of the pipelined loop
     ([17, 32, 3, 20, 0, 25, 16, 9], 0),      # 17..32 rows: the third form
