@@ -78,10 +78,11 @@ cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H,
 
 // X_R = X R on f16 matrix cores from a split copy of R (cq_rotation_split), accurate to about fp32
 bool cq_rotate_split_supported(int T, int H);
-bool cq_rotate_split_preferred(int T, int H);  // supported, and enough tiles to beat the fp32 kernel
-size_t cq_rotate_split_workspace_bytes(int T, int H);
-cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, float* XR_out, void* workspace,
-                                 hipStream_t s);
+bool cq_rotate_split_preferred(int T, int H);  // the layer's choice between it and the fp32 kernel
+int cq_rotate_split_parts(int T, int H);       // K parts of the layer's rotation
+size_t cq_rotate_split_workspace_bytes(int T, int H);   // of the launch, without partial sums
+cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, float* XR_out,
+                                 void* workspace, hipStream_t s);
 
 // online-Hadamard variant: h' = h H / sqrt(I) per row, then integer codes (int8 and/or bf16 copies) and scales
 bool cq_hadamard_supported(int I);

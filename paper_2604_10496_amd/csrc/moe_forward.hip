@@ -57,13 +57,20 @@ cq_status validate_layer(const cq_layer* L, int T) {
 // Many tokens and a split copy of R at hand: the rotation runs on the f16 matrix cores.
 bool use_split_rotation(const cq_layer* L, int T) { return L->R_split && cq_rotate_split_preferred(T, L->H); }
 
+// its partial sums, in front of the launch's own workspace (0: one part, written to X_R)
+size_t split_partials_bytes(int parts, int T, int H) {
+  return parts > 1 ? cq_align_up((size_t)parts * T * H * sizeof(float), 256) : 0;
+}
+
 // Batches large enough for the large-tile product get the codes a second time as bf16, so that staging
 // them into LDS is a plain copy.
 bool use_bf16_codes(const cq_layer* L, int T) {
   return cq_gemm_uses_large_tiles(&L->gate_up, (int)((long)T * (L->top_k + L->S)), CQ_EPI_SWIGLU, T);
 }
 
-void make_layout(const cq_layer* L, int T, cq_moe_layout* o) {
+// rot_parts: K parts of the rotation on the f16 matrix cores.  available: bytes of the workspace at hand; one that was
+// sized for another batch and is too small for the parts that are best gets fewer of them.
+void make_layout(const cq_layer* L, int T, cq_moe_layout* o, int* rot_parts, size_t available = ~(size_t)0) {
   const size_t M = (size_t)T * (L->top_k + L->S), A = (size_t)T * L->top_k;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -88,13 +95,9 @@ void make_layout(const cq_layer* L, int T, cq_moe_layout* o) {
   o->HQ = take(L->h_bits ? M * L->I : 0);
   o->HQ16 = take(hq16 ? M * L->I * 2 : 0);
   o->hscale = take(L->h_bits ? M * 4 : 0);
-  size_t scratch = cq_rotate_quant_workspace_bytes(T, L->H);
+  size_t scratch = 0;
   const size_t r = cq_route_permute_workspace_bytes(T, L->H, L->E, L->top_k);
   if (r > scratch) scratch = r;
-  if (use_split_rotation(L, T)) {
-    const size_t x = cq_rotate_split_workspace_bytes(T, L->H);
-    if (x > scratch) scratch = x;
-  }
   // the layer feeds both products 16-bit operands (bf16 codes, f16 h): tile lists only
   if (use_bf16_codes(L, T)) {
     const size_t g1 = cq_gemm_large_workspace_bytes(L->gate_up.G, (int)M, L->gate_up.K, false);
@@ -106,6 +109,22 @@ void make_layout(const cq_layer* L, int T, cq_moe_layout* o) {
       g2 += cq_gemm_large_workspace_bytes(L->down.G, (int)M, L->down.K, false, L->down.N);
     if (g2 > scratch) scratch = g2;
   }
+  const size_t fp32_rotation = cq_rotate_quant_workspace_bytes(T, L->H);
+  *rot_parts = 1;
+  if (use_split_rotation(L, T)) {
+    // as many K parts as fill the chip -- but a batch that fits the library's own array with the fp32 rotation's
+    // partial sums fits it with these as well (fewer parts, then)
+    const size_t fixed = cq_rotate_split_workspace_bytes(T, L->H);
+    auto total = [&](size_t bytes) { return off + cq_align_up(bytes > scratch ? bytes : scratch, 256); };
+    size_t limit = total(fp32_rotation) <= CQ_STATIC_SCRATCH_BYTES ? (size_t)CQ_STATIC_SCRATCH_BYTES : ~(size_t)0;
+    if (available < limit) limit = available;
+    *rot_parts = cq_rotate_split_parts(T, L->H);
+    while (*rot_parts > 1 && total(fixed + split_partials_bytes(*rot_parts, T, L->H)) > limit) *rot_parts /= 2;
+    const size_t x = fixed + split_partials_bytes(*rot_parts, T, L->H);
+    if (x > scratch) scratch = x;
+  } else if (fp32_rotation > scratch) {
+    scratch = fp32_rotation;
+  }
   o->scratch = take(scratch);
   o->total = off;
 }
@@ -115,7 +134,8 @@ void make_layout(const cq_layer* L, int T, cq_moe_layout* o) {
 extern "C" size_t cq_moe_workspace_bytes(const cq_layer* L, int T) {
   if (validate_layer(L, T) != CQ_OK) return 0;
   cq_moe_layout lay;
-  make_layout(L, T, &lay);
+  int rot_parts;
+  make_layout(L, T, &lay, &rot_parts);
   return lay.total;
 }
 
@@ -123,7 +143,8 @@ extern "C" cq_status cq_moe_workspace_layout(const cq_layer* L, int T, cq_moe_la
   if (!out) return CQ_ERR_NULL;
   const cq_status st = validate_layer(L, T);
   if (st != CQ_OK) return st;
-  make_layout(L, T, out);
+  int rot_parts;
+  make_layout(L, T, out, &rot_parts);
   return CQ_OK;
 }
 
@@ -136,7 +157,8 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
   if (st != CQ_OK) return st;
   if (!X || !Y) return CQ_ERR_NULL;
   cq_moe_layout lay;
-  make_layout(L, T, &lay);
+  int rot_parts;
+  make_layout(L, T, &lay, &rot_parts, workspace_bytes);
   if (!workspace || workspace_bytes < lay.total) return CQ_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   float* XR = (float*)(ws + lay.XR);
@@ -157,6 +179,20 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
   hipStream_t hs = (hipStream_t)stream;
   auto mark = [&](int i) -> bool { return !ev || hipEventRecord(ev[i], hs) == hipSuccess; };
 
+  // a1: X_R as `parts` partial sums at `part`
+  auto rotate = [&](int* parts, float** part) {
+    if (use_split_rotation(L, T)) {
+      *parts = rot_parts;
+      *part = rot_parts > 1 ? (float*)scratch : XR;
+      return cq_rotate_split_launch(X, L->R_split, T, L->H, rot_parts, *part,
+                                    (char*)scratch + split_partials_bytes(rot_parts, T, L->H), hs);
+    }
+    const cq_gemm_f32_plan p = cq_gemm_f32_make_plan(T, L->H, L->H);
+    *parts = p.ksplit;
+    *part = p.ksplit > 1 ? (float*)scratch : XR;
+    return cq_gemm_f32_launch(X, L->R, 0, T, L->H, L->H, p, *part, nullptr, 0, hs);
+  };
+
   if (!mark(0)) return CQ_ERR_HIP;
   const bool bf16_codes = use_bf16_codes(L, T);
   bool fuse_route = false;   // a5 folded into the gate/up launch (decode-sized batches)
@@ -173,9 +209,9 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
   } else if (cq_front_small_supported(T, L->H, L->E, L->top_k)) {
     // decode-sized batch: the rotation; one launch for quantization and logits; one for top-k and grouping
     // (the second stage boundary therefore falls between the rotation and everything else)
-    const cq_gemm_f32_plan p = cq_gemm_f32_make_plan(T, L->H, L->H);
-    float* part = p.ksplit > 1 ? (float*)scratch : XR;
-    st = cq_gemm_f32_launch(X, L->R, 0, T, L->H, L->H, p, part, nullptr, 0, hs);
+    int parts;
+    float* part;
+    st = rotate(&parts, &part);
     if (st != CQ_OK) return st;
     if (!mark(1)) return CQ_ERR_HIP;
     // when the gate/up launch can do the grouping itself, the front launch also selects the experts and
@@ -183,7 +219,7 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     fuse_route = cq_gemm_can_fuse_route(&L->gate_up, T, L->E, L->S, L->top_k, CQ_EPI_SWIGLU);
     // (the front launch selects the experts whenever a launch that only groups can follow it)
     const bool front_topk = fuse_route || cq_group_small_supported(T, L->E, L->top_k);
-    st = cq_front_small_launch(part, p.ksplit, T, L->H, L->act_bits, L->Wr, L->bias, L->E, XR, Q, Q16, scale, logits,
+    st = cq_front_small_launch(part, parts, T, L->H, L->act_bits, L->Wr, L->bias, L->E, XR, Q, Q16, scale, logits,
                                L->top_k, front_topk ? ids : nullptr, front_topk ? tw : nullptr, hs);
     if (st != CQ_OK) return st;
     if (!fuse_route) {
@@ -195,9 +231,11 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     if (!mark(2)) return CQ_ERR_HIP;
   } else {
     if (use_split_rotation(L, T)) {
-      st = cq_rotate_split_launch(X, L->R_split, T, L->H, XR, scratch, hs);
+      int parts;
+      float* part;
+      st = rotate(&parts, &part);
       if (st != CQ_OK) return st;
-      st = cq_quantize_launch(XR, 1, T, L->H, L->act_bits, XR, Q, Q16, scale, nullptr, hs);
+      st = cq_quantize_launch(part, parts, T, L->H, L->act_bits, XR, Q, Q16, scale, nullptr, hs);
     } else {
       st = cq_rotate_quant_ex(X, L->R, T, L->H, L->act_bits, XR, Q, Q16, scale, scratch, scratch_bytes, stream);
     }
@@ -255,7 +293,8 @@ extern "C" cq_status cq_moe_forward_static(const cq_layer* L, const float* X, in
   if (st != CQ_OK) return st;
   if (!X || !Y) return CQ_ERR_NULL;
   cq_moe_layout lay;
-  make_layout(L, T, &lay);
+  int rot_parts;
+  make_layout(L, T, &lay, &rot_parts);
   if (lay.total > (size_t)CQ_STATIC_SCRATCH_BYTES) return CQ_ERR_WORKSPACE;  // batch too large for the array
   void* ws = nullptr;
   st = static_scratch(&ws);

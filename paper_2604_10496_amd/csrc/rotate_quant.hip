@@ -123,6 +123,22 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   }
 }
 
+// Four columns of row t of the sum of ksplit partial matrices, in ascending order; the loads are requested together,
+// seven at a time (clamped to the last one: loaded again, not added).
+__device__ __forceinline__ float4 sum_partials(const float* part, int ksplit, int T, int t, int H, int c) {
+  float4 v = *reinterpret_cast<const float4*>(part + (size_t)t * H + c);
+  for (int z0 = 1; z0 < ksplit; z0 += 7) {
+    float4 p[7];
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+      p[i] = *reinterpret_cast<const float4*>(part + ((size_t)min(z0 + i, ksplit - 1) * T + t) * H + c);
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+      if (z0 + i < ksplit) { v.x += p[i].x; v.y += p[i].y; v.z += p[i].z; v.w += p[i].w; }
+  }
+  return v;
+}
+
 // Few tokens: a row is spread over several workgroups.  Pass 1 reduces the K-split partials in a fixed
 // order, keeps X_R and folds the chunk maximum into amax_bits[t] with an integer atomic max (the bit
 // pattern of a non-negative float orders like the float, and a maximum does not depend on the order of
@@ -134,11 +150,7 @@ __global__ __launch_bounds__(256) void reduce_amax_kernel(const float* part, int
   const int c = (blockIdx.x * 256 + tid) * 4;
   float amax = 0.f;
   if (c < H) {
-    float4 v = *reinterpret_cast<const float4*>(part + (size_t)t * H + c);
-    for (int z = 1; z < ksplit; ++z) {
-      const float4 p = *reinterpret_cast<const float4*>(part + ((size_t)z * T + t) * H + c);
-      v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-    }
+    const float4 v = sum_partials(part, ksplit, T, t, H, c);
     if (!in_place) *reinterpret_cast<float4*>(XR + (size_t)t * H + c) = v;
     amax = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
   }
@@ -187,11 +199,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float* part, int ks
   float amax = 0.f;
   float* xr = XR + (size_t)t * H;
   for (int c = tid * 4; c < H; c += 256 * 4) {
-    float4 v = *reinterpret_cast<const float4*>(part + (size_t)t * H + c);
-    for (int z = 1; z < ksplit; ++z) {
-      const float4 p = *reinterpret_cast<const float4*>(part + ((size_t)z * T + t) * H + c);
-      v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-    }
+    const float4 v = sum_partials(part, ksplit, T, t, H, c);
     if (!in_place) *reinterpret_cast<float4*>(xr + c) = v;
     amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
   }

@@ -14,7 +14,8 @@
 //
 // Kernel: workgroup tile 256 output columns x 128 tokens, four wavefronts, each owning 64 columns (as
 // MFMA "A" rows, two blocks of 32) and all 128 tokens (2 x 4 accumulator blocks of 32x32).  R fragments
-// go from global memory (L2) straight into registers, one step (64 k) ahead; token tiles (both halves)
+// go from global memory (L2) straight into registers, one step (64 k) ahead
+// (two steps ahead, with 64 more registers, was measured: no faster, so it is not their latency that bounds the loop); token tiles (both halves)
 // arrive by direct global->LDS loads, four steps deep.
 #include "cq_internal.h"
 #include "cq_async.h"
@@ -104,10 +105,12 @@ struct RotArgs {
   const uint16_t* Xh;      // [T, K] f16
   const uint16_t* Xl;      // [T, K] f16 (times 2^11)
   const float* row_pow2;   // [T]
-  float* XR;               // [T, N] fp32
+  float* XR;               // [T, N] fp32, or (K parts) partial sums [parts][T][N]
   int T, N, K;
   int row_tiles;           // N / 256
-  int n_work;              // token tiles x row tiles
+  int tok_tiles;           // ceil(T / 128)
+  int ksteps;              // K steps (of 64) per K part, a multiple of four
+  int n_work;              // token tiles x row tiles x K parts
 };
 
 // pairs of f16 times 2^11 (exact: an exponent shift)
@@ -135,17 +138,19 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
   const int per = (p.n_work + 7) >> 3;
   const int work = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= per || work >= p.n_work) return;
-  const int tile = work / p.row_tiles, rt = work - tile * p.row_tiles;
+  // (the token tiles of a K part and a column tile follow each other: they share its piece of R)
+  const int rest = work / p.tok_tiles, tile = work - rest * p.tok_tiles;
+  const int kz = rest / p.row_tiles, rt = rest - kz * p.row_tiles;
   const int mrow0 = tile * kTok, mcnt = min(kTok, p.T - mrow0);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r32 = lane & 31, g2 = lane >> 5;
   const int N = p.N, K = p.K;
-  const int nS = K / kStepK, nJ = K / 16;
+  const int nS = p.ksteps, sb = kz * p.ksteps, nJ = K / 16;   // this workgroup's K steps: sb .. sb + nS - 1
   // this wavefront's two column blocks: nb0, nb0 + 1.  Fragment (rb, sub-step j, plane pl) of lane l is at
   // Rs + (((nb0 + rb)*nJ + j)*2 + pl)*1024 + 16 l: a uniform base, the lane offset, an immediate.
   const int nb0 = __builtin_amdgcn_readfirstlane((rt * kCols + wave * 64) / 32);
-  const uint8_t* wbase = p.Rs + (size_t)nb0 * nJ * 2048;
+  const uint8_t* wbase = p.Rs + ((size_t)nb0 * nJ + (size_t)sb * 4) * 2048;
   const size_t rbstride = (size_t)nJ * 2048;
   const uint32_t lane16 = (uint32_t)lane * 16;
 
@@ -161,8 +166,8 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
     const int chunk = (lane & 7) ^ ((tok >> 1) & 7);
     aoff[i] = (row * (uint32_t)K + (uint32_t)chunk * 8) * 2;
   }
-  const uint8_t* xh = reinterpret_cast<const uint8_t*>(p.Xh);
-  const uint8_t* xl = reinterpret_cast<const uint8_t*>(p.Xl);
+  const uint8_t* xh = reinterpret_cast<const uint8_t*>(p.Xh) + (size_t)sb * kStepBytes;
+  const uint8_t* xl = reinterpret_cast<const uint8_t*>(p.Xl) + (size_t)sb * kStepBytes;
   const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(wave * 32 * kStepBytes);
   auto fetch_tile_part = [&](int s, int buf, int i) {  // tokens 32w + 8i .. +7 of step s, both planes
     const size_t o = (size_t)s * kStepBytes;
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
       const int tok = pass * 64 + tl;
       if (tok < mcnt) {
         const uint32_t at = (uint32_t)tl * kOutStride + (uint32_t)pc * 16;
-        float* dst = p.XR + (size_t)(mrow0 + tok) * N + (size_t)rt * kCols + pc * 4;
+        float* dst = p.XR + ((size_t)kz * p.T + mrow0 + tok) * N + (size_t)rt * kCols + pc * 4;
         *reinterpret_cast<cq_v4u*>(dst) = *reinterpret_cast<const lds_v4u*>((uintptr_t)at);
       }
     }
@@ -326,10 +331,29 @@ bool cq_rotate_split_supported(int T, int H) {
   return H % 256 == 0 && H >= 256 && T >= 256 && (long)T * H * 2 < (1L << 32);
 }
 
-// The tile grid must be able to fill a good part of the chip: below that the fp32 kernel, which splits K
-// over workgroups, is faster (measured: T = 512, H = 2048 -> 32 tiles: 72 us against 53 us).
+// K parts of the layer's rotation: the tiles of 128 tokens x 256 columns are cut along K until they fill the chip, in
+// parts of whole rounds of the pipeline (four steps, 256 k) that are powers of two, whose partial sums [parts][T][H] the
+// quantization adds in a fixed order.  (T = 512, H = 4096: 64 tiles, one K loop of 64 steps on a quarter of the chip
+// took 124 us, in four parts 52 us; T = 77: 43 us on the fp32 matrix cores, 23 us in 16 parts.)  The sum over K in parts
+// is also the more accurate one: an accumulator rounds at the size of its own partial sum.  At most 20 MiB of partial
+// sums up to 128 tokens, so that the layer's workspace there stays about what its other steps need.
+int cq_rotate_split_parts(int T, int H) {
+  const long tiles = (long)((T + kTok - 1) / kTok) * (H / kCols);
+  int parts = 1;
+  while (tiles * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0 &&
+         (T > kTok || (long)parts * 2 * T * H * 4 <= (20L << 20)))
+    parts *= 2;
+  return parts;
+}
+
+// Whether the layer's rotation takes this path: from 48 tiles on (also with a short K), and where K can be cut from 64
+// tokens at H = 4096 and 128 at H = 2048 on.  Below, the fp32 kernel's
+// 16-token tiles waste less (whole layer, fp32 against this path: H = 4096, 33 tokens 176 / 175 us, 48 tokens 192 / 191, 64
+// tokens 216 / 202; H = 2048, 48 tokens 144 / 151, 128 tokens 173 / 172, 300 tokens 219 / 206).
+// Error of X_R against float64 (2-norm): fp32 kernel 3.4e-7 .. 5.9e-7 at 77 .. 200 tokens, this path 1.7e-7 .. 2.1e-7.
 bool cq_rotate_split_preferred(int T, int H) {
-  return cq_rotate_split_supported(T, H) && (long)((T + kTok - 1) / kTok) * (H / kCols) >= 48;
+  if (cq_rotate_split_supported(T, H) && (long)((T + kTok - 1) / kTok) * (H / kCols) >= 48) return true;
+  return H % 256 == 0 && H >= 1024 && T >= 64 && (long)T * H >= (1L << 18) && (long)T * H * 2 < (1L << 32);
 }
 
 extern "C" size_t cq_rotate_quant_split_workspace_bytes(int T, int H) {
@@ -344,7 +368,7 @@ extern "C" cq_status cq_rotate_quant_split(const float* X, const void* R_split, 
   if (!cq_rotate_split_supported(T, H)) return CQ_ERR_SHAPE;
   if (act_bits != 4 && act_bits != 8) return CQ_ERR_UNSUPPORTED;
   if (!workspace || workspace_bytes < cq_rotate_split_workspace_bytes(T, H)) return CQ_ERR_WORKSPACE;
-  const cq_status st = cq_rotate_split_launch(X, R_split, T, H, XR_out, workspace, (hipStream_t)stream);
+  const cq_status st = cq_rotate_split_launch(X, R_split, T, H, 1, XR_out, workspace, (hipStream_t)stream);
   if (st != CQ_OK) return st;
   return cq_quantize_launch(XR_out, 1, T, H, act_bits, XR_out, Q_out, nullptr, scale_out, nullptr, (hipStream_t)stream);
 }
@@ -368,8 +392,9 @@ size_t cq_rotate_split_workspace_bytes(int T, int H) {
 }
 
 // X_R = X R from the split R; XR_out [T, H] fp32.  workspace: cq_rotate_split_workspace_bytes(T, H).
-cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, float* XR_out, void* workspace,
-                                 hipStream_t s) {
+// parts > 1: XR_out receives partial sums [parts][T][H].
+cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, float* XR_out,
+                                 void* workspace, hipStream_t s) {
   static std::atomic<bool> configured{false};
   const cq_status cst = cq_configure_lds(rot_split_kernel, kRotLdsBytes, configured, true);
   if (cst != CQ_OK) return cst;
@@ -388,7 +413,9 @@ cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int
   a.N = H;
   a.K = H;
   a.row_tiles = H / kCols;
-  a.n_work = ((T + kTok - 1) / kTok) * a.row_tiles;
+  a.tok_tiles = (T + kTok - 1) / kTok;
+  a.ksteps = H / kStepK / parts;
+  a.n_work = a.tok_tiles * a.row_tiles * parts;
   const int per = (a.n_work + 7) / 8;
   hipLaunchKernelGGL(rot_split_kernel, dim3(per * 8), dim3(256), kRotLdsBytes, s, a);
   return cq_check_launch();

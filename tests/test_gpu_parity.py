@@ -1142,6 +1142,38 @@ def test_layer_reduced_shapes(B, name, over):
 
 
 @pytest.mark.parametrize("name,over", [
+    ("mixtral_decode", dict(H=4096, I=64, T=64, E=4)),              # one token tile, 16 K parts, decode front end
+    ("mixtral_decode", dict(H=4096, I=64, T=129, E=4)),             # a second tile of one token
+    ("dsv2lite", dict(H=2048, I=64, T=130, E=32)),                  # the quantization kernels that spread a row
+    ("dsv2lite", dict(H=1024, I=64, T=300, E=32)),                  # ... and the one that does not; 4 parts
+])
+def test_layer_rotation_in_k_parts(B, name, over):
+    """The layer's rotation on the f16 matrix cores cut along K (partial sums added by the quantization), also with a
+    workspace that another batch was sized for: smaller than what the query says, it gets fewer K parts."""
+    import ctypes
+    import torch
+    cfg = synth.small_variant(synth.CONFIGS[name], **over)
+    _check_layer(B, cfg, label=f"{name}-k-parts")
+    L = Hp.make_inputs(cfg)
+    layer = B.device_layer_from_inputs(L)
+    lib, s, X = B.load_library(), layer.struct(), _dev(L.X)
+    full = B.cq_moe_forward(layer, X).cpu().numpy().astype(np.float64)
+    XR = B.moe_intermediates(layer, cfg.T)["XR"].cpu().numpy().astype(np.float64)
+    ref = O.rotate(L.X, L.R)
+    assert (np.abs(XR - ref).max(axis=1) / np.abs(ref).max(axis=1)).max() <= 4e-6
+    need = lib.cq_moe_workspace_bytes(ctypes.byref(s), cfg.T)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    Y = torch.empty((cfg.T, cfg.H), dtype=torch.float32, device="cuda")
+    st = lib.cq_moe_forward(ctypes.byref(s), X.data_ptr(), cfg.T, Y.data_ptr(), ws.data_ptr(),
+                            need - 2 * cfg.T * cfg.H * 4, torch.cuda.current_stream().cuda_stream)
+    assert st == B.CQ_OK
+    # (another summation order of X_R: codes may differ at ties, one step of a code moves a token by about 1e-2)
+    assert Hp.row_rel_l2(Y.cpu().numpy(), full).max() < 5e-2
+    assert lib.cq_moe_forward(ctypes.byref(s), X.data_ptr(), cfg.T, Y.data_ptr(), ws.data_ptr(),
+                              Y.numel() * 4, torch.cuda.current_stream().cuda_stream) == 4   # CQ_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("name,over", [
     ("mixtral_decode", dict(H=4096, I=256, T=16)),                         # the decode shape's front end and gate/up K
     ("mixtral_decode", dict(H=4096, I=128, T=1)),                          # one token: six experts without rows
     ("mixtral_decode", dict(H=4096, I=128, T=5, E=16, top_k=1)),           # most experts empty
