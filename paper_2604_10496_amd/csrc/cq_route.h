@@ -128,6 +128,60 @@ __device__ __forceinline__ void wave_topk_regs(float val, int E, int k, int lane
   }
 }
 
+// The same for up to 128 experts, two per lane (val[s]: the logit of expert 64 s + lane): still one wavefront on its own,
+// no workgroup barrier; the selected pairs are sorted through 64 entries of LDS of this wavefront's own (LDS operations
+// of one wavefront complete in order).  Called by all 64 lanes.
+__device__ __forceinline__ void wave_topk_regs2(const float (&val)[2], int E, int k, int lane, int* lds_id, float* lds_val,
+                                                int32_t* ids_out, float* w_out, int* lds_ids = nullptr) {
+  const uint64_t lt = lanemask_lt(lane);
+  uint32_t key[2];
+  bool valid[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    valid[s] = s * 64 + lane < E;
+    key[s] = valid[s] ? order_key(val[s]) : 0u;
+  }
+  uint32_t kth = 0u;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t cand = kth | (1u << bit);
+    if (__popcll(__ballot(valid[0] && key[0] >= cand)) + __popcll(__ballot(valid[1] && key[1] >= cand)) >= k) kth = cand;
+  }
+  const int need = k - __popcll(__ballot(valid[0] && key[0] > kth)) - __popcll(__ballot(valid[1] && key[1] > kth));
+  const uint64_t eq0 = __ballot(valid[0] && key[0] == kth), eq1 = __ballot(valid[1] && key[1] == kth);
+  const bool sel[2] = {valid[0] && (key[0] > kth || (key[0] == kth && __popcll(eq0 & lt) < need)),
+                       valid[1] && (key[1] > kth || (key[1] == kth && __popcll(eq0) + __popcll(eq1 & lt) < need))};
+  int rank[2] = {0, 0};
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+    for (uint64_t m = __ballot(sel[s]); m; m &= m - 1) {
+      const int j = __ffsll((long long)m) - 1;
+      const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key[s], j);
+      // (expert 64 s + j against this lane's two: of equal keys the lower id comes first)
+      rank[0] += (kj > key[0] || (kj == key[0] && s == 0 && j < lane)) ? 1 : 0;
+      rank[1] += (kj > key[1] || (kj == key[1] && (s == 0 || j < lane))) ? 1 : 0;
+    }
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+    if (sel[s]) {
+      lds_id[rank[s]] = s * 64 + lane;
+      lds_val[rank[s]] = val[s];
+    }
+  __builtin_amdgcn_wave_barrier();
+  const int id_sorted = lds_id[lane < k ? lane : 0];
+  const float v_sorted = lds_val[lane < k ? lane : 0];
+  const float top = lds_val[0];
+  const float ex = lane < k ? expf(v_sorted - top) : 0.f;
+  float sum = ex;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane < k) {
+    ids_out[lane] = id_sorted;
+    if (lds_ids) lds_ids[lane] = id_sorted;
+    w_out[lane] = ex / sum;
+  }
+  __builtin_amdgcn_wave_barrier();   // (the entries may be reused by the caller's next token)
+}
+
 // lane that holds the n-th (from 0) set bit of a ballot mask; n < popcount(mask)
 __device__ __forceinline__ int nth_set_lane(uint64_t mask, int n, int lane) {
   const bool hit = ((mask >> lane) & 1ull) && __popcll(mask & lanemask_lt(lane)) == n;

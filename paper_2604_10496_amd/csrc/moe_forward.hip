@@ -98,7 +98,7 @@ void make_layout(const cq_layer* L, int T, cq_moe_layout* o, int* rot_parts, siz
   size_t scratch = 0;
   const size_t r = cq_route_permute_workspace_bytes(T, L->H, L->E, L->top_k);
   if (r > scratch) scratch = r;
-  // the layer feeds both products 16-bit operands (bf16 codes, f16 h): tile lists only
+  // (the layer feeds both products 16-bit operands, bf16 codes and f16 h: no room for converted rows)
   if (use_bf16_codes(L, T)) {
     const size_t g1 = cq_gemm_large_workspace_bytes(L->gate_up.G, (int)M, L->gate_up.K, false);
     if (g1 > scratch) scratch = g1;
@@ -193,6 +193,10 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     return cq_gemm_f32_launch(X, L->R, 0, T, L->H, L->H, p, *part, nullptr, 0, hs);
   };
 
+  // a5 alone (the counting sort's workspace lies at the start of the scratch area, which a3 / a4 no longer use)
+  auto group = [&]() {
+    return cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
+  };
   if (!mark(0)) return CQ_ERR_HIP;
   const bool bf16_codes = use_bf16_codes(L, T);
   bool fuse_route = false;   // a5 folded into the gate/up launch (decode-sized batches)
@@ -214,16 +218,15 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     st = rotate(&parts, &part);
     if (st != CQ_OK) return st;
     if (!mark(1)) return CQ_ERR_HIP;
-    // when the gate/up launch can do the grouping itself, the front launch also selects the experts and
-    // the routing launch falls away
-    fuse_route = cq_gemm_can_fuse_route(&L->gate_up, T, L->E, L->S, L->top_k, CQ_EPI_SWIGLU);
-    // (the front launch selects the experts whenever a launch that only groups can follow it)
-    const bool front_topk = fuse_route || cq_group_small_supported(T, L->E, L->top_k);
+    // With few experts the front launch also selects them and a launch that only groups follows it; when the gate/up
+    // launch can do the grouping itself, that one falls away, too.
+    const bool front_topk = cq_front_small_selects(L->E);
+    fuse_route = front_topk && cq_gemm_can_fuse_route(&L->gate_up, T, L->E, L->S, L->top_k, CQ_EPI_SWIGLU);
     st = cq_front_small_launch(part, parts, T, L->H, L->act_bits, L->Wr, L->bias, L->E, XR, Q, Q16, scale, logits,
                                L->top_k, front_topk ? ids : nullptr, front_topk ? tw : nullptr, hs);
     if (st != CQ_OK) return st;
     if (!fuse_route) {
-      st = front_topk ? cq_group_small_launch(ids, tw, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, hs)
+      st = front_topk ? group()
                       : cq_route_permute(nullptr, nullptr, nullptr, logits, T, L->H, L->E, L->top_k, L->S, logits, ids,
                                          tw, offsets, perm, inv_perm, src_token, scratch, scratch_bytes, stream);
       if (st != CQ_OK) return st;

@@ -15,10 +15,14 @@
 
 namespace {
 
-template <int MB, int WM, bool BT, int D>
+// NB: 16-column blocks per wavefront, 4 for the row-major B; the transposed B also comes with one (up to 16 columns --
+// the router logits of few experts: four blocks would be three of padding.  8 experts, 512 and 4096 tokens:
+// 25 -> 8 us and 41 -> 17 us).
+template <int MB, int WM, bool BT, int D, int NB = 4>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                        float* __restrict__ C, int T, int N, int K, int kchunk,
                                                        uint32_t* __restrict__ zero_me, int zero_n) {
+  static_assert(BT || NB == 4, "a 16-byte load of the row-major B is four columns");
   constexpr int WN = 4 / WM;
   // side job of the first workgroup: clear a small buffer the next kernel accumulates into
   if (zero_me && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
@@ -27,7 +31,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   const int wave = threadIdx.x >> 6;
   const int wm = wave % WM, wn = wave / WM;
   const int t0 = (blockIdx.y * WM + wm) * 16 * MB;
-  const int c0 = (blockIdx.x * WN + wn) * 64;
+  const int c0 = (blockIdx.x * WN + wn) * 16 * NB;
   if (t0 >= T || c0 >= N) return;
   const int j = lane & 15, g = lane >> 4;
   const int kbeg = blockIdx.z * kchunk;
@@ -40,9 +44,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     const int row = min(t0 + 16 * mb + j, T - 1);  // rows past T only feed outputs that are never stored
     pa[mb] = A + (size_t)row * K + 4 * g;
   }
-  const float* pb[4];
+  constexpr int NX = BT ? NB : 4;   // 16-byte loads of B per step
+  const float* pb[NX];
 #pragma unroll
-  for (int x = 0; x < 4; ++x) {
+  for (int x = 0; x < NX; ++x) {
     if (BT) {
       const int col = min(c0 + 16 * x + j, N - 1);
       pb[x] = B + (size_t)col * K + 4 * g;
@@ -51,21 +56,21 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     }
   }
 
-  cq_v4f acc[MB][4];
+  cq_v4f acc[MB][NB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int n = 0; n < 4; ++n) acc[mb][n] = cq_v4f{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < NB; ++n) acc[mb][n] = cq_v4f{0.f, 0.f, 0.f, 0.f};
 
   // register ring of D K-steps; loads are unconditional (step index clamped) so that every wait
   // covers exactly one slot
-  float4 ra[D][MB], rb[D][4];
+  float4 ra[D][MB], rb[D][NX];
   auto load = [&](float4* a, float4* b, int step) {
     const int ks = kbeg + 16 * min(step, steps - 1);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) a[mb] = *reinterpret_cast<const float4*>(pa[mb] + ks);
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < NX; ++x)
       b[x] = BT ? *reinterpret_cast<const float4*>(pb[x] + ks)
                 : *reinterpret_cast<const float4*>(pb[x] + (size_t)ks * N);
   };
@@ -75,18 +80,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       const int st = s0 + d;
-      float4 a_cur[MB], b_cur[4];
+      float4 a_cur[MB], b_cur[NX];
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) a_cur[mb] = ra[d][mb];
 #pragma unroll
-      for (int x = 0; x < 4; ++x) b_cur[x] = rb[d][x];
+      for (int x = 0; x < NX; ++x) b_cur[x] = rb[d][x];
       load(ra[d], rb[d], st + D);
       if (st < steps) {
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
 #pragma unroll
-          for (int n = 0; n < 4; ++n) {
-            const float4 bq = BT ? b_cur[n] : b_cur[m];
+          for (int n = 0; n < NB; ++n) {
+            const float4 bq = BT ? b_cur[n] : b_cur[m < NX ? m : 0];
             const int be = BT ? m : n;
             const float bval = be == 0 ? bq.x : be == 1 ? bq.y : be == 2 ? bq.z : bq.w;
 #pragma unroll
@@ -111,13 +116,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       if (tok >= T) continue;
       if (BT) {
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
+        for (int n = 0; n < NB; ++n) {
           const int col = c0 + 16 * n + j;
           if (col < N) Cz[(size_t)tok * N + col] = acc[mb][n][v];
         }
       } else {
-        float4 o = make_float4(acc[mb][0][v], acc[mb][1][v], acc[mb][2][v], acc[mb][3][v]);
-        *reinterpret_cast<float4*>(Cz + (size_t)tok * N + c0 + 4 * j) = o;
+        if constexpr (NB == 4)
+          *reinterpret_cast<float4*>(Cz + (size_t)tok * N + c0 + 4 * j) =
+              make_float4(acc[mb][0][v], acc[mb][1][v], acc[mb][2][v], acc[mb][3][v]);
       }
     }
   }
@@ -231,9 +237,10 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float* part, int ks
 
 cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K) {
   cq_gemm_f32_plan p;
-  p.mb = T >= 64 ? 4 : 1;
-  const int tm = p.mb == 4 ? 128 : 16;
-  const int tn = p.mb == 4 ? 128 : 256;
+  p.mb = T >= 64 && N > 16 ? 4 : 1;
+  const bool narrow = N <= 16;   // (one column block per wavefront, its four wavefronts on 64 tokens)
+  const int tm = p.mb == 4 ? 128 : narrow ? 64 : 16;
+  const int tn = p.mb == 4 ? 128 : narrow ? 16 : 256;
   const long wgs = (long)((N + tn - 1) / tn) * ((T + tm - 1) / tm);
   int ks = (int)(256 / wgs);   // K chunks such that one round of workgroups covers the launch (96 tiles: 2, not 3)
   if (ks > 16) ks = 16;
@@ -250,7 +257,10 @@ cq_status cq_gemm_f32_launch(const float* A, const float* B, int b_transposed, i
                              const cq_gemm_f32_plan& plan, float* C, uint32_t* zero_me, int zero_n, hipStream_t s) {
   const int kchunk = plan.kchunk;
   dim3 block(256);
-  if (plan.mb == 4) {
+  if (b_transposed && N <= 16) {
+    hipLaunchKernelGGL((gemm_f32_kernel<1, 4, true, 8, 1>), dim3(1, (T + 63) / 64, plan.ksplit), block, 0, s, A, B, C, T, N,
+                       K, kchunk, zero_me, zero_n);
+  } else if (plan.mb == 4) {
     dim3 grid((N + 127) / 128, (T + 127) / 128, plan.ksplit);
     if (b_transposed)
       hipLaunchKernelGGL((gemm_f32_kernel<4, 2, true, 2>), grid, block, 0, s, A, B, C, T, N, K, kchunk, zero_me,

@@ -17,34 +17,51 @@ using namespace cq_route;
 constexpr int kMaxSlots = 16;       // experts per lane: E <= 1024
 constexpr int kPermBlock = 256;     // assignments per counting-sort block (one wavefront, 4 rounds)
 
+// One wavefront per token.  The K-split partial logits are requested eight at a time (one after the other they were the
+// kernel: 13 us at 512 tokens, 16 partials) and added in ascending order.
+// NSLOT experts per lane: 1 and 2 select in registers, 16 (more than 128 experts) through LDS.
+template <int NSLOT>
 __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ part, int ksplit,
                                                    const float* __restrict__ bias, int T, int E, int k,
                                                    float* __restrict__ logits_out, int32_t* __restrict__ ids,
                                                    float* __restrict__ w) {
-  __shared__ uint32_t s_key[4][64];
+  __shared__ uint32_t s_key[NSLOT > 2 ? 4 : 1][64];
   __shared__ int s_id[4][64];
   __shared__ float s_val[4][64];
-  __shared__ float s_sorted[4][64];
+  __shared__ float s_sorted[NSLOT > 2 ? 4 : 1][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int t = blockIdx.x * 4 + wave;
   const bool active = t < T;
+  if (NSLOT <= 2 && !active) return;   // (no workgroup barrier there)
   const int nslot = (E + 63) / 64;
-  float val[kMaxSlots];
+  float val[NSLOT];
 #pragma unroll
-  for (int s = 0; s < kMaxSlots; ++s) {
+  for (int s = 0; s < NSLOT; ++s) {
     const int e = s * 64 + lane;
     val[s] = 0.f;
     if (s < nslot && e < E && active) {
       float x = part[(size_t)t * E + e];
-      for (int z = 1; z < ksplit; ++z) x += part[((size_t)z * T + t) * E + e];
+      for (int z0 = 1; z0 < ksplit; z0 += 8) {
+        float q[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) q[i] = part[((size_t)min(z0 + i, ksplit - 1) * T + t) * E + e];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (z0 + i < ksplit) x += q[i];
+      }
       if (bias) x += bias[e];
       if (logits_out) logits_out[(size_t)t * E + e] = x;
       val[s] = x;
     }
   }
   const size_t o = active ? (size_t)t * k : 0;
-  wave_topk<kMaxSlots>(val, nslot, E, k, active, lane, s_key[wave], s_id[wave], s_val[wave], s_sorted[wave], ids + o,
-                       w + o, nullptr);
+  if constexpr (NSLOT == 1)
+    wave_topk_regs(val[0], E, k, lane, ids + o, w + o);
+  else if constexpr (NSLOT == 2)
+    wave_topk_regs2(val, E, k, lane, s_id[wave], s_val[wave], ids + o, w + o);
+  else
+    wave_topk<NSLOT>(val, nslot, E, k, active, lane, s_key[wave], s_id[wave], s_val[wave], s_sorted[wave], ids + o, w + o,
+                     nullptr);
 }
 
 // Router logits for decode-sized batches: one workgroup per (token, four experts); its four wavefronts
@@ -104,44 +121,27 @@ __global__ __launch_bounds__(1024) void route_fused_kernel(const float* logits_i
                                                            int32_t* __restrict__ ids, float* __restrict__ w,
                                                            int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
                                                            int32_t* __restrict__ inv_perm,
-                                                           int32_t* __restrict__ src_token, int ids_given) {
-  __shared__ uint32_t s_key[16][64];
+                                                           int32_t* __restrict__ src_token) {
   __shared__ int s_id[16][64];
   __shared__ float s_val[16][64];
-  __shared__ float s_sorted[16][64];
   __shared__ int s_ids[kFusedMaxAssign];
   __shared__ int s_chunk[16][kFusedMaxE];
   __shared__ int s_off[kFusedMaxE + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nslot = (E + 63) / 64;
-  // ids_given: the experts were selected already (ids and w hold them): only the grouping is left
-  if (ids_given)
-    for (int a = tid; a < T * k; a += 1024) s_ids[a] = ids[a];
-  // at most 64 experts: every wavefront takes its tokens through the register top-k on its own, no barriers
-  if (!ids_given && nslot == 1)
-    for (int t = wave; t < T; t += 16) {
-      const float v = lane < E ? logits_in[(size_t)t * E + lane] : 0.f;
-      if (logits_out && logits_out != logits_in && lane < E) logits_out[(size_t)t * E + lane] = v;
-      wave_topk_regs(v, E, k, lane, ids + (size_t)t * k, w + (size_t)t * k, s_ids + t * k);
-    }
-  for (int t0 = 0; t0 < (ids_given || nslot == 1 ? 0 : T); t0 += 16) {
-    const int t = t0 + wave;
-    const bool active = t < T;
-    float val[2] = {0.f, 0.f};
-    if (active) {
+  // every wavefront takes its tokens through the register top-k on its own, no barriers
+  for (int t = wave; t < T; t += 16) {
+    float v[2];
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
-        if (s < nslot && s * 64 + lane < E) val[s] = logits_in[(size_t)t * E + s * 64 + lane];
-      if (logits_out && logits_out != logits_in) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-          if (s < nslot && s * 64 + lane < E) logits_out[(size_t)t * E + s * 64 + lane] = val[s];
-      }
+    for (int i = 0; i < 2; ++i) {
+      const int e = i * 64 + lane;
+      v[i] = e < E ? logits_in[(size_t)t * E + e] : 0.f;
+      if (logits_out && logits_out != logits_in && e < E) logits_out[(size_t)t * E + e] = v[i];
     }
-    const size_t o = active ? (size_t)t * k : 0;
-    wave_topk<2>(val, nslot, E, k, active, lane, s_key[wave], s_id[wave], s_val[wave], s_sorted[wave], ids + o, w + o,
-                 active ? s_ids + o : nullptr);
+    if (nslot == 1) wave_topk_regs(v[0], E, k, lane, ids + (size_t)t * k, w + (size_t)t * k, s_ids + t * k);
+    else wave_topk_regs2(v, E, k, lane, s_id[wave], s_val[wave], ids + (size_t)t * k, w + (size_t)t * k, s_ids + t * k);
   }
+  __syncthreads();
   // ---- stable grouping by expert: wavefront c ranks assignments 64c .. 64c+63 ----
   const int A = T * k;
   for (int i = tid; i < 16 * kFusedMaxE; i += 1024) (&s_chunk[0][0])[i] = 0;
@@ -184,6 +184,91 @@ __global__ __launch_bounds__(1024) void route_fused_kernel(const float* logits_i
     for (int i = tid; i < S * T; i += 1024) src_token[A + i] = i % T;
 }
 
+// The stable grouping alone, in one workgroup, for up to 16 * 64 * CH assignments and 128 experts: wavefront w takes a
+// contiguous run of them, 64 at a time; a running count per (wavefront, expert) in LDS and the ballot match masks give
+// every assignment its rank among the wavefront's assignments to the same expert, and the counts' exclusive prefix over
+// the wavefronts and over the experts gives the position.  One launch instead of the counting sort's three (histogram,
+// one-workgroup scan over its blocks, scatter: 15 us at 3072 assignments, 6.5 us so).
+// (One workgroup stores from one compute unit: 12 us at 8192 assignments, 24 us at 16384, where the counting sort
+// takes 17 since its scan requests the block counts together.)
+constexpr int kGroupMaxChunks = 8;
+template <int CH>
+__global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__ ids, int T, int E, int k, int S,
+                                                     int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+                                                     int32_t* __restrict__ inv_perm, int32_t* __restrict__ src_token) {
+  __shared__ int s_cnt[16][kFusedMaxE];
+  __shared__ int s_off[kFusedMaxE + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int A = T * k;
+  const int chunks = (A + 1023) / 1024;   // of 64 assignments, per wavefront
+  const int a0 = wave * chunks * 64 + lane;
+  int id[CH], rank[CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int a = a0 + c * 64;
+    id[c] = c < chunks && a < A ? ids[a] : -1;
+  }
+  for (int i = lane; i < kFusedMaxE; i += 64) s_cnt[wave][i] = 0;
+  __builtin_amdgcn_wave_barrier();   // (a wavefront's own row: its LDS operations complete in order)
+  const uint64_t lt = lanemask_lt(lane);
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    if (c < chunks) {
+      const bool valid = id[c] >= 0;
+      uint64_t mask = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < 7; ++bit) {
+        const bool set = (id[c] >> bit) & 1;
+        const uint64_t bal = __ballot(valid && set);
+        mask &= set ? bal : ~bal;
+      }
+      const int before = valid ? s_cnt[wave][id[c]] : 0;
+      const int in_chunk = __popcll(mask & lt);
+      rank[c] = before + in_chunk;
+      __builtin_amdgcn_wave_barrier();
+      if (valid && in_chunk == 0) s_cnt[wave][id[c]] = before + __popcll(mask);
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  __syncthreads();
+  if (tid < kFusedMaxE) {
+    int tot = 0;
+    if (tid < E)
+      for (int c = 0; c < 16; ++c) {   // exclusive prefix over the wavefronts, in place
+        const int v = s_cnt[c][tid];
+        s_cnt[c][tid] = tot;
+        tot += v;
+      }
+    int incl = tot;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
+    }
+    s_off[tid + 1] = incl;   // (within this wavefront's 64 experts; the second 64 get the first 64's total below)
+  }
+  if (tid == 0) s_off[0] = 0;
+  __syncthreads();
+  const int first64 = s_off[64];
+  __syncthreads();
+  if (tid >= 64 && tid < kFusedMaxE) s_off[tid + 1] += first64;
+  __syncthreads();
+  if (tid <= E) offsets[tid] = s_off[tid];
+  for (int s = tid; s < S; s += 1024) offsets[E + s + 1] = A + (s + 1) * T;
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int a = a0 + c * 64;
+    if (id[c] >= 0) {
+      const int pos = s_off[id[c]] + s_cnt[wave][id[c]] + rank[c];
+      perm[pos] = a;
+      inv_perm[a] = pos;
+      if (src_token) src_token[pos] = a / k;
+    }
+  }
+  if (src_token)
+    for (int i = tid; i < S * T; i += 1024) src_token[A + i] = i % T;
+}
+
 // pass 1: per-block histogram of expert ids
 __global__ __launch_bounds__(64) void perm_hist_kernel(const int32_t* __restrict__ ids, int n_assign, int E,
                                                        int32_t* __restrict__ blockhist) {
@@ -208,10 +293,16 @@ __global__ __launch_bounds__(1024) void perm_scan_kernel(int32_t* __restrict__ b
   const int tid = threadIdx.x;
   int total = 0;
   if (tid < E) {
-    for (int b = 0; b < nb; ++b) {
-      const int c = blockhist[(size_t)b * E + tid];
-      blockhist[(size_t)b * E + tid] = total;
-      total += c;
+    for (int b0 = 0; b0 < nb; b0 += 16) {   // (16 counts requested together)
+      int c[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) c[i] = blockhist[(size_t)min(b0 + i, nb - 1) * E + tid];
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (b0 + i < nb) {
+          blockhist[(size_t)(b0 + i) * E + tid] = total;
+          total += c[i];
+        }
     }
   }
   tot[tid] = tid < E ? total : 0;
@@ -270,8 +361,16 @@ __global__ __launch_bounds__(64) void perm_scatter_kernel(const int32_t* __restr
 
 cq_status cq_topk_launch(const float* logit_partials, int ksplit, const float* bias, int T, int E, int top_k,
                          float* logits_out, int32_t* topk_ids, float* topk_w, hipStream_t s) {
-  hipLaunchKernelGGL(topk_kernel, dim3((T + 3) / 4), dim3(256), 0, s, logit_partials, ksplit, bias, T, E, top_k,
-                     logits_out, topk_ids, topk_w);
+  const dim3 grid((T + 3) / 4);
+  if (E <= 64)
+    hipLaunchKernelGGL(topk_kernel<1>, grid, dim3(256), 0, s, logit_partials, ksplit, bias, T, E, top_k, logits_out,
+                       topk_ids, topk_w);
+  else if (E <= 128)
+    hipLaunchKernelGGL(topk_kernel<2>, grid, dim3(256), 0, s, logit_partials, ksplit, bias, T, E, top_k, logits_out,
+                       topk_ids, topk_w);
+  else
+    hipLaunchKernelGGL(topk_kernel<kMaxSlots>, grid, dim3(256), 0, s, logit_partials, ksplit, bias, T, E, top_k,
+                       logits_out, topk_ids, topk_w);
   return cq_check_launch();
 }
 
@@ -283,6 +382,15 @@ size_t cq_permute_workspace_bytes(int T, int E, int top_k) {
 cq_status cq_permute_launch(const int32_t* topk_ids, int T, int E, int top_k, int n_shared, int32_t* expert_offsets,
                             int32_t* perm, int32_t* inv_perm, int32_t* src_token, void* workspace, hipStream_t s) {
   const int n_assign = T * top_k;
+  if (n_assign <= 1024 * kGroupMaxChunks && E <= kFusedMaxE) {
+    if (n_assign <= 1024 * 4)
+      hipLaunchKernelGGL(group_kernel<4>, dim3(1), dim3(1024), 0, s, topk_ids, T, E, top_k, n_shared, expert_offsets, perm,
+                         inv_perm, src_token);
+    else
+      hipLaunchKernelGGL(group_kernel<kGroupMaxChunks>, dim3(1), dim3(1024), 0, s, topk_ids, T, E, top_k, n_shared,
+                         expert_offsets, perm, inv_perm, src_token);
+    return cq_check_launch();
+  }
   const int nb = (n_assign + kPermBlock - 1) / kPermBlock;
   int idbits = 0;
   while ((1 << idbits) < E) ++idbits;
@@ -319,7 +427,9 @@ extern "C" cq_status cq_route_permute(const float* XR, const float* Wr, const fl
   const size_t part_bytes = cq_align_up((size_t)p.ksplit * T * E * sizeof(float), 256);
   cq_status st;
   // decode-sized problems: a small logits kernel, then top-k + grouping fused in one workgroup
-  if ((long)T * top_k <= kFusedMaxAssign && E <= kFusedMaxE && (!XR || (long)T * E * H <= (1L << 22))) {
+  // (more than 64 tokens: four and more selections one after the other in a wavefront; top-k over many
+  // workgroups and a launch that only groups are faster: 21 against 10 us at 100 tokens)
+  if ((long)T * top_k <= kFusedMaxAssign && E <= kFusedMaxE && T <= 64 && (!XR || (long)T * E * H <= (1L << 22))) {
     const float* lg = logits_in;
     if (XR) {
       float* dst = logits_out ? logits_out : (float*)workspace;
@@ -328,7 +438,7 @@ extern "C" cq_status cq_route_permute(const float* XR, const float* Wr, const fl
     }
     hipLaunchKernelGGL(route_fused_kernel, dim3(1), dim3(1024), 0, s, lg, T, E, top_k, n_shared,
                        XR ? (float*)nullptr : logits_out, topk_ids, topk_w, expert_offsets, perm, inv_perm,
-                       src_token, 0);
+                       src_token);
     return cq_check_launch();
   }
   if (XR) {
@@ -339,25 +449,6 @@ extern "C" cq_status cq_route_permute(const float* XR, const float* Wr, const fl
     st = cq_topk_launch(logits_in, 1, nullptr, T, E, top_k, logits_out, topk_ids, topk_w, s);
   }
   if (st != CQ_OK) return st;
-  // (up to 1024 assignments: one workgroup groups them in one launch instead of the three counting-sort passes)
-  if ((long)T * top_k <= kFusedMaxAssign && E <= kFusedMaxE) {
-    hipLaunchKernelGGL(route_fused_kernel, dim3(1), dim3(1024), 0, s, (const float*)nullptr, T, E, top_k, n_shared,
-                       (float*)nullptr, topk_ids, topk_w, expert_offsets, perm, inv_perm, src_token, 1);
-    return cq_check_launch();
-  }
   return cq_permute_launch(topk_ids, T, E, top_k, n_shared, expert_offsets, perm, inv_perm, src_token,
                            (char*)workspace + part_bytes, s);
-}
-
-// a5 alone for decode-sized batches whose experts were selected by the front launch: the one-workgroup kernel
-// without its top-k loop.  Requires T * top_k <= 1024 and E <= 128 (cq_group_small_supported).
-bool cq_group_small_supported(int T, int E, int top_k) {
-  return (long)T * top_k <= kFusedMaxAssign && E <= kFusedMaxE;
-}
-cq_status cq_group_small_launch(int32_t* topk_ids, float* topk_w, int T, int E, int top_k, int n_shared,
-                                int32_t* expert_offsets, int32_t* perm, int32_t* inv_perm, int32_t* src_token,
-                                hipStream_t s) {
-  hipLaunchKernelGGL(route_fused_kernel, dim3(1), dim3(1024), 0, s, (const float*)nullptr, T, E, top_k, n_shared,
-                     (float*)nullptr, topk_ids, topk_w, expert_offsets, perm, inv_perm, src_token, 1);
-  return cq_check_launch();
 }

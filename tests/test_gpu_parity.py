@@ -215,6 +215,33 @@ def test_route_limits(B, T, E, k):
     assert np.array_equal(got["ids"].cpu().numpy()[0], np.arange(k))
 
 
+@pytest.mark.parametrize("T,E,k", [
+    (64, 65, 3), (50, 128, 8), (7, 128, 64),        # one workgroup: two experts per lane
+    (65, 64, 6), (65, 128, 64), (200, 100, 5),      # top-k over workgroups, then the grouping in one
+    (512, 128, 8), (1024, 128, 8), (4096, 4, 2),    # 4096 and 8192 assignments: the grouping's largest
+    (1025, 128, 8), (1367, 33, 6),                  # ... and just more: the three-pass counting sort
+])
+def test_route_selection_and_grouping_forms(B, T, E, k):
+    """Given logits with many exact ties through every form of top-k and grouping, and shared experts behind them."""
+    rng = np.random.default_rng(T + E + k)
+    logits = rng.integers(-4, 5, size=(T, E)).astype(np.float32)
+    ids, w = O.route_topk(logits, k)
+    off, perm, inv = O.permute_by_expert(ids, E)
+    got = B.cq_route_permute(None, None, None, k, n_shared=1, logits_in=_dev(logits))
+    _check_routing(got, ids, w, off, perm, inv, T, k, 1)
+
+
+@pytest.mark.parametrize("T,H,E", [(65, 64, 1), (130, 320, 16), (300, 4096, 9), (700, 256, 17)])
+def test_route_logits_of_few_experts(B, T, H, E):
+    """Router logits of up to 16 experts (one column block per wavefront) and just more, ragged token blocks and K."""
+    rng = np.random.default_rng(T + H + E)
+    XR, Wr = rng.standard_normal((T, H)).astype(np.float32), rng.standard_normal((E, H)).astype(np.float32)
+    got = B.cq_route_permute(_dev(XR), _dev(Wr), None, 1)["logits"].cpu().numpy()
+    ref = XR.astype(np.float64) @ Wr.astype(np.float64).T
+    # fp32 products and sums over H terms of magnitude about 1: error about 2^-24 sqrt(H) times the terms' rms sum
+    assert np.abs(got - ref).max() <= 1e-6 * H
+
+
 def test_gemm_degenerate_launches(B):
     """No rows at all, and groups that are all empty: nothing is written, CQ_OK is returned."""
     rng = np.random.default_rng(17)
