@@ -131,8 +131,8 @@ cq_status cq_rotate_quant(const float* X, const float* R, int T, int H, int act_
 
 /*
  * a1 for many tokens: a copy of R (AOS section) as two f16 planes, R = Rh + 2^-11 Rl, in the order the
- * matrix-core fragments are loaded in.  With it cq_moe_forward computes X R (for T >= 256, H % 256 == 0)
- * as Xh Rh + 2^-11 (Xh Rl + Xl Rh) on the f16 matrix cores with fp32 accumulation: every operand is
+ * matrix-core fragments are loaded in.  With it cq_moe_forward computes X R (for H % 256 == 0 and enough
+ * tokens: from 64 at H = 4096) as Xh Rh + 2^-11 (Xh Rl + Xl Rh) on the f16 matrix cores with fp32 accumulation: every operand is
  * represented to 2^-23 of its size and only the 2^-22 Xl Rl term is dropped, so the result is as accurate
  * as the fp32 product and the codes still differ from an exact evaluation only at rounding ties.
  *   R [H,H] f32 device, H % 32 == 0; out: cq_rotation_split_bytes(H) bytes of device memory, owned by

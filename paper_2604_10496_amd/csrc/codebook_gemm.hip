@@ -136,7 +136,7 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
     // about one workgroup per compute unit: the per-workgroup prologue (activation staging, first
     // table, ring fill) is paid once and there is no partially filled last round of workgroups
     cq_gemm_split_plan(W, M_total, epilogue, &a.ksplit, &a.ksteps, max_group_rows);
-    a.partials = (float*)workspace;  // partial sums first, then the large-tile kernel's lists
+    a.partials = (float*)workspace;  // partial sums first, then the large-tile kernel's
     a.part_stride = (size_t)M_total * W->N;
     // The kernel itself divides these workgroups among the groups that have rows (cq_route::pick_group).  Up to 32
     // such groups share one round of them evenly enough; with more, the whole number of workgroups per group can
@@ -155,7 +155,7 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
     a.grid = a.slots * a.rounds > n_max ? a.slots * a.rounds : n_max;
   }
   // Groups of up to 32 rows go to the streaming kernel above; larger ones to the large-tile kernel (when
-  // the row count allows its 256-row tiles), which runs off a device-built tile list.  Block-wise tables
+  // the row count allows its 256-row tiles), which derives its token tiles from the group offsets.  Block-wise tables
   // go to the large-tile kernel with every group, except tables of 1024 weights at decode sizes, which the
   // streaming kernel's pipelined loop takes (cq_gemm_blockwise_streams).
   const bool bw_streams = cq_gemm_blockwise_streams(W, M_total, epilogue, max_group_rows) && cq_tables_per_row(W) > 1;
@@ -176,10 +176,6 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
   a.max_rows = large ? small_max : 0x7fffffff;
   void* large_ws = (char*)workspace + cq_gemm_partials_bytes(W, M_total, epilogue, max_group_rows);
   cq_status st;
-  if (large) {
-    st = cq_gemm_build_lists(W, group_offsets, M_total, small_max, large_ws, s, cq_gemm_large_tail_split(W, epilogue, out_kind), half);
-    if (st != CQ_OK) return st;
-  }
   if (blockwise) {
     // (with a K split the kernel stores fp32 partial sums, per split, where the streaming kernel would)
     st = cq_gemm_large_launch(W, A, a_kind, row_scale, row_gather, group_offsets, M_total, small_max, epilogue,

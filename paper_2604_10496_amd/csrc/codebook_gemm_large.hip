@@ -16,14 +16,15 @@
 //   * LDS holds only the activation tiles.  They arrive by direct global->LDS loads (no staging
 //     registers, no ds_write), four tiles deep, and each wavefront reads a tile once per K step.
 // The activation operand is 16-bit (bf16 integer codes or f16 rows); other kinds are converted by a
-// small pre-pass.  Token tiles come from a device-built work list (groups are ragged and their sizes
-// are only known on the device); the list index is remapped so that tiles sharing activations run on
+// small pre-pass.  The token tiles are derived in the kernel from the group offsets (groups are ragged and their sizes
+// are only known on the device); the work index is remapped so that tiles sharing activations run on
 // the same XCD (L2).
 #include <type_traits>
 
 #include "cq_internal.h"
 #include "cq_async.h"
 #include "cq_decode.h"
+#include "cq_route.h"
 
 void cq_large_tile_caps(int G, int M_total, int* cap0, int* cap1);
 
@@ -51,10 +52,9 @@ struct LargeArgs {
   const int32_t* scale_gather; // sorted row -> entry of row_scale, or NULL
   void* out;
   int out_ld;
-  const int32_t* tiles;   // widest tiles [cap][4]: group, first row (absolute sorted row), row count, unused
-  const int32_t* tiles1;  // the next width (tile_widths), same layout
-  const int32_t* tiles2;  // 64-token tiles, same layout
-  const int32_t* n_tiles; // the builder's counts: [0] entries in tiles, [1] in tiles1, [5] in tiles2
+  const int32_t* group_offsets;   // [G + 1]
+  int G;
+  int small_max;          // groups with at most this many rows are left to the streaming kernel
   int row_tiles;          // N / 256
   int nblk;               // centroid tables per weight row (1: one table over all of K)
   int gsteps;             // K steps per table (block-wise tables: group size / 64, a multiple of 8)
@@ -63,14 +63,14 @@ struct LargeArgs {
   // out + z * part_stride elements; ksteps covers all of K when there is no split
   int ksteps;
   size_t part_stride;
-  // K split of the tiles of a plain fp32 product with a long K (tail_part != NULL): the builder chooses S = n_tiles[6]
-  // parts in {1, 2, 4} for the tiles of the two narrow widths w1 and w2, which come last; split z > 0 of the j-th
-  // w1-token (w2-token) tile stores its partial sums at rows j*w1 (tail_rows1 + j*w2) of slice z-1 of tail_part,
-  // [S-1][tail_rows][N] fp32 -- or, when the launch has fewer rows than such slots (tail_abs), at the tile's own sorted
-  // rows; the widest tiles then come in n_tiles[7] parts.  tail_sum_kernel adds the slices to `out` in the order z = 1,
-  // 2, ...
+  // K split of the tiles of a plain fp32 product with a long K (tail_part != NULL): the tiles of the two narrow widths
+  // w1 and w2, which come last, are cut into kS1 parts in {1, 2, 4} (tile_map); split z > 0 of the j-th w1-token
+  // (w2-token) tile stores its partial sums at rows j*w1 (tail_rows1 + j*w2) of slice z-1 of tail_part,
+  // [kS1-1][tail_rows][N] fp32 -- or, when the launch has fewer rows than such slots (tail_abs), at the tile's own sorted
+  // rows; the widest tiles then come in kS0 parts.  tail_sum_kernel adds the slices to `out` in the order z = 1, 2, ...
   float* tail_part;
-  int w1, w2;         // the two narrow widths of the launch
+  int w0, w1, w2;     // the three widths of the launch
+  int at_once;        // workgroups of it that the chip runs at a time
   int tail_rows1;     // rows reserved for the w1-token tiles (capacity of that list * w1)
   int tail_rows;      // rows per slice
   int tail_abs;       // 1: a slice has M_total rows and a tile stores at its own sorted rows (fewer rows than slots)
@@ -441,6 +441,103 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   }
 }
 
+// inclusive sum over the lanes of a wavefront (data-parallel moves inside rows of 16 lanes, then across them)
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast 31 into rows 2 and 3
+  return x;
+}
+
+// The launch's token tiles, derived by every wavefront from the group offsets (a launch that built lists of them cost 5
+// us, twice per layer): a group with more than small_max rows is cut into tiles of w0 (while more than w1 rows remain),
+// then one of w1 or (up to w2 rows left) w2.  List 0 holds the w0-wide tiles, lists 1 and 2 the last tiles of the groups,
+// each in group order.  Lane l looks at group 64 r + l in round r; the offsets of the first two rounds stay in registers,
+// those of further ones are loaded again when a tile is looked up.  All members but the lane's own group are uniform.
+struct tile_map {
+  int n0, n1, n2;           // tiles per list
+  int kS0, kS1;             // K parts of a tile of list 0, and of lists 1 and 2
+  int from[2], to[2];       // offsets of the lane's groups of rounds 0 and 1
+  int base, m0, a, last, incl;   // this round: the lane's group: first row, whole tiles, rows left; tiles up to it
+  uint64_t m1, m2;          // ... its groups whose last tile is in list 1, 2
+
+  __device__ __forceinline__ void round(const LargeArgs& p, int f, int t) {
+    m0 = f;
+    const int me = t - f > p.small_max ? t - f : 0;
+    a = me / p.w0;
+    last = me - a * p.w0;
+    if (last > p.w1) { ++a; last -= p.w0; }   // (negative: the last whole tile is not full)
+    m1 = __ballot(last > p.w2);
+    m2 = __ballot(last > 0 && last <= p.w2);
+    incl = wave_scan(a);
+  }
+  __device__ __forceinline__ void load(const LargeArgs& p, int lane, int at, int& f, int& t) {
+    const int g = at + lane;
+    f = g < p.G ? p.group_offsets[g] : 0;
+    t = g < p.G ? p.group_offsets[g + 1] : 0;
+  }
+  __device__ __forceinline__ void add() {
+    n0 += __builtin_amdgcn_readlane(incl, 63);
+    n1 += __popcll(m1);
+    n2 += __popcll(m2);
+  }
+  __device__ __forceinline__ void init(const LargeArgs& p, int lane) {
+    n0 = n1 = n2 = 0;
+    load(p, lane, 0, from[0], to[0]);
+    load(p, lane, 64, from[1], to[1]);
+    for (base = 128; base < p.G; base += 64) {
+      int f, t;
+      load(p, lane, base, f, t);
+      round(p, f, t);
+      add();
+    }
+    if (p.G > 64) {
+      round(p, from[1], to[1]);
+      add();
+    }
+    round(p, from[0], to[0]);
+    add();
+    base = 0;
+    // K parts: the narrow tiles come last; when there are fewer of them than the chip runs at a time, the end of the
+    // launch runs on a part of it for the length of a whole K loop -- parts of K on more workgroups shorten it.  A launch
+    // of few tiles in all (tail_abs: any tile can have partial sums) leaves most of the chip idle for a whole K loop
+    // otherwise.
+    kS0 = kS1 = 1;
+    if (p.tail_part) {
+      const int narrow = (n1 + n2) * p.row_tiles, all = narrow + n0 * p.row_tiles;
+      while (kS1 < kTailSplitMax && narrow > 0 && narrow * kS1 * 2 <= p.at_once) kS1 *= 2;
+      while (p.tail_abs && kS0 < kTailSplitMax && n0 > 0 && all * kS0 * 2 <= p.at_once) kS0 *= 2;
+    }
+  }
+  // group, first sorted row and row count of tile t of a list (t < the list's n)
+  __device__ __forceinline__ void find(const LargeArgs& p, int lane, int list, int t, int& grp, int& row0, int& cnt) {
+    for (;;) {
+      const int here = list == 0 ? __builtin_amdgcn_readlane(incl, 63) : __popcll(list == 1 ? m1 : m2);
+      if (t < here) break;
+      t -= here;
+      base += 64;
+      int f = from[1], u = to[1];
+      if (base > 64) load(p, lane, base, f, u);
+      round(p, f, u);
+    }
+    int src, i;
+    if (list == 0) {
+      src = __ffsll((long long)__ballot(incl > t)) - 1;
+      i = t - (__builtin_amdgcn_readlane(incl, src) - __builtin_amdgcn_readlane(a, src));
+    } else {
+      src = cq_route::nth_set_lane(list == 1 ? m1 : m2, t, lane);
+      i = __builtin_amdgcn_readlane(a, src);
+    }
+    const int whole = __builtin_amdgcn_readlane(a, src), rest = __builtin_amdgcn_readlane(last, src);
+    grp = base + src;
+    row0 = __builtin_amdgcn_readlane(m0, src) + i * p.w0;
+    cnt = min(p.w0, whole * p.w0 + rest - i * p.w0);
+  }
+};
+
 // Work items = (token tile, row tile, K part); tiles of the three widths in ONE launch so that the short lists do not
 // leave most of the chip idle.  Two forms:
 //   * whole tiles, 256 / 128 / 64 tokens, one workgroup per compute unit (all 512 registers of a lane, four or eight
@@ -458,44 +555,42 @@ template <bool F16, int EPI, int OUTK, bool BLK, bool PRE, bool HALF>
 __global__ __launch_bounds__(256, HALF ? 2 : 1) void gemm_large_kernel(const LargeArgs p) {
   using W = tile_widths<HALF>;
   constexpr int kDeep = HALF ? 4 : 8;   // pipeline depth of the narrower tiles: less matrix time per step, needs more
-  const int kS1 = p.tail_part ? p.n_tiles[6] : 1;                  // K parts of a tile of the two narrow widths
-  const int kS0 = p.tail_part && p.tail_abs ? p.n_tiles[7] : 1;    // ... of a wide one (launches of few tiles)
-  const int xcd = blockIdx.x & 7;
+  const int lane = threadIdx.x & 63, xcd = blockIdx.x & 7;
   int slot = blockIdx.x >> 3;
-  // work item `slot` of this XCD's share of a list of n items of kS parts each
-  auto item = [&](int n, int kS, int& tile, int& rt, int& kz) {
+  tile_map map;
+  map.init(p, lane);
+  const int row_tiles = p.row_tiles;
+  // work item `slot` of this XCD's share of a list: its tile, row tile and K part
+  int grp, row0, cnt, tile, rt, kz;
+  auto item = [&](int list, int kS) {
+    const int n = (list == 0 ? map.n0 : list == 1 ? map.n1 : map.n2) * row_tiles * kS;
     const int work = xcd * ((n + 7) >> 3) + slot;
-    const int per_tile = p.row_tiles * kS;
+    if (work >= n) return false;
+    const int per_tile = row_tiles * kS;
     tile = work / per_tile;
     const int rest = work - tile * per_tile;
     rt = rest / kS;
     kz = rest - rt * kS;
-    return work < n;
+    map.find(p, lane, list, tile, grp, row0, cnt);
+    return true;
   };
-  int tile, rt, kz;
-  const int n0 = p.n_tiles[0] * p.row_tiles * kS0, n1 = p.n_tiles[1] * p.row_tiles * kS1,
-            n2 = p.n_tiles[5] * p.row_tiles * kS1;
-  if (slot < (n0 + 7) >> 3) {
-    if (!item(n0, kS0, tile, rt, kz)) return;
-    const int32_t* t = p.tiles + tile * 4;
-    large_tile<F16, EPI, OUTK, W::w0 / 32, 4, BLK, PRE, HALF>(p, t[0], t[1], t[2], rt, kz, kS0, t[1]);
+  const int s0 = (map.n0 * row_tiles * map.kS0 + 7) >> 3, s1 = (map.n1 * row_tiles * map.kS1 + 7) >> 3,
+            s2 = (map.n2 * row_tiles * map.kS1 + 7) >> 3;
+  if (slot < s0) {
+    if (item(0, map.kS0)) large_tile<F16, EPI, OUTK, W::w0 / 32, 4, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS0, row0);
     return;
   }
-  slot -= (n0 + 7) >> 3;
-  if (slot < (n1 + 7) >> 3) {
-    if (!item(n1, kS1, tile, rt, kz)) return;
-    const int32_t* t = p.tiles1 + tile * 4;
-    large_tile<F16, EPI, OUTK, W::w1 / 32, kDeep, BLK, PRE, HALF>(p, t[0], t[1], t[2], rt, kz, kS1,
-                                                                  p.tail_abs ? t[1] : tile * W::w1);
+  slot -= s0;
+  if (slot < s1) {
+    if (item(1, map.kS1))
+      large_tile<F16, EPI, OUTK, W::w1 / 32, kDeep, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS1,
+                                                                    p.tail_abs ? row0 : tile * W::w1);
     return;
   }
-  slot -= (n1 + 7) >> 3;
-  if (slot < (n2 + 7) >> 3) {
-    if (!item(n2, kS1, tile, rt, kz)) return;
-    const int32_t* t = p.tiles2 + tile * 4;
-    large_tile<F16, EPI, OUTK, W::w2 / 32, kDeep, BLK, PRE, HALF>(p, t[0], t[1], t[2], rt, kz, kS1,
-                                                                  p.tail_abs ? t[1] : p.tail_rows1 + tile * W::w2);
-  }
+  slot -= s1;
+  if (slot < s2 && item(2, map.kS1))
+    large_tile<F16, EPI, OUTK, W::w2 / 32, kDeep, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS1,
+                                                                  p.tail_abs ? row0 : p.tail_rows1 + tile * W::w2);
 }
 
 // out[row] += slice 0 + slice 1 + ... of the tiles' K parts, in that order (see LargeArgs::tail_part).
@@ -505,11 +600,13 @@ constexpr int kTailSumRows = 8;
 __global__ __launch_bounds__(256) void tail_sum_kernel(const LargeArgs p, int cap1) {
   const int list = (int)blockIdx.y < cap1 ? 1 : (int)blockIdx.y < 2 * cap1 ? 2 : 0;
   const int j = (int)blockIdx.y - (list == 0 ? 2 : list - 1) * cap1;
-  const int kS = list == 0 ? p.n_tiles[7] : p.n_tiles[6];
-  if (kS <= 1) return;
-  if (j >= p.n_tiles[list == 2 ? 5 : list]) return;
-  const int32_t* t = (list == 0 ? p.tiles : list == 1 ? p.tiles1 : p.tiles2) + j * 4;
-  const int mrow0 = t[1], mcnt = t[2];
+  const int lane = threadIdx.x & 63;
+  tile_map map;
+  map.init(p, lane);
+  const int kS = list == 0 ? map.kS0 : map.kS1;
+  if (kS <= 1 || j >= (list == 0 ? map.n0 : list == 1 ? map.n1 : map.n2)) return;
+  int grp, mrow0, mcnt;
+  map.find(p, lane, list, j, grp, mrow0, mcnt);
   const int row0 = p.tail_abs ? mrow0 : list == 2 ? p.tail_rows1 + j * p.w2 : j * p.w1;
   const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
   const int r0 = blockIdx.z * kTailSumRows;
@@ -547,15 +644,19 @@ __global__ __launch_bounds__(256) void tail_sum_kernel(const LargeArgs p, int ca
 constexpr int narrow_depth(int C) { return C >= 2 ? 4 : 8; }
 template <bool F16, int EPI, int OUTK, bool BLK, bool PRE, int C>
 __global__ __launch_bounds__(256, 2) void gemm_narrow_kernel(const LargeArgs p) {
-  const int n_2 = p.n_tiles[5] * p.row_tiles;
-  const int per64 = (n_2 + 7) >> 3;
+  const int lane = threadIdx.x & 63;
+  tile_map map;
+  map.init(p, lane);
+  const int n2 = map.n2 * p.row_tiles;
+  const int per = (n2 + 7) >> 3;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  if (slot >= per64) return;
-  const int work = xcd * per64 + slot;
-  if (work >= n_2) return;
+  if (slot >= per) return;
+  const int work = xcd * per + slot;
+  if (work >= n2) return;
   const int tile = work / p.row_tiles, rt = work - tile * p.row_tiles;
-  const int32_t* t = p.tiles2 + tile * 4;
-  large_tile<F16, EPI, OUTK, C, narrow_depth(C), BLK, PRE>(p, t[0], t[1], t[2], rt);
+  int grp, row0, cnt;
+  map.find(p, lane, 2, tile, grp, row0, cnt);
+  large_tile<F16, EPI, OUTK, C, narrow_depth(C), BLK, PRE>(p, grp, row0, cnt, rt);
 }
 
 // Pre-pass for activation kinds the main kernel does not read: sorted row m of the result is row
@@ -588,88 +689,6 @@ __global__ __launch_bounds__(256) void convert_rows_kernel(const void* __restric
     o[3] = f32_to_f16_sat(f1.z) | (f32_to_f16_sat(f1.w) << 16);
   }
   *reinterpret_cast<uint4*>(out + (size_t)m * K + (size_t)c * 8) = make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// One workgroup: cut every group with more than `small_max` rows into token tiles of w0 (while more than w1 rows
-// remain), then one of w1 or (up to w2 rows left) w2, in group order (deterministic); the streaming kernel takes the
-// other groups.  counts: [0] w0-wide tiles, [1] w1-wide tiles, [5] w2-wide tiles, [6] K parts of the two narrow
-// widths, [7] K parts of the w0-wide tiles.  at_once: workgroups of the launch that the chip runs at a time.
-__global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __restrict__ offsets, int G, int small_max,
-                                                           int n_units,
-                                                           int32_t* __restrict__ tiles0, int32_t* __restrict__ tiles1,
-                                                           int32_t* __restrict__ tiles2,
-                                                           int32_t* __restrict__ counts, int split_max, int split_all,
-                                                           int w0, int w1, int w2, int at_once) {
-  __shared__ int n_0[1024], n_1[1024], n_2[1024];
-  __shared__ int base_0, base_1, base_2;
-  const int tid = threadIdx.x;
-  if (tid == 0) { base_0 = 0; base_1 = 0; base_2 = 0; }
-  __syncthreads();
-  for (int g0 = 0; g0 < G; g0 += 1024) {
-    const int g = g0 + tid;
-    int a = 0, b = 0, b64 = 0, m0 = 0, me = 0;
-    if (g < G) {
-      m0 = offsets[g];
-      me = offsets[g + 1] - m0;
-      if (me > small_max) {
-        a = me / w0;
-        const int rem = me - a * w0;
-        if (rem > w1) ++a; else if (rem > w2) b = 1; else if (rem > 0) b64 = 1;
-      }
-    }
-    n_0[tid] = a;
-    n_1[tid] = b;
-    n_2[tid] = b64;
-    __syncthreads();
-    if (tid == 0) {  // exclusive prefix in group order
-      int s_0 = base_0, s_1 = base_1, s_2 = base_2;
-      const int n = min(1024, G - g0);
-      for (int i = 0; i < n; ++i) {
-        const int x = n_0[i], y = n_1[i], y2 = n_2[i];
-        n_0[i] = s_0; n_1[i] = s_1; n_2[i] = s_2;
-        s_0 += x; s_1 += y; s_2 += y2;
-      }
-      base_0 = s_0; base_1 = s_1; base_2 = s_2;
-    }
-    __syncthreads();
-    if (g < G && me > small_max) {
-      int at = n_0[tid];
-      for (int i = 0; i < a; ++i) {
-        tiles0[(at + i) * 4 + 0] = g;
-        tiles0[(at + i) * 4 + 1] = m0 + i * w0;
-        tiles0[(at + i) * 4 + 2] = min(w0, me - i * w0);
-        tiles0[(at + i) * 4 + 3] = 0;
-      }
-      if (b || b64) {
-        int32_t* t = b ? tiles1 + n_1[tid] * 4 : tiles2 + n_2[tid] * 4;
-        t[0] = g;
-        t[1] = m0 + a * w0;
-        t[2] = me - a * w0;
-        t[3] = 0;
-      }
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    counts[0] = base_0;
-    counts[1] = base_1;
-    counts[5] = base_2;
-    // [6] K parts of the narrow tiles (split_max > 1: a plain fp32 product with a long K).  The narrow tiles
-    // come last; when there are fewer of them than the chip runs at a time, the tail of the launch runs on a part of the
-    // chip for the length of a whole K loop -- parts of K on more workgroups shorten it.
-    {
-      const int narrow = (base_1 + base_2) * (n_units / 4);
-      int parts = 1;
-      while (parts < split_max && narrow > 0 && narrow * parts * 2 <= at_once) parts *= 2;
-      counts[6] = parts;
-      // [7] K parts of the widest tiles: a launch of few tiles in all (split_all: its partial sums are kept by
-      // sorted row, so any tile can have them) leaves most of the chip idle for a whole K loop otherwise
-      const int all = narrow + base_0 * (n_units / 4);
-      parts = 1;
-      while (split_all && parts < split_max && base_0 > 0 && all * parts * 2 <= at_once) parts *= 2;
-      counts[7] = parts;
-    }
-  }
 }
 
 template <bool F16, int EPI, int OUTK, bool BLK, bool PRE, int C>
@@ -714,12 +733,7 @@ cq_status launch_tiles(LargeArgs a, int max0, int max1, hipStream_t s) {
 }
 
 template <bool F16, int EPI, int OUTK, bool BLK, bool PRE>
-cq_status launch_both(LargeArgs a, const int32_t* t0, const int32_t* t1, const int32_t* counts, int max0,
-                      int max1, int narrow, hipStream_t s) {
-  a.tiles = t0;
-  a.tiles1 = t1;
-  a.tiles2 = t1 + (size_t)max1 * 4;
-  a.n_tiles = counts;
+cq_status launch_both(LargeArgs a, int max0, int max1, int narrow, hipStream_t s) {
   if constexpr (BLK) {
     if (narrow == 32) return launch_narrow<F16, EPI, OUTK, BLK, PRE, 1>(a, max1, s);
     if (narrow == 64) return launch_narrow<F16, EPI, OUTK, BLK, PRE, 2>(a, max1, s);
@@ -730,39 +744,30 @@ cq_status launch_both(LargeArgs a, const int32_t* t0, const int32_t* t1, const i
 }
 
 template <bool F16, bool BLK, bool PRE>
-cq_status dispatch_large_pre(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t0, const int32_t* t1,
-                             const int32_t* counts, int max0, int max1, int narrow, hipStream_t s) {
+cq_status dispatch_large_pre(const LargeArgs& a, int epilogue, int out_kind, int max0, int max1, int narrow, hipStream_t s) {
   if (epilogue == CQ_EPI_SWIGLU)
     return out_kind == CQ_OUT_F16
-               ? launch_both<F16, CQ_EPI_SWIGLU, CQ_OUT_F16, BLK, PRE>(a, t0, t1, counts, max0, max1, narrow, s)
-               : launch_both<F16, CQ_EPI_SWIGLU, CQ_OUT_F32, BLK, PRE>(a, t0, t1, counts, max0, max1, narrow, s);
+               ? launch_both<F16, CQ_EPI_SWIGLU, CQ_OUT_F16, BLK, PRE>(a, max0, max1, narrow, s)
+               : launch_both<F16, CQ_EPI_SWIGLU, CQ_OUT_F32, BLK, PRE>(a, max0, max1, narrow, s);
   return out_kind == CQ_OUT_F16
-             ? launch_both<F16, CQ_EPI_NONE, CQ_OUT_F16, BLK, PRE>(a, t0, t1, counts, max0, max1, narrow, s)
-             : launch_both<F16, CQ_EPI_NONE, CQ_OUT_F32, BLK, PRE>(a, t0, t1, counts, max0, max1, narrow, s);
+             ? launch_both<F16, CQ_EPI_NONE, CQ_OUT_F16, BLK, PRE>(a, max0, max1, narrow, s)
+             : launch_both<F16, CQ_EPI_NONE, CQ_OUT_F32, BLK, PRE>(a, max0, max1, narrow, s);
 }
 
 template <bool F16, bool BLK>
-cq_status dispatch_large_blk(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t0, const int32_t* t1,
-                             const int32_t* counts, int max0, int max1, int narrow, hipStream_t s) {
+cq_status dispatch_large_blk(const LargeArgs& a, int epilogue, int out_kind, int max0, int max1, int narrow, hipStream_t s) {
   return a.prepacked
-             ? dispatch_large_pre<F16, BLK, true>(a, epilogue, out_kind, t0, t1, counts, max0, max1, narrow, s)
-             : dispatch_large_pre<F16, BLK, false>(a, epilogue, out_kind, t0, t1, counts, max0, max1, narrow, s);
+             ? dispatch_large_pre<F16, BLK, true>(a, epilogue, out_kind, max0, max1, narrow, s)
+             : dispatch_large_pre<F16, BLK, false>(a, epilogue, out_kind, max0, max1, narrow, s);
 }
 
 // The two-workgroup kernel for 64-token tiles exists for block-wise tables only (the streaming kernel takes
 // the small groups otherwise).
 template <bool F16>
-cq_status dispatch_large(const LargeArgs& a, int epilogue, int out_kind, const int32_t* t0, const int32_t* t1,
-                         const int32_t* counts, int max0, int max1, int narrow, hipStream_t s) {
+cq_status dispatch_large(const LargeArgs& a, int epilogue, int out_kind, int max0, int max1, int narrow, hipStream_t s) {
   return a.nblk > 1
-             ? dispatch_large_blk<F16, true>(a, epilogue, out_kind, t0, t1, counts, max0, max1, narrow, s)
-             : dispatch_large_blk<F16, false>(a, epilogue, out_kind, t0, t1, counts, max0, max1, narrow == kHalf ? kHalf : 0, s);
-}
-
-size_t tile_list_bytes(int G, int M_total) {
-  int c0, c1;
-  cq_large_tile_caps(G, M_total, &c0, &c1);
-  return cq_align_up(256 + ((size_t)(c0 + 2 * c1) * 4) * sizeof(int32_t), 256);
+             ? dispatch_large_blk<F16, true>(a, epilogue, out_kind, max0, max1, narrow, s)
+             : dispatch_large_blk<F16, false>(a, epilogue, out_kind, max0, max1, narrow == kHalf ? kHalf : 0, s);
 }
 
 }  // namespace
@@ -809,10 +814,9 @@ size_t tail_part_bytes(int G, int M_total, int N, bool half) {
 }
 }  // namespace
 
-// tile lists, plus (tail_N > 0: a plain fp32 product of N columns whose K is long enough) the partial sums of
-// the tiles' K parts, plus (with_conversion) room for the activations as 16-bit rows [M_total, K]
+// (tail_N > 0: a plain fp32 product of N columns whose K is long enough) the partial sums of the tiles' K parts, plus (with_conversion) room for the activations as 16-bit rows [M_total, K]
 size_t cq_gemm_large_workspace_bytes(int G, int M_total, int K, bool with_conversion, int tail_N) {
-  size_t n = tile_list_bytes(G, M_total);
+  size_t n = 0;
   if (tail_N > 0 && K / kStepK >= kTailMinSteps) n += tail_part_bytes(G, M_total, tail_N, false);   // (whole tiles have the more slots)
   if (with_conversion) n += cq_align_up((size_t)M_total * K * sizeof(uint16_t), 256);
   return n;
@@ -826,33 +830,11 @@ bool cq_gemm_large_supported(const cq_codebook_weights* W) {
   return nblk == 1 || (W->group_k % (8 * kStepK) == 0 && (long)W->N * nblk * (CQ_N_CENTROIDS * 2) < (1L << 31));
 }
 
-// Builds the work lists in `workspace` (first step of a launch that uses the large-tile kernel).
-cq_status cq_gemm_build_lists(const cq_codebook_weights* W, const int32_t* group_offsets, int M_total, int small_max,
-                              void* workspace, hipStream_t s, bool tail_split, bool half) {
-  int cap0, cap1;
-  cq_large_tile_caps(W->G, M_total, &cap0, &cap1);
-  bool split_all = false;
-  if (tail_split) (void)tail_slice_rows(W->G, M_total, half, &split_all);   // partial sums by sorted row: any tile may split
-  int32_t* counts = (int32_t*)workspace;
-  int32_t* t0 = counts + 64;
-  int32_t* t1 = t0 + (size_t)cap0 * 4;
-  int32_t* t2 = t1 + (size_t)cap1 * 4;
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(1024), 0, s, group_offsets, W->G, small_max, W->N / 64,
-                     t0, t1, t2, counts, tail_split ? kTailSplitMax : 1, split_all ? 1 : 0,
-                     half ? tile_widths<true>::w0 : tile_widths<false>::w0, half ? tile_widths<true>::w1 : tile_widths<false>::w1,
-                     tile_widths<true>::w2, kAtOnce[half]);
-  return cq_check_launch();
-}
-
-// the lists must have been built by cq_gemm_build_lists in the same workspace
 cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int a_kind, const float* row_scale,
                                const int32_t* row_gather, const int32_t* group_offsets, int M_total, int small_max,
                                int epilogue, void* out, int out_kind, void* workspace, hipStream_t s, bool half) {
   int cap0, cap1;
   cq_large_tile_caps(W->G, M_total, &cap0, &cap1);
-  int32_t* counts = (int32_t*)workspace;
-  int32_t* t0 = counts + 64;
-  int32_t* t1 = t0 + (size_t)cap0 * 4;
   LargeArgs a;
   a.idx = W->prepacked ? (const uint8_t*)W->prepacked : W->idx;
   a.cent = W->cent;
@@ -865,10 +847,10 @@ cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int 
   a.scale_gather = row_gather;
   a.out = out;
   a.out_ld = epilogue == CQ_EPI_SWIGLU ? W->N / 2 : W->N;
-  a.tiles = nullptr;
-  a.tiles1 = nullptr;
-  a.tiles2 = nullptr;
-  a.n_tiles = nullptr;
+  a.group_offsets = group_offsets;
+  a.G = W->G;
+  a.small_max = small_max;
+  a.at_once = kAtOnce[half];
   a.row_tiles = W->N / kLargeRows;
   a.nblk = cq_tables_per_row(W);
   a.gsteps = a.nblk > 1 ? W->group_k / kStepK : W->K / kStepK;
@@ -877,11 +859,11 @@ cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int 
     cq_gemm_split_plan(W, M_total, epilogue, &ksplit, &a.ksteps);  // a split is planned for 64-token launches only
     a.part_stride = ksplit > 1 ? (size_t)M_total * W->N : 0;
   }
-  // workspace: tile lists, then the partial sums of the narrow tiles' K parts (if the launch may split them:
-  // the builder was told so with the same rule), then the 16-bit copy of the rows
-  size_t ws_off = tile_list_bytes(W->G, M_total);
+  // workspace: the partial sums of the tiles' K parts (if the launch may split them), then the 16-bit copy of the rows
+  size_t ws_off = 0;
   const bool tail = cq_gemm_large_tail_split(W, epilogue, out_kind);
   a.tail_part = nullptr;
+  a.w0 = half ? tile_widths<true>::w0 : tile_widths<false>::w0;
   a.w1 = half ? tile_widths<true>::w1 : tile_widths<false>::w1;
   a.w2 = tile_widths<true>::w2;
   a.tail_rows1 = cap1 * a.w1;
@@ -913,14 +895,10 @@ cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int 
   const int narrow = half ? kHalf : M_total <= 32 ? 32 : M_total <= 64 ? 64 : 0;
   // (for the grid: every widest tile of a launch of whole tiles covers more than 128 rows)
   const int max0 = half ? cap0 : M_total / (tile_widths<false>::w1 + 1) + 1;
-  const cq_status st = f16 ? dispatch_large<true>(a, epilogue, out_kind, t0, t1, counts, max0, cap1, narrow, s)
-                           : dispatch_large<false>(a, epilogue, out_kind, t0, t1, counts, max0, cap1, narrow, s);
+  const cq_status st = f16 ? dispatch_large<true>(a, epilogue, out_kind, max0, cap1, narrow, s)
+                           : dispatch_large<false>(a, epilogue, out_kind, max0, cap1, narrow, s);
   if (st != CQ_OK || !tail) return st;
-  // (a launch of a few dozen workgroups that return at once when the builder chose not to split)
-  a.tiles = t0;
-  a.tiles1 = t1;
-  a.tiles2 = t1 + (size_t)cap1 * 4;
-  a.n_tiles = counts;
+  // (a launch of a few dozen workgroups that return at once when nothing is split)
   hipLaunchKernelGGL(tail_sum_kernel, dim3((W->N / 4 + 255) / 256, 2 * cap1 + (a.tail_abs ? cap0 : 0), (half ? tile_widths<true>::w0 : tile_widths<false>::w0) / kTailSumRows),
                      dim3(256), 0, s, a, cap1);
   return cq_check_launch();

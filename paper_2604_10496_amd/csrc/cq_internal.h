@@ -149,10 +149,7 @@ bool cq_gemm_uses_large_tiles(const cq_codebook_weights* W, int M_total, int epi
 size_t cq_gemm_large_workspace_bytes(int G, int M_total, int K, bool with_conversion, int tail_N = 0);
 // narrow tiles of a plain fp32 product with a long K are cut into K parts (their partial sums live in the workspace)
 bool cq_gemm_large_tail_split(const cq_codebook_weights* W, int epilogue, int out_kind);
-// work lists of the large-tile kernel (device-built: group sizes are device data), of the groups with more than
-// small_max rows
-cq_status cq_gemm_build_lists(const cq_codebook_weights* W, const int32_t* group_offsets, int M_total, int small_max,
-                              void* workspace, hipStream_t s, bool tail_split, bool half);
+// the groups with more than small_max rows
 cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int a_kind, const float* row_scale,
                                const int32_t* row_gather, const int32_t* group_offsets, int M_total, int small_max,
                                int epilogue, void* out, int out_kind, void* workspace, hipStream_t s, bool half);
