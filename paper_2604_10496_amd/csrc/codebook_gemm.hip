@@ -31,6 +31,21 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restri
   }
 }
 
+// upper bound on the rows of a group
+int row_bound(int M_total, int max_group_rows) {
+  return max_group_rows > 0 && max_group_rows < M_total ? max_group_rows : M_total;
+}
+
+// Batches a little too large for one pass of 32 rows: where few groups have more, a second pass over their indices on
+// workgroups of its own is cheaper than the large-tile launch behind a streaming launch (and the launches that add up
+// both kinds' partial sums).  With a long K, groups of at most 128 rows, and fewer than 28 rows per group on average (20
+// with block-wise tables, whose form for 17..32 rows spills): us per layer of the Mixtral shape, two launches against
+// passes: 33 tokens 174 / 169, 77 tokens 207 / 192, 110 tokens 291 / 254; block-wise tables (narrow tiles against passes)
+// 40 tokens 360 / 266, 77 tokens 389 / 350, 100 tokens 372 / 393.
+bool streams_in_passes(const cq_codebook_weights* W, int M_total, int max_group_rows) {
+  return W->K > 2048 && row_bound(M_total, max_group_rows) <= 128 && (long)M_total < (cq_tables_per_row(W) > 1 ? 20L : 28L) * W->G;
+}
+
 // Whether a K range of ksteps steps runs the streaming kernel's pipelined unit loop: 8 or 7 steps for every wavefront,
 // or (one table per row) up to 4 with empty ones in between.
 bool pipelined(int ksteps, bool blockwise) {
@@ -45,12 +60,11 @@ bool pipelined(int ksteps, bool blockwise) {
 // into ranges of at most 4096 that different workgroups stream, and their partial sums are added in a
 // fixed order afterwards.  Plain products only (a nonlinear epilogue needs the whole sum).
 // Block-wise tables on the streaming kernel's pipelined loop: tables of 1024 weights (two K steps per wavefront
-// and table), groups of at most 32 rows (the loop's limit), and K ranges of whole tables that give every wavefront
+// and table), passes of 32 rows (the loop's limit; see streams_in_passes for more), and K ranges of whole tables that give every wavefront
 // exactly 8 steps (4096 weights) or 4 (2048); a nonlinear epilogue needs all of K in one range.
 bool cq_gemm_blockwise_streams(const cq_codebook_weights* W, int M_total, int epilogue, int max_group_rows) {
   if (kWaves != 8 || cq_is_w2(W) || W->group_k != 1024 || W->K % 2048 != 0) return false;
-  const int bound = max_group_rows > 0 && max_group_rows < M_total ? max_group_rows : M_total;
-  if (bound > 32) return false;
+  if (row_bound(M_total, max_group_rows) > 32 && !streams_in_passes(W, M_total, max_group_rows)) return false;
   return epilogue == CQ_EPI_NONE || W->K == 4096;
 }
 
@@ -143,12 +157,11 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
     // leave a good part of the chip idle (129 groups: one workgroup each on 256 compute units), so the grid has room
     // for two or four rounds of which the kernel uses what is cheapest.
     const bool large_too = cq_gemm_uses_large_tiles(W, M_total, epilogue, max_group_rows);
-    const int n_max = W->G < M_total ? W->G : M_total;   // groups that can have rows
+    const int n_max = (W->G < M_total ? W->G : M_total) + M_total / cq_route::kPassRows;   // passes over groups with rows
     // Where the pipelined loop is not available (other K), a group of 17..32 rows runs the plain loop on one
     // set of workgroups, several times slower per unit than the small groups around it: many short workgroups
     // then, so that the compute units the small groups leave early take the rest of the big ones.
-    const int row_bound = max_group_rows > 0 && max_group_rows < M_total ? max_group_rows : M_total;
-    const int target = row_bound > 16 && !pipelined(a.ksteps, cq_tables_per_row(W) > 1) ? 1024 : 256;
+    const int target = row_bound(M_total, max_group_rows) > 16 && !pipelined(a.ksteps, cq_tables_per_row(W) > 1) ? 1024 : 256;
     a.G = W->G;
     a.slots = target / a.ksplit > 1 ? target / a.ksplit : 1;
     a.rounds = target != 256 || (n_max <= 32 && !large_too) ? 1 : n_max <= 256 ? 2 : 4;
@@ -229,6 +242,11 @@ bool cq_gemm_uses_large_tiles(const cq_codebook_weights* W, int M_total, int epi
   if (cq_tables_per_row(W) > 1 && cq_gemm_blockwise_streams(W, M_total, epilogue, max_group_rows)) return false;
   // no group can have more rows than the streaming kernel takes: nothing for the large tiles to do
   if (cq_tables_per_row(W) == 1 && max_group_rows > 0 && max_group_rows <= kSmallMaxRows) return false;
+  if (cq_tables_per_row(W) == 1 && !cq_is_w2(W) && streams_in_passes(W, M_total, max_group_rows)) {
+    int ksplit, ksteps;
+    cq_gemm_split_plan(W, M_total, epilogue, &ksplit, &ksteps, max_group_rows);
+    if (pipelined(ksteps, false)) return false;
+  }
   return !cq_is_w2(W) && cq_gemm_large_supported(W) && (M_total > kSmallMaxRows || cq_tables_per_row(W) > 1);
 }
 

@@ -179,7 +179,6 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
   const int Qpad = (Qmax + kRing - 1) / kRing * kRing;
   const uint32_t lanebase0 = (uint32_t)(r32 * 4);
   const uint32_t lanebase1 = (uint32_t)((32 + r32) * 4);
-  const int n_tb = (Me + 31) >> 5;
 
   // four scaled sums of token row m for the weight rows row .. row + 3, through the epilogue
   auto store_quad = [&](const int m, const int row, const float (&x)[4]) {
@@ -563,8 +562,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
 #endif
   if constexpr (QT > 0) return;   // (block-wise tables exist in the pipelined loop only; the launcher sees to that)
 
-  for (int tb = 0; tb < n_tb; ++tb) {
-    const int Mb = min(32, Me - 32 * tb);
+  {
+    const int Mb = Me;
     const int Mpad = Mb <= 8 ? 8 : Mb <= 16 ? 16 : 32;     // divides the workgroup: a thread stages one token
     const int KSfull = 32768 / Mpad;                       // k values per slab (slab bytes / 2 / Mpad)
     const int qPerSlab = (KSfull >> 6) / NW;               // wavefront steps per slab
@@ -578,7 +577,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
     const bool svalid = st < Mb;
     size_t srow = 0;
     if (svalid) {
-      const int m = m0 + 32 * tb + st;
+      const int m = m0 + st;
       srow = (p.row_gather ? (size_t)p.row_gather[m] : (size_t)m) * K;
     }
     // Four chunks per pass, all loads issued before the first conversion (unconditional, clamped to the
@@ -641,7 +640,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
     // per-token scale of this lane's output column (loop invariant: loaded once per token block)
     float sc = 1.f;
     if (p.row_scale && r32 < Mb) {
-      const int m = m0 + 32 * tb + r32;
+      const int m = m0 + r32;
       sc = p.row_scale[p.row_gather ? p.row_gather[m] : m];
     }
     cent_load(u0);
@@ -790,7 +789,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
         }
         __syncthreads();  // the next unit's table overwrites this region
         if (r32 < Mb) {
-          const int m = m0 + 32 * tb + r32;
+          const int m = m0 + r32;
 #pragma unroll
           for (int h = 0; h < RPW / 4; ++h) {
             // MFMA 32x32 output: register v of a lane holds row 8*(v/4) + 4*(lane/32) + v%4, column lane%32
@@ -823,7 +822,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
       const uint32_t lbase[2] = {lanebase0, lanebase1};  // byte offset of this lane's row slot in a table entry
       float sc16 = 1.f;
       if (p.row_scale && i16 < Mb) {
-        const int m = m0 + 32 * tb + i16;
+        const int m = m0 + i16;
         sc16 = p.row_scale[p.row_gather ? p.row_gather[m] : m];
       }
       uint4 ring[kRing][2];
@@ -962,7 +961,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
           }
         }
         if (i16 < Mb) {
-          const int m = m0 + 32 * tb + i16;
+          const int m = m0 + i16;
           const int r = 2 * wave;
           const int row = u * 64 + (r >> 3) * 32 + ((r >> 2) & 1) * 16 + g4 * 4 + (r & 3);
           const float x0 = sc16 * val[0], x1 = sc16 * val[1];
@@ -995,7 +994,6 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
       if (sep) run_units16(std::false_type{});
       else run_units(std::false_type{});
     }
-    __syncthreads();  // the slab is restaged for the next token block
   }
 }
 

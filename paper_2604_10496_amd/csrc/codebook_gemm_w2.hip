@@ -386,7 +386,7 @@ cq_status cq_gemm_w2_launch(const cq_codebook_weights* W, const void* A, int a_k
   {
     // about one workgroup per compute unit, divided by the kernel among the groups that have rows (see the rule for
     // the rounds at the 4-bit kernel's launcher)
-    const int n_max = W->G < M_total ? W->G : M_total;
+    const int n_max = (W->G < M_total ? W->G : M_total) + M_total / cq_route::kPassRows;
     a.G = W->G;
     a.slots = 256 / a.ksplit > 1 ? 256 / a.ksplit : 1;
     a.rounds = n_max <= 32 ? 1 : n_max <= 256 ? 2 : 4;

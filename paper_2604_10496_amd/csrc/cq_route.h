@@ -207,43 +207,75 @@ __device__ __forceinline__ int workgroups_per_group(int n_act, int n_units, int 
 
 // The group that workgroup `b` of a streaming launch works on, chosen among the groups that have between 1 and
 // max_rows rows (the others cost the launch nothing: with one workgroup set per group of the layer, a batch of one
-// token left three quarters of the chip without work).  Sets the group, its first row and row count, this
-// workgroup's number among the group's workgroups and their count; false: no work for this workgroup.  All values are
-// uniform over the wavefront.  Called by all 64 lanes.
+// token left three quarters of the chip without work).  A group of more than kPassRows rows counts once per kPassRows of
+// them: further workgroups stream its indices again for the further rows.  Sets the group, its first row and row count
+// (of this pass), this workgroup's number among the pass's workgroups and their count; false: no work for this workgroup.
+// All values are uniform over the wavefront.  Called by all 64 lanes.
+constexpr int kPassRows = 32;
 struct group_share {
   int grp, m0, Me, chunk, chunks;
 };
 __device__ __forceinline__ bool pick_group(const int32_t* __restrict__ offsets, int G, int max_rows, int n_units,
                                            int slots, int rmax, int b, int lane, group_share& o) {
-  int base = 0, first, rows;
-  auto load = [&]() {
-    const int g = base + lane;
+  // the offsets of the first 128 groups are requested together and stay in registers, those of further rounds of 64
+  // groups are loaded again below
+  int f0, r0, f1 = 0, r1 = 0;
+  auto load = [&](int at, int& first, int& rows) {
+    const int g = at + lane;
     first = g < G ? offsets[g] : 0;
-    rows = g < G ? offsets[g + 1] - first : 0;
-    return (uint64_t)__ballot(rows > 0 && rows <= max_rows);
+    rows = (g < G ? offsets[g + 1] : 0) - first;
   };
-  uint64_t mask = load();
-  int n_act = __popcll(mask);
-  for (int g0 = 64; g0 < G; g0 += 64) {   // (more than 64 groups: the further rounds are loaded again below)
-    const int g = g0 + lane;
-    const int me = g < G ? offsets[g + 1] - offsets[g] : 0;
-    n_act += __popcll(__ballot(me > 0 && me <= max_rows));
+  load(0, f0, r0);
+  if (G > 64) load(64, f1, r1);
+  auto clip = [&](int& rows) { if (rows > max_rows) rows = 0; };
+  clip(r0);
+  clip(r1);
+  auto count = [&](int rows) {   // passes over the groups of a round
+    int n = __popcll(__ballot(rows > 0));
+    for (int j = 1;; ++j) {
+      const int c = __popcll(__ballot(rows > j * kPassRows));
+      if (c == 0) return n;
+      n += c;
+    }
+  };
+  int n_act = count(r0);
+  if (G > 64) n_act += count(r1);
+  for (int at = 128; at < G; at += 64) {
+    int f, r;
+    load(at, f, r);
+    clip(r);
+    n_act += count(r);
   }
   if (n_act == 0) return false;
   o.chunks = workgroups_per_group(n_act, n_units, slots, rmax, lane);
   int n = b / o.chunks;
   if (n >= n_act) return false;
   o.chunk = b - n * o.chunks;
-  while (n >= __popcll(mask)) {
-    n -= __popcll(mask);
-    base += 64;
-    mask = load();
+  int base = 0, first = f0, rows = r0;
+  for (int j = 0;;) {
+    const uint64_t mask = __ballot(rows > j * kPassRows);
+    const int c = __popcll(mask);
+    if (n < c) {
+      const int src = nth_set_lane(mask, n, lane);
+      o.grp = base + src;
+      o.m0 = __builtin_amdgcn_readlane(first, src) + j * kPassRows;
+      o.Me = min(kPassRows, __builtin_amdgcn_readlane(rows, src) - j * kPassRows);
+      return true;
+    }
+    n -= c;
+    ++j;
+    if (c == 0) {   // (n < n_act: some later round has the pass)
+      j = 0;
+      base += 64;
+      if (base == 64) {
+        first = f1;
+        rows = r1;
+      } else {
+        load(base, first, rows);
+        clip(rows);
+      }
+    }
   }
-  const int src = nth_set_lane(mask, n, lane);
-  o.grp = base + src;
-  o.m0 = __builtin_amdgcn_readlane(first, src);
-  o.Me = __builtin_amdgcn_readlane(rows, src);
-  return true;
 }
 
 // a5 folded into a product launch for decode-sized batches (cq_route_fuse): the rows of group `grp`, derived by

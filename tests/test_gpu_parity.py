@@ -510,6 +510,8 @@ def test_gemm_instantiation_matrix(B, a_kind, epi, out_kind, blockwise, prepacke
     (300, 64, 512, {g: 1 + g % 2 for g in range(300)}),    # more groups than one round holds
     (66, 256, 2048, {g: 16 + g % 19 for g in range(3, 60, 7)}),   # ... next to large tiles (33 and 34 rows)
     (9, 448, 2048, {8: 32}), (200, 64, 4096, {199: 20, 100: 3}), (4, 128, 3584, {2: 32, 3: 24}),
+    # groups of more than 32 rows in passes: long K, few rows on average (the last in a second round of 64 groups)
+    (8, 256, 4096, {0: 65, 3: 33, 5: 1, 7: 20}), (8, 256, 14336, {1: 97, 6: 31}), (70, 256, 3584, {2: 64, 69: 34, 65: 3}),
 ])
 def test_gemm_streaming_workgroups_by_active_groups(B, G, N, K, rows, prepacked):
     """The streaming launch gives workgroups to the groups that have rows only: few active groups among many (also
@@ -639,7 +641,9 @@ BLOCKWISE_CASES = [(256, 1024, 512, [3, 40]), (256, 1408, 1024, [1, 0, 33, 300])
                    # tables of 1024 weights, at most 16 rows in all, K a multiple of 2048: the streaming kernel's
                    # pipelined loop with a table switch every two steps (K ranges of 4096 or 2048 weights)
                    (256, 2048, 1024, [3, 0, 9, 4]), (512, 4096, 1024, [16]), (256, 6144, 1024, [1, 8]),
-                   (256, 14336, 1024, [7, 5]), (256, 8192, 1024, [2, 12])]
+                   (256, 14336, 1024, [7, 5]), (256, 8192, 1024, [2, 12]),
+                   # ... up to 128 rows in passes of 32 while groups have fewer than 20 on average
+                   (256, 4096, 1024, [40, 0, 33, 17, 8, 0, 0, 0]), (256, 14336, 1024, [33, 0, 2, 0])]
 
 
 @pytest.mark.parametrize("prepacked", [True, False])
