@@ -235,12 +235,19 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float* part, int ks
 
 }  // namespace
 
+// Few columns (router logits): one wavefront spans them and the four wavefronts take 64 tokens; on tiles of 128 or 256
+// columns half or more of them had none.  64 experts, tiles of 128 columns against this: 100 tokens 14.3 / 9.2 us, 512
+// tokens 16 / 11 us, 3000 tokens 24 / 25 us (nothing left to gain); 40 tokens on 16-token tiles 5.7 / 7.7 us.
+namespace {
+bool spans_columns(int T, int N) { return N <= 16 || (N <= 64 && T >= 64 && T <= 1024); }
+}  // namespace
+
 cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K) {
   cq_gemm_f32_plan p;
-  p.mb = T >= 64 && N > 16 ? 4 : 1;
-  const bool narrow = N <= 16;   // (one column block per wavefront, its four wavefronts on 64 tokens)
+  const bool narrow = N != K && spans_columns(T, N);   // (a square B is a rotation)
+  p.mb = T >= 64 && !narrow ? 4 : 1;
   const int tm = p.mb == 4 ? 128 : narrow ? 64 : 16;
-  const int tn = p.mb == 4 ? 128 : narrow ? 16 : 256;
+  const int tn = p.mb == 4 ? 128 : narrow ? 64 : 256;
   const long wgs = (long)((N + tn - 1) / tn) * ((T + tm - 1) / tm);
   int ks = (int)(256 / wgs);   // K chunks such that one round of workgroups covers the launch (96 tiles: 2, not 3)
   if (ks > 16) ks = 16;
@@ -257,9 +264,12 @@ cq_status cq_gemm_f32_launch(const float* A, const float* B, int b_transposed, i
                              const cq_gemm_f32_plan& plan, float* C, uint32_t* zero_me, int zero_n, hipStream_t s) {
   const int kchunk = plan.kchunk;
   dim3 block(256);
-  if (b_transposed && N <= 16) {
-    hipLaunchKernelGGL((gemm_f32_kernel<1, 4, true, 8, 1>), dim3(1, (T + 63) / 64, plan.ksplit), block, 0, s, A, B, C, T, N,
-                       K, kchunk, zero_me, zero_n);
+  if (b_transposed && spans_columns(T, N)) {
+    const dim3 grid(1, (T + 63) / 64, plan.ksplit);
+    if (N <= 16)
+      hipLaunchKernelGGL((gemm_f32_kernel<1, 4, true, 8, 1>), grid, block, 0, s, A, B, C, T, N, K, kchunk, zero_me, zero_n);
+    else
+      hipLaunchKernelGGL((gemm_f32_kernel<1, 4, true, 4, 4>), grid, block, 0, s, A, B, C, T, N, K, kchunk, zero_me, zero_n);
   } else if (plan.mb == 4) {
     dim3 grid((N + 127) / 128, (T + 127) / 128, plan.ksplit);
     if (b_transposed)
