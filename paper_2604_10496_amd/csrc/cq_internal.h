@@ -72,7 +72,6 @@ cq_status cq_rotate_quant_ex(const float* X, const float* R, int T, int H, int a
 // logits in one launch.  Supported sizes also fit the one-workgroup routing kernel that follows.
 // topk_ids / topk_w [T, top_k]: NULL, or the launch also selects every token's experts (a4).
 bool cq_front_small_supported(int T, int H, int E, int top_k);
-bool cq_front_small_selects(int E);   // whether it can select the experts
 cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H, int act_bits, const float* Wr,
                                 const float* bias, int E, float* XR, int8_t* Q, uint16_t* Q16, float* scale,
                                 float* logits, int top_k, int32_t* topk_ids, float* topk_w, hipStream_t s);

@@ -7,12 +7,8 @@
 // (up to 16 partial sums and the router rows of up to 8 experts) are issued before the first use: the
 // kernel costs about one memory latency.
 //
-// More than 16 experts: one workgroup per token and 16 experts, each of which adds up the row again (it costs less than
-// a launch: DeepSeek-V2-Lite shape at 16 tokens, five launches before the gate/up product were 29 us, three are
-// 23 us).
-//
-// A token's top-k (a4) needs nothing but the token's own logits, so with up to 16 experts the same workgroup can select
-// the experts and form their weights (topk_ids given); the grouping by expert (a5), which needs every token's
+// A token's top-k (a4) needs nothing but the token's own logits, so the same workgroup can select the
+// experts and form their weights (topk_ids given); the grouping by expert (a5), which needs every token's
 // choice, is then left to the launch that follows.
 //
 // (Letting the workgroup that finishes last also do the grouping, behind a device-scope fence and a ticket
@@ -30,19 +26,13 @@ constexpr int kEarlyE = 8;        // experts whose router rows are requested up 
 
 template <int NC>
 __global__ __launch_bounds__(kFrontThreads) void front_small_kernel(
-    const float* part, int ksplit, int in_place, int T, int H, float qmax, const float* __restrict__ Wr_all,
-    const float* __restrict__ bias_all, int E_all, float* XR, int8_t* __restrict__ Q, uint16_t* __restrict__ Q16,
-    float* __restrict__ scale, float* __restrict__ logits_all, int top_k, int32_t* __restrict__ topk_ids,
+    const float* part, int ksplit, int in_place, int T, int H, float qmax, const float* __restrict__ Wr,
+    const float* __restrict__ bias, int E, float* XR, int8_t* __restrict__ Q, uint16_t* __restrict__ Q16,
+    float* __restrict__ scale, float* __restrict__ logits, int top_k, int32_t* __restrict__ topk_ids,
     float* __restrict__ topk_w) {
   __shared__ float red[16];
   __shared__ float lred[16][kFrontMaxE];
   const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // blockIdx.y: block of kFrontMaxE experts; the first block's workgroup also writes the rotated row and its codes
-  const int e0 = blockIdx.y * kFrontMaxE;
-  const bool first = blockIdx.y == 0;
-  const int E = min(kFrontMaxE, E_all - e0);
-  const float* Wr = Wr_all + (size_t)e0 * H;
-  const float* bias = bias_all ? bias_all + e0 : nullptr;
 
   float4 v[NC];
   float lsum[kFrontMaxE];
@@ -70,7 +60,7 @@ __global__ __launch_bounds__(kFrontThreads) void front_small_kernel(
         const float4 q = *reinterpret_cast<const float4*>(part + ((size_t)z * T + t) * H + c);
         acc.x += q.x; acc.y += q.y; acc.z += q.z; acc.w += q.w;
       }
-      if (!in_place && first) *reinterpret_cast<float4*>(XR + (size_t)t * H + c) = acc;
+      if (!in_place) *reinterpret_cast<float4*>(XR + (size_t)t * H + c) = acc;
       v[i] = acc;
       amax = fmaxf(amax, fmaxf(fmaxf(fabsf(acc.x), fabsf(acc.y)), fmaxf(fabsf(acc.z), fabsf(acc.w))));
       // ---- this thread's share of the router logits ----
@@ -100,7 +90,7 @@ __global__ __launch_bounds__(kFrontThreads) void front_small_kernel(
 #pragma unroll
   for (int i = 1; i < 16; ++i) amax = fmaxf(amax, red[i]);
   const float s = amax == 0.f ? 1.f : amax / qmax;
-  if (tid == 0 && first) scale[t] = s;
+  if (tid == 0) scale[t] = s;
   {
     float x = 0.f;
     if (tid < E) {
@@ -108,15 +98,13 @@ __global__ __launch_bounds__(kFrontThreads) void front_small_kernel(
 #pragma unroll
       for (int i = 1; i < 16; ++i) x += lred[i][tid];
       if (bias) x += bias[tid];
-      logits_all[(size_t)t * E_all + e0 + tid] = x;
+      logits[(size_t)t * E + tid] = x;
     }
     // a4 for this token: the logits are in the lanes of wavefront 0, which selects on its own (no LDS, no
     // barrier) while the other wavefronts go on to the codes
     if (topk_ids && wave == 0)   // (uniform per wavefront)
       cq_route::wave_topk_regs(x, E, top_k, lane, topk_ids + (size_t)t * top_k, topk_w + (size_t)t * top_k);
   }
-
-  if (!first) return;
 
   // ---- integer codes: round to nearest, ties to even (v_rndne_f32) ----
 #pragma unroll
@@ -142,12 +130,9 @@ __global__ __launch_bounds__(kFrontThreads) void front_small_kernel(
 
 bool cq_front_small_supported(int T, int H, int E, int top_k) {
   // the limits of the one-workgroup routing kernel that follows, and of this kernel's registers
-  // (more than 16 experts: blocks of them add the row up again; at 100 tokens and 64 experts that takes 24 us, as much as
-  // the separate launches)
-  return (long)T * top_k <= 1024 && E <= 128 && H <= 2 * 4 * kFrontThreads && H % 4 == 0 &&
-         (long)T * E * H <= (E <= kFrontMaxE ? 1L << 23 : 1L << 22);
+  return (long)T * top_k <= 1024 && E <= kFrontMaxE && H <= 2 * 4 * kFrontThreads && H % 4 == 0 &&
+         (long)T * E * H <= (1L << 23);
 }
-bool cq_front_small_selects(int E) { return E <= kFrontMaxE; }
 
 cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H, int act_bits, const float* Wr,
                                 const float* bias, int E, float* XR, int8_t* Q, uint16_t* Q16, float* scale,
@@ -155,10 +140,10 @@ cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H,
   const float qmax = (float)((1 << (act_bits - 1)) - 1);
   const int in_place = (partials == XR && ksplit == 1) ? 1 : 0;
   if (H <= 4 * kFrontThreads)
-    hipLaunchKernelGGL(front_small_kernel<1>, dim3(T, (E + kFrontMaxE - 1) / kFrontMaxE), dim3(kFrontThreads), 0, s, partials, ksplit, in_place, T, H, qmax,
+    hipLaunchKernelGGL(front_small_kernel<1>, dim3(T), dim3(kFrontThreads), 0, s, partials, ksplit, in_place, T, H, qmax,
                        Wr, bias, E, XR, Q, Q16, scale, logits, top_k, topk_ids, topk_w);
   else
-    hipLaunchKernelGGL(front_small_kernel<2>, dim3(T, (E + kFrontMaxE - 1) / kFrontMaxE), dim3(kFrontThreads), 0, s, partials, ksplit, in_place, T, H, qmax,
+    hipLaunchKernelGGL(front_small_kernel<2>, dim3(T), dim3(kFrontThreads), 0, s, partials, ksplit, in_place, T, H, qmax,
                        Wr, bias, E, XR, Q, Q16, scale, logits, top_k, topk_ids, topk_w);
   return cq_check_launch();
 }

@@ -193,10 +193,6 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     return cq_gemm_f32_launch(X, L->R, 0, T, L->H, L->H, p, *part, nullptr, 0, hs);
   };
 
-  // a5 alone (the counting sort's workspace lies at the start of the scratch area, which a3 / a4 no longer use)
-  auto group = [&]() {
-    return cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
-  };
   if (!mark(0)) return CQ_ERR_HIP;
   const bool bf16_codes = use_bf16_codes(L, T);
   bool fuse_route = false;   // a5 folded into the gate/up launch (decode-sized batches)
@@ -218,17 +214,15 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     st = rotate(&parts, &part);
     if (st != CQ_OK) return st;
     if (!mark(1)) return CQ_ERR_HIP;
-    // With few experts the front launch also selects them and a launch that only groups follows it; when the gate/up
-    // launch can do the grouping itself, that one falls away, too.
-    const bool front_topk = cq_front_small_selects(L->E);
-    fuse_route = front_topk && cq_gemm_can_fuse_route(&L->gate_up, T, L->E, L->S, L->top_k, CQ_EPI_SWIGLU);
+    // The front launch also selects the experts; when the gate/up launch can do the grouping itself, the launch that
+    // only groups falls away.
+    fuse_route = cq_gemm_can_fuse_route(&L->gate_up, T, L->E, L->S, L->top_k, CQ_EPI_SWIGLU);
     st = cq_front_small_launch(part, parts, T, L->H, L->act_bits, L->Wr, L->bias, L->E, XR, Q, Q16, scale, logits,
-                               L->top_k, front_topk ? ids : nullptr, front_topk ? tw : nullptr, hs);
+                               L->top_k, ids, tw, hs);
     if (st != CQ_OK) return st;
     if (!fuse_route) {
-      st = front_topk ? group()
-                      : cq_route_permute(nullptr, nullptr, nullptr, logits, T, L->H, L->E, L->top_k, L->S, logits, ids,
-                                         tw, offsets, perm, inv_perm, src_token, scratch, scratch_bytes, stream);
+      // (the counting sort's workspace lies at the start of the scratch area, which nothing uses any more)
+      st = cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
       if (st != CQ_OK) return st;
     }
     if (!mark(2)) return CQ_ERR_HIP;
