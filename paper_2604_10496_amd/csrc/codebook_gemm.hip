@@ -60,8 +60,9 @@ bool pipelined(int ksteps, bool blockwise) {
 // into ranges of at most 4096 that different workgroups stream, and their partial sums are added in a
 // fixed order afterwards.  Plain products only (a nonlinear epilogue needs the whole sum).
 // Block-wise tables on the streaming kernel's pipelined loop: tables of 1024 weights (two K steps per wavefront
-// and table), passes of 32 rows (the loop's limit; see streams_in_passes for more), and K ranges of whole tables that give every wavefront
-// exactly 8 steps (4096 weights) or 4 (2048); a nonlinear epilogue needs all of K in one range.
+// and table), up to 32 rows (the loop's limit; in passes of 32 where streams_in_passes says so), and K ranges of whole
+// tables that give every wavefront exactly 8 steps (4096 weights) or 4 (2048); a nonlinear epilogue needs all of K in one
+// range.
 bool cq_gemm_blockwise_streams(const cq_codebook_weights* W, int M_total, int epilogue, int max_group_rows) {
   if (kWaves != 8 || cq_is_w2(W) || W->group_k != 1024 || W->K % 2048 != 0) return false;
   if (row_bound(M_total, max_group_rows) > 32 && !streams_in_passes(W, M_total, max_group_rows)) return false;

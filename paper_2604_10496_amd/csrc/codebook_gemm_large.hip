@@ -33,7 +33,7 @@ namespace {
 constexpr int kLargeRows = 256;  // weight rows per workgroup
 constexpr int kStepK = 64;       // K per pipeline step
 constexpr int kStepBytes = kStepK * 2;  // one token's share of a step in LDS and in global memory
-// tokens of the tiles of the three work lists: whole tiles (one workgroup per compute unit), half tiles (two)
+// tokens of the tiles of the three widths: whole tiles (one workgroup per compute unit), half tiles (two)
 template <bool HALF>
 struct tile_widths {
   static constexpr int w0 = HALF ? 128 : 256, w1 = HALF ? 96 : 128, w2 = 64;
@@ -119,7 +119,7 @@ constexpr int epilogue_row_stride(int epi, int outk) {
 template <bool F16, int EPI, int OUTK, int C, int D, bool BLK, bool PRE, bool A32 = false>
 __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, const int mrow0_, const int mcnt_,
                                            const int rt_, const int kz_ = 0, const int kS_ = 1, const int tail_row0 = 0) {
-  // (uniform, but read through the work lists: kept in scalar registers from here on)
+  // (uniform, but derived per work item: kept in scalar registers from here on)
   const int grp = __builtin_amdgcn_readfirstlane(grp_), mrow0 = __builtin_amdgcn_readfirstlane(mrow0_);
   const int mcnt = __builtin_amdgcn_readfirstlane(mcnt_), rt = __builtin_amdgcn_readfirstlane(rt_);
   const int kz = __builtin_amdgcn_readfirstlane(kz_), kS = __builtin_amdgcn_readfirstlane(kS_);
@@ -461,7 +461,7 @@ struct tile_map {
   int n0, n1, n2;           // tiles per list
   int kS0, kS1;             // K parts of a tile of list 0, and of lists 1 and 2
   int from[2], to[2];       // offsets of the lane's groups of rounds 0 and 1
-  int base, m0, a, last, incl;   // this round: the lane's group: first row, whole tiles, rows left; tiles up to it
+  int base, m0, a, last, incl;   // this batch of 64: the lane's group: first row, whole tiles, rows left; tiles up to it
   uint64_t m1, m2;          // ... its groups whose last tile is in list 1, 2
 
   __device__ __forceinline__ void round(const LargeArgs& p, int f, int t) {
