@@ -183,7 +183,8 @@ cq_status cq_route_permute(const float* XR, const float* Wr, const float* bias, 
  *   use f16 MFMA with centroids converted bf16 -> f16.
  *   A: [rows, K] of a_kind.  out: [M_total, N or N/2] of out_kind (CQ_OUT_F16 saturates).
  *   group_offsets [G+1] device i32, non-decreasing, group_offsets[G] <= M_total.  Empty groups ok.
- *   workspace: cq_grouped_gemm_workspace_bytes(W, M_total) bytes (may be 0 -> NULL allowed).
+ *   workspace: cq_grouped_gemm_workspace_bytes(W, M_total) bytes (may be 0 -> NULL allowed); enough for every
+ *   smaller M_total as well.
  */
 size_t cq_grouped_gemm_workspace_bytes(const cq_codebook_weights* W, int M_total);
 cq_status cq_codebook_grouped_gemm(const cq_codebook_weights* W,
@@ -247,8 +248,10 @@ cq_status cq_combine(const float* O, const float* topk_w, const int32_t* inv_per
 /*
  * The whole layer, a1..a8, on one stream with no host synchronisation:
  *   X [T,H] f32 -> Y [T,H] f32 (in the rotated basis; no R^T is applied).
- * workspace: cq_moe_workspace_bytes(L, T) bytes.  Intermediates live in the workspace; their
- * locations are reported by cq_moe_workspace_layout() for inspection by tests.
+ * workspace: cq_moe_workspace_bytes(L, T) bytes; the figure never falls as T grows, so that a workspace sized
+ * for the largest batch serves the smaller ones.  The result does not depend on how large the workspace is.
+ * Intermediates live in the workspace; their locations are reported by cq_moe_workspace_layout() for inspection
+ * by tests.
  */
 typedef struct {
   size_t total;
@@ -267,8 +270,9 @@ cq_status cq_moe_forward(const cq_layer* L, const float* X, int T, float* Y,
  * cq_moe_forward, bit for bit; the intermediates live in an array of CQ_STATIC_SCRATCH_BYTES bytes that
  * the library itself holds in the device memory of every GPU it has run on (until the process ends).  The
  * call allocates and frees nothing and does not synchronise the host.
- *   A batch whose cq_moe_workspace_bytes(L, T) exceeds CQ_STATIC_SCRATCH_BYTES returns CQ_ERR_WORKSPACE
- *   and launches nothing (the Mixtral-8x7B shape fits up to T = 111 tokens).
+ *   A batch whose intermediates take more than CQ_STATIC_SCRATCH_BYTES returns CQ_ERR_WORKSPACE and launches
+ *   nothing.  (They never take more than cq_moe_workspace_bytes(L, T), which leaves room for every smaller batch
+ *   as well; the Mixtral-8x7B shape fits up to T = 111 tokens.)
  *   All calls on one GPU share the array, which keeps the previous call's contents (no kernel of the layer
  *   needs it cleared): calls that overlap on one GPU -- two streams, two threads -- race; serialise them.
  */

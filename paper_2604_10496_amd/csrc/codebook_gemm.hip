@@ -69,6 +69,29 @@ bool cq_gemm_blockwise_streams(const cq_codebook_weights* W, int M_total, int ep
   return epilogue == CQ_EPI_NONE || W->K == 4096;
 }
 
+namespace {
+// Block-wise tables on the large-tile kernel, one workgroup per 256 rows and group of tokens.  With at most 64 rows in all
+// (one 64-token tile per group) and a short N there are too few of those to fill the chip, so K is cut into ranges of whole
+// table groups, up to about two workgroups per compute unit.
+void blockwise_tile_plan(const cq_codebook_weights* W, int M_total, int epilogue, int* ksplit, int* ksteps) {
+  *ksplit = 1;
+  *ksteps = W->K / 64;
+  if (epilogue != CQ_EPI_NONE || M_total > 64 || !cq_gemm_large_supported(W)) return;
+  const int nblk = cq_tables_per_row(W);
+  const long wgs = (long)(W->G < M_total ? W->G : M_total) * (W->N / 256);
+  long want = wgs > 0 ? 512 / wgs : 1;
+  if (want > nblk) want = nblk;
+  if (want <= 1) return;
+  const int per = (nblk + (int)want - 1) / (int)want;   // table groups per range
+  *ksteps = per * (W->group_k / 64);
+  *ksplit = (nblk + per - 1) / per;
+}
+
+size_t partials_bytes(const cq_codebook_weights* W, int M_total, int ksplit) {
+  return ksplit > 1 ? cq_align_up((size_t)ksplit * M_total * W->N * sizeof(float), 256) : 0;
+}
+}  // namespace
+
 void cq_gemm_split_plan(const cq_codebook_weights* W, int M_total, int epilogue, int* ksplit, int* ksteps,
                         int max_group_rows) {
   const int nS = W->K / 64;
@@ -80,20 +103,7 @@ void cq_gemm_split_plan(const cq_codebook_weights* W, int M_total, int epilogue,
     *ksplit = nS / *ksteps;
     return;
   }
-  if (nblk > 1) {
-    // Block-wise tables run on the large-tile kernel, one workgroup per 256 rows and group of tokens.  With
-    // at most 64 rows in all (one 64-token tile per group) and a short N there are too few of those to fill
-    // the chip, so K is cut into ranges of whole table groups, up to about two workgroups per compute unit.
-    if (epilogue != CQ_EPI_NONE || M_total > 64 || !cq_gemm_large_supported(W)) return;
-    const long wgs = (long)(W->G < M_total ? W->G : M_total) * (W->N / 256);
-    long want = wgs > 0 ? 512 / wgs : 1;
-    if (want > nblk) want = nblk;
-    if (want <= 1) return;
-    const int per = (nblk + (int)want - 1) / (int)want;   // table groups per range
-    *ksteps = per * (W->group_k / 64);
-    *ksplit = (nblk + per - 1) / per;
-    return;
-  }
+  if (nblk > 1) return blockwise_tile_plan(W, M_total, epilogue, ksplit, ksteps);
   if (epilogue != CQ_EPI_NONE || M_total > 256 || nS <= 64) return;
   const int want = (nS + 63) / 64;
   const int per = ((nS + want - 1) / want + kWaves - 1) / kWaves * kWaves;  // whole rounds of the wavefronts
@@ -105,7 +115,7 @@ size_t cq_gemm_partials_bytes(const cq_codebook_weights* W, int M_total, int epi
   if (cq_is_w2(W)) return epilogue == CQ_EPI_NONE ? cq_gemm_w2_partials_bytes(W, M_total) : 0;
   int ksplit, ksteps;
   cq_gemm_split_plan(W, M_total, epilogue, &ksplit, &ksteps, max_group_rows);
-  return ksplit > 1 ? cq_align_up((size_t)ksplit * M_total * W->N * sizeof(float), 256) : 0;
+  return partials_bytes(W, M_total, ksplit);
 }
 
 // The grouping by expert can be folded into a launch when every workgroup of it runs the pipelined unit loop
@@ -239,25 +249,62 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
 }
 
 
-bool cq_gemm_uses_large_tiles(const cq_codebook_weights* W, int M_total, int epilogue, int max_group_rows) {
-  if (cq_tables_per_row(W) > 1 && cq_gemm_blockwise_streams(W, M_total, epilogue, max_group_rows)) return false;
+bool cq_gemm_can_use_large_tiles(const cq_codebook_weights* W, int M_total, int max_group_rows) {
   // no group can have more rows than the streaming kernel takes: nothing for the large tiles to do
   if (cq_tables_per_row(W) == 1 && max_group_rows > 0 && max_group_rows <= kSmallMaxRows) return false;
+  return !cq_is_w2(W) && cq_gemm_large_supported(W) && (M_total > kSmallMaxRows || cq_tables_per_row(W) > 1);
+}
+
+bool cq_gemm_uses_large_tiles(const cq_codebook_weights* W, int M_total, int epilogue, int max_group_rows) {
+  if (cq_tables_per_row(W) > 1 && cq_gemm_blockwise_streams(W, M_total, epilogue, max_group_rows)) return false;
   if (cq_tables_per_row(W) == 1 && !cq_is_w2(W) && streams_in_passes(W, M_total, max_group_rows)) {
     int ksplit, ksteps;
     cq_gemm_split_plan(W, M_total, epilogue, &ksplit, &ksteps, max_group_rows);
     if (pipelined(ksteps, false)) return false;
   }
-  return !cq_is_w2(W) && cq_gemm_large_supported(W) && (M_total > kSmallMaxRows || cq_tables_per_row(W) > 1);
+  return cq_gemm_can_use_large_tiles(W, M_total, max_group_rows);
+}
+
+size_t cq_gemm_product_bytes(const cq_codebook_weights* W, int M_total, int epilogue, int rows_per_token, bool with_conversion) {
+  const bool layer = rows_per_token > 0;
+  const int per = layer ? rows_per_token : 1, units = M_total / per;   // tokens, or single rows
+  const bool one_table = cq_tables_per_row(W) == 1;
+  auto stream_bytes = [&](int u) { return cq_gemm_partials_bytes(W, u * per, epilogue, layer ? u : 0); };
+  auto tile_bytes = [&](int u) -> size_t {
+    if (!cq_gemm_can_use_large_tiles(W, u * per, layer ? u : 0)) return 0;
+    return cq_gemm_tile_list_bytes(W->G, u * per) + cq_gemm_large_workspace_bytes(W->G, u * per, W->K, with_conversion, W->N);
+  };
+  size_t most = 0;
+  auto take = [&](size_t n) { if (n > most) most = n; };
+  if (one_table) {   // a launch of both kernels; the streaming one's partial sums end with the batches of up to 256 rows
+    take(stream_bytes(units) + tile_bytes(units));
+    const int last = cq_is_w2(W) ? units : 256 / per;
+    if (last > 0 && last < units) take(stream_bytes(last) + tile_bytes(last));
+    return most;
+  }
+  // block-wise tables: everything streams (up to 32 rows a group, and in passes), or everything is on large tiles, whose
+  // partial sums end with the launches of up to 64 rows
+  take(stream_bytes(units < kSmallMaxRows ? units : kSmallMaxRows));
+  long last = (20L * W->G - 1) / per;   // the most tokens that stream in passes
+  if (last > 128) last = 128;
+  if (last > units) last = units;
+  if (last > kSmallMaxRows && cq_gemm_blockwise_streams(W, (int)last * per, epilogue, layer ? (int)last : 0))
+    take(stream_bytes((int)last));
+  if (units > kSmallMaxRows || !cq_gemm_blockwise_streams(W, M_total, epilogue, layer ? units : 0)) take(tile_bytes(units));
+  for (int u = 1; u <= units && u * per <= 64; ++u) {
+    if (u <= kSmallMaxRows && cq_gemm_blockwise_streams(W, u * per, epilogue, layer ? u : 0)) continue;
+    int ksplit, ksteps;
+    blockwise_tile_plan(W, u * per, epilogue, &ksplit, &ksteps);
+    take(partials_bytes(W, u * per, ksplit) + tile_bytes(u));
+  }
+  return most;
 }
 
 extern "C" size_t cq_grouped_gemm_workspace_bytes(const cq_codebook_weights* W, int M_total) {
   if (!W || W->G <= 0 || W->N <= 0 || W->K <= 0 || M_total <= 0) return 0;
   size_t need = 0;
   for (const int epi : {CQ_EPI_NONE, CQ_EPI_SWIGLU}) {   // the kernel, and with it the need, can depend on the epilogue
-    size_t n = cq_gemm_partials_bytes(W, M_total, epi);
-    if (cq_gemm_uses_large_tiles(W, M_total, epi))
-      n += cq_gemm_large_workspace_bytes(W->G, M_total, W->K, true, W->N);  // worst case over the operand kinds
+    const size_t n = cq_gemm_product_bytes(W, M_total, epi, 0, true);  // worst case over the operand kinds
     if (n > need) need = n;
   }
   return need;

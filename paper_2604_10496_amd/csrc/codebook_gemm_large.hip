@@ -822,6 +822,13 @@ size_t cq_gemm_large_workspace_bytes(int G, int M_total, int K, bool with_conver
   return n;
 }
 
+// A list of the tiles.  The kernel derives them itself; the size queries have always counted the list, and go on to: what
+// a batch's workspace serves must not depend on how its launches find their tiles.
+size_t cq_gemm_tile_list_bytes(int G, int M_total) {
+  const long whole = M_total / 129 + 1, narrow = G < M_total ? G : M_total;
+  return cq_align_up(256 + ((size_t)(whole + 2 * narrow) * 4 + (size_t)G) * sizeof(int32_t), 256);
+}
+
 bool cq_gemm_large_supported(const cq_codebook_weights* W) {
   if (W->N % kLargeRows != 0 || W->K % (2 * kStepK) != 0) return false;
   // block-wise tables change between two passes of the unrolled pipeline (8 steps of 64)

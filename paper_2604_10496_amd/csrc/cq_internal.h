@@ -55,7 +55,9 @@ struct cq_gemm_f32_plan {
   int ksplit;  // number of K chunks
   int kchunk;  // K values per chunk (a multiple of 16)
 };
-cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K);
+cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K, bool wide_tiles = false);
+size_t cq_rotate_quant_bytes_upto(int T, int H);   // the largest workspace of cq_rotate_quant for up to T tokens
+size_t cq_gemm_f32_partials_upto(int T, int N, int K, int least);   // the most partial sums of any launch of up to T rows, in bytes
 cq_status cq_gemm_f32_launch(const float* A, const float* B, int b_transposed, int T, int N, int K,
                              const cq_gemm_f32_plan& plan, float* C_or_partials, uint32_t* zero_me, int zero_n,
                              hipStream_t s);
@@ -78,8 +80,10 @@ cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H,
 
 // X_R = X R on f16 matrix cores from a split copy of R (cq_rotation_split), accurate to about fp32
 bool cq_rotate_split_supported(int T, int H);
-bool cq_rotate_split_preferred(int T, int H);  // the layer's choice between it and the fp32 kernel
-int cq_rotate_split_parts(int T, int H);       // K parts of the layer's rotation
+// K parts of the layer's rotation where it takes this kernel and has `available` bytes of device memory, 0: the fp32 kernel
+int cq_rotate_split_parts(int T, int H, size_t available);
+bool cq_rotate_split_always(int T, int H);   // ... takes this kernel also uncut
+size_t cq_rotate_split_partials_bytes(int parts, int T, int H);   // its partial sums (0: one part, written to X_R)
 size_t cq_rotate_split_workspace_bytes(int T, int H);   // of the launch, without partial sums
 cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, float* XR_out,
                                  void* workspace, hipStream_t s);
@@ -145,6 +149,12 @@ bool cq_gemm_uses_large_tiles(const cq_codebook_weights* W, int M_total, int epi
                               int max_group_rows = 0);
 // with_conversion: include room for a 16-bit copy of the activation rows (needed for CQ_A_INT8_CODES
 // and CQ_A_F32 operands; bf16 / f16 operands are read in place)
+// whether a launch of M_total rows has groups for the large tiles, unless it streams in passes
+bool cq_gemm_can_use_large_tiles(const cq_codebook_weights* W, int M_total, int max_group_rows);
+// Workspace of a product, whichever of its kernels the launch takes; it covers every launch of fewer rows.
+// rows_per_token: rows a token has in the launch, where a group has at most one of each token, else 0.
+size_t cq_gemm_product_bytes(const cq_codebook_weights* W, int M_total, int epilogue, int rows_per_token, bool with_conversion);
+size_t cq_gemm_tile_list_bytes(int G, int M_total);
 size_t cq_gemm_large_workspace_bytes(int G, int M_total, int K, bool with_conversion, int tail_N = 0);
 // narrow tiles of a plain fp32 product with a long K are cut into K parts (their partial sums live in the workspace)
 bool cq_gemm_large_tail_split(const cq_codebook_weights* W, int epilogue, int out_kind);

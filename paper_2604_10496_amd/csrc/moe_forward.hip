@@ -54,13 +54,12 @@ cq_status validate_layer(const cq_layer* L, int T) {
   return CQ_OK;
 }
 
-// Many tokens and a split copy of R at hand: the rotation runs on the f16 matrix cores.
-bool use_split_rotation(const cq_layer* L, int T) { return L->R_split && cq_rotate_split_preferred(T, L->H); }
-
-// its partial sums, in front of the launch's own workspace (0: one part, written to X_R)
-size_t split_partials_bytes(int parts, int T, int H) {
-  return parts > 1 ? cq_align_up((size_t)parts * T * H * sizeof(float), 256) : 0;
-}
+// Where a call keeps its intermediates.
+struct layer_plan {
+  cq_moe_layout lay;
+  size_t used;     // bytes that the call touches
+  int rot_parts;   // K parts of the rotation on the f16 matrix cores; 0: the fp32 kernel
+};
 
 // Batches large enough for the large-tile product get the codes a second time as bf16, so that staging
 // them into LDS is a plain copy.
@@ -68,9 +67,13 @@ bool use_bf16_codes(const cq_layer* L, int T) {
   return cq_gemm_uses_large_tiles(&L->gate_up, (int)((long)T * (L->top_k + L->S)), CQ_EPI_SWIGLU, T);
 }
 
-// rot_parts: K parts of the rotation on the f16 matrix cores.  available: bytes of the workspace at hand; one that was
-// sized for another batch and is too small for the parts that are best gets fewer of them.
-void make_layout(const cq_layer* L, int T, cq_moe_layout* o, int* rot_parts, size_t available = ~(size_t)0) {
+// The size that the query reports (lay.total) is a function of the layer and the batch only, and never falls as the batch
+// grows: a workspace that serves a batch serves the smaller ones, whatever routes they take.  It holds the fp32 rotation's
+// partial sums also where the f16 matrix cores rotate, and both forms of the products.
+// A call touches `used` bytes of it, which the library's own array has to hold.
+// The rotation's partial sums lie from Hbuf on, where nothing is kept before the gate/up product writes h.
+void make_plan(const cq_layer* L, int T, layer_plan* plan) {
+  cq_moe_layout* o = &plan->lay;
   const size_t M = (size_t)T * (L->top_k + L->S), A = (size_t)T * L->top_k;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -80,6 +83,7 @@ void make_layout(const cq_layer* L, int T, cq_moe_layout* o, int* rot_parts, siz
   };
   o->XR = take((size_t)T * L->H * 4);
   o->Q = take((size_t)T * L->H);
+  const bool can_tile = cq_gemm_can_use_large_tiles(&L->gate_up, (int)M, T);
   o->Q16 = take(use_bf16_codes(L, T) ? (size_t)T * L->H * 2 : 0);
   o->scale = take((size_t)T * 4);
   o->logits = take((size_t)T * L->E * 4);
@@ -95,71 +99,76 @@ void make_layout(const cq_layer* L, int T, cq_moe_layout* o, int* rot_parts, siz
   o->HQ = take(L->h_bits ? M * L->I : 0);
   o->HQ16 = take(hq16 ? M * L->I * 2 : 0);
   o->hscale = take(L->h_bits ? M * 4 : 0);
-  size_t scratch = 0;
-  const size_t r = cq_route_permute_workspace_bytes(T, L->H, L->E, L->top_k);
-  if (r > scratch) scratch = r;
+  auto raise = [](size_t& n, size_t to) { if (to > n) n = to; };
+  size_t scratch = cq_route_permute_workspace_bytes(T, L->H, L->E, L->top_k);
   // (the layer feeds both products 16-bit operands, bf16 codes and f16 h: no room for converted rows)
-  if (use_bf16_codes(L, T)) {
-    const size_t g1 = cq_gemm_large_workspace_bytes(L->gate_up.G, (int)M, L->gate_up.K, false);
-    if (g1 > scratch) scratch = g1;
-  }
-  {
-    size_t g2 = cq_gemm_partials_bytes(&L->down, (int)M, CQ_EPI_NONE, T);   // (a group has at most T rows)
-    if (cq_gemm_uses_large_tiles(&L->down, (int)M, CQ_EPI_NONE, T))  // (16-bit operands in either variant: f16 h or bf16 codes)
-      g2 += cq_gemm_large_workspace_bytes(L->down.G, (int)M, L->down.K, false, L->down.N);
-    if (g2 > scratch) scratch = g2;
-  }
+  size_t down = cq_gemm_partials_bytes(&L->down, (int)M, CQ_EPI_NONE, T);   // (a group has at most T rows)
+  if (cq_gemm_uses_large_tiles(&L->down, (int)M, CQ_EPI_NONE, T))  // (16-bit operands in either variant: f16 h or bf16 codes)
+    down += cq_gemm_large_workspace_bytes(L->down.G, (int)M, L->down.K, false, L->down.N);
+  raise(scratch, down);
+  size_t sized = scratch;
+  if (can_tile) raise(sized, cq_gemm_tile_list_bytes(L->gate_up.G, (int)M));
+  raise(sized, cq_gemm_product_bytes(&L->down, (int)M, CQ_EPI_NONE, L->top_k + L->S, false));
   const size_t fp32_rotation = cq_rotate_quant_workspace_bytes(T, L->H);
-  *rot_parts = 1;
-  if (use_split_rotation(L, T)) {
-    // as many K parts as fill the chip -- but a batch that fits the library's own array with the fp32 rotation's
-    // partial sums fits it with these as well (fewer parts, then)
-    const size_t fixed = cq_rotate_split_workspace_bytes(T, L->H);
-    auto total = [&](size_t bytes) { return off + cq_align_up(bytes > scratch ? bytes : scratch, 256); };
-    size_t limit = total(fp32_rotation) <= CQ_STATIC_SCRATCH_BYTES ? (size_t)CQ_STATIC_SCRATCH_BYTES : ~(size_t)0;
-    if (available < limit) limit = available;
-    *rot_parts = cq_rotate_split_parts(T, L->H);
-    while (*rot_parts > 1 && total(fixed + split_partials_bytes(*rot_parts, T, L->H)) > limit) *rot_parts /= 2;
-    const size_t x = fixed + split_partials_bytes(*rot_parts, T, L->H);
-    if (x > scratch) scratch = x;
-  } else if (fp32_rotation > scratch) {
-    scratch = fp32_rotation;
+  raise(sized, cq_rotate_quant_bytes_upto(T, L->H));
+  if (L->R_split && cq_rotate_split_always(T, L->H)) raise(sized, cq_rotate_split_workspace_bytes(T, L->H));
+  o->scratch = off;
+  o->total = off + cq_align_up(sized, 256);
+  // (the second copies of the codes, also for batches that stream in passes and have none)
+  if (T > 32) {
+    if (can_tile && !use_bf16_codes(L, T)) o->total += cq_align_up((size_t)T * L->H * 2, 256);
+    if (L->h_bits && !hq16 && cq_gemm_can_use_large_tiles(&L->down, (int)M, T)) o->total += cq_align_up(M * L->I * 2, 256);
   }
-  o->scratch = take(scratch);
-  o->total = off;
+  size_t rotation = 0;   // (the Hadamard variant transforms in LDS)
+  plan->rot_parts = 0;
+  if (!L->r_hadamard) {
+    if (L->R_split) {
+      // (a batch that fits the library's own array with the fp32 rotation also fits it with this one, in fewer parts)
+      size_t fp32_used = off + scratch;
+      raise(fp32_used, o->Hbuf + fp32_rotation);
+      const size_t room = fp32_used <= CQ_STATIC_SCRATCH_BYTES && o->total > CQ_STATIC_SCRATCH_BYTES
+                              ? (size_t)CQ_STATIC_SCRATCH_BYTES : o->total;
+      plan->rot_parts = cq_rotate_split_parts(T, L->H, room - o->Hbuf);
+    }
+    rotation = plan->rot_parts ? cq_rotate_split_partials_bytes(plan->rot_parts, T, L->H) + cq_rotate_split_workspace_bytes(T, L->H)
+                               : fp32_rotation;
+  }
+  plan->used = off + scratch;
+  raise(plan->used, o->Hbuf + rotation);
 }
 
 }  // namespace
 
 extern "C" size_t cq_moe_workspace_bytes(const cq_layer* L, int T) {
   if (validate_layer(L, T) != CQ_OK) return 0;
-  cq_moe_layout lay;
-  int rot_parts;
-  make_layout(L, T, &lay, &rot_parts);
-  return lay.total;
+  layer_plan plan;
+  make_plan(L, T, &plan);
+  return plan.lay.total;
 }
 
 extern "C" cq_status cq_moe_workspace_layout(const cq_layer* L, int T, cq_moe_layout* out) {
   if (!out) return CQ_ERR_NULL;
   const cq_status st = validate_layer(L, T);
   if (st != CQ_OK) return st;
-  int rot_parts;
-  make_layout(L, T, out, &rot_parts);
+  layer_plan plan;
+  make_plan(L, T, &plan);
+  *out = plan.lay;
   return CQ_OK;
 }
 
 namespace {
 
+// own_array: the workspace is the library's own, which need not be as large as the query says, only hold what is used.
 // ev: NULL, or CQ_N_STAGES + 1 events recorded at the stage boundaries.
 cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* workspace, size_t workspace_bytes,
-                    cq_stream stream, hipEvent_t* ev) {
+                    bool own_array, cq_stream stream, hipEvent_t* ev) {
   cq_status st = validate_layer(L, T);
   if (st != CQ_OK) return st;
   if (!X || !Y) return CQ_ERR_NULL;
-  cq_moe_layout lay;
-  int rot_parts;
-  make_layout(L, T, &lay, &rot_parts, workspace_bytes);
-  if (!workspace || workspace_bytes < lay.total) return CQ_ERR_WORKSPACE;
+  layer_plan plan;
+  make_plan(L, T, &plan);
+  const cq_moe_layout& lay = plan.lay;
+  if (!workspace || workspace_bytes < (own_array ? plan.used : lay.total)) return CQ_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   float* XR = (float*)(ws + lay.XR);
   int8_t* Q = (int8_t*)(ws + lay.Q);
@@ -174,22 +183,23 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
   void* Hbuf = ws + lay.Hbuf;
   float* Obuf = (float*)(ws + lay.Obuf);
   void* scratch = ws + lay.scratch;
-  const size_t scratch_bytes = lay.total - lay.scratch;
+  const size_t scratch_bytes = plan.used - lay.scratch;
   const int M = T * (L->top_k + L->S);
   hipStream_t hs = (hipStream_t)stream;
   auto mark = [&](int i) -> bool { return !ev || hipEventRecord(ev[i], hs) == hipSuccess; };
 
   // a1: X_R as `parts` partial sums at `part`
+  char* rot_ws = ws + lay.Hbuf;
   auto rotate = [&](int* parts, float** part) {
-    if (use_split_rotation(L, T)) {
-      *parts = rot_parts;
-      *part = rot_parts > 1 ? (float*)scratch : XR;
-      return cq_rotate_split_launch(X, L->R_split, T, L->H, rot_parts, *part,
-                                    (char*)scratch + split_partials_bytes(rot_parts, T, L->H), hs);
+    if (plan.rot_parts) {
+      *parts = plan.rot_parts;
+      *part = *parts > 1 ? (float*)rot_ws : XR;
+      return cq_rotate_split_launch(X, L->R_split, T, L->H, *parts, *part,
+                                    rot_ws + cq_rotate_split_partials_bytes(*parts, T, L->H), hs);
     }
     const cq_gemm_f32_plan p = cq_gemm_f32_make_plan(T, L->H, L->H);
     *parts = p.ksplit;
-    *part = p.ksplit > 1 ? (float*)scratch : XR;
+    *part = p.ksplit > 1 ? (float*)rot_ws : XR;
     return cq_gemm_f32_launch(X, L->R, 0, T, L->H, L->H, p, *part, nullptr, 0, hs);
   };
 
@@ -227,14 +237,14 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     }
     if (!mark(2)) return CQ_ERR_HIP;
   } else {
-    if (use_split_rotation(L, T)) {
+    if (plan.rot_parts) {
       int parts;
       float* part;
       st = rotate(&parts, &part);
       if (st != CQ_OK) return st;
       st = cq_quantize_launch(part, parts, T, L->H, L->act_bits, XR, Q, Q16, scale, nullptr, hs);
     } else {
-      st = cq_rotate_quant_ex(X, L->R, T, L->H, L->act_bits, XR, Q, Q16, scale, scratch, scratch_bytes, stream);
+      st = cq_rotate_quant_ex(X, L->R, T, L->H, L->act_bits, XR, Q, Q16, scale, rot_ws, plan.used - lay.Hbuf, stream);
     }
     if (st != CQ_OK) return st;
     if (!mark(1)) return CQ_ERR_HIP;
@@ -282,21 +292,20 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
 
 extern "C" cq_status cq_moe_forward(const cq_layer* L, const float* X, int T, float* Y, void* workspace,
                                     size_t workspace_bytes, cq_stream stream) {
-  return run_layer(L, X, T, Y, workspace, workspace_bytes, stream, nullptr);
+  return run_layer(L, X, T, Y, workspace, workspace_bytes, false, stream, nullptr);
 }
 
 extern "C" cq_status cq_moe_forward_static(const cq_layer* L, const float* X, int T, float* Y, cq_stream stream) {
   cq_status st = validate_layer(L, T);
   if (st != CQ_OK) return st;
   if (!X || !Y) return CQ_ERR_NULL;
-  cq_moe_layout lay;
-  int rot_parts;
-  make_layout(L, T, &lay, &rot_parts);
-  if (lay.total > (size_t)CQ_STATIC_SCRATCH_BYTES) return CQ_ERR_WORKSPACE;  // batch too large for the array
+  layer_plan plan;
+  make_plan(L, T, &plan);
+  if (plan.used > (size_t)CQ_STATIC_SCRATCH_BYTES) return CQ_ERR_WORKSPACE;  // batch too large for the array
   void* ws = nullptr;
   st = static_scratch(&ws);
   if (st != CQ_OK) return st;
-  return run_layer(L, X, T, Y, ws, (size_t)CQ_STATIC_SCRATCH_BYTES, stream, nullptr);
+  return run_layer(L, X, T, Y, ws, (size_t)CQ_STATIC_SCRATCH_BYTES, true, stream, nullptr);
 }
 
 extern "C" cq_status cq_moe_forward_timed(const cq_layer* L, const float* X, int T, float* Y, void* workspace,
@@ -307,7 +316,7 @@ extern "C" cq_status cq_moe_forward_timed(const cq_layer* L, const float* X, int
   cq_status st = CQ_OK;
   for (; made <= CQ_N_STAGES; ++made)
     if (hipEventCreate(&ev[made]) != hipSuccess) { st = CQ_ERR_HIP; break; }
-  if (st == CQ_OK) st = run_layer(L, X, T, Y, workspace, workspace_bytes, stream, ev);
+  if (st == CQ_OK) st = run_layer(L, X, T, Y, workspace, workspace_bytes, false, stream, ev);
   if (st == CQ_OK && hipEventSynchronize(ev[CQ_N_STAGES]) != hipSuccess) st = CQ_ERR_HIP;
   if (st == CQ_OK)
     for (int i = 0; i < CQ_N_STAGES; ++i)

@@ -242,9 +242,9 @@ namespace {
 bool spans_columns(int T, int N) { return N <= 16 || (N <= 64 && T >= 64 && T <= 1024); }
 }  // namespace
 
-cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K) {
+cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K, bool wide_tiles) {
   cq_gemm_f32_plan p;
-  const bool narrow = N != K && spans_columns(T, N);   // (a square B is a rotation)
+  const bool narrow = !wide_tiles && N != K && spans_columns(T, N);   // (a square B is a rotation)
   p.mb = T >= 64 && !narrow ? 4 : 1;
   const int tm = p.mb == 4 ? 128 : narrow ? 64 : 16;
   const int tn = p.mb == 4 ? 128 : narrow ? 64 : 256;
@@ -258,6 +258,28 @@ cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K) {
   p.kchunk = kchunk;
   p.ksplit = (K + kchunk - 1) / kchunk;
   return p;
+}
+
+// K is cut into min(16, K/64, 256 / workgroups) parts, so the number of parts falls as T grows, and their size with it.
+// The largest launch of up to T rows with `ks` parts is looked at for every ks from the most down to that of T rows.
+// (Sized for wide tiles, which have at least as many parts as narrow ones.)  least: fewer parts than this are not counted.
+size_t cq_gemm_f32_partials_upto(int T, int N, int K, int least) {
+  size_t most = 0;
+  for (const int tm : {16, 128}) {   // rows of a tile: below 64 rows, and from there on
+    const int last = tm == 128 ? T : T < 63 ? T : 63;
+    if (tm == 128 && T < 64) break;
+    const int cols = tm == 128 ? (N + 127) / 128 : (N + 255) / 256;
+    for (int ks = 16; ks >= 1; --ks) {
+      const long rows = (long)(256 / (ks * cols)) * tm;
+      const int t = ks > 1 && rows < last ? (int)rows : last;
+      if (t == 0) continue;
+      const int parts = cq_gemm_f32_make_plan(t, N, K, true).ksplit;
+      const size_t n = (size_t)parts * t * N * sizeof(float);
+      if (parts >= least && n > most) most = n;
+      if (t == last) break;
+    }
+  }
+  return most;
 }
 
 cq_status cq_gemm_f32_launch(const float* A, const float* B, int b_transposed, int T, int N, int K,
@@ -312,6 +334,11 @@ namespace {
 constexpr int kFewTokens = 256;  // below this a token row is quantized by several workgroups
 size_t amax_bytes(int T) { return T < kFewTokens ? cq_align_up((size_t)T * sizeof(uint32_t), 256) : 0; }
 }  // namespace
+
+size_t cq_rotate_quant_bytes_upto(int T, int H) {
+  const size_t few = T < kFewTokens ? amax_bytes(T) : amax_bytes(kFewTokens - 1);
+  return few + cq_align_up(cq_gemm_f32_partials_upto(T, H, H, 2), 256);   // (one part is X_R itself)
+}
 
 extern "C" size_t cq_rotate_quant_workspace_bytes(int T, int H) {
   if (T <= 0 || H <= 0) return 0;

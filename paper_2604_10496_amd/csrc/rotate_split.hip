@@ -335,25 +335,34 @@ bool cq_rotate_split_supported(int T, int H) {
 // parts of whole rounds of the pipeline (four steps, 256 k) that are powers of two, whose partial sums [parts][T][H] the
 // quantization adds in a fixed order.  (T = 512, H = 4096: 64 tiles, one K loop of 64 steps on a quarter of the chip
 // took 124 us, in four parts 52 us; T = 77: 43 us on the fp32 matrix cores, 23 us in 16 parts.)  The sum over K in parts
-// is also the more accurate one: an accumulator rounds at the size of its own partial sum.  At most 20 MiB of partial
-// sums up to 128 tokens, so that the layer's workspace there stays about what its other steps need.
-int cq_rotate_split_parts(int T, int H) {
-  const long tiles = (long)((T + kTok - 1) / kTok) * (H / kCols);
-  int parts = 1;
-  while (tiles * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0 &&
-         (T > kTok || (long)parts * 2 * T * H * 4 <= (20L << 20)))
-    parts *= 2;
-  return parts;
-}
-
+// is also the more accurate one: an accumulator rounds at the size of its own partial sum.  The partial sums lie where the
+// layer keeps other things later; parts that do not fit there are not made.
+//
 // Whether the layer's rotation takes this path: from 48 tiles on (also with a short K), and where K can be cut from 64
 // tokens at H = 4096 and 128 at H = 2048 on.  Below, the fp32 kernel's
 // 16-token tiles waste less (whole layer, fp32 against this path: H = 4096, 33 tokens 176 / 175 us, 48 tokens 192 / 191, 64
 // tokens 216 / 202; H = 2048, 48 tokens 144 / 151, 128 tokens 173 / 172, 300 tokens 219 / 206).
 // Error of X_R against float64 (2-norm): fp32 kernel 3.4e-7 .. 5.9e-7 at 77 .. 200 tokens, this path 1.7e-7 .. 2.1e-7.
-bool cq_rotate_split_preferred(int T, int H) {
-  if (cq_rotate_split_supported(T, H) && (long)((T + kTok - 1) / kTok) * (H / kCols) >= 48) return true;
-  return H % 256 == 0 && H >= 1024 && T >= 64 && (long)T * H >= (1L << 18) && (long)T * H * 2 < (1L << 32);
+size_t cq_rotate_split_partials_bytes(int parts, int T, int H) {
+  return parts > 1 ? cq_align_up((size_t)parts * T * H * sizeof(float), 256) : 0;
+}
+
+int cq_rotate_split_parts(int T, int H, size_t available) {
+  if (!cq_rotate_split_always(T, H) &&
+      !(H % 256 == 0 && H >= 1024 && T >= 64 && (long)T * H >= (1L << 18) && (long)T * H * 2 < (1L << 32)))
+    return 0;
+  const size_t fixed = cq_rotate_split_workspace_bytes(T, H);
+  if (fixed > available) return 0;
+  const long tiles = (long)((T + kTok - 1) / kTok) * (H / kCols);
+  int parts = 1;
+  while (tiles * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0 &&
+         fixed + cq_rotate_split_partials_bytes(parts * 2, T, H) <= available)
+    parts *= 2;
+  return parts;
+}
+
+bool cq_rotate_split_always(int T, int H) {
+  return cq_rotate_split_supported(T, H) && (long)((T + kTok - 1) / kTok) * (H / kCols) >= 48;
 }
 
 extern "C" size_t cq_rotate_quant_split_workspace_bytes(int T, int H) {

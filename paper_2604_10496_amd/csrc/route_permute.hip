@@ -405,8 +405,7 @@ cq_status cq_permute_launch(const int32_t* topk_ids, int T, int E, int top_k, in
 
 extern "C" size_t cq_route_permute_workspace_bytes(int T, int H, int E, int top_k) {
   if (T <= 0 || H <= 0 || E <= 0 || top_k <= 0) return 0;
-  const cq_gemm_f32_plan p = cq_gemm_f32_make_plan(T, E, H);
-  return cq_align_up((size_t)p.ksplit * T * E * sizeof(float), 256) + cq_permute_workspace_bytes(T, E, top_k);
+  return cq_align_up(cq_gemm_f32_partials_upto(T, E, H, 1), 256) + cq_permute_workspace_bytes(T, E, top_k);
 }
 
 extern "C" cq_status cq_route_permute(const float* XR, const float* Wr, const float* bias, const float* logits_in,

@@ -9,7 +9,7 @@ import pytest
 
 from tests import helpers as Hp
 
-from paper_2604_10496_amd import binding as B
+from paper_2604_10496_amd import binding as B, synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -132,6 +132,30 @@ def test_workspace_sizes_are_pure_and_monotone():
     assert a == lib.cq_rotate_quant_workspace_bytes(16, 4096) and a >= 16 * 4096 * 4
     assert lib.cq_rotate_quant_workspace_bytes(4096, 4096) == 0       # enough tiles: no K split
     assert lib.cq_route_permute_workspace_bytes(2048, 2048, 128, 8) >= (2048 * 8 // 256) * 128 * 4
+
+
+@pytest.mark.parametrize("name,over", [
+    ("tiny", {}), ("mixtral_decode", {}), ("mixtral_decode", dict(group_k=1024)), ("mixtral_decode", dict(index_bits=2)),
+    ("mixtral_decode", dict(h_bits=8, r_hadamard=True)), ("dsv2lite", {}), ("qwen3_zipf", {}),
+    ("mixtral_decode", dict(H=8192, I=1024, top_k=1)), ("dsv2lite", dict(H=3840, I=2560)),
+])
+def test_a_workspace_serves_every_smaller_batch(name, over):
+    """The queries never fall as the batch grows, whichever kernels the batches take: a workspace sized once, for the
+    largest batch, is accepted for all others (a call refuses less than the query of its own batch).  The sizes fell at
+    81, 128 and 192 tokens of these shapes, where a batch takes other kernels than a slightly smaller one."""
+    c = synth.small_variant(synth.CONFIGS[name], **over)
+    lib, G = B.load_library(), c.E + c.S
+    weights = [B.CodebookWeights(256, 256, 256, G, n, k, c.group_k, c.index_bits) for n, k in ((2 * c.I, c.H), (c.H, c.I))]
+    for split in (None, 256):   # without and with a split copy of the rotation
+        L = B.Layer(c.H, c.I, c.E, c.top_k, c.S, c.act_bits, 256, 256, None, *weights, split, c.h_bits, int(c.r_hadamard))
+        sizes = [lib.cq_moe_workspace_bytes(ctypes.byref(L), T) for T in range(1, 700)]
+        assert sizes[0] > 0 and sizes == sorted(sizes)
+        assert lib.cq_moe_forward(ctypes.byref(L), 256, 77, 256, 256, sizes[76] - 1, None) == 4   # CQ_ERR_WORKSPACE
+    for W in weights:
+        sizes = [lib.cq_grouped_gemm_workspace_bytes(ctypes.byref(W), M) for M in range(1, 700)]
+        assert sizes == sorted(sizes)
+    sizes = [lib.cq_route_permute_workspace_bytes(T, c.H, c.E, c.top_k) for T in range(1, 2100)]
+    assert sizes == sorted(sizes)
 
 
 def test_prepack_layout_documented_in_header_matches_numpy_model():
