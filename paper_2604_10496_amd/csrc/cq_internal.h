@@ -83,6 +83,7 @@ bool cq_rotate_split_supported(int T, int H);
 // K parts of the layer's rotation where it takes this kernel and has `available` bytes of device memory, 0: the fp32 kernel
 int cq_rotate_split_parts(int T, int H, size_t available);
 bool cq_rotate_split_always(int T, int H);   // ... takes this kernel also uncut
+size_t cq_rotate_split_bytes_upto(int T, int H);   // the most device memory that it takes for any batch of up to T tokens
 size_t cq_rotate_split_partials_bytes(int parts, int T, int H);   // its partial sums (0: one part, written to X_R)
 size_t cq_rotate_split_workspace_bytes(int T, int H);   // of the launch, without partial sums
 cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, float* XR_out,

@@ -119,6 +119,7 @@ void make_plan(const cq_layer* L, int T, layer_plan* plan) {
     if (can_tile && !use_bf16_codes(L, T)) o->total += cq_align_up((size_t)T * L->H * 2, 256);
     if (L->h_bits && !hq16 && cq_gemm_can_use_large_tiles(&L->down, (int)M, T)) o->total += cq_align_up(M * L->I * 2, 256);
   }
+  if (L->R_split && !L->r_hadamard) raise(o->total, o->Hbuf + cq_align_up(cq_rotate_split_bytes_upto(T, L->H), 256));
   size_t rotation = 0;   // (the Hadamard variant transforms in LDS)
   plan->rot_parts = 0;
   if (!L->r_hadamard) {

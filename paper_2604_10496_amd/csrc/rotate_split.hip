@@ -336,7 +336,7 @@ bool cq_rotate_split_supported(int T, int H) {
 // quantization adds in a fixed order.  (T = 512, H = 4096: 64 tiles, one K loop of 64 steps on a quarter of the chip
 // took 124 us, in four parts 52 us; T = 77: 43 us on the fp32 matrix cores, 23 us in 16 parts.)  The sum over K in parts
 // is also the more accurate one: an accumulator rounds at the size of its own partial sum.  The partial sums lie where the
-// layer keeps other things later; parts that do not fit there are not made.
+// layer keeps other things later.
 //
 // Whether the layer's rotation takes this path: from 48 tiles on (also with a short K), and where K can be cut from 64
 // tokens at H = 4096 and 128 at H = 2048 on.  Below, the fp32 kernel's
@@ -347,17 +347,39 @@ size_t cq_rotate_split_partials_bytes(int parts, int T, int H) {
   return parts > 1 ? cq_align_up((size_t)parts * T * H * sizeof(float), 256) : 0;
 }
 
-int cq_rotate_split_parts(int T, int H, size_t available) {
-  if (!cq_rotate_split_always(T, H) &&
-      !(H % 256 == 0 && H >= 1024 && T >= 64 && (long)T * H >= (1L << 18) && (long)T * H * 2 < (1L << 32)))
-    return 0;
-  const size_t fixed = cq_rotate_split_workspace_bytes(T, H);
-  if (fixed > available) return 0;
+namespace {
+// parts that fill the chip
+int full_parts(int T, int H) {
   const long tiles = (long)((T + kTok - 1) / kTok) * (H / kCols);
   int parts = 1;
-  while (tiles * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0 &&
-         fixed + cq_rotate_split_partials_bytes(parts * 2, T, H) <= available)
-    parts *= 2;
+  while (tiles * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0) parts *= 2;
+  return parts;
+}
+bool layer_sized(int T, int H) {
+  return H % 256 == 0 && H >= 1024 && T >= 64 && (long)T * H >= (1L << 18) && (long)T * H * 2 < (1L << 32);
+}
+}  // namespace
+
+// (The parts fall as T grows, and the bytes with them: each number of parts counts with the largest T that has it.)
+size_t cq_rotate_split_bytes_upto(int T, int H) {
+  size_t most = 0;
+  if (H % kCols != 0 || T < 64) return 0;
+  for (int parts = 1; parts <= 256; parts *= 2) {
+    const long last = 256 / (parts * (long)(H / kCols)) * kTok;
+    const int t = parts > 1 && last < T ? (int)last : T;
+    if (t < 64 || !(cq_rotate_split_always(t, H) || layer_sized(t, H))) continue;
+    const size_t n = cq_rotate_split_workspace_bytes(t, H) + cq_rotate_split_partials_bytes(full_parts(t, H), t, H);
+    if (n > most) most = n;
+  }
+  return most;
+}
+
+int cq_rotate_split_parts(int T, int H, size_t available) {
+  if (!cq_rotate_split_always(T, H) && !layer_sized(T, H)) return 0;
+  const size_t fixed = cq_rotate_split_workspace_bytes(T, H);
+  if (fixed > available) return 0;
+  int parts = full_parts(T, H);
+  while (parts > 1 && fixed + cq_rotate_split_partials_bytes(parts, T, H) > available) parts /= 2;
   return parts;
 }
 
