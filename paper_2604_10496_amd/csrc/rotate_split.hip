@@ -338,25 +338,33 @@ bool cq_rotate_split_supported(int T, int H) {
 // is also the more accurate one: an accumulator rounds at the size of its own partial sum.  The partial sums lie where the
 // layer keeps other things later.
 //
-// Whether the layer's rotation takes this path: from 48 tiles on (also with a short K), and where K can be cut from 64
-// tokens at H = 4096 and 128 at H = 2048 on.  Below, the fp32 kernel's
-// 16-token tiles waste less (whole layer, fp32 against this path: H = 4096, 33 tokens 176 / 175 us, 48 tokens 192 / 191, 64
-// tokens 216 / 202; H = 2048, 48 tokens 144 / 151, 128 tokens 173 / 172, 300 tokens 219 / 206).
+// Whether the layer's rotation takes this path: uncut from 48 tiles on, cut into parts where these make at least 44
+// workgroups -- from 64 tokens on, or, narrower than 3072 columns, from a second tile of tokens, and narrower than 2048 from
+// 513 tokens on.  A workgroup's K loop takes about 1.7 us per step, so a width whose K steps do not divide by 8 (an odd
+// multiple of 256) stays with the fp32 kernel until it has tiles enough uncut.  Rotation and quantization, fp32 kernel
+// against this one, us (workgroups of this one): H = 4096, 64 tokens 49 / 38 (256), 129..160 86 / 52; H = 3072, 96 tokens
+// 40 / 40 (48), 160 59 / 42; H = 2048, 128 tokens 28 / 29 (64), 160 34 / 30 (128); H = 3840 (one part), 128 tokens 53 / 117
+// (15), 256 87 / 117 (30), 300 147 / 121 (45); H = 2304 (one part), 512 tokens 72 / 80 (36), 640 95 / 81 (45); H = 2560 (two),
+// 256 tokens 49 / 53 (40), 300 62 / 55 (60); H = 1024, 400 tokens 26 / 28 (64), 513 28 / 29 (80), 769 33 / 30.
 // Error of X_R against float64 (2-norm): fp32 kernel 3.4e-7 .. 5.9e-7 at 77 .. 200 tokens, this path 1.7e-7 .. 2.1e-7.
 size_t cq_rotate_split_partials_bytes(int parts, int T, int H) {
   return parts > 1 ? cq_align_up((size_t)parts * T * H * sizeof(float), 256) : 0;
 }
 
 namespace {
-// parts that fill the chip
+// full_parts: parts that fill the chip
+constexpr int kFewest = 44;   // fewest workgroups of a launch in parts
+long tiles(int T, int H) { return (long)((T + kTok - 1) / kTok) * (H / kCols); }
 int full_parts(int T, int H) {
-  const long tiles = (long)((T + kTok - 1) / kTok) * (H / kCols);
   int parts = 1;
-  while (tiles * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0) parts *= 2;
+  while (tiles(T, H) * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0) parts *= 2;
   return parts;
 }
-bool layer_sized(int T, int H) {
-  return H % 256 == 0 && H >= 1024 && T >= 64 && (long)T * H >= (1L << 18) && (long)T * H * 2 < (1L << 32);
+bool preferred(int T, int H) {
+  if (cq_rotate_split_always(T, H)) return true;
+  if (H % kCols != 0 || H < 1024 || (long)T * H < (1L << 18) || (long)T * H * 2 >= (1L << 32)) return false;
+  if (T < (H >= 3072 ? 64 : H >= 2048 ? kTok + 1 : 513)) return false;
+  return tiles(T, H) * full_parts(T, H) >= kFewest;
 }
 }  // namespace
 
@@ -367,7 +375,7 @@ size_t cq_rotate_split_bytes_upto(int T, int H) {
   for (int parts = 1; parts <= 256; parts *= 2) {
     const long last = 256 / (parts * (long)(H / kCols)) * kTok;
     const int t = parts > 1 && last < T ? (int)last : T;
-    if (t < 64 || !(cq_rotate_split_always(t, H) || layer_sized(t, H))) continue;
+    if (!preferred(t, H)) continue;   // (then no smaller batch of as many parts is, either)
     const size_t n = cq_rotate_split_workspace_bytes(t, H) + cq_rotate_split_partials_bytes(full_parts(t, H), t, H);
     if (n > most) most = n;
   }
@@ -375,16 +383,16 @@ size_t cq_rotate_split_bytes_upto(int T, int H) {
 }
 
 int cq_rotate_split_parts(int T, int H, size_t available) {
-  if (!cq_rotate_split_always(T, H) && !layer_sized(T, H)) return 0;
+  if (!preferred(T, H)) return 0;
   const size_t fixed = cq_rotate_split_workspace_bytes(T, H);
   if (fixed > available) return 0;
   int parts = full_parts(T, H);
   while (parts > 1 && fixed + cq_rotate_split_partials_bytes(parts, T, H) > available) parts /= 2;
-  return parts;
+  return cq_rotate_split_always(T, H) || tiles(T, H) * parts >= kFewest ? parts : 0;
 }
 
 bool cq_rotate_split_always(int T, int H) {
-  return cq_rotate_split_supported(T, H) && (long)((T + kTok - 1) / kTok) * (H / kCols) >= 48;
+  return cq_rotate_split_supported(T, H) && tiles(T, H) >= 48;
 }
 
 extern "C" size_t cq_rotate_quant_split_workspace_bytes(int T, int H) {

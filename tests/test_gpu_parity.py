@@ -1175,8 +1175,8 @@ def test_layer_reduced_shapes(B, name, over):
 @pytest.mark.parametrize("name,over", [
     ("mixtral_decode", dict(H=4096, I=64, T=64, E=4)),              # one token tile, 16 K parts, decode front end
     ("mixtral_decode", dict(H=4096, I=64, T=129, E=4)),             # a second tile of one token
-    ("dsv2lite", dict(H=2048, I=64, T=130, E=32)),                  # the quantization kernels that spread a row
-    ("dsv2lite", dict(H=1024, I=64, T=300, E=32)),                  # ... and the one that does not; 4 parts
+    ("dsv2lite", dict(H=2048, I=64, T=130, E=32)),                  # quantization in a launch of its own, 8 parts
+    ("dsv2lite", dict(H=1024, I=64, T=520, E=32)),                  # ... 4 parts
 ])
 def test_layer_rotation_in_k_parts(B, name, over):
     """The layer's rotation on the f16 matrix cores cut along K (partial sums added by the quantization).  The number of
@@ -1204,6 +1204,32 @@ def test_layer_rotation_in_k_parts(B, name, over):
         assert np.array_equal(Y.cpu().numpy().astype(np.float64), full)
     for n in (need - 1, need - 2 * cfg.T * cfg.H * 4, Y.numel() * 4):
         assert forward(n) == 4   # CQ_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("H,T,f16", [
+    (1280, 256, False), (1792, 300, False), (2304, 256, False), (3840, 100, False),   # K cannot be cut, too few tiles
+    (2304, 700, True), (3840, 300, True),                                             # ... and enough of them
+    (2560, 200, False), (2560, 300, True),                                            # two parts: 20 and 30 tiles
+    (2048, 128, False), (2048, 129, True), (1024, 512, False), (1024, 513, True),
+])
+def test_layer_rotation_rule(B, H, T, f16):
+    """Which batches rotate on the f16 matrix cores: with a copy of R for them, the layer's X_R is what it is without one,
+    bit for bit, where the rule keeps the fp32 kernel -- a K loop that cannot be cut takes longer there."""
+    rng = np.random.default_rng(H + T)
+    cfg = synth.small_variant(synth.CONFIGS["dsv2lite"], H=H, I=64, E=17, S=0, top_k=1, T=T)
+    W = [B.DeviceCodebook(*_rand_weights(rng, 17, n, k)) for n, k in ((128, H), (H, 64))]
+    R = rng.standard_normal((H, H)).astype(np.float32) / np.float32(np.sqrt(H))
+    layer = B.DeviceLayer(cfg, R, rng.standard_normal((17, H)).astype(np.float32), None, *W)
+    X = rng.standard_normal((T, H)).astype(np.float32)
+    XR = []
+    for split in (layer.R_split, None):
+        layer.R_split, layer._ws = split, None
+        B.cq_moe_forward(layer, _dev(X))
+        XR.append(B.moe_intermediates(layer, T)["XR"].cpu().numpy())
+    assert np.array_equal(XR[0], XR[1]) == (not f16)
+    ref = X.astype(np.float64) @ R.astype(np.float64)
+    for got in XR:
+        assert (np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)).max() <= 4e-6
 
 
 @pytest.mark.parametrize("name,over", [
