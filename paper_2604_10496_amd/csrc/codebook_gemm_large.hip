@@ -441,17 +441,6 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   }
 }
 
-// inclusive sum over the lanes of a wavefront (data-parallel moves inside rows of 16 lanes, then across them)
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr 1, 2, 4, 8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast 31 into rows 2 and 3
-  return x;
-}
-
 // The launch's token tiles, derived by every wavefront from the group offsets (a launch that built lists of them cost 5
 // us, twice per layer): a group with more than small_max rows is cut into tiles of w0 (while more than w1 rows remain),
 // then one of w1 or (up to w2 rows left) w2.  List 0 holds the w0-wide tiles, lists 1 and 2 the last tiles of the groups,
@@ -472,7 +461,7 @@ struct tile_map {
     if (last > p.w1) { ++a; last -= p.w0; }   // (negative: the last whole tile is not full)
     m1 = __ballot(last > p.w2);
     m2 = __ballot(last > 0 && last <= p.w2);
-    incl = wave_scan(a);
+    incl = cq_route::wave_scan(a);
   }
   __device__ __forceinline__ void load(const LargeArgs& p, int lane, int at, int& f, int& t) {
     const int g = at + lane;

@@ -182,6 +182,17 @@ __device__ __forceinline__ void wave_topk_regs2(const float (&val)[2], int E, in
   __builtin_amdgcn_wave_barrier();   // (the entries may be reused by the caller's next token)
 }
 
+// inclusive sum over the lanes of a wavefront (data-parallel moves inside rows of 16 lanes, then across them)
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast 31 into rows 2 and 3
+  return x;
+}
+
 // lane that holds the n-th (from 0) set bit of a ballot mask; n < popcount(mask)
 __device__ __forceinline__ int nth_set_lane(uint64_t mask, int n, int lane) {
   const bool hit = ((mask >> lane) & 1ull) && __popcll(mask & lanemask_lt(lane)) == n;
@@ -208,8 +219,10 @@ __device__ __forceinline__ int workgroups_per_group(int n_act, int n_units, int 
 // The group that workgroup `b` of a streaming launch works on, chosen among the groups that have between 1 and
 // max_rows rows (the others cost the launch nothing: with one workgroup set per group of the layer, a batch of one
 // token left three quarters of the chip without work).  A group of more than kPassRows rows counts once per kPassRows of
-// them: further workgroups stream its indices again for the further rows.  Sets the group, its first row and row count
-// (of this pass), this workgroup's number among the pass's workgroups and their count; false: no work for this workgroup.
+// them: further workgroups stream its indices again for the further rows.  Passes are counted with sums over the lanes: a
+// product that has no large tiles has thousands of them (16384 rows in one group of N = 1088, K = 2048: with a ballot per
+// pass in every workgroup 235 us, so 131).  Sets the group, its first row and row count (of this pass), this workgroup's
+// number among the pass's workgroups and their count; false: no work for this workgroup.
 // All values are uniform over the wavefront.  Called by all 64 lanes.
 constexpr int kPassRows = 32;
 struct group_share {
@@ -230,13 +243,10 @@ __device__ __forceinline__ bool pick_group(const int32_t* __restrict__ offsets, 
   auto clip = [&](int& rows) { if (rows > max_rows) rows = 0; };
   clip(r0);
   clip(r1);
+  auto passes = [&](int rows) { return (rows + kPassRows - 1) / kPassRows; };
+  auto sum = [&](int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); };
   auto count = [&](int rows) {   // passes over the groups of a round
-    int n = __popcll(__ballot(rows > 0));
-    for (int j = 1;; ++j) {
-      const int c = __popcll(__ballot(rows > j * kPassRows));
-      if (c == 0) return n;
-      n += c;
-    }
+    return __ballot(rows > kPassRows) ? sum(passes(rows)) : (int)__popcll(__ballot(rows > 0));
   };
   int n_act = count(r0);
   if (G > 64) n_act += count(r1);
@@ -251,29 +261,36 @@ __device__ __forceinline__ bool pick_group(const int32_t* __restrict__ offsets, 
   int n = b / o.chunks;
   if (n >= n_act) return false;
   o.chunk = b - n * o.chunks;
-  int base = 0, first = f0, rows = r0;
-  for (int j = 0;;) {
-    const uint64_t mask = __ballot(rows > j * kPassRows);
-    const int c = __popcll(mask);
+  int first = f0, rows = r0;
+  for (int base = 0;;) {   // (n < n_act: this round or a later one has the pass)
+    const int c = count(rows);
     if (n < c) {
-      const int src = nth_set_lane(mask, n, lane);
+      // the first passes of all groups come first, then the second ones, ...: pass j of all of them is preceded by as many
+      // as sum(min(passes, j)); the largest j whose predecessors are no more than n, bit by bit
+      int j = 0, before = 0;
+      if (__ballot(rows > kPassRows))
+        for (int step = 1 << 26; step; step >>= 1)
+          if (__ballot(passes(rows) > j + step - 1)) {
+            const int m = sum(min(passes(rows), j + step));
+            if (m <= n) {
+              j += step;
+              before = m;
+            }
+          }
+      const int src = nth_set_lane(__ballot(rows > j * kPassRows), n - before, lane);
       o.grp = base + src;
       o.m0 = __builtin_amdgcn_readlane(first, src) + j * kPassRows;
       o.Me = min(kPassRows, __builtin_amdgcn_readlane(rows, src) - j * kPassRows);
       return true;
     }
     n -= c;
-    ++j;
-    if (c == 0) {   // (n < n_act: some later round has the pass)
-      j = 0;
-      base += 64;
-      if (base == 64) {
-        first = f1;
-        rows = r1;
-      } else {
-        load(base, first, rows);
-        clip(rows);
-      }
+    base += 64;
+    if (base == 64) {
+      first = f1;
+      rows = r1;
+    } else {
+      load(base, first, rows);
+      clip(rows);
     }
   }
 }

@@ -512,6 +512,8 @@ def test_gemm_instantiation_matrix(B, a_kind, epi, out_kind, blockwise, prepacke
     (9, 448, 2048, {8: 32}), (200, 64, 4096, {199: 20, 100: 3}), (4, 128, 3584, {2: 32, 3: 24}),
     # groups of more than 32 rows in passes: long K, few rows on average (the last in a second round of 64 groups)
     (8, 256, 4096, {0: 65, 3: 33, 5: 1, 7: 20}), (8, 256, 14336, {1: 97, 6: 31}), (70, 256, 3584, {2: 64, 69: 34, 65: 3}),
+    # ... and of many passes, no large tiles for these N or K: passes of several groups, also in the second round of 64
+    (3, 64, 576, {0: 1030, 2: 33}), (70, 128, 1472, {3: 700, 64: 1, 66: 2100, 69: 32}), (1, 192, 2048, {0: 4128}),
 ])
 def test_gemm_streaming_workgroups_by_active_groups(B, G, N, K, rows, prepacked):
     """The streaming launch gives workgroups to the groups that have rows only: few active groups among many (also
