@@ -153,8 +153,10 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
   }
   const int grp = share.grp, m0 = share.m0, Me = share.Me;
   // units of this workgroup: a contiguous run in the plain loop, every chunks-th unit in the pipelined one
-  const int u0 = (int)((long)nUnits * share.chunk / share.chunks);
-  const int u1 = (int)((long)nUnits * (share.chunk + 1) / share.chunks);
+  // (the first nUnits % chunks workgroups take one unit more)
+  const int per_chunk = nUnits / share.chunks, more = nUnits - per_chunk * share.chunks;
+  const int u0 = share.chunk * per_chunk + min(share.chunk, more);
+  const int u1 = u0 + per_chunk + (share.chunk < more ? 1 : 0);
   const size_t rowbytes = (size_t)K >> 1;
   const uint8_t* gbase = p.idx + (size_t)grp * N * rowbytes;
   const int r32 = lane & 31, g2 = lane >> 5;

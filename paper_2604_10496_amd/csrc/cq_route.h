@@ -203,8 +203,10 @@ __device__ __forceinline__ int nth_set_lane(uint64_t mask, int n, int lane) {
 // `slots` workgroups of the launch at a time and its grid holds rmax rounds of them.  With r rounds a group gets
 // c = r * slots / n_act workgroups; a workgroup costs its units plus about one unit of prologue (first table, ring
 // fill, activation rows), so the launch costs about r * (1 + ceil(n_units / c)): lane r - 1 prices r rounds and the
-// cheapest (the fewest rounds among equals) wins.  Called by all 64 lanes; rmax is 1, 2 or 4.
+// cheapest (the fewest rounds among equals) wins.  Called by all 64 lanes; rmax is 1, 2 or 4.  (With one round there is
+// nothing to price: two lane permutations less in front of the first load, 0.5 .. 1 us of the layer at 2 .. 20 tokens.)
 __device__ __forceinline__ int workgroups_per_group(int n_act, int n_units, int slots, int rmax, int lane) {
+  if (rmax == 1) return max(1, min(n_units, slots / n_act));
   const int r = min(lane, 3) + 1;
   const int c = min(n_units, (r * slots) / n_act);
   // (price and choice in one number: a unit of price is 2^12; prices stay below 2^19 / 4)
