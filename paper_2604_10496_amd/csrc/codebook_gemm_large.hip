@@ -274,8 +274,10 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   // the group barriers below ask the scheduler for exactly that).
   // The B fragments live in one register set: as soon as the two MFMAs of a token block are issued,
   // its registers take the block's fragment of the next sub-step (a full sub-step of slack).
-  // vector ALU operations per MFMA that the scheduler is asked for: two decode8 calls per 2 C MFMAs
-  constexpr int kValu = C >= 8 ? 4 : C == 4 ? 6 : 12;
+  // vector ALU operations per MFMA that the scheduler is asked for: in half tiles two decode8 calls per 2 C MFMAs.  (Whole
+  // tiles have no second workgroup on the compute unit whose products could run under the decoding: four per MFMA also
+  // where the tile is narrow; block-wise tables, gate/up + down at 96 tokens 350 -> 344 us, at 200 tokens 400 -> 396.)
+  constexpr int kValu = !A32 || C >= 8 ? 4 : C == 4 ? 6 : 12;
   cq_v4u af[2][2];
   cq_v4u bfr[C];
   uint32_t ident = 0x03020100u;   // kept in a vector register (see decode8)
