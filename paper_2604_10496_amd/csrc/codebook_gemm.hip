@@ -36,14 +36,15 @@ int row_bound(int M_total, int max_group_rows) {
   return max_group_rows > 0 && max_group_rows < M_total ? max_group_rows : M_total;
 }
 
-// Batches a little too large for one pass of 32 rows: where few groups have more, a second pass over their indices on
+// Batches a little too large for one pass: where few groups have more rows, a second pass over their indices on
 // workgroups of its own is cheaper than the large-tile launch behind a streaming launch (and the launches that add up
-// both kinds' partial sums).  With a long K, groups of at most 128 rows, and fewer than 28 rows per group on average (20
-// with block-wise tables, whose form for 17..32 rows spills): us per layer of the Mixtral shape, two launches against
-// passes: 33 tokens 174 / 169, 77 tokens 207 / 192, 110 tokens 291 / 254; block-wise tables (narrow tiles against passes)
-// 40 tokens 360 / 266, 77 tokens 389 / 350, 100 tokens 372 / 393.
+// both kinds' partial sums).  With a long K, groups of at most 128 rows, and fewer than 28 rows per group on average (25
+// with block-wise tables, in passes of 16 rows): us per layer of the Mixtral shape, two launches against passes: 33 tokens
+// 174 / 169, 77 tokens 207 / 192, 110 tokens 291 / 254; block-wise tables (large tiles against passes) 40 tokens
+// 347 / 232, 79 tokens 369 / 325, 92 tokens 359 / 340, 104 tokens 363 / 359, 111 tokens 362 / 377.
+long rows_in_passes(const cq_codebook_weights* W) { return (cq_tables_per_row(W) > 1 ? 25L : 28L) * W->G; }
 bool streams_in_passes(const cq_codebook_weights* W, int M_total, int max_group_rows) {
-  return W->K > 2048 && row_bound(M_total, max_group_rows) <= 128 && (long)M_total < (cq_tables_per_row(W) > 1 ? 20L : 28L) * W->G;
+  return W->K > 2048 && row_bound(M_total, max_group_rows) <= 128 && (long)M_total < rows_in_passes(W);
 }
 
 // Whether a K range of ksteps steps runs the streaming kernel's pipelined unit loop: 8 or 7 steps for every wavefront,
@@ -60,7 +61,7 @@ bool pipelined(int ksteps, bool blockwise) {
 // into ranges of at most 4096 that different workgroups stream, and their partial sums are added in a
 // fixed order afterwards.  Plain products only (a nonlinear epilogue needs the whole sum).
 // Block-wise tables on the streaming kernel's pipelined loop: tables of 1024 weights (two K steps per wavefront
-// and table), up to 32 rows (the loop's limit; in passes of 32 where streams_in_passes says so), and K ranges of whole
+// and table), up to 32 rows (more where streams_in_passes says so; in passes either way), and K ranges of whole
 // tables that give every wavefront exactly 8 steps (4096 weights) or 4 (2048); a nonlinear epilogue needs all of K in one
 // range.
 bool cq_gemm_blockwise_streams(const cq_codebook_weights* W, int M_total, int epilogue, int max_group_rows) {
@@ -168,7 +169,8 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
     // leave a good part of the chip idle (129 groups: one workgroup each on 256 compute units), so the grid has room
     // for two or four rounds of which the kernel uses what is cheapest.
     const bool large_too = cq_gemm_uses_large_tiles(W, M_total, epilogue, max_group_rows);
-    const int n_max = (W->G < M_total ? W->G : M_total) + M_total / cq_route::kPassRows;   // passes over groups with rows
+    const int pass_rows = cq_tables_per_row(W) > 1 && a.ksteps == 8 * kWaves ? kBlockwisePassRows : cq_route::kPassRows;
+    const int n_max = (W->G < M_total ? W->G : M_total) + M_total / pass_rows;   // passes over groups with rows
     // Where the pipelined loop is not available (other K), a group of 17..32 rows runs the plain loop on one
     // set of workgroups, several times slower per unit than the small groups around it: many short workgroups
     // then, so that the compute units the small groups leave early take the rest of the big ones.
@@ -285,7 +287,7 @@ size_t cq_gemm_product_bytes(const cq_codebook_weights* W, int M_total, int epil
   // block-wise tables: everything streams (up to 32 rows a group, and in passes), or everything is on large tiles, whose
   // partial sums end with the launches of up to 64 rows
   take(stream_bytes(units < kSmallMaxRows ? units : kSmallMaxRows));
-  long last = (20L * W->G - 1) / per;   // the most tokens that stream in passes
+  long last = (rows_in_passes(W) - 1) / per;   // the most tokens that stream in passes
   if (last > 128) last = 128;
   if (last > units) last = units;
   if (last > kSmallMaxRows && cq_gemm_blockwise_streams(W, (int)last * per, epilogue, layer ? (int)last : 0))

@@ -98,6 +98,11 @@ constexpr int kWaves = CQ_GEMM_WAVES;  // wavefronts per workgroup: they split K
 // every unit: 8 where that divides 2Q (4 steps = 64 KiB in flight per compute unit; 16 was measured 5 % slower at
 // Q = 8), Q for 7 steps (14 was measured 4 % slower), else all half steps of a unit.
 constexpr int pipe_ring_depth(int Q) { return (2 * Q) % 8 == 0 ? 8 : Q == 7 ? 7 : 2 * Q; }
+// Rows of a pass with block-wise tables and 8 steps per wavefront.  FORM 2 of the pipelined loop needs 49 to 112 registers
+// more than there are with the table switches in it, and its spilled activations are loaded again in every unit, behind
+// the index stream: whole layer of the Mixtral shape in passes of 32 and of 16 rows, 20 tokens 212.7 / 211.5 us, 32 tokens
+// 218 / 217, 40 tokens 293 / 237, 60 tokens 340 / 272, 79 tokens 352 / 311.
+constexpr int kBlockwisePassRows = 16;
 constexpr int kSlabCheck = 16 / kWaves;  // smallest number of wavefront steps in a slab (Mpad = 32)
 
 
@@ -119,7 +124,8 @@ __device__ __forceinline__ cq_v16f mfma32(const cq_v4u a, const uint4 b, cq_v16f
 // instantiation.
 // QT > 0: block-wise centroid tables, one per 512 * QT weights of a row (QT K steps per wavefront and table; QT
 // divides QS); the instantiation then holds nothing but the pipelined loop.  0: one table per row.
-template <int AK, int EPI, int OUTK, int kRing, int QS, int QT = 0>
+// ROWS: rows of a pass, 32, or 16 without FORM 2 of the pipelined loop (block-wise tables with 8 steps, kBlockwisePassRows).
+template <int AK, int EPI, int OUTK, int kRing, int QS, int QT = 0, int ROWS = 32>
 __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmArgs p) {
   constexpr bool F16 = (AK == CQ_A_F16 || AK == CQ_A_F32);
   constexpr int NW = kWaves;
@@ -144,11 +150,12 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
   bool fused = false;
   if constexpr (QS > 0) fused = p.route.ids != nullptr;
   if (fused) {
-    if (!cq_route::pick_group_from_ids(p.route, nUnits, p.slots, p.rounds, blockIdx.x, lane, share)) return;
+    if (!cq_route::pick_group_from_ids<ROWS>(p.route, nUnits, p.slots, p.rounds, blockIdx.x, lane, share)) return;
     cq_route::group_rows_from_ids(p.route, share.grp, lane, blockIdx.x == 0 && blockIdx.z == 0 && wave == 0, share.m0,
                                   share.Me, row_token);
+    if constexpr (ROWS < cq_route::kPassRows) cq_route::take_pass<ROWS>(share, lane, row_token);
   } else {
-    if (!cq_route::pick_group(p.group_offsets, p.G, p.max_rows, nUnits, p.slots, p.rounds, blockIdx.x, lane, share))
+    if (!cq_route::pick_group<ROWS>(p.group_offsets, p.G, p.max_rows, nUnits, p.slots, p.rounds, blockIdx.x, lane, share))
       return;
   }
   const int grp = share.grp, m0 = share.m0, Me = share.Me;
@@ -556,8 +563,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
   if constexpr (QS > 0) {
     if (Me <= 32 && (QS < 7 && QT == 0 ? nS <= QS * NW : nS == QS * NW)) {
       if (Me <= 8) run_units_pipe(std::integral_constant<int, 0>{});
-      else if (Me <= 16) run_units_pipe(std::integral_constant<int, 1>{});
-      else run_units_pipe(std::integral_constant<int, 2>{});
+      else if (ROWS == 16 || Me <= 16) run_units_pipe(std::integral_constant<int, 1>{});
+      else if constexpr (ROWS > 16) run_units_pipe(std::integral_constant<int, 2>{});
       return;
     }
   }
@@ -999,9 +1006,9 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_small_kernel(const GemmAr
   }
 }
 
-template <int AK, int EPI, int OUTK, int RING, int QS, int QT = 0>
+template <int AK, int EPI, int OUTK, int RING, int QS, int QT = 0, int ROWS = 32>
 cq_status launch_small_ring(const GemmArgs& a, hipStream_t s) {
-  auto kern = gemm_small_kernel<AK, EPI, OUTK, RING, QS, QT>;
+  auto kern = gemm_small_kernel<AK, EPI, OUTK, RING, QS, QT, ROWS>;
   static std::atomic<bool> configured{false};
   const cq_status cst = cq_configure_lds(kern, kTableBytes + kSlabBytes + kRedBytes, configured, true);
   if (cst != CQ_OK) return cst;
@@ -1015,7 +1022,7 @@ template <int AK, int EPI, int OUTK>
 cq_status launch_small(const GemmArgs& a, int qt, hipStream_t s) {
   const int per_wave = (a.ksteps + kWaves - 1) / kWaves;  // steps of a wavefront in the (first) K range
   if (qt != 0) {
-    if (kWaves == 8 && qt == 2 && a.ksteps == 8 * kWaves) return launch_small_ring<AK, EPI, OUTK, 8, 8, 2>(a, s);
+    if (kWaves == 8 && qt == 2 && a.ksteps == 8 * kWaves) return launch_small_ring<AK, EPI, OUTK, 8, 8, 2, kBlockwisePassRows>(a, s);
     if (kWaves == 8 && qt == 2 && a.ksteps == 4 * kWaves) return launch_small_ring<AK, EPI, OUTK, 8, 4, 2>(a, s);
     return CQ_ERR_UNSUPPORTED;
   }

@@ -229,7 +229,9 @@ __device__ __forceinline__ int workgroups_per_group(int n_act, int n_units, int 
 constexpr int kPassRows = 32;
 struct group_share {
   int grp, m0, Me, chunk, chunks;
+  int pass;   // (pick_group_from_ids: number of the pass within the group)
 };
+template <int PASS = kPassRows>
 __device__ __forceinline__ bool pick_group(const int32_t* __restrict__ offsets, int G, int max_rows, int n_units,
                                            int slots, int rmax, int b, int lane, group_share& o) {
   // the offsets of the first 128 groups are requested together and stay in registers, those of further rounds of 64
@@ -245,10 +247,10 @@ __device__ __forceinline__ bool pick_group(const int32_t* __restrict__ offsets, 
   auto clip = [&](int& rows) { if (rows > max_rows) rows = 0; };
   clip(r0);
   clip(r1);
-  auto passes = [&](int rows) { return (rows + kPassRows - 1) / kPassRows; };
+  auto passes = [&](int rows) { return (rows + PASS - 1) / PASS; };
   auto sum = [&](int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); };
   auto count = [&](int rows) {   // passes over the groups of a round
-    return __ballot(rows > kPassRows) ? sum(passes(rows)) : (int)__popcll(__ballot(rows > 0));
+    return __ballot(rows > PASS) ? sum(passes(rows)) : (int)__popcll(__ballot(rows > 0));
   };
   int n_act = count(r0);
   if (G > 64) n_act += count(r1);
@@ -270,7 +272,7 @@ __device__ __forceinline__ bool pick_group(const int32_t* __restrict__ offsets, 
       // the first passes of all groups come first, then the second ones, ...: pass j of all of them is preceded by as many
       // as sum(min(passes, j)); the largest j whose predecessors are no more than n, bit by bit
       int j = 0, before = 0;
-      if (__ballot(rows > kPassRows))
+      if (__ballot(rows > PASS))
         for (int step = 1 << 26; step; step >>= 1)
           if (__ballot(passes(rows) > j + step - 1)) {
             const int m = sum(min(passes(rows), j + step));
@@ -279,10 +281,10 @@ __device__ __forceinline__ bool pick_group(const int32_t* __restrict__ offsets, 
               before = m;
             }
           }
-      const int src = nth_set_lane(__ballot(rows > j * kPassRows), n - before, lane);
+      const int src = nth_set_lane(__ballot(rows > j * PASS), n - before, lane);
       o.grp = base + src;
-      o.m0 = __builtin_amdgcn_readlane(first, src) + j * kPassRows;
-      o.Me = min(kPassRows, __builtin_amdgcn_readlane(rows, src) - j * kPassRows);
+      o.m0 = __builtin_amdgcn_readlane(first, src) + j * PASS;
+      o.Me = min(PASS, __builtin_amdgcn_readlane(rows, src) - j * PASS);
       return true;
     }
     n -= c;
@@ -345,25 +347,55 @@ __device__ __forceinline__ void group_rows_from_ids(const cq_route_fuse& rt, int
 }
 
 // pick_group for a launch with the grouping folded in: the active experts are those among the selected ids (at most
-// 64 experts: one bit each), and every shared expert is active.  m0 and Me come from group_rows_from_ids.
+// 64 experts: one bit each), and every shared expert is active; at most 2 PASS tokens, so that a group has one or two
+// passes: all first ones of the experts, then all second ones, then the shared experts'.  m0 and Me come from
+// group_rows_from_ids and take_pass.
+template <int PASS = kPassRows>
 __device__ __forceinline__ bool pick_group_from_ids(const cq_route_fuse& rt, int n_units, int slots, int rmax, int b,
                                                     int lane, group_share& o) {
   const int n_assign = rt.T * rt.top_k;
   const int id = lane < n_assign ? rt.ids[lane] : 0x7fffffff;
-  uint64_t mask = 0;
+  uint64_t mask = 0, two = 0;   // experts with rows, and with more than a pass takes
   if (rt.E <= n_assign) {
-    for (int e = 0; e < rt.E; ++e)
-      if (__ballot(id == e)) mask |= 1ull << e;
+    for (int e = 0; e < rt.E; ++e) {
+      const uint64_t m = __ballot(id == e);
+      if (m) mask |= 1ull << e;
+      if (PASS < kPassRows && __popcll(m) > PASS) two |= 1ull << e;
+    }
   } else {
     for (int a = 0; a < n_assign; ++a) mask |= 1ull << __builtin_amdgcn_readlane(id, a);
+    if (PASS < kPassRows)
+      for (uint64_t m = mask; m; m &= m - 1) {
+        const int e = __ffsll((long long)m) - 1;
+        if (__popcll(__ballot(id == e)) > PASS) two |= 1ull << e;
+      }
   }
-  const int n_exp = __popcll(mask);
-  o.chunks = workgroups_per_group(n_exp + rt.S, n_units, slots, rmax, lane);
+  const int n_exp = __popcll(mask), n_two = __popcll(two), per_shared = rt.T > PASS ? 2 : 1;
+  const int n_all = n_exp + n_two + rt.S * per_shared;
+  o.chunks = workgroups_per_group(n_all, n_units, slots, rmax, lane);
   const int n = b / o.chunks;
-  if (n >= n_exp + rt.S) return false;
+  if (n >= n_all) return false;
   o.chunk = b - n * o.chunks;
-  o.grp = n < n_exp ? nth_set_lane(mask, n, lane) : rt.E + n - n_exp;
+  o.pass = 0;
+  if (n < n_exp) {
+    o.grp = nth_set_lane(mask, n, lane);
+  } else if (n < n_exp + n_two) {
+    o.grp = nth_set_lane(two, n - n_exp, lane);
+    o.pass = 1;
+  } else {
+    const int i = n - n_exp - n_two;
+    o.grp = rt.E + (per_shared == 2 ? i >> 1 : i);
+    o.pass = per_shared == 2 ? i & 1 : 0;
+  }
   return true;
+}
+
+// the rows of the share's pass, from those of its group (group_rows_from_ids): row i's token moves to lane i - PASS * pass
+template <int PASS>
+__device__ __forceinline__ void take_pass(group_share& o, int lane, int& row_token) {
+  row_token = __shfl(row_token, lane + PASS * o.pass);
+  o.m0 += PASS * o.pass;
+  o.Me = min(PASS, o.Me - PASS * o.pass);
 }
 
 }  // namespace cq_route

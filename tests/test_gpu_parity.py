@@ -644,7 +644,7 @@ BLOCKWISE_CASES = [(256, 1024, 512, [3, 40]), (256, 1408, 1024, [1, 0, 33, 300])
                    # pipelined loop with a table switch every two steps (K ranges of 4096 or 2048 weights)
                    (256, 2048, 1024, [3, 0, 9, 4]), (512, 4096, 1024, [16]), (256, 6144, 1024, [1, 8]),
                    (256, 14336, 1024, [7, 5]), (256, 8192, 1024, [2, 12]),
-                   # ... up to 128 rows in passes of 32 while groups have fewer than 20 on average
+                   # ... up to 128 rows in passes while groups have fewer than 25 on average
                    (256, 4096, 1024, [40, 0, 33, 17, 8, 0, 0, 0]), (256, 14336, 1024, [33, 0, 2, 0])]
 
 
@@ -1245,12 +1245,17 @@ def test_layer_rotation_rule(B, H, T, f16):
     ("mixtral_decode", dict(H=4096, I=128, T=32, E=2, top_k=2)),           # 32-row groups: both halves of every group
     ("mixtral_decode", dict(H=4096, I=256, T=29, E=4, top_k=2)),           # groups around 16 rows
     ("mixtral_decode", dict(H=4096, I=192, T=21, E=8, top_k=3, S=1)),      # 63 assignments, a shared expert of 21 rows
-    ("dsv2lite", dict(H=2048, I=192, T=10, E=16, top_k=6)),                # K = 2048: not folded (plain unit loop); 2 shared experts
+    ("dsv2lite", dict(H=2048, I=192, T=10, E=16, top_k=6)),                # K = 2048: 4 K steps per wavefront; 2 shared experts
+    # block-wise tables, passes of 16 rows: groups of 17..24 rows have two, the shared expert's rows as well
+    ("mixtral_decode", dict(H=4096, I=256, T=24, E=2, top_k=2, group_k=1024)),
+    ("mixtral_decode", dict(H=4096, I=256, T=21, E=8, top_k=2, S=1, group_k=1024, zipf_s=2.0)),
+    ("mixtral_decode", dict(H=4096, I=256, T=17, E=16, top_k=1, S=2, group_k=1024, zipf_s=3.0)),
+    ("mixtral_decode", dict(H=4096, I=256, T=32, E=16, top_k=2, group_k=1024, zipf_s=2.0)),
 ])
 def test_layer_grouping_folded_into_gate_up(B, name, over):
-    """Decode-sized batches whose gate/up product has K = 4096 or 3584: the front launch selects the experts and
-    the gate/up launch groups the rows itself (no routing launch); ids, weights, offsets, perm, inv_perm,
-    src_token and the output are held to the oracle like everywhere else."""
+    """Decode-sized batches whose gate/up product has K = 4096, 3584 or at most 2048: the front launch selects the experts
+    and the gate/up launch groups the rows itself (no routing launch); ids, weights, offsets, perm, inv_perm, src_token and
+    the output are held to the oracle like everywhere else."""
     cfg = synth.small_variant(synth.CONFIGS[name], **over)
     _check_layer(B, cfg, label=f"{name}-folded")
 
