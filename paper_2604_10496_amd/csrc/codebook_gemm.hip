@@ -38,11 +38,12 @@ int row_bound(int M_total, int max_group_rows) {
 
 // Batches a little too large for one pass: where few groups have more rows, a second pass over their indices on
 // workgroups of its own is cheaper than the large-tile launch behind a streaming launch (and the launches that add up
-// both kinds' partial sums).  With a long K, groups of at most 128 rows, and fewer than 28 rows per group on average (25
+// both kinds' partial sums).  With a long K, groups of at most 128 rows, and fewer than 28 rows per group on average (23
 // with block-wise tables, in passes of 16 rows): us per layer of the Mixtral shape, two launches against passes: 33 tokens
 // 174 / 169, 77 tokens 207 / 192, 110 tokens 291 / 254; block-wise tables (large tiles against passes) 40 tokens
-// 347 / 232, 79 tokens 369 / 325, 92 tokens 359 / 340, 104 tokens 363 / 359, 111 tokens 362 / 377.
-long rows_in_passes(const cq_codebook_weights* W) { return (cq_tables_per_row(W) > 1 ? 25L : 28L) * W->G; }
+// 347 / 232, 79 tokens 369 / 325, 92 tokens 359 / 340, 104 tokens 363 / 359, 111 tokens 362 / 377 (from 24 rows per
+// group on the partial sums of wider layers no longer fit into the library's own array, which held these batches).
+long rows_in_passes(const cq_codebook_weights* W) { return (cq_tables_per_row(W) > 1 ? 23L : 28L) * W->G; }
 bool streams_in_passes(const cq_codebook_weights* W, int M_total, int max_group_rows) {
   return W->K > 2048 && row_bound(M_total, max_group_rows) <= 128 && (long)M_total < rows_in_passes(W);
 }

@@ -644,7 +644,7 @@ BLOCKWISE_CASES = [(256, 1024, 512, [3, 40]), (256, 1408, 1024, [1, 0, 33, 300])
                    # pipelined loop with a table switch every two steps (K ranges of 4096 or 2048 weights)
                    (256, 2048, 1024, [3, 0, 9, 4]), (512, 4096, 1024, [16]), (256, 6144, 1024, [1, 8]),
                    (256, 14336, 1024, [7, 5]), (256, 8192, 1024, [2, 12]),
-                   # ... up to 128 rows in passes while groups have fewer than 25 on average
+                   # ... up to 128 rows in passes while groups have fewer than 23 on average
                    (256, 4096, 1024, [40, 0, 33, 17, 8, 0, 0, 0]), (256, 14336, 1024, [33, 0, 2, 0])]
 
 
