@@ -58,6 +58,7 @@ cq_status validate_layer(const cq_layer* L, int T) {
 struct layer_plan {
   cq_moe_layout lay;
   size_t used;     // bytes that the call touches
+  size_t rot_at;   // partial sums of the rotation
   int rot_parts;   // K parts of the rotation on the f16 matrix cores; 0: the fp32 kernel
 };
 
@@ -134,8 +135,9 @@ void make_plan(const cq_layer* L, int T, layer_plan* plan) {
     rotation = plan->rot_parts ? cq_rotate_split_partials_bytes(plan->rot_parts, T, L->H) + cq_rotate_split_workspace_bytes(T, L->H)
                                : fp32_rotation;
   }
+  plan->rot_at = off + rotation <= o->total && off + rotation <= CQ_STATIC_SCRATCH_BYTES ? o->scratch : o->Hbuf;
   plan->used = off + scratch;
-  raise(plan->used, o->Hbuf + rotation);
+  raise(plan->used, plan->rot_at + rotation);
 }
 
 }  // namespace
@@ -190,7 +192,7 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
   auto mark = [&](int i) -> bool { return !ev || hipEventRecord(ev[i], hs) == hipSuccess; };
 
   // a1: X_R as `parts` partial sums at `part`
-  char* rot_ws = ws + lay.Hbuf;
+  char* rot_ws = ws + plan.rot_at;
   auto rotate = [&](int* parts, float** part) {
     if (plan.rot_parts) {
       *parts = plan.rot_parts;
@@ -245,7 +247,7 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
       if (st != CQ_OK) return st;
       st = cq_quantize_launch(part, parts, T, L->H, L->act_bits, XR, Q, Q16, scale, nullptr, hs);
     } else {
-      st = cq_rotate_quant_ex(X, L->R, T, L->H, L->act_bits, XR, Q, Q16, scale, rot_ws, plan.used - lay.Hbuf, stream);
+      st = cq_rotate_quant_ex(X, L->R, T, L->H, L->act_bits, XR, Q, Q16, scale, rot_ws, plan.used - plan.rot_at, stream);
     }
     if (st != CQ_OK) return st;
     if (!mark(1)) return CQ_ERR_HIP;
