@@ -1260,6 +1260,29 @@ def test_layer_grouping_folded_into_gate_up(B, name, over):
     _check_layer(B, cfg, label=f"{name}-folded")
 
 
+@pytest.mark.parametrize("over,rows", [
+    # gate/up in passes of 32 rows (gathered rows, row scales, the gated epilogue), down on half tiles
+    (dict(H=4096, I=128, T=45, zipf_s=2.0), 33), (dict(H=4096, I=128, T=77, zipf_s=1.5), 65),   # (from 64 tokens: split rotation)
+    (dict(H=3584, I=128, T=111, act_bits=4, zipf_s=1.0), 65),
+    # down in passes, in two K ranges that the combine adds; gate/up on half tiles
+    (dict(H=256, I=8192, T=60, zipf_s=1.5), 33), (dict(H=512, I=4352, T=100, zipf_s=1.0), 33),
+    # both with shared experts of all tokens
+    (dict(H=4096, I=128, T=40, S=1), 40), (dict(H=256, I=4096, T=64, E=16, top_k=1, S=1, h_bits=8), 64),
+    # block-wise tables in passes of 16 rows, and the down product's in passes of 32 (K ranges of 2048)
+    (dict(H=4096, I=256, T=40, group_k=1024, zipf_s=1.0), 17), (dict(H=256, I=6144, T=91, group_k=1024, zipf_s=0.5), 33),
+    (dict(H=512, I=4096, T=70, group_k=1024, zipf_s=1.0), 33),
+])
+def test_layer_streams_in_passes(B, over, rows):
+    """Medium batches with a long K: the layer's products stream, groups of more than a pass's rows in several passes.
+    `rows`: at least this many in the largest group."""
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], **over)
+    L = Hp.make_inputs(cfg, with_experts=False)
+    ids, _ = O.route_topk(O.router_logits(O.rotate(L.X, L.R), L.Wr, L.bias), cfg.top_k)
+    largest = max(np.bincount(ids.reshape(-1), minlength=cfg.E).max(), cfg.T if cfg.S else 0)
+    assert rows <= largest <= 128 and cfg.T * (cfg.top_k + cfg.S) < (23 if cfg.group_k else 28) * (cfg.E + cfg.S)
+    _check_layer(B, cfg, label=f"passes, {largest} rows")
+
+
 @pytest.mark.parametrize("T", [16, 27])
 def test_layer_folded_grouping_with_exactly_tied_experts(B, T):
     """Two experts with the same router row have bit-identical logits for every token (on the GPU as in the
