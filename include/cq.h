@@ -75,8 +75,9 @@ enum { CQ_OUT_F32 = 0, CQ_OUT_F16 = 1 };
  *             [G, N, ceil(K/g), 16] and weight k of a row is decoded through table k / g (the last group
  *             is shorter when g does not divide K).  g must be a multiple of 512 and N of 256
  *             (other values: CQ_ERR_UNSUPPORTED).  Which kernel runs is the library's choice (prefill-sized
- *             groups: large token tiles; g = 1024 with at most 16 rows per group and K a multiple of 2048:
- *             the streaming kernel); the results do not depend on it beyond fp32 summation order.
+ *             groups: large token tiles; g = 1024 and K a multiple of 2048, with groups of up to 32 rows, or of up to
+ *             128 in batches of few rows per group: the streaming kernel); the results do not depend on it beyond fp32
+ *             summation order.
  *   index_bits 0 or 4: the format above.  2: the smallest budget of the ablation on centroid budgets (W2, four
  *             centroids per row) streamed as stored, at half the bytes: idx is [G, N, K/4] bytes, the indices
  *             of a row as one little-endian bit stream (weight j in bits 2(j%4), 2(j%4)+1 of byte j/4), cent is
@@ -132,9 +133,10 @@ cq_status cq_rotate_quant(const float* X, const float* R, int T, int H, int act_
 /*
  * a1 for many tokens: a copy of R (AOS section) as two f16 planes, R = Rh + 2^-11 Rl, in the order the
  * matrix-core fragments are loaded in.  With it cq_moe_forward computes X R (for H % 256 == 0 and enough
- * tokens: from 64 at H = 4096) as Xh Rh + 2^-11 (Xh Rl + Xl Rh) on the f16 matrix cores with fp32 accumulation: every operand is
- * represented to 2^-23 of its size and only the 2^-22 Xl Rl term is dropped, so the result is as accurate
- * as the fp32 product and the codes still differ from an exact evaluation only at rounding ties.
+ * tokens: from 64 at H = 4096, 129 at H = 2048, 513 at H = 1024) as Xh Rh + 2^-11 (Xh Rl + Xl Rh) on the f16
+ * matrix cores with fp32 accumulation: every operand is represented to 2^-23 of its size and only the 2^-22
+ * Xl Rl term is dropped, so the result is as accurate as the fp32 product and the codes still differ from an
+ * exact evaluation only at rounding ties.
  *   R [H,H] f32 device, H % 32 == 0; out: cq_rotation_split_bytes(H) bytes of device memory, owned by
  *   the caller, read by every later cq_moe_forward on a layer whose R_split points to it.
  */
@@ -177,8 +179,8 @@ cq_status cq_route_permute(const float* XR, const float* Wr, const float* bias, 
  *     out[m, n] = (row_scale ? row_scale[src(m)] : 1) * acc[m, n]          (CQ_EPI_NONE, N outputs)
  *     out[m, i] = SiLU(sc*acc[m,2i]) * (sc*acc[m,2i+1])                    (CQ_EPI_SWIGLU, N/2 outputs)
  *   Weights are never materialised: packed indices stream from HBM, are turned into centroid
- *   values through a table staged in LDS (groups of up to 32 rows) or held in registers (larger
- *   groups, and all groups when the tables are block-wise), and feed the matrix cores directly.  Integer codes and
+ *   values through a table staged in LDS (the streaming kernel: small groups, and medium batches with a long K) or
+ *   held in registers (the large-tile kernel: the others), and feed the matrix cores directly.  Integer codes and
  *   bf16 centroids are exact operands (bf16 MFMA, fp32 accumulation); CQ_A_F16 / CQ_A_F32 rows
  *   use f16 MFMA with centroids converted bf16 -> f16.
  *   A: [rows, K] of a_kind.  out: [M_total, N or N/2] of out_kind (CQ_OUT_F16 saturates).

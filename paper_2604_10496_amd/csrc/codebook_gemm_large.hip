@@ -26,8 +26,6 @@
 #include "cq_decode.h"
 #include "cq_route.h"
 
-void cq_large_tile_caps(int G, int M_total, int* cap0, int* cap1);
-
 namespace {
 
 constexpr int kLargeRows = 256;  // weight rows per workgroup
@@ -110,7 +108,7 @@ constexpr int epilogue_row_stride(int epi, int outk) {
 }
 
 // One tile: 256 weight rows (row tile rt) x up to 32*C tokens (rows mrow0 .. mrow0+mcnt-1 of group grp).
-// F16: the activations are f16 (else bf16); C = CT/32 token blocks (8, 4 or 2); D = depth of the load
+// F16: the activations are f16 (else bf16); C = CT/32 token blocks (8, 4, 3, 2 or 1); D = depth of the load
 // pipeline in K steps (a power of two; narrow tiles spend less matrix time per step and need more).
 // BLK: block-wise centroid tables (p.nblk per row, each serving p.gsteps K steps).  PRE: the indices are the
 // prepacked copy (whose nibble arrangement decodes with four operations fewer per 8 weights).
@@ -761,14 +759,14 @@ cq_status dispatch_large(const LargeArgs& a, int epilogue, int out_kind, int max
              : dispatch_large_blk<F16, false>(a, epilogue, out_kind, max0, max1, narrow == kHalf ? kHalf : 0, s);
 }
 
-}  // namespace
-
 // Upper bounds on the tile counts for M_total rows in G groups (host side; sizes on the device vary).
-void cq_large_tile_caps(int G, int M_total, int* cap0, int* cap1) {
+void tile_caps(int G, int M_total, int* cap0, int* cap1) {
   *cap0 = M_total / (tile_widths<true>::w1 + 1) + 1;   // every widest tile covers more than w1 rows (96, or 128)
   *cap1 = G < M_total ? G : M_total;  // at most one per group
   if (*cap1 < 1) *cap1 = 1;
 }
+
+}  // namespace
 
 // The tiles of a plain fp32 product with a long K may be cut into K parts (LargeArgs::tail_part).
 bool cq_gemm_large_tail_split(const cq_codebook_weights* W, int epilogue, int out_kind) {
@@ -792,7 +790,7 @@ namespace {
 // rows when those are fewer
 int tail_slice_rows(int G, int M_total, bool half, bool* absolute) {
   int c0, c1;
-  cq_large_tile_caps(G, M_total, &c0, &c1);
+  tile_caps(G, M_total, &c0, &c1);
   const int slots = c1 * (half ? tile_widths<true>::w1 + tile_widths<true>::w2 : tile_widths<false>::w1 + tile_widths<false>::w2);
   *absolute = M_total < slots;
   return *absolute ? M_total : slots;
@@ -832,7 +830,7 @@ cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int 
                                const int32_t* row_gather, const int32_t* group_offsets, int M_total, int small_max,
                                int epilogue, void* out, int out_kind, void* workspace, hipStream_t s, bool half) {
   int cap0, cap1;
-  cq_large_tile_caps(W->G, M_total, &cap0, &cap1);
+  tile_caps(W->G, M_total, &cap0, &cap1);
   LargeArgs a;
   a.idx = W->prepacked ? (const uint8_t*)W->prepacked : W->idx;
   a.cent = W->cent;

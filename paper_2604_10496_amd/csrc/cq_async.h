@@ -14,11 +14,6 @@ namespace cq_async {
 // no static LDS (verified by the launcher): dynamic LDS starts at address 0 and byte offsets are LDS
 // addresses.
 
-// 16 bytes per lane from global memory into the registers `dst`; valid only after a vm_wait that
-// names `dst`
-static __device__ __forceinline__ void load_global_async(cq_v4u& dst, const uint8_t* src) {
-  asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(dst) : "v"(src) : "memory");
-}
 // (m0 is a reserved register: the compiler loads it right before each use of its own and does not
 // keep values in it, which is what clobbering it here relies on)
 #pragma clang diagnostic ignored "-Winline-asm"

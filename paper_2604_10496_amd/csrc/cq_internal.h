@@ -71,7 +71,7 @@ cq_status cq_rotate_quant_ex(const float* X, const float* R, int T, int H, int a
                              size_t workspace_bytes, cq_stream stream);
 
 // Decode-sized batches: quantization of the rotated rows (given as K-split partial sums) and the router
-// logits in one launch.  Supported sizes also fit the one-workgroup routing kernel that follows.
+// logits in one launch.
 // topk_ids / topk_w [T, top_k]: NULL, or the launch also selects every token's experts (a4).
 bool cq_front_small_supported(int T, int H, int E, int top_k);
 cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H, int act_bits, const float* Wr,
@@ -127,7 +127,7 @@ size_t cq_gemm_partials_bytes(const cq_codebook_weights* W, int M_total, int epi
 // K split of a product: ksplit ranges of ksteps K steps (of 64) each; 1 and K/64 when K is not split
 void cq_gemm_split_plan(const cq_codebook_weights* W, int M_total, int epilogue, int* ksplit, int* ksteps,
                         int max_group_rows = 0);
-// block-wise tables of 1024 weights on the streaming kernel (groups of at most 16 rows, K ranges of whole tables)
+// block-wise tables of 1024 weights on the streaming kernel (up to 32 rows per group, or in passes; K ranges of whole tables)
 bool cq_gemm_blockwise_streams(const cq_codebook_weights* W, int M_total, int epilogue, int max_group_rows = 0);
 // W2 weights streamed as stored (index_bits = 2): quadruple tables in LDS, decode-sized groups
 static inline bool cq_is_w2(const cq_codebook_weights* W) { return W->index_bits == 2; }
@@ -163,7 +163,7 @@ bool cq_gemm_large_tail_split(const cq_codebook_weights* W, int epilogue, int ou
 cq_status cq_gemm_large_launch(const cq_codebook_weights* W, const void* A, int a_kind, const float* row_scale,
                                const int32_t* row_gather, const int32_t* group_offsets, int M_total, int small_max,
                                int epilogue, void* out, int out_kind, void* workspace, hipStream_t s, bool half);
-// whether a launch of it runs half tiles (lists and product alike); a_rows: rows of A, 0 if unknown
+// whether a launch of it runs half tiles of two workgroups per compute unit; a_rows: rows of A, 0 if unknown
 bool cq_gemm_uses_half_tiles(const cq_codebook_weights* W, int M_total, long a_rows);
 
 #endif  // CQ_INTERNAL_H_

@@ -18,11 +18,11 @@ __device__ __forceinline__ uint64_t lanemask_lt(int lane) { return (1ull << lane
 // Top-k of one token by one wavefront.  val[s] is the logit of expert s*64 + lane.  Called by all
 // wavefronts of the workgroup together (it contains workgroup barriers); sk/si/sv/ss are this
 // wavefront's 64-entry LDS scratch arrays.  Writes ids (descending logit, ties -> lower id) and the
-// softmax over the selected logits; lds_ids, if given, also receives the ids.
+// softmax over the selected logits.
 template <int NSLOT>
 __device__ __forceinline__ void wave_topk(const float (&val)[NSLOT], int nslot, int E, int k, bool active, int lane,
                                           uint32_t* sk, int* si, float* sv, float* ss, int32_t* ids_out,
-                                          float* w_out, int* lds_ids) {
+                                          float* w_out) {
   const uint64_t lt = lanemask_lt(lane);
   uint32_t key[NSLOT];
 #pragma unroll
@@ -73,7 +73,6 @@ __device__ __forceinline__ void wave_topk(const float (&val)[NSLOT], int nslot, 
       rank += (ok > mk || (ok == mk && oi < mi)) ? 1 : 0;
     }
     ids_out[rank] = mi;
-    if (lds_ids) lds_ids[rank] = mi;
     ss[rank] = sv[lane];
   }
   __syncthreads();

@@ -129,7 +129,8 @@ __global__ __launch_bounds__(kFrontThreads) void front_small_kernel(
 }  // namespace
 
 bool cq_front_small_supported(int T, int H, int E, int top_k) {
-  // the limits of the one-workgroup routing kernel that follows, and of this kernel's registers
+  // (one workgroup per token reads the router's rows again: beyond this the separate launches are cheaper; E and H: the
+  // kernel's registers)
   return (long)T * top_k <= 1024 && E <= kFrontMaxE && H <= 2 * 4 * kFrontThreads && H % 4 == 0 &&
          (long)T * E * H <= (1L << 23);
 }

@@ -60,8 +60,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ par
   else if constexpr (NSLOT == 2)
     wave_topk_regs2(val, E, k, lane, s_id[wave], s_val[wave], ids + o, w + o);
   else
-    wave_topk<NSLOT>(val, nslot, E, k, active, lane, s_key[wave], s_id[wave], s_val[wave], s_sorted[wave], ids + o, w + o,
-                     nullptr);
+    wave_topk<NSLOT>(val, nslot, E, k, active, lane, s_key[wave], s_id[wave], s_val[wave], s_sorted[wave], ids + o, w + o);
 }
 
 // Router logits for decode-sized batches: one workgroup per (token, four experts); its four wavefronts
@@ -190,7 +189,7 @@ __global__ __launch_bounds__(1024) void route_fused_kernel(const float* logits_i
 // the wavefronts and over the experts gives the position.  One launch instead of the counting sort's three (histogram,
 // one-workgroup scan over its blocks, scatter: 15 us at 3072 assignments, 6.5 us so).
 // (One workgroup stores from one compute unit: 12 us at 8192 assignments, 24 us at 16384, where the counting sort
-// takes 17 since its scan requests the block counts together.)
+// takes 19 in its three launches.)
 constexpr int kGroupMaxChunks = 8;
 template <int CH>
 __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__ ids, int T, int E, int k, int S,
