@@ -346,7 +346,9 @@ bool cq_rotate_split_supported(int T, int H) {
 // 40 / 40 (48), 160 59 / 42; H = 2048, 128 tokens 28 / 29 (64), 160 34 / 30 (128); H = 3840 (one part), 128 tokens 53 / 117
 // (15), 256 87 / 117 (30), 300 147 / 121 (45); H = 2304 (one part), 512 tokens 72 / 80 (36), 640 95 / 81 (45); H = 2560 (two),
 // 256 tokens 49 / 53 (40), 300 62 / 55 (60); H = 1024, 400 tokens 26 / 28 (64), 513 28 / 29 (80), 769 33 / 30.
-// Error of X_R against float64 (2-norm): fp32 kernel 3.4e-7 .. 5.9e-7 at 77 .. 200 tokens, this path 1.7e-7 .. 2.1e-7.
+// Error of X_R against float64, fp32 kernel / this path, 2-norm (and largest, of the row's maximum): H = 4096, 64 .. 256
+// tokens 3.9e-7 .. 6.0e-7 / 1.9e-7 .. 2.1e-7 (1.1e-6 .. 2.2e-6 / 5.3e-7 .. 6.4e-7); H = 2048, 129 .. 600 tokens 3.2e-7 ..
+// 4.7e-7 / 2.3e-7 .. 2.7e-7 (9.8e-7 .. 1.8e-6 / 6.4e-7 .. 1.1e-6).
 size_t cq_rotate_split_partials_bytes(int parts, int T, int H) {
   return parts > 1 ? cq_align_up((size_t)parts * T * H * sizeof(float), 256) : 0;
 }
