@@ -3,10 +3,12 @@
 // like the layer's input.
 //
 // H_I = H_m (x) H_p with p = 2^k and m = 1 (I a power of two) or m = 4 * (odd part of I) in {12, 28, 44}, H_m
-// from Paley's constructions (index i = a*p + b).  One workgroup per row keeps the row in LDS: k butterfly
+// from Paley's constructions (index i = a*p + b).  The general kernel: one workgroup per row keeps it in LDS, k butterfly
 // stages over the blocks of p (a fast Walsh-Hadamard transform, two stages per barrier), then every thread
 // combines the m values at its positions b with the signs of H_m (a compile-time table), scales, and the row
 // maximum gives the integer codes.  Cost O(I (log p + m)) per row instead of O(I^2).
+#include <type_traits>
+
 #include "cq_internal.h"
 
 namespace {
@@ -148,6 +150,247 @@ __global__ __launch_bounds__(kHadThreads) void hadamard_quant_kernel(const float
   }
 }
 
+// ---- the sizes of the configured layers, in registers ----
+// H_I = H_A (x) H_P with P = 32 .. 512: A is the Paley order, or for a power of two 16 of its factors of 2.
+// Bound by memory (4 bytes in, 1 to 7 out per value); one pass through LDS is what is left of the exchanges:
+//   1. thread b of a row loads its A values (whole cache lines per wavefront), combines them with H_A in registers and
+//      writes them to LDS;
+//   2. 16 lanes take one of the A blocks of P, a lane the values b = 64 h + 4 l + j of it: the bits of j and h are
+//      butterflies in registers, those of l are data-parallel moves inside a row of 16 lanes.
+// The general kernel above (an LDS pass per two bits, every value combined from LDS) against this one, back-to-back calls
+// that also store the fp32 rows: 4096 rows of 14336 174 / 103 us (5.1 TB/s of what it reads and writes), of 4096 47.5 / 24.4,
+// of 2048 29.9 / 18.0, of 1408 56 / 15.5, of 768 16.4 / 14.7 (a call alone takes 14); 1001 rows of 14336 47.6 / 25.9.
+//
+// Step 2 across lanes.  With s_j the sign of bit j of the lane and P_j the exchange of lanes that differ in it, a stage is
+// v <- s_j v + P_j v.  On x = (product of all s_j) v it becomes x <- x - s_j P_j x, one multiply-add on a moved operand, and
+// after the last stage x = v.  There is no move for lanes that differ in bit 2 alone; lanes that differ in bits 0..2 have
+// one (row_half_mirror), so bits are taken in the basis {1, 2, 7, 8} of the lane number: lane l then ends with output
+// y(l) = (l0 ^ l2, l1 ^ l2, l0 ^ l1 ^ l2, l3) of the 16 instead of l.
+
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
+// v <- H_A v (rows of the sign tables: inputs, columns: outputs)
+template <int A>
+__device__ __forceinline__ void combine(float (&v)[A]) {
+  if constexpr (A == 16) {
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (!(i & d)) {
+          const float a = v[i], b = v[i | d];
+          v[i] = a + b;
+          v[i | d] = a - b;
+        }
+  } else if constexpr (A == 28) {
+    // H_28 = S (x) [[1,1],[1,-1]] + I (x) [[1,-1],[-1,-1]]: with p = x0 + x1 and d = x0 - x1 of a pair, out0 = S p + d and
+    // out1 = S d - p (418 additions instead of 756)
+    constexpr PaleySigns<28> sg{};
+    float p[14], d[14];
+#pragma unroll
+    for (int i = 0; i < 14; ++i) {
+      p[i] = v[2 * i] + v[2 * i + 1];
+      d[i] = v[2 * i] - v[2 * i + 1];
+    }
+#pragma unroll
+    for (int j = 0; j < 14; ++j) {
+      float a = d[j], b = -p[j];
+#pragma unroll
+      for (int i = 0; i < 14; ++i)
+        if (i != j) {   // (S[i][j]: the sign of the pair's first entry)
+          a += sg.neg[2 * i][2 * j] ? -p[i] : p[i];
+          b += sg.neg[2 * i][2 * j] ? -d[i] : d[i];
+        }
+      v[2 * j] = a;
+      v[2 * j + 1] = b;
+    }
+  } else {
+    constexpr PaleySigns<A> sg{};
+    float o[A];
+#pragma unroll
+    for (int j = 0; j < A; ++j) {
+      float a = 0.f;
+#pragma unroll
+      for (int i = 0; i < A; ++i) a += sg.neg[i][j] ? -v[i] : v[i];
+      o[j] = a;
+    }
+#pragma unroll
+    for (int j = 0; j < A; ++j) v[j] = o[j];
+  }
+}
+
+// NT threads per row (P of them, or 64 where P = 32), ROWS rows per workgroup
+template <int A, int LOGP, int NT, int ROWS>
+__global__ __launch_bounds__(NT * ROWS) void hadamard_rows_kernel(const float* __restrict__ Hin, int M, float qmax,
+                                                                  int8_t* __restrict__ Q, uint16_t* __restrict__ Q16,
+                                                                  float* __restrict__ scale, float* __restrict__ HR) {
+  constexpr int P = 1 << LOGP, I = A * P;
+  constexpr int kStride = P + 16;                      // of a block in LDS (floats): four blocks on different banks
+  constexpr int L = P < 64 ? 8 : 16;                   // lanes per block in step 2
+  constexpr int HI = P / (4 * L);                      // values of h
+  constexpr int kItems = A * L, N2 = (kItems + NT - 1) / NT;
+  extern __shared__ float rows_lds[];
+  __shared__ float red[ROWS][NT / 64];
+  const int sub = threadIdx.x / NT, tid = threadIdx.x - sub * NT;
+  const int row = blockIdx.x * ROWS + sub;
+  const bool real = row < M;
+  const size_t base = (size_t)(real ? row : M - 1) * I;   // (rows past the end read the last one and store nothing)
+  const float* src = Hin + base;
+  float* lds = rows_lds + sub * (A * kStride);
+
+  // ---- step 1 ----
+  if constexpr (P < 64) {
+    // A = 44, 32 positions: the two half wavefronts share the outputs of a position.  The core of H_44 is circulant
+    // (chi(out - in) modulo 43), so the second half does the same sums on inputs that are renumbered by 22.
+    static_assert(A == 44 || P >= 64, "two half wavefronts");
+    constexpr int q = 43;
+    const int b = tid & 31, h = tid >> 5;
+    const float* s0 = src + b + (1 + 22 * h) * P;                    // w[i] = v[1 + (i + 22 h) mod 43], i < 21
+    const float* s1 = src + b + (h ? 1 - 21 : 1) * P;                // ... and from 21 on
+    float w[q];
+#pragma unroll
+    for (int i = 0; i < q; ++i) w[i] = i < 21 ? s0[i * P] : s1[i * P];
+    const float v0 = src[b];
+    float out0 = v0;
+#pragma unroll
+    for (int i = 0; i < q; ++i) out0 -= w[i];
+    constexpr PaleySigns<44> sg{};
+#pragma unroll
+    for (int i = 0; i < 22; ++i) {
+      float a = v0 + w[i];
+#pragma unroll
+      for (int j = 0; j < q; ++j)
+        if (j != i) a += sg.neg[1 + j][1 + i] ? -w[j] : w[j];
+      const int n = 1 + i + 22 * h;                                  // (22 + 21 is output 1 again: output 0 in its place)
+      if (i == 21) a = h ? out0 : a;
+      lds[(i == 21 && h ? 0 : n) * kStride + b] = a;
+    }
+  } else {
+    float v[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) v[a] = src[a * P + tid];
+    combine<A>(v);
+#pragma unroll
+    for (int a = 0; a < A; ++a) lds[a * kStride + tid] = v[a];
+  }
+  if constexpr (NT > 64) __syncthreads();
+  else __builtin_amdgcn_wave_barrier();   // (a row is one wavefront's: its LDS operations complete in order)
+
+  // ---- step 2 ----
+  const int l = tid & (L - 1);
+  const int l0 = l & 1, l1 = (l >> 1) & 1, l2 = (l >> 2) & 1, l3 = (l >> 3) & 1;
+  const float sign = (l0 ^ l1 ^ l2 ^ l3) ? -1.f : 1.f;               // product of the four below
+  const float m1 = (l0 ^ l2) ? 1.f : -1.f, m2 = (l1 ^ l2) ? 1.f : -1.f, m4 = l2 ? 1.f : -1.f, m8 = l3 ? 1.f : -1.f;   // -s_j
+  const int y = (l0 ^ l2) | ((l1 ^ l2) << 1) | ((l0 ^ l1 ^ l2) << 2) | (l3 << 3);
+  const float norm = 1.f / sqrtf((float)I);
+  float x[N2][HI][4];
+  float amax = 0.f;
+#pragma unroll
+  for (int n = 0; n < N2; ++n) {
+    const int item = tid + n * NT;
+    const int a = (item < kItems ? item : 0) / L;
+#pragma unroll
+    for (int h = 0; h < HI; ++h) {
+      const float4 t = *reinterpret_cast<const float4*>(lds + a * kStride + h * (4 * L) + l * 4);
+      const float s0 = t.x + t.y, s1 = t.x - t.y, s2 = t.z + t.w, s3 = t.z - t.w;
+      x[n][h][0] = s0 + s2; x[n][h][1] = s1 + s3; x[n][h][2] = s0 - s2; x[n][h][3] = s1 - s3;
+    }
+#pragma unroll
+    for (int d = 1; d < HI; d <<= 1)
+#pragma unroll
+      for (int h = 0; h < HI; ++h)
+        if (!(h & d))
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float u = x[n][h][j], w = x[n][h | d][j];
+            x[n][h][j] = u + w;
+            x[n][h | d][j] = u - w;
+          }
+#pragma unroll
+    for (int h = 0; h < HI; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float u = x[n][h][j] * sign;
+        u = fmaf(m1, lane_move<0xB1>(u), u);             // quad_perm 1 0 3 2
+        u = fmaf(m2, lane_move<0x4E>(u), u);             // quad_perm 2 3 0 1
+        u = fmaf(m4, lane_move<0x141>(u), u);            // row_half_mirror
+        if constexpr (L == 16) u = fmaf(m8, lane_move<0x128>(u), u);   // row_ror 8
+        u *= norm;
+        x[n][h][j] = u;
+        if (kItems % NT == 0 || item < kItems) amax = fmaxf(amax, fabsf(u));
+      }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+  if constexpr (NT > 64) {
+    if ((tid & 63) == 0) red[sub][tid >> 6] = amax;
+    __syncthreads();
+    amax = red[sub][0];
+#pragma unroll
+    for (int i = 1; i < NT / 64; ++i) amax = fmaxf(amax, red[sub][i]);
+  }
+  const float sc = amax == 0.f ? 1.f : amax / qmax;
+  if (!real) return;
+  if (tid == 0) scale[row] = sc;
+
+  // ---- integer codes: round to nearest, ties to even ----
+  // The quotient by the row's scale from its reciprocal, with the remainder of the product taken into account (Markstein's
+  // division: the correctly rounded quotient but for the ends of the exponent range, where the division is kept): three
+  // operations instead of ten.
+  const bool fast = sc > 1e-30f && sc < 1e30f;
+  float inv = __builtin_amdgcn_rcpf(sc);
+  inv = fmaf(fmaf(-sc, inv, 1.f), inv, inv);
+  auto codes = [&](auto by_inverse) {
+#pragma unroll
+    for (int n = 0; n < N2; ++n) {
+      const int item = tid + n * NT;
+      if (kItems % NT != 0 && item >= kItems) break;
+      const size_t at = base + (item / L) * P + y * 4;
+#pragma unroll
+      for (int h = 0; h < HI; ++h) {
+        const float* u = x[n][h];
+        const size_t e = at + h * (4 * L);
+        if (HR) *reinterpret_cast<float4*>(HR + e) = make_float4(u[0], u[1], u[2], u[3]);
+        float r[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float v;
+          if constexpr (decltype(by_inverse)::value) {
+            v = u[j] * inv;
+            v = fmaf(fmaf(-v, sc, u[j]), inv, v);
+          } else {
+            v = u[j] / sc;
+          }
+          r[j] = fminf(fmaxf(rintf(v), -qmax), qmax);
+        }
+        const uint32_t packed = ((uint32_t)(int)r[0] & 0xffu) | (((uint32_t)(int)r[1] & 0xffu) << 8) |
+                                (((uint32_t)(int)r[2] & 0xffu) << 16) | (((uint32_t)(int)r[3] & 0xffu) << 24);
+        if (Q) *reinterpret_cast<uint32_t*>(Q + e) = packed;
+        if (Q16)  // the same codes as bf16 bit patterns (exact: small integers)
+          *reinterpret_cast<uint2*>(Q16 + e) =
+              make_uint2((__float_as_uint(r[0]) >> 16) | (__float_as_uint(r[1]) & 0xffff0000u),
+                         (__float_as_uint(r[2]) >> 16) | (__float_as_uint(r[3]) & 0xffff0000u));
+      }
+    }
+  };
+  if (fast) codes(std::true_type{});
+  else codes(std::false_type{});
+}
+
+template <int A, int LOGP, int NT, int ROWS>
+cq_status launch_rows(const float* Hin, int M, float qmax, int8_t* Q, uint16_t* Q16, float* scale, float* HR, hipStream_t s) {
+  constexpr int lds = ROWS * A * ((1 << LOGP) + 16) * 4;
+  auto kern = hadamard_rows_kernel<A, LOGP, NT, ROWS>;
+  static std::atomic<bool> configured{false};
+  const cq_status st = cq_configure_lds(kern, lds, configured, false);
+  if (st != CQ_OK) return st;
+  hipLaunchKernelGGL(kern, dim3((M + ROWS - 1) / ROWS), dim3(NT * ROWS), lds, s, Hin, M, qmax, Q, Q16, scale, HR);
+  return cq_check_launch();
+}
+
 // I = m * 2^k with m in {1, 12, 28, 44}; false if I has no such form
 bool had_split(int I, int* m, int* p, int* k) {
   if (I <= 0) return false;
@@ -184,6 +427,15 @@ cq_status cq_hadamard_quant_launch(const float* Hin, int M, int I, int bits, int
       return CQ_ERR_HIP;
   }
   const float qmax = (float)((1 << (bits - 1)) - 1);
+  // sizes with an instantiation in registers
+  switch (I) {
+    case 14336: return launch_rows<28, 9, 512, 1>(Hin, M, qmax, Q, Q16, scale, HR, s);
+    case 4096: return launch_rows<16, 8, 256, 1>(Hin, M, qmax, Q, Q16, scale, HR, s);
+    case 2048: return launch_rows<16, 7, 128, 2>(Hin, M, qmax, Q, Q16, scale, HR, s);
+    case 1408: return launch_rows<44, 5, 64, 4>(Hin, M, qmax, Q, Q16, scale, HR, s);
+    case 768: return launch_rows<12, 6, 64, 4>(Hin, M, qmax, Q, Q16, scale, HR, s);
+    default: break;
+  }
   const size_t lds = (size_t)I * 4;
   switch (m) {
     case 1:

@@ -1355,6 +1355,31 @@ def test_hadamard_quant(B, M, I, bits):
     assert n_tie <= max(2, M * I // 500)
 
 
+@pytest.mark.parametrize("I", [14336, 4096, 2048, 1408, 768])
+@pytest.mark.parametrize("M", [1, 5])
+def test_hadamard_quant_in_registers(B, M, I):
+    """The sizes with a kernel of their own: one row and a number that its workgroups' rows do not divide; rows at both
+    ends of the exponent range take the division instead of the reciprocal.  Bound: an output is a sum of I terms in at
+    most 15 + 41 roundings of 2^-24 (14 stages, 42 terms of H_44 one after the other), each relative to a partial sum that is
+    no larger than the row's 2-norm times a few: 4e-6 of the row's maximum, as for the other sizes."""
+    rng = np.random.default_rng(7 * I + M)
+    h = rng.standard_normal((M, I)).astype(np.float32)
+    h[M // 2] *= np.float32(1e-33)
+    if M > 1:
+        h[0, I - 1] = -300.0
+        h[1] = 0.0
+        h[3] *= np.float32(1e32)
+    for bits in (4, 8):
+        out = B.cq_hadamard_quant(_dev(h), bits)
+        ref = O.hadamard_rows(h)
+        q_ref, s_ref = O.quantize(ref, bits)
+        HR = out["HR"].cpu().numpy().astype(np.float64)
+        err = np.abs(HR - ref).max(axis=1) / np.maximum(np.abs(ref).max(axis=1), 1e-300)
+        assert err.max() <= 4e-6
+        assert np.allclose(out["scale"].cpu().numpy(), s_ref, rtol=1e-5, atol=0)
+        assert Hp.check_codes(out["Q"].cpu().numpy(), q_ref, ref, s_ref) <= max(2, M * I // 500)
+
+
 @pytest.mark.parametrize("name,over", [
     ("tiny", dict(H=1024, I=1536, T=48, group_k=512)),                      # 2 and 3 tables per row, few rows per expert
     ("mixtral_prefill", dict(H=1024, I=1408, T=400, group_k=1024)),         # short last group (1408 = 1024 + 384)
