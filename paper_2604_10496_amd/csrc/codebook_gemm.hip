@@ -38,14 +38,20 @@ int row_bound(int M_total, int max_group_rows) {
 
 // Batches a little too large for one pass: where few groups have more rows, a second pass over their indices on
 // workgroups of its own is cheaper than the large-tile launch behind a streaming launch (and the launches that add up
-// both kinds' partial sums).  With a long K, groups of at most 128 rows, and fewer than 28 rows per group on average (23
+// both kinds' partial sums).  With groups of at most 128 rows and fewer than 28 rows per group on average (23
 // with block-wise tables, in passes of 16 rows): us per layer of the Mixtral shape, two launches against passes: 33 tokens
 // 174 / 169, 77 tokens 207 / 192, 110 tokens 291 / 254; block-wise tables (large tiles against passes) 40 tokens
 // 347 / 232, 79 tokens 369 / 325, 92 tokens 359 / 340, 104 tokens 363 / 359, 111 tokens 362 / 377 (from 24 rows per
 // group on the partial sums of wider layers no longer fit into the library's own array, which held these batches).
+// Short K (2048 and less), where the large tiles took the small groups as well: 8 rows cost a tile what 64 do, so a group that
+// fits one pass is cheaper streamed (66 groups x 2816 x 2048: 8 rows 60 / 46 us, 32 rows 62 / 58; two passes 110), whole
+// layers of the DeepSeek-V2-Lite shape on tiles and in passes: 33 tokens 126 / 106, 64 tokens 140 / 123, 128 tokens
+// 151 / 144 (256: 167 / 178); Qwen3 shape, whose rows are very uneven, 33 tokens 88 / 79, 96 tokens 118 / 116, 128 tokens
+// 124.3 / 123.5 (192: 132 / 149).
 long rows_in_passes(const cq_codebook_weights* W) { return (cq_tables_per_row(W) > 1 ? 23L : 28L) * W->G; }
 bool streams_in_passes(const cq_codebook_weights* W, int M_total, int max_group_rows) {
-  return W->K > 2048 && row_bound(M_total, max_group_rows) <= 128 && (long)M_total < rows_in_passes(W);
+  if (W->K <= 2048 && cq_tables_per_row(W) > 1) return false;
+  return row_bound(M_total, max_group_rows) <= 128 && (long)M_total < rows_in_passes(W);
 }
 
 // Whether a K range of ksteps steps runs the streaming kernel's pipelined unit loop: 8 or 7 steps for every wavefront,
@@ -193,7 +199,7 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
   const bool converts = a_kind == CQ_A_INT8_CODES || a_kind == CQ_A_F32;
   const bool half = large && cq_gemm_uses_half_tiles(W, M_total, converts || !row_gather ? M_total : a_rows);
   // Where large tiles run anyway, they take the small groups as well and the streaming launch falls away if that is the
-  // cheaper: with a short K always (DeepSeek-V2-Lite shape, gate/up + down at 40 tokens: 92 us against 105 us in two
+  // cheaper: with a short K always where it has not gone to passes above (DeepSeek-V2-Lite shape, gate/up + down at 40 tokens: 92 us against 105 us in two
   // launches, Qwen3 shape 46 against 78), with a long one from 28 rows per group on (Mixtral shape at 64 tokens 245
   // against 172 us, at 96 tokens 241 against 246, at 128 tokens the whole layer 290 against 302).
   const bool no_small = blockwise || (half && (W->K <= 2048 || (long)M_total >= 28L * W->G)) ||

@@ -1262,19 +1262,22 @@ def test_layer_grouping_folded_into_gate_up(B, name, over):
 
 
 @pytest.mark.parametrize("over,rows", [
-    # gate/up in passes of 32 rows (gathered rows, row scales, the gated epilogue), down on half tiles
+    # gate/up in passes of 32 rows (gathered rows, row scales, the gated epilogue)
     (dict(H=4096, I=128, T=45, zipf_s=2.0), 33), (dict(H=4096, I=128, T=77, zipf_s=1.5), 65),   # (from 64 tokens: split rotation)
     (dict(H=3584, I=128, T=111, act_bits=4, zipf_s=1.0), 65),
-    # down in passes, in two K ranges that the combine adds; gate/up on half tiles
+    # down in passes, in two K ranges that the combine adds
     (dict(H=256, I=8192, T=60, zipf_s=1.5), 33), (dict(H=512, I=4352, T=100, zipf_s=1.0), 33),
     # both with shared experts of all tokens
     (dict(H=4096, I=128, T=40, S=1), 40), (dict(H=256, I=4096, T=64, E=16, top_k=1, S=1, h_bits=8), 64),
+    # short K: one to four steps per wavefront, the last one missing in some (K = 704, 1408)
+    (dict(H=1024, I=768, T=100, E=16, zipf_s=1.0), 33), (dict(H=2048, I=1408, T=70, E=16, top_k=4, S=1, act_bits=4), 70),
+    (dict(H=512, I=704, T=128, E=24, S=1, h_bits=8), 128),
     # block-wise tables in passes of 16 rows, and the down product's in passes of 32 (K ranges of 2048)
     (dict(H=4096, I=256, T=40, group_k=1024, zipf_s=1.0), 17), (dict(H=256, I=6144, T=91, group_k=1024, zipf_s=0.5), 33),
     (dict(H=512, I=4096, T=70, group_k=1024, zipf_s=1.0), 33),
 ])
 def test_layer_streams_in_passes(B, over, rows):
-    """Medium batches with a long K: the layer's products stream, groups of more than a pass's rows in several passes.
+    """Medium batches: the layer's products stream, groups of more than a pass's rows in several passes.
     `rows`: at least this many in the largest group."""
     cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], **over)
     L = Hp.make_inputs(cfg, with_experts=False)
