@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "cq_internal.h"
+#include "cq_quotient.h"
 
 namespace {
 
@@ -337,13 +338,8 @@ __global__ __launch_bounds__(NT * ROWS) void hadamard_rows_kernel(const float* _
   if (tid == 0) scale[row] = sc;
 
   // ---- integer codes: round to nearest, ties to even ----
-  // The quotient by the row's scale from its reciprocal, with the remainder of the product taken into account (Markstein's
-  // division: the correctly rounded quotient but for the ends of the exponent range, where the division is kept): three
-  // operations instead of ten.
-  const bool fast = sc > 1e-30f && sc < 1e30f;
-  float inv = __builtin_amdgcn_rcpf(sc);
-  inv = fmaf(fmaf(-sc, inv, 1.f), inv, inv);
-  auto codes = [&](auto by_inverse) {
+  const cq_quotient by(sc);
+  auto codes = [&](auto fast) {
 #pragma unroll
     for (int n = 0; n < N2; ++n) {
       const int item = tid + n * NT;
@@ -356,16 +352,7 @@ __global__ __launch_bounds__(NT * ROWS) void hadamard_rows_kernel(const float* _
         if (HR) *reinterpret_cast<float4*>(HR + e) = make_float4(u[0], u[1], u[2], u[3]);
         float r[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float v;
-          if constexpr (decltype(by_inverse)::value) {
-            v = u[j] * inv;
-            v = fmaf(fmaf(-v, sc, u[j]), inv, v);
-          } else {
-            v = u[j] / sc;
-          }
-          r[j] = fminf(fmaxf(rintf(v), -qmax), qmax);
-        }
+        for (int j = 0; j < 4; ++j) r[j] = fminf(fmaxf(rintf(by.get<decltype(fast)::value>(u[j])), -qmax), qmax);
         const uint32_t packed = ((uint32_t)(int)r[0] & 0xffu) | (((uint32_t)(int)r[1] & 0xffu) << 8) |
                                 (((uint32_t)(int)r[2] & 0xffu) << 16) | (((uint32_t)(int)r[3] & 0xffu) << 24);
         if (Q) *reinterpret_cast<uint32_t*>(Q + e) = packed;
@@ -376,7 +363,7 @@ __global__ __launch_bounds__(NT * ROWS) void hadamard_rows_kernel(const float* _
       }
     }
   };
-  if (fast) codes(std::true_type{});
+  if (by.fast) codes(std::true_type{});
   else codes(std::false_type{});
 }
 

@@ -11,7 +11,10 @@
 // row-major B the four elements of a 16-byte load are four neighbouring columns, which become
 // four column sets {c0 + 4j + n}; for the transposed B they are four K values of column
 // c0 + 16n + j.  No LDS: operands are small enough to be served by L1/L2.
+#include <type_traits>
+
 #include "cq_internal.h"
+#include "cq_quotient.h"
 
 namespace {
 
@@ -194,11 +197,84 @@ __global__ __launch_bounds__(256) void codes_kernel(const float* __restrict__ XR
   }
 }
 
-// One workgroup per token: reduce the K-split partials in a fixed order, keep X_R, find the row
-// maximum, then round x / s to the nearest integer (ties to even, v_rndne_f32).
+// One workgroup per token: reduce the K-split partials in a fixed order, keep X_R, find the row maximum, then round x / s to
+// the nearest integer (ties to even, v_rndne_f32).  The row stays in registers, NV groups of four columns per thread, whose
+// partial sums are requested together (one after the other, with the row read back from X_R and a division per value, 512
+// rows of 4096 with 4 parts took 13.3 us, now 10.3; 4096 rows of 4096 27.9 / 20.4; 2048 rows of 2048 with 2 parts 15.0 / 13.6).
+template <int NV>
 __global__ __launch_bounds__(256) void quantize_kernel(const float* part, int ksplit, int in_place, int T, int H,
                                                        float qmax, float* XR, int8_t* __restrict__ Q,
                                                        uint16_t* __restrict__ Q16, float* __restrict__ scale) {
+  __shared__ float red[4];
+  const int t = blockIdx.x;
+  const int tid = threadIdx.x;
+  constexpr int kAtOnce = NV >= 8 ? 1 : NV >= 4 ? 3 : 7;   // partial matrices whose loads are in flight together
+  float* xr = XR + (size_t)t * H;
+  float4 v[NV];
+  float amax = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = min((i * 256 + tid) * 4, H - 4);   // (columns past the end: the last ones again, not kept)
+    v[i] = *reinterpret_cast<const float4*>(part + (size_t)t * H + c);
+  }
+  for (int z0 = 1; z0 < ksplit; z0 += kAtOnce) {
+    float4 p[kAtOnce][NV];
+#pragma unroll
+    for (int z = 0; z < kAtOnce; ++z)
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int c = min((i * 256 + tid) * 4, H - 4);
+        p[z][i] = *reinterpret_cast<const float4*>(part + ((size_t)min(z0 + z, ksplit - 1) * T + t) * H + c);
+      }
+#pragma unroll
+    for (int z = 0; z < kAtOnce; ++z)
+      if (z0 + z < ksplit)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) { v[i].x += p[z][i].x; v[i].y += p[z][i].y; v[i].z += p[z][i].z; v[i].w += p[z][i].w; }
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = (i * 256 + tid) * 4;
+    if (c < H) {
+      if (!in_place) *reinterpret_cast<float4*>(xr + c) = v[i];
+      amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[i].x), fabsf(v[i].y)), fmaxf(fabsf(v[i].z), fabsf(v[i].w))));
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+  if ((tid & 63) == 0) red[tid >> 6] = amax;
+  __syncthreads();
+  amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  const float s = amax == 0.f ? 1.f : amax / qmax;
+  if (tid == 0) scale[t] = s;
+  int8_t* q = Q + (size_t)t * H;
+  const cq_quotient by(s);
+  auto codes = [&](auto fast) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = (i * 256 + tid) * 4;
+      if (c >= H) break;
+      const float r0 = fminf(fmaxf(rintf(by.get<decltype(fast)::value>(v[i].x)), -qmax), qmax);
+      const float r1 = fminf(fmaxf(rintf(by.get<decltype(fast)::value>(v[i].y)), -qmax), qmax);
+      const float r2 = fminf(fmaxf(rintf(by.get<decltype(fast)::value>(v[i].z)), -qmax), qmax);
+      const float r3 = fminf(fmaxf(rintf(by.get<decltype(fast)::value>(v[i].w)), -qmax), qmax);
+      const uint32_t packed = ((uint32_t)(int)r0 & 0xffu) | (((uint32_t)(int)r1 & 0xffu) << 8) |
+                              (((uint32_t)(int)r2 & 0xffu) << 16) | (((uint32_t)(int)r3 & 0xffu) << 24);
+      *reinterpret_cast<uint32_t*>(q + c) = packed;
+      if (Q16)
+        *reinterpret_cast<uint2*>(Q16 + (size_t)t * H + c) =
+            make_uint2((__float_as_uint(r0) >> 16) | (__float_as_uint(r1) & 0xffff0000u),
+                       (__float_as_uint(r2) >> 16) | (__float_as_uint(r3) & 0xffff0000u));
+    }
+  };
+  if (by.fast) codes(std::true_type{});
+  else codes(std::false_type{});
+}
+
+// rows wider than the registers of the kernel above hold
+__global__ __launch_bounds__(256) void quantize_wide_kernel(const float* part, int ksplit, int in_place, int T, int H,
+                                                            float qmax, float* XR, int8_t* __restrict__ Q,
+                                                            uint16_t* __restrict__ Q16, float* __restrict__ scale) {
   __shared__ float red[4];
   const int t = blockIdx.x;
   const int tid = threadIdx.x;
@@ -324,8 +400,9 @@ cq_status cq_quantize_launch(const float* partials, int ksplit, int T, int H, in
     hipLaunchKernelGGL(codes_kernel, grid, dim3(256), 0, s, (const float*)XR_out, (const uint32_t*)amax_bits, H, qmax,
                        Q_out, Q16_out, scale_out);
   } else {
-    hipLaunchKernelGGL(quantize_kernel, dim3(T), dim3(256), 0, s, partials, ksplit, in_place, T, H, qmax, XR_out,
-                       Q_out, Q16_out, scale_out);
+    auto kern = H <= 1024 ? quantize_kernel<1> : H <= 2048 ? quantize_kernel<2> : H <= 4096 ? quantize_kernel<4>
+                : H <= 8192 ? quantize_kernel<8> : quantize_wide_kernel;
+    hipLaunchKernelGGL(kern, dim3(T), dim3(256), 0, s, partials, ksplit, in_place, T, H, qmax, XR_out, Q_out, Q16_out, scale_out);
   }
   return cq_check_launch();
 }

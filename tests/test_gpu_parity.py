@@ -150,6 +150,29 @@ def test_rotate_quant_identity_and_grid(B):
     assert not z["Q"].cpu().numpy().any() and np.array_equal(z["scale"].cpu().numpy(), np.ones(3, np.float32))
 
 
+@pytest.mark.parametrize("H", [64, 1024, 1088, 2048, 4096, 4160, 8192, 8256])
+@pytest.mark.parametrize("bits", [4, 8])
+def test_quantize_rows_in_registers(B, H, bits):
+    """Quantization of whole rows by one workgroup, around the row lengths where its kernels change, with R = I: the codes
+    are those of the IEEE quotient x / s in fp32, value for value (rows at both ends of the exponent range included, where
+    the reciprocal gives way to the division)."""
+    rng = np.random.default_rng(H + bits)
+    T = 257
+    X = rng.standard_normal((T, H)).astype(np.float32)
+    X[5] *= np.float32(1e-33)
+    X[6] *= np.float32(1e33)
+    X[7] = 0.0
+    X[8, H // 2] = 1e4
+    out = B.cq_rotate_quant(_dev(X), _dev(np.eye(H, dtype=np.float32)), bits)
+    XR = out["XR"].cpu().numpy()
+    assert np.array_equal(XR, X)
+    qmax = np.float32(2 ** (bits - 1) - 1)
+    s = np.abs(X).max(axis=1) / qmax
+    s[7] = 1.0
+    assert np.array_equal(out["scale"].cpu().numpy(), s)
+    assert np.array_equal(out["Q"].cpu().numpy().astype(np.float32), np.clip(np.rint(X / s[:, None]), -qmax, qmax))
+
+
 # ---------------------------------------------------------------------------------------------
 # routing and permutation: bit-exact
 # ---------------------------------------------------------------------------------------------
