@@ -316,12 +316,17 @@ __global__ __launch_bounds__(256) void quantize_wide_kernel(const float* part, i
 // tokens 16 / 11 us, 3000 tokens 24 / 25 us (nothing left to gain); 40 tokens on 16-token tiles 5.7 / 7.7 us.
 namespace {
 bool spans_columns(int T, int N) { return N <= 16 || (N <= 64 && T >= 64 && T <= 1024); }
+
+// Rotation of so few values that tiles of 128 x 128 leave most of the chip idle: tiles of 16 x 256 also from 64 tokens on
+// (layer of width 256 at 64, 128, 256 and 512 tokens 36.3 -> 32.2, 40.2 -> 36.3, 43.5 -> 39.8 and 49.1 -> 45.1 us; of width
+// 2048 at 64 and 128 tokens 122.5 -> 117.4 and 143.9 -> 140.6).
+bool few_rows(int T, int N, int K) { return N == K && (long)T * N <= (1L << 18); }
 }  // namespace
 
 cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K, bool wide_tiles) {
   cq_gemm_f32_plan p;
   const bool narrow = !wide_tiles && N != K && spans_columns(T, N);   // (a square B is a rotation)
-  p.mb = T >= 64 && !narrow ? 4 : 1;
+  p.mb = T >= 64 && !narrow && (wide_tiles || !few_rows(T, N, K)) ? 4 : 1;
   const int tm = p.mb == 4 ? 128 : narrow ? 64 : 16;
   const int tn = p.mb == 4 ? 128 : narrow ? 64 : 256;
   const long wgs = (long)((N + tn - 1) / tn) * ((T + tm - 1) / tm);
@@ -338,7 +343,8 @@ cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K, bool wide_tiles) {
 
 // K is cut into min(16, K/64, 256 / workgroups) parts, so the number of parts falls as T grows, and their size with it.
 // The largest launch of up to T rows with `ks` parts is looked at for every ks from the most down to that of T rows.
-// (Sized for wide tiles, which have at least as many parts as narrow ones.)  least: fewer parts than this are not counted.
+// (Sized for wide tiles, which have at least as many parts as narrow ones: a tile of 16 x 256 covers a quarter of one of
+// 128 x 128.)  least: fewer parts than this are not counted.
 size_t cq_gemm_f32_partials_upto(int T, int N, int K, int least) {
   size_t most = 0;
   for (const int tm : {16, 128}) {   // rows of a tile: below 64 rows, and from there on
@@ -419,7 +425,7 @@ size_t cq_rotate_quant_bytes_upto(int T, int H) {
 
 extern "C" size_t cq_rotate_quant_workspace_bytes(int T, int H) {
   if (T <= 0 || H <= 0) return 0;
-  const cq_gemm_f32_plan p = cq_gemm_f32_make_plan(T, H, H);
+  const cq_gemm_f32_plan p = cq_gemm_f32_make_plan(T, H, H, true);   // (the more parts: also where the launch has fewer)
   return amax_bytes(T) + (p.ksplit > 1 ? cq_align_up((size_t)p.ksplit * T * H * sizeof(float), 256) : 0);
 }
 

@@ -91,7 +91,9 @@ def test_decode_dense_blockwise_bit_exact(B, N, K, g):
 # rotate + quantize
 # ---------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("T,H,bits", [(64, 256, 8), (1, 64, 8), (17, 128, 4), (130, 192, 8), (16, 1024, 4),
-                                      (200, 512, 4)])
+                                      (200, 512, 4),
+                                      # 2^18 values: the largest batch on tiles of 16 rows, and the next
+                                      (1024, 256, 4), (1025, 256, 8), (128, 2048, 8)])
 def test_rotate_quant(B, T, H, bits):
     cfg = synth.small_variant(synth.CONFIGS["tiny"], T=T, H=H, act_bits=bits, outlier_channels=(3, 41))
     L = synth.make_layer(cfg, with_experts=False)
