@@ -4,9 +4,10 @@
 // Top-k: one wavefront per token.  Logits become order-preserving 32-bit keys; the k-th largest key
 // is found by a bitwise descent that counts candidates with wave ballots (32 rounds, no sorting);
 // equal keys are admitted in ascending expert id with a ballot prefix count; the <= 64 survivors are
-// ranked by (logit descending, id ascending).  Permutation: a three-pass counting sort over blocks
-// of 256 assignments whose in-block ranks come from ballot match masks, so the order inside every
-// expert is ascending assignment number (a stable sort) and the result is unique.
+// ranked by (logit descending, id ascending).  Permutation: ranks from ballot match masks
+// and counts in LDS, in one workgroup or in several that each count everything; beyond 128 experts or
+// 65535 assignments a three-pass counting sort over blocks of 256.  The order inside every expert is
+// ascending assignment number (a stable sort), so the result is unique.
 #include "cq_internal.h"
 #include "cq_route.h"
 
@@ -188,9 +189,9 @@ __global__ __launch_bounds__(1024) void route_fused_kernel(const float* logits_i
 // every assignment its rank among the wavefront's assignments to the same expert, and the counts' exclusive prefix over
 // the wavefronts and over the experts gives the position.  One launch instead of the counting sort's three (histogram,
 // one-workgroup scan over its blocks, scatter: 15 us at 3072 assignments, 6.5 us so).
-// (One workgroup stores from one compute unit: 12 us at 8192 assignments, 24 us at 16384, where the counting sort
-// takes 19 in its three launches.)
-constexpr int kGroupMaxChunks = 8;
+// (One workgroup stores from one compute unit: 5 us at 4096 assignments, 12 us at 8192, 24 us at 16384; more than 4096 go to
+// group_chunks_kernel.)
+constexpr int kGroupMaxChunks = 4;
 template <int CH>
 __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__ ids, int T, int E, int k, int S,
                                                      int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
@@ -266,6 +267,98 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
   }
   if (src_token)
     for (int i = tid; i < S * T; i += 1024) src_token[A + i] = i % T;
+}
+
+// The same for more assignments and up to 128 experts, still in one launch: workgroup b ranks assignments 1024 b .. + 1023,
+// and finds out by itself what precedes them -- it counts the ids of all assignments, those in front of its own in the upper
+// half word (a token selects an expert at most once: counts stay below 2^16 for fewer tokens than that).  Four copies of the
+// counters keep the additions to a popular expert apart.  Counting everything again in every workgroup costs it about a
+// microsecond per 16384 assignments and saves two launches and their waits: 16384 assignments to 128 experts 8 us
+// against 19 in the counting sort's three launches, 8192 to 8 experts 6 against 12 in one workgroup.
+constexpr int kGroupChunk = 1024;
+constexpr int kGroupMostAssign = 65535;   // (one expert may have them all)
+__global__ __launch_bounds__(1024) void group_chunks_kernel(const int32_t* __restrict__ ids, int T, int E, int k, int S,
+                                                            int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+                                                            int32_t* __restrict__ inv_perm,
+                                                            int32_t* __restrict__ src_token) {
+  __shared__ uint32_t s_cnt[4][kFusedMaxE];
+  __shared__ int s_wave[16][kFusedMaxE];
+  __shared__ int s_off[kFusedMaxE + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int A = T * k, start = blockIdx.x * kGroupChunk;
+  for (int i = tid; i < 4 * kFusedMaxE; i += 1024) (&s_cnt[0][0])[i] = 0u;
+  for (int i = tid; i < 16 * kFusedMaxE; i += 1024) (&s_wave[0][0])[i] = 0;
+  const int a = start + tid;
+  const bool valid = a < A;
+  const int id = valid ? ids[a] : 0;
+  __syncthreads();
+  // ---- all assignments: how many to every expert, and how many of them in front of this workgroup's ----
+  for (int i0 = tid * 4; i0 < A; i0 += 4 * 4096) {   // (four loads of four ids requested together)
+    int4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = i0 + j * 4096;
+      v[j] = i + 3 < A ? *reinterpret_cast<const int4*>(ids + i) : make_int4(-1, -1, -1, -1);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = i0 + j * 4096;
+      const uint32_t one = i < start ? 0x10001u : 1u;   // (start is a multiple of four)
+      int e[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+      if (i < A && i + 3 >= A)   // the last few
+        for (int m = 0; m < A - i; ++m) e[m] = ids[i + m];
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (e[m] >= 0) atomicAdd(&s_cnt[m][e[m]], one);
+    }
+  }
+  // ---- this workgroup's: rank among the wavefront's assignments to the same expert ----
+  uint64_t mask = __ballot(valid);
+#pragma unroll
+  for (int bit = 0; bit < 7; ++bit) {
+    const bool set = (id >> bit) & 1;
+    const uint64_t bal = __ballot(valid && set);
+    mask &= set ? bal : ~bal;
+  }
+  const int rank = __popcll(mask & lanemask_lt(lane));
+  if (valid && rank == 0) s_wave[wave][id] = __popcll(mask);
+  __syncthreads();
+  if (tid < kFusedMaxE) {
+    uint32_t all = 0u;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) all += s_cnt[c][tid];
+    int before = (int)(all >> 16);
+    for (int c = 0; c < 16; ++c) {   // positions of the wavefronts' first assignments, relative to the expert's first row
+      const int v = s_wave[c][tid];
+      s_wave[c][tid] = before;
+      before += v;
+    }
+    int incl = (int)(all & 0xffffu);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
+    }
+    s_off[tid + 1] = incl;   // (within this wavefront's 64 experts; the second 64 get the first 64's total below)
+  }
+  if (tid == 0) s_off[0] = 0;
+  __syncthreads();
+  const int first64 = s_off[64];
+  __syncthreads();
+  if (tid >= 64 && tid < kFusedMaxE) s_off[tid + 1] += first64;
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    if (tid <= E) offsets[tid] = s_off[tid];
+    for (int s = tid; s < S; s += 1024) offsets[E + s + 1] = A + (s + 1) * T;
+  }
+  if (valid) {
+    const int pos = s_off[id] + s_wave[wave][id] + rank;
+    perm[pos] = a;
+    inv_perm[a] = pos;
+    if (src_token) src_token[pos] = a / k;
+  }
+  if (src_token)
+    for (int i = start + tid; i < S * T; i += (int)gridDim.x * kGroupChunk) src_token[A + i] = i % T;
 }
 
 // pass 1: per-block histogram of expert ids
@@ -381,13 +474,13 @@ size_t cq_permute_workspace_bytes(int T, int E, int top_k) {
 cq_status cq_permute_launch(const int32_t* topk_ids, int T, int E, int top_k, int n_shared, int32_t* expert_offsets,
                             int32_t* perm, int32_t* inv_perm, int32_t* src_token, void* workspace, hipStream_t s) {
   const int n_assign = T * top_k;
-  if (n_assign <= 1024 * kGroupMaxChunks && E <= kFusedMaxE) {
-    if (n_assign <= 1024 * 4)
-      hipLaunchKernelGGL(group_kernel<4>, dim3(1), dim3(1024), 0, s, topk_ids, T, E, top_k, n_shared, expert_offsets, perm,
-                         inv_perm, src_token);
-    else
+  if (n_assign <= kGroupMostAssign && E <= kFusedMaxE) {
+    if (n_assign <= 1024 * kGroupMaxChunks)
       hipLaunchKernelGGL(group_kernel<kGroupMaxChunks>, dim3(1), dim3(1024), 0, s, topk_ids, T, E, top_k, n_shared,
                          expert_offsets, perm, inv_perm, src_token);
+    else
+      hipLaunchKernelGGL(group_chunks_kernel, dim3((n_assign + kGroupChunk - 1) / kGroupChunk), dim3(1024), 0, s, topk_ids, T,
+                         E, top_k, n_shared, expert_offsets, perm, inv_perm, src_token);
     return cq_check_launch();
   }
   const int nb = (n_assign + kPermBlock - 1) / kPermBlock;

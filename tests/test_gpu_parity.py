@@ -243,8 +243,10 @@ def test_route_limits(B, T, E, k):
 @pytest.mark.parametrize("T,E,k", [
     (64, 65, 3), (50, 128, 8), (7, 128, 64),        # one workgroup: two experts per lane
     (65, 64, 6), (65, 128, 64), (200, 100, 5),      # top-k over workgroups, then the grouping in one
-    (512, 128, 8), (1024, 128, 8), (4096, 4, 2),    # 4096 and 8192 assignments: the grouping's largest
-    (1025, 128, 8), (1367, 33, 6),                  # ... and just more: the three-pass counting sort
+    (512, 128, 8),                                  # 4096 assignments: the largest grouping in one workgroup
+    (4097, 8, 1), (2049, 100, 3), (1024, 128, 8), (4096, 4, 2), (2048, 128, 8),   # in several, the last one ragged or full
+    (65535, 3, 1), (65536, 3, 1),                   # the most of them, and the counting sort
+    (1025, 128, 8), (1367, 33, 6),
 ])
 def test_route_selection_and_grouping_forms(B, T, E, k):
     """Given logits with many exact ties through every form of top-k and grouping, and shared experts behind them."""
