@@ -89,6 +89,10 @@ size_t cq_rotate_split_workspace_bytes(int T, int H);   // of the launch, withou
 cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, float* XR_out,
                                  void* workspace, hipStream_t s);
 
+// the same for few tokens: parts (1: `out` is X_R) of the partial sums [parts][T][H] that the launch leaves, 0: not taken
+int cq_rotate_few_parts(int T, int H);
+cq_status cq_rotate_few_launch(const float* X, const void* R_split, int T, int H, float* out, hipStream_t s);
+
 // online-Hadamard variant: h' = h H / sqrt(I) per row, then integer codes (int8 and/or bf16 copies) and scales
 bool cq_hadamard_supported(int I);
 cq_status cq_hadamard_quant_launch(const float* Hin, int M, int I, int bits, int8_t* Q, uint16_t* Q16, float* scale,

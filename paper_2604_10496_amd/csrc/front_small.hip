@@ -21,10 +21,10 @@ namespace {
 
 constexpr int kFrontMaxE = 16;    // experts whose logits a token's workgroup forms
 constexpr int kFrontThreads = 1024;
-constexpr int kBatch = 15;        // partial sums 1..15 are requested together with sum 0
 constexpr int kEarlyE = 8;        // experts whose router rows are requested up front
 
-template <int NC>
+// kBatch: partial sums 1..kBatch are requested together with sum 0
+template <int NC, int kBatch>
 __global__ __launch_bounds__(kFrontThreads) void front_small_kernel(
     const float* part, int ksplit, int in_place, int T, int H, float qmax, const float* __restrict__ Wr,
     const float* __restrict__ bias, int E, float* XR, int8_t* __restrict__ Q, uint16_t* __restrict__ Q16,
@@ -140,11 +140,10 @@ cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H,
                                 float* logits, int top_k, int32_t* topk_ids, float* topk_w, hipStream_t s) {
   const float qmax = (float)((1 << (act_bits - 1)) - 1);
   const int in_place = (partials == XR && ksplit == 1) ? 1 : 0;
-  if (H <= 4 * kFrontThreads)
-    hipLaunchKernelGGL(front_small_kernel<1>, dim3(T), dim3(kFrontThreads), 0, s, partials, ksplit, in_place, T, H, qmax,
-                       Wr, bias, E, XR, Q, Q16, scale, logits, top_k, topk_ids, topk_w);
-  else
-    hipLaunchKernelGGL(front_small_kernel<2>, dim3(T), dim3(kFrontThreads), 0, s, partials, ksplit, in_place, T, H, qmax,
-                       Wr, bias, E, XR, Q, Q16, scale, logits, top_k, topk_ids, topk_w);
+  const bool few = ksplit <= 4;   // (the rotation of few tokens: 2 or 4 parts; a part past the end costs a load)
+  auto kern = H <= 4 * kFrontThreads ? (few ? front_small_kernel<1, 3> : front_small_kernel<1, 15>)
+                                     : (few ? front_small_kernel<2, 3> : front_small_kernel<2, 15>);
+  hipLaunchKernelGGL(kern, dim3(T), dim3(kFrontThreads), 0, s, partials, ksplit, in_place, T, H, qmax, Wr, bias, E, XR, Q,
+                     Q16, scale, logits, top_k, topk_ids, topk_w);
   return cq_check_launch();
 }

@@ -60,6 +60,7 @@ struct layer_plan {
   size_t used;     // bytes that the call touches
   size_t rot_at;   // partial sums of the rotation
   int rot_parts;   // K parts of the rotation on the f16 matrix cores; 0: the fp32 kernel
+  bool rot_few;    // ... by the kernel for few tokens
 };
 
 // Batches large enough for the large-tile product get the codes a second time as bf16, so that staging
@@ -123,6 +124,7 @@ void make_plan(const cq_layer* L, int T, layer_plan* plan) {
   if (L->R_split && !L->r_hadamard) raise(o->total, o->Hbuf + cq_align_up(cq_rotate_split_bytes_upto(T, L->H), 256));
   size_t rotation = 0;   // (the Hadamard variant transforms in LDS)
   plan->rot_parts = 0;
+  plan->rot_few = false;
   if (!L->r_hadamard) {
     if (L->R_split) {
       // (a batch that fits the library's own array with the fp32 rotation also fits it with this one, in fewer parts)
@@ -131,9 +133,16 @@ void make_plan(const cq_layer* L, int T, layer_plan* plan) {
       const size_t room = fp32_used <= CQ_STATIC_SCRATCH_BYTES && o->total > CQ_STATIC_SCRATCH_BYTES
                               ? (size_t)CQ_STATIC_SCRATCH_BYTES : o->total;
       plan->rot_parts = cq_rotate_split_parts(T, L->H, room - o->Hbuf);
+      const int few = cq_rotate_few_parts(T, L->H);
+      // (its partial sums are never more than the fp32 kernel's, which every size holds)
+      if (few && cq_rotate_split_partials_bytes(few, T, L->H) <= fp32_rotation) {
+        plan->rot_few = true;
+        plan->rot_parts = few;
+      }
     }
-    rotation = plan->rot_parts ? cq_rotate_split_partials_bytes(plan->rot_parts, T, L->H) + cq_rotate_split_workspace_bytes(T, L->H)
-                               : fp32_rotation;
+    rotation = plan->rot_few ? cq_rotate_split_partials_bytes(plan->rot_parts, T, L->H)
+               : plan->rot_parts ? cq_rotate_split_partials_bytes(plan->rot_parts, T, L->H) + cq_rotate_split_workspace_bytes(T, L->H)
+                                 : fp32_rotation;
   }
   plan->rot_at = off + rotation <= o->total && off + rotation <= CQ_STATIC_SCRATCH_BYTES ? o->scratch : o->Hbuf;
   plan->used = off + scratch;
@@ -197,6 +206,7 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     if (plan.rot_parts) {
       *parts = plan.rot_parts;
       *part = *parts > 1 ? (float*)rot_ws : XR;
+      if (plan.rot_few) return cq_rotate_few_launch(X, L->R_split, T, L->H, *part, hs);
       return cq_rotate_split_launch(X, L->R_split, T, L->H, *parts, *part,
                                     rot_ws + cq_rotate_split_partials_bytes(*parts, T, L->H), hs);
     }

@@ -132,6 +132,10 @@ __device__ __forceinline__ cq_v16f mfma_f16(const cq_v4u a, const cq_v4u b, cq_v
                                                 0, 0);
 }
 
+__device__ __forceinline__ cq_v4f mfma_f16_16(const cq_v4u a, const cq_v4u b, cq_v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(cq_v8f16, a), __builtin_bit_cast(cq_v8f16, b), c, 0, 0, 0);
+}
+
 __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
   // XCD-aware remap of the linear workgroup id (ids go round-robin over the 8 XCDs): XCD x takes a
   // contiguous share of the work, so that neighbours in its L2 share token tiles and columns of R
@@ -324,7 +328,239 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
   }
 }
 
+// ---- few tokens ----------------------------------------------------------------------------------------------------
+// Bound by reading R once.  The fp32 kernel's workgroups read pieces of 1 KiB, 16 KiB apart, and stay at 3.8 TB/s (64 MiB in
+// 17 us, also without its matrix instructions; more loads in flight make it slower); the split copy lies in fragment order,
+// so that a workgroup of one block of 32 columns reads one contiguous run.  Eight wavefronts share its K range (N sub-steps
+// of 16 each), the activations of a wavefront's sub-steps live in its registers, split there: the power of two that a row is
+// divided by is that of its largest entry in the wavefront's own slice of K, which can only be closer.
+// TB: blocks of 32 tokens; 0: up to 16 tokens on the 16x16x32 shape, whose lanes (token l%16, k group l/16) all hold
+// activations of their own (half the loads and conversions).  A pair of fragments becomes its two operands of 16 columns with
+// one lane swap per pair of dwords; lane row g then carries sub-step g%2 of the pair, k group g/2.
+constexpr int kFewWaves = 8;
+struct RotFewArgs {
+  const uint8_t* Rs;
+  const float* X;
+  float* out;       // [parts][T][H], or X_R itself with one part
+  int T, H, parts;
+};
+
+template <int N, int TB_>
+__global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFewArgs p) {
+  constexpr bool HALF = TB_ == 0;
+  constexpr int TB = HALF ? 1 : TB_;
+  constexpr int NX = HALF ? N / 2 : N;  // activation fragments of a lane
+  constexpr int kMost = HALF ? 16 : 8;
+  constexpr int D = N < kMost ? N : kMost;   // sub-steps of R in flight (2 KiB each)
+  extern __shared__ float few_lds[];   // [wavefront][token block][quad of columns][lane] float4
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r32 = lane & 31, g2 = lane >> 5;
+  const int nb = (int)blockIdx.x / p.parts, kz = (int)blockIdx.x - nb * p.parts;
+  const int j0 = (kz * kFewWaves + wave) * N;           // this wavefront's first sub-step
+  const uint4* frag = reinterpret_cast<const uint4*>(p.Rs) + ((size_t)nb * (p.H / 16) + j0) * 128 + lane;
+  uint4 ring[D][2];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    ring[d][0] = frag[(size_t)d * 128];
+    ring[d][1] = frag[(size_t)d * 128 + 64];
+  }
+  // this lane's activations: token r32 of every block, values 8 g2 .. + 7 of every sub-step, as f16 planes
+  // (HALF: token lane%16, of every pair of sub-steps the values 8 (lane/32) .. + 7 of sub-step lane/16%2)
+  cq_v4u xh[TB][NX], xl[TB][NX];
+  const int tcol = HALF ? lane & 15 : r32;
+  const int xoff = HALF ? ((lane >> 4) & 1) * 16 + g2 * 8 : g2 * 8;
+  float pow2[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    const float* x = p.X + (size_t)min(tb * 32 + tcol, p.T - 1) * p.H + (size_t)j0 * 16 + xoff;   // (rows past the end are not stored)
+    constexpr int kApart = HALF ? 32 : 16;
+    float4 v[NX][2];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      v[j][0] = *reinterpret_cast<const float4*>(x + j * kApart);
+      v[j][1] = *reinterpret_cast<const float4*>(x + j * kApart + 4);
+    }
+    float amax = 0.f;
+#pragma unroll
+    for (int j = 0; j < NX; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v[j][h].x), fabsf(v[j][h].y))), fmaxf(fabsf(v[j][h].z), fabsf(v[j][h].w)));
+    amax = fmaxf(amax, __shfl_xor(amax, 32));
+    if constexpr (HALF) amax = fmaxf(amax, __shfl_xor(amax, 16));
+    const uint32_t ebits = __float_as_uint(amax) & 0x7f800000u;
+    pow2[tb] = ebits == 0u ? 1.f : __uint_as_float(ebits);
+    const float inv = ebits == 0x7f800000u ? 1.f : 1.f / pow2[tb];   // exact: a power of two
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      const float a[8] = {v[j][0].x * inv, v[j][0].y * inv, v[j][0].z * inv, v[j][0].w * inv,
+                          v[j][1].x * inv, v[j][1].y * inv, v[j][1].z * inv, v[j][1].w * inv};
+      uint32_t hi[4], lo[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float h0 = f16_value(a[2 * i]), h1 = f16_value(a[2 * i + 1]);
+        hi[i] = f16_bits(h0) | (f16_bits(h1) << 16);
+        lo[i] = f16_bits((a[2 * i] - h0) * kLoScale) | (f16_bits((a[2 * i + 1] - h1) * kLoScale) << 16);
+      }
+      xh[tb][j] = cq_v4u{hi[0], hi[1], hi[2], hi[3]};
+      xl[tb][j] = cq_v4u{lo[0], lo[1], lo[2], lo[3]};
+    }
+  }
+  float4* lds = reinterpret_cast<float4*>(few_lds);
+  if constexpr (HALF) {
+    cq_v4f acc[2];   // columns 0..15 and 16..31
+    acc[0] = acc[1] = cq_v4f{0.f, 0.f, 0.f, 0.f};
+    typedef __attribute__((ext_vector_type(2))) unsigned pair_u32;
+#pragma unroll
+    for (int j = 0; j < N; j += 2) {
+      cq_v4u r[2][2];   // [plane][column half]
+#pragma unroll
+      for (int pl = 0; pl < 2; ++pl) {
+        const cq_v4u f0 = __builtin_bit_cast(cq_v4u, ring[j % D][pl]), f1 = __builtin_bit_cast(cq_v4u, ring[(j + 1) % D][pl]);
+        const pair_u32 w0 = __builtin_amdgcn_permlane16_swap(f0[0], f1[0], false, false);
+        const pair_u32 w1 = __builtin_amdgcn_permlane16_swap(f0[1], f1[1], false, false);
+        const pair_u32 w2 = __builtin_amdgcn_permlane16_swap(f0[2], f1[2], false, false);
+        const pair_u32 w3 = __builtin_amdgcn_permlane16_swap(f0[3], f1[3], false, false);
+        r[pl][0] = cq_v4u{w0[0], w1[0], w2[0], w3[0]};
+        r[pl][1] = cq_v4u{w0[1], w1[1], w2[1], w3[1]};
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (j + i + D < N) {
+          ring[(j + i) % D][0] = frag[(size_t)(j + i + D) * 128];
+          ring[(j + i) % D][1] = frag[(size_t)(j + i + D) * 128 + 64];
+        }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        acc[h] = mfma_f16_16(times_2048(r[0][h]), xh[0][j / 2], acc[h]);
+        acc[h] = mfma_f16_16(r[1][h], xh[0][j / 2], acc[h]);
+        acc[h] = mfma_f16_16(r[0][h], xl[0][j / 2], acc[h]);
+      }
+    }
+    // MFMA 16x16 output: register v of a lane holds column (of R) 4*(lane/16) + v, token lane%16
+    const bool bad = __float_as_uint(pow2[0]) == 0x7f800000u;   // (an infinite entry: an infinite row, as in fp32)
+    const float sc = pow2[0] * kLoUnscale;
+    auto val = [&](float a) { return bad ? pow2[0] : sc * a; };
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      lds[(wave * 2 + h) * 64 + lane] = make_float4(val(acc[h][0]), val(acc[h][1]), val(acc[h][2]), val(acc[h][3]));
+    __syncthreads();
+    if (tid >= 128) return;
+    float4 s = lds[tid];
+#pragma unroll
+    for (int w = 1; w < kFewWaves; ++w) {
+      const float4 o = lds[w * 128 + tid];
+      s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
+    }
+    if (tcol < p.T)
+      *reinterpret_cast<float4*>(p.out + ((size_t)kz * p.T + tcol) * p.H + nb * 32 + wave * 16 + (lane >> 4) * 4) = s;
+    return;
+  }
+  cq_v16f acc[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[tb][i] = 0.f;
+#pragma unroll
+  for (int j = 0; j < N && !HALF; ++j) {
+    const cq_v4u rh = __builtin_bit_cast(cq_v4u, ring[j % D][0]), rl = __builtin_bit_cast(cq_v4u, ring[j % D][1]);
+    if (j + D < N) {
+      ring[j % D][0] = frag[(size_t)(j + D) * 128];
+      ring[j % D][1] = frag[(size_t)(j + D) * 128 + 64];
+    }
+    const cq_v4u rs = times_2048(rh);
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      acc[tb] = mfma_f16(rs, xh[tb][j % NX], acc[tb]);
+      acc[tb] = mfma_f16(rl, xh[tb][j % NX], acc[tb]);
+      acc[tb] = mfma_f16(rh, xl[tb][j % NX], acc[tb]);
+    }
+  }
+  // MFMA 32x32 output: register v of a lane holds column (of R) 8*(v/4) + 4*(lane/32) + v%4, token lane%32
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    const bool bad = __float_as_uint(pow2[tb]) == 0x7f800000u;   // (an infinite entry: an infinite row, as in fp32)
+    const float sc = pow2[tb] * kLoUnscale;
+    auto val = [&](float a) { return bad ? pow2[tb] : sc * a; };
+#pragma unroll
+    for (int vb = 0; vb < 4; ++vb)
+      lds[((wave * TB + tb) * 4 + vb) * 64 + lane] =
+          make_float4(val(acc[tb][4 * vb]), val(acc[tb][4 * vb + 1]), val(acc[tb][4 * vb + 2]), val(acc[tb][4 * vb + 3]));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i0 = 0; i0 < TB * 256; i0 += 64 * kFewWaves) {   // the wavefronts' sums, in their order
+    const int i = i0 + tid;
+    if (i >= TB * 256) break;
+    const int tok = (i >> 8) * 32 + r32, vb = (i >> 6) & 3;
+    float4 s = lds[i];
+#pragma unroll
+    for (int w = 1; w < kFewWaves; ++w) {
+      const float4 o = lds[w * TB * 256 + i];
+      s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
+    }
+    if (tok < p.T)
+      *reinterpret_cast<float4*>(p.out + ((size_t)kz * p.T + tok) * p.H + nb * 32 + vb * 8 + g2 * 4) = s;
+  }
+}
+
+template <int N, int TB>
+cq_status launch_few(const RotFewArgs& a, hipStream_t s) {
+  constexpr int lds = kFewWaves * (TB == 0 ? 2048 : TB * 4096);
+  static std::atomic<bool> configured{false};
+  const cq_status st = cq_configure_lds(rot_few_kernel<N, TB>, lds, configured, false);
+  if (st != CQ_OK) return st;
+  hipLaunchKernelGGL((rot_few_kernel<N, TB>), dim3((unsigned)(a.H / 32 * a.parts)), dim3(64 * kFewWaves), lds, s, a);
+  return cq_check_launch();
+}
+
+template <int N>
+cq_status launch_few_tokens(const RotFewArgs& a, hipStream_t s) {
+  if (a.T <= 16) return launch_few<N, 0>(a, s);
+  if (a.T <= 32) return launch_few<N, 1>(a, s);
+  if constexpr (N <= 8) {
+    if (a.T <= 64) return launch_few<N, 2>(a, s);
+    if constexpr (N <= 4) {
+      if (a.T <= 128) return launch_few<N, 4>(a, s);
+    }
+  }
+  return CQ_ERR_UNSUPPORTED;
+}
+
 }  // namespace
+
+// Sub-steps of 16 k per wavefront of the kernel for few tokens, 0: not taken.  Layer of 8 small experts, fp32 kernel / this
+// one, us at 1, 16 and 32 tokens: H = 1024 26.4 / 25.7, 27.4 / 26.9, 29.9 / 29.7; 2048 30.0 / 28.0, 32.3 / 30.0, 35.0 / 32.5;
+// 3072 38.7 / 36.0, 43.4 / 42.0, 50.0 / 47.4; 4096 45.6 / 41.1, 49.7 / 46.0, 53.8 / 51.2; 8192 86 / 86, 91 / 95, 116 / 123.
+// 33 and 64 tokens: H = 1024 31.1 / 32.2, 34.1 / 35.2; 1536 35.5 / 34.2, 40.2 / 36.8; 2560 51.4 / 48.4, 59.6 / 54.6; 4096
+// 170.8 / 171.2 at 40 tokens of the Mixtral shape.  128 tokens: 1536 (144 workgroups) 50.3 / 52.5, 2048 (256) 58.6 / 56.5,
+// 2560 (400) 71.3 / 72.9.  Whole layers at 1 and 16 tokens: Mixtral shape 72.8 / 67.5, 149.7 / 144.0; DeepSeek-V2-Lite shape
+// 46.9 / 42.9, 85.3 / 80.0.
+// Error of X_R against float64 over those widths and batches, 2-norm (and largest, of the row's maximum): fp32 kernel 1.5e-7
+// .. 5.0e-7 (2.9e-7 .. 1.6e-6), this one 1.4e-7 .. 2.3e-7 (2.5e-7 .. 5.9e-7), and smaller at each of them.
+static int few_steps(int T, int H) {
+  if (H % 512 != 0 || H < 1024 || H > 4096 || T > 128) return 0;
+  if (T > 32 && (H < 1536 || H >= 3072)) return 0;
+  const int blocks = H / 32;
+  if (T > 64 && (blocks * (H / 512) < 192 || blocks * (H / 512) > 256)) return 0;   // (a round of the chip)
+  const int most = T <= 32 ? 16 : T <= 64 ? 8 : 4;   // (registers: activations of T tokens x 16 n values)
+  for (int n = most; n > 4; n /= 2)
+    if (H % (16 * kFewWaves * n) == 0 && blocks * (H / (16 * kFewWaves * n)) >= 192) return n;
+  return 4;
+}
+int cq_rotate_few_parts(int T, int H) {
+  const int n = few_steps(T, H);
+  return n ? H / (16 * kFewWaves * n) : 0;
+}
+cq_status cq_rotate_few_launch(const float* X, const void* R_split, int T, int H, float* out, hipStream_t s) {
+  const RotFewArgs a = {(const uint8_t*)R_split, X, out, T, H, cq_rotate_few_parts(T, H)};
+  switch (few_steps(T, H)) {
+    case 16: return launch_few_tokens<16>(a, s);
+    case 8: return launch_few_tokens<8>(a, s);
+    case 4: return launch_few_tokens<4>(a, s);
+    default: return CQ_ERR_UNSUPPORTED;
+  }
+}
 
 bool cq_rotate_split_supported(int T, int H) {
   // whole column tiles and K steps in fours; enough tokens to fill tiles; 32-bit byte offsets into a plane

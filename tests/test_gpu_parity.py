@@ -152,6 +152,39 @@ def test_rotate_quant_identity_and_grid(B):
     assert not z["Q"].cpu().numpy().any() and np.array_equal(z["scale"].cpu().numpy(), np.ones(3, np.float32))
 
 
+@pytest.mark.parametrize("H,batches", [(1024, [1, 16, 17, 32, 33]), (1536, [5, 16, 31, 64]), (2048, [1, 17, 40, 65, 128]),
+                                       (3584, [16, 32]), (4096, [1, 15, 17, 32, 33])])
+def test_rotation_of_few_tokens(B, H, batches):
+    """The layer's rotation from the split copy of R at decode-sized batches, around the numbers of tokens and the widths
+    where its kernels change: every row within 4e-6 of its maximum (two f16 planes: 2^-22 of a product, and fp32 sums),
+    rows of any scale; an all-zero row stays zero, an infinite entry makes its own row infinite and no other."""
+    import torch
+    rng = np.random.default_rng(H)
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], H=H, I=64, T=1, outlier_channels=())
+    R = torch.linalg.qr(torch.from_numpy(rng.standard_normal((H, H)).astype(np.float32)))[0].contiguous()
+    cb = [B.DeviceCodebook(*_rand_weights(rng, cfg.E, N, K), prepack=True) for N, K in ((128, H), (H, 64))]
+    layer = B.DeviceLayer(cfg, R, torch.from_numpy(rng.standard_normal((cfg.E, H)).astype(np.float32)) / H ** 0.5, None, *cb)
+    R64 = R.double().cuda()
+    for T in batches:
+        X = rng.standard_normal((T, H)).astype(np.float32)
+        X[:, 3] *= 100.0
+        X[T // 2] *= np.float32(3e4)
+        X[T - 1] *= np.float32(1e-6)
+        if T > 4:
+            X[1] = 0.0
+            X[2, H // 2] = np.inf
+        B.cq_moe_forward(layer, _dev(X))
+        torch.cuda.synchronize()
+        XR = B.moe_intermediates(layer, T)["XR"].double()
+        Xd = _dev(X).double()
+        ok = torch.isfinite(Xd).all(dim=1)
+        ref = Xd[ok] @ R64
+        err = ((XR[ok] - ref).abs().amax(dim=1) / ref.abs().amax(dim=1).clamp_min(1e-300)).max().item()
+        _say(f"rotation of few tokens H={H} T={T}: {err:.2e}")
+        assert err <= 4e-6
+        assert not torch.isfinite(XR[~ok]).any()
+
+
 @pytest.mark.parametrize("H", [64, 1024, 1088, 2048, 4096, 4160, 8192, 8256])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_quantize_rows_in_registers(B, H, bits):
