@@ -78,6 +78,12 @@ cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H,
                                 const float* bias, int E, float* XR, int8_t* Q, uint16_t* Q16, float* scale,
                                 float* logits, int top_k, int32_t* topk_ids, float* topk_w, hipStream_t s);
 
+// Quantization, router logits and top-k in one launch for any batch (Q NULL: the rows are quantized already).
+bool cq_front_rows_supported(int T, int H, int E, int top_k);
+cq_status cq_front_rows_launch(const float* partials, int ksplit, int T, int H, int act_bits, const float* Wr,
+                               const float* bias, int E, float* XR, int8_t* Q, uint16_t* Q16, float* scale,
+                               float* logits, int top_k, int32_t* topk_ids, float* topk_w, hipStream_t s);
+
 // X_R = X R on f16 matrix cores from a split copy of R (cq_rotation_split), accurate to about fp32
 bool cq_rotate_split_supported(int T, int H);
 // K parts of the layer's rotation where it takes this kernel and has `available` bytes of device memory, 0: the fp32 kernel

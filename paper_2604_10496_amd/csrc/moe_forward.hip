@@ -225,8 +225,16 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     st = cq_hadamard_quant_launch(X, T, L->H, L->act_bits, Q, Q16, scale, XR, hs);
     if (st != CQ_OK) return st;
     if (!mark(1)) return CQ_ERR_HIP;
-    st = cq_route_permute(XR, L->Wr, L->bias, nullptr, T, L->H, L->E, L->top_k, L->S, logits, ids, tw, offsets, perm,
-                          inv_perm, src_token, scratch, scratch_bytes, stream);
+    // (the rows are quantized: logits and top-k in one launch; 32 tokens 68.4 us per layer of the Qwen3 shape without, 70.8
+    // with it, 64 tokens 84.4 / 80.2, 512 tokens 144.2 / 142.8)
+    if (T > 32 && cq_front_rows_supported(T, L->H, L->E, L->top_k)) {
+      st = cq_front_rows_launch(XR, 1, T, L->H, L->act_bits, L->Wr, L->bias, L->E, XR, nullptr, nullptr, nullptr, logits,
+                                L->top_k, ids, tw, hs);
+      if (st == CQ_OK) st = cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
+    } else {
+      st = cq_route_permute(XR, L->Wr, L->bias, nullptr, T, L->H, L->E, L->top_k, L->S, logits, ids, tw, offsets, perm,
+                            inv_perm, src_token, scratch, scratch_bytes, stream);
+    }
     if (st != CQ_OK) return st;
     if (!mark(2)) return CQ_ERR_HIP;
   } else if (cq_front_small_supported(T, L->H, L->E, L->top_k)) {
@@ -248,6 +256,18 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
       st = cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
       if (st != CQ_OK) return st;
     }
+    if (!mark(2)) return CQ_ERR_HIP;
+  } else if (cq_front_rows_supported(T, L->H, L->E, L->top_k)) {
+    // larger batches: the rotation; quantization, logits and top-k in one launch; the grouping (stage boundary as above)
+    int parts;
+    float* part;
+    st = rotate(&parts, &part);
+    if (st != CQ_OK) return st;
+    if (!mark(1)) return CQ_ERR_HIP;
+    st = cq_front_rows_launch(part, parts, T, L->H, L->act_bits, L->Wr, L->bias, L->E, XR, Q, Q16, scale, logits, L->top_k,
+                              ids, tw, hs);
+    if (st == CQ_OK) st = cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
+    if (st != CQ_OK) return st;
     if (!mark(2)) return CQ_ERR_HIP;
   } else {
     if (plan.rot_parts) {

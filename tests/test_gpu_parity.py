@@ -1321,6 +1321,19 @@ def test_layer_grouping_folded_into_gate_up(B, name, over):
     _check_layer(B, cfg, label=f"{name}-folded")
 
 
+@pytest.mark.parametrize("over", [
+    dict(E=32, H=1024, I=64, T=32, top_k=4),                            # one token per workgroup, the smallest batch
+    dict(E=128, H=256, I=64, T=256, top_k=8, zipf_s=1.1),               # ... and the largest; two experts per lane, a bias
+    dict(E=64, H=512, I=64, T=257, top_k=6, S=1),                       # two tokens, the last one alone
+    dict(E=100, H=1088, I=64, T=511, top_k=3, act_bits=4),              # wavefronts without a second expert; a ragged row
+    dict(E=9, H=4096, I=64, T=512, top_k=2),                            # the largest batch and width
+    dict(E=64, H=512, I=64, T=33, top_k=6, r_hadamard=True),            # rows quantized before: logits and top-k only
+])
+def test_layer_front_rows(B, over):
+    """Quantization, router logits and top-k in one launch (32 to 512 tokens): around its numbers of tokens and experts."""
+    _check_layer(B, synth.small_variant(synth.CONFIGS["mixtral_decode"], **over), label="front rows")
+
+
 @pytest.mark.parametrize("over,rows", [
     # gate/up in passes of 32 rows (gathered rows, row scales, the gated epilogue)
     (dict(H=4096, I=128, T=45, zipf_s=2.0), 33), (dict(H=4096, I=128, T=77, zipf_s=1.5), 65),   # (from 64 tokens: split rotation)
