@@ -158,19 +158,23 @@ __global__ __launch_bounds__(1024) void route_fused_kernel(const float* logits_i
   const int rank = __popcll(mask & lanemask_lt(lane));
   if (valid && rank == 0) s_chunk[wave][id] = __popcll(mask);
   __syncthreads();
-  if (tid < E) {
+  if (tid < kFusedMaxE) {
     int tot = 0;
-    for (int c = 0; c < 16; ++c) {  // exclusive prefix over chunks, in place
-      const int v = s_chunk[c][tid];
-      s_chunk[c][tid] = tot;
-      tot += v;
-    }
-    s_off[tid + 1] = tot;
+    if (tid < E)
+      for (int c = 0; c < 16; ++c) {  // exclusive prefix over chunks, in place
+        const int v = s_chunk[c][tid];
+        s_chunk[c][tid] = tot;
+        tot += v;
+      }
+    // inclusive sum over the wavefront's 64 experts (the second 64 get the first 64's total below; one thread that walked
+    // over all of them cost the layer 1 us at 64 experts and 2 at 128)
+    s_off[tid + 1] = wave_scan(tot);
   }
   if (tid == 0) s_off[0] = 0;
   __syncthreads();
-  if (tid == 0)
-    for (int e = 0; e < E; ++e) s_off[e + 1] += s_off[e];
+  const int first64 = s_off[64];
+  __syncthreads();
+  if (tid >= 64 && tid < kFusedMaxE) s_off[tid + 1] += first64;
   __syncthreads();
   if (tid <= E) offsets[tid] = s_off[tid];
   for (int s = tid; s < S; s += 1024) offsets[E + s + 1] = A + (s + 1) * T;
