@@ -10,7 +10,8 @@
 //     of register-resident byte tables (two 8-entry halves; a third perm, steered by bit 3 of the
 //     index, picks between them), one or two more perm levels interleave the bytes into bf16/f16 pairs.
 //     About 1.4 ALU operations per MFMA at 256 tokens, mostly hidden behind the matrix pipe (with two wavefronts on a
-//     SIMD v_perm_b32 was measured at 4.8 clocks, plain logic and shifts at 2.6: 21 weights per clock and compute unit);
+//     SIMD v_perm_b32 and the other three-operand operations take 4.6 clocks, two-operand ones 4.1, an MFMA about 10 of the
+//     issue beside them: 184 operations per step and wavefront are what half tiles of up to 64 tokens wait for);
 //     With block-wise tables (one per group of g weights along K, g a multiple of 512) the two tables are
 //     replaced every g/64 steps; the raw tables of the next group are requested one group ahead;
 //   * LDS holds only the activation tiles.  They arrive by direct global->LDS loads (no staging

@@ -520,9 +520,6 @@ cq_status launch_few_tokens(const RotFewArgs& a, hipStream_t s) {
   if (a.T <= 32) return launch_few<N, 1>(a, s);
   if constexpr (N <= 8) {
     if (a.T <= 64) return launch_few<N, 2>(a, s);
-    if constexpr (N <= 4) {
-      if (a.T <= 128) return launch_few<N, 4>(a, s);
-    }
   }
   return CQ_ERR_UNSUPPORTED;
 }
@@ -533,17 +530,15 @@ cq_status launch_few_tokens(const RotFewArgs& a, hipStream_t s) {
 // one, us at 1, 16 and 32 tokens: H = 1024 26.4 / 25.7, 27.4 / 26.9, 29.9 / 29.7; 2048 30.0 / 28.0, 32.3 / 30.0, 35.0 / 32.5;
 // 3072 38.7 / 36.0, 43.4 / 42.0, 50.0 / 47.4; 4096 45.6 / 41.1, 49.7 / 46.0, 53.8 / 51.2; 8192 86 / 86, 91 / 95, 116 / 123.
 // 33 and 64 tokens: H = 1024 31.1 / 32.2, 34.1 / 35.2; 1536 35.5 / 34.2, 40.2 / 36.8; 2560 51.4 / 48.4, 59.6 / 54.6; 4096
-// 170.8 / 171.2 at 40 tokens of the Mixtral shape.  128 tokens: 1536 (144 workgroups) 50.3 / 52.5, 2048 (256) 58.6 / 56.5,
-// 2560 (400) 71.3 / 72.9.  Whole layers at 1 and 16 tokens: Mixtral shape 72.8 / 67.5, 149.7 / 144.0; DeepSeek-V2-Lite shape
+// 170.8 / 171.2 at 40 tokens of the Mixtral shape.  Whole layers at 1 and 16 tokens: Mixtral shape 72.8 / 67.5, 149.7 / 144.0; DeepSeek-V2-Lite shape
 // 46.9 / 42.9, 85.3 / 80.0.
 // Error of X_R against float64 over those widths and batches, 2-norm (and largest, of the row's maximum): fp32 kernel 1.5e-7
 // .. 5.0e-7 (2.9e-7 .. 1.6e-6), this one 1.4e-7 .. 2.3e-7 (2.5e-7 .. 5.9e-7), and smaller at each of them.
 static int few_steps(int T, int H) {
-  if (H % 512 != 0 || H < 1024 || H > 4096 || T > 128) return 0;
+  if (H % 512 != 0 || H < 1024 || H > 4096 || T > 64) return 0;
   if (T > 32 && (H < 1536 || H >= 3072)) return 0;
   const int blocks = H / 32;
-  if (T > 64 && (blocks * (H / 512) < 192 || blocks * (H / 512) > 256)) return 0;   // (a round of the chip)
-  const int most = T <= 32 ? 16 : T <= 64 ? 8 : 4;   // (registers: activations of T tokens x 16 n values)
+  const int most = T <= 32 ? 16 : 8;   // (registers: activations of T tokens x 16 n values)
   for (int n = most; n > 4; n /= 2)
     if (H % (16 * kFewWaves * n) == 0 && blocks * (H / (16 * kFewWaves * n)) >= 192) return n;
   return 4;
