@@ -337,6 +337,9 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
 // TB: blocks of 32 tokens; 0: up to 16 tokens on the 16x16x32 shape, whose lanes (token l%16, k group l/16) all hold
 // activations of their own (half the loads and conversions).  A pair of fragments becomes its two operands of 16 columns with
 // one lane swap per pair of dwords; lane row g then carries sub-step g%2 of the pair, k group g/2.
+// Xh Rh has an accumulator of its own and the two small products share another, so that the large one is rounded once per
+// step and not three times: together with sums over the wavefronts in pairs the error of X_R falls from 2.1e-7 to 1.5e-7 at
+// H = 4096 and from 1.5e-7 to 1.2e-7 at H = 1024, at the same time per call.
 constexpr int kFewWaves = 8;
 struct RotFewArgs {
   const uint8_t* Rs;
@@ -344,6 +347,21 @@ struct RotFewArgs {
   float* out;       // [parts][T][H], or X_R itself with one part
   int T, H, parts;
 };
+
+// the wavefronts' sums, `apart` entries from each other, in pairs (one after the other, the eight roundings were a third of
+// the error; in float64 the layer took 0.2 us longer and the error was 4 % smaller)
+__device__ __forceinline__ float4 few_sum(const float4* lds, int apart) {
+  float4 v[kFewWaves];
+#pragma unroll
+  for (int w = 0; w < kFewWaves; ++w) v[w] = lds[w * apart];
+#pragma unroll
+  for (int d = 1; d < kFewWaves; d *= 2)
+#pragma unroll
+    for (int w = 0; w < kFewWaves; w += 2 * d) {
+      v[w].x += v[w + d].x; v[w].y += v[w + d].y; v[w].z += v[w + d].z; v[w].w += v[w + d].w;
+    }
+  return v[0];
+}
 
 template <int N, int TB_>
 __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFewArgs p) {
@@ -408,8 +426,8 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
   }
   float4* lds = reinterpret_cast<float4*>(few_lds);
   if constexpr (HALF) {
-    cq_v4f acc[2];   // columns 0..15 and 16..31
-    acc[0] = acc[1] = cq_v4f{0.f, 0.f, 0.f, 0.f};
+    cq_v4f acc[2], low[2];   // columns 0..15 and 16..31
+    acc[0] = acc[1] = low[0] = low[1] = cq_v4f{0.f, 0.f, 0.f, 0.f};
     typedef __attribute__((ext_vector_type(2))) unsigned pair_u32;
 #pragma unroll
     for (int j = 0; j < N; j += 2) {
@@ -432,35 +450,30 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
         }
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        acc[h] = mfma_f16_16(times_2048(r[0][h]), xh[0][j / 2], acc[h]);
-        acc[h] = mfma_f16_16(r[1][h], xh[0][j / 2], acc[h]);
-        acc[h] = mfma_f16_16(r[0][h], xl[0][j / 2], acc[h]);
+        acc[h] = mfma_f16_16(r[0][h], xh[0][j / 2], acc[h]);
+        low[h] = mfma_f16_16(r[1][h], xh[0][j / 2], low[h]);
+        low[h] = mfma_f16_16(r[0][h], xl[0][j / 2], low[h]);
       }
     }
     // MFMA 16x16 output: register v of a lane holds column (of R) 4*(lane/16) + v, token lane%16
     const bool bad = __float_as_uint(pow2[0]) == 0x7f800000u;   // (an infinite entry: an infinite row, as in fp32)
-    const float sc = pow2[0] * kLoUnscale;
-    auto val = [&](float a) { return bad ? pow2[0] : sc * a; };
+    auto val = [&](float a, float l) { return bad ? pow2[0] : pow2[0] * fmaf(l, kLoUnscale, a); };
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      lds[(wave * 2 + h) * 64 + lane] = make_float4(val(acc[h][0]), val(acc[h][1]), val(acc[h][2]), val(acc[h][3]));
+      lds[(wave * 2 + h) * 64 + lane] = make_float4(val(acc[h][0], low[h][0]), val(acc[h][1], low[h][1]),
+                                                    val(acc[h][2], low[h][2]), val(acc[h][3], low[h][3]));
     __syncthreads();
     if (tid >= 128) return;
-    float4 s = lds[tid];
-#pragma unroll
-    for (int w = 1; w < kFewWaves; ++w) {
-      const float4 o = lds[w * 128 + tid];
-      s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
-    }
     if (tcol < p.T)
-      *reinterpret_cast<float4*>(p.out + ((size_t)kz * p.T + tcol) * p.H + nb * 32 + wave * 16 + (lane >> 4) * 4) = s;
+      *reinterpret_cast<float4*>(p.out + ((size_t)kz * p.T + tcol) * p.H + nb * 32 + wave * 16 + (lane >> 4) * 4) =
+          few_sum(lds + tid, 128);
     return;
   }
-  cq_v16f acc[TB];
+  cq_v16f acc[TB], low[TB];
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[tb][i] = 0.f;
+    for (int i = 0; i < 16; ++i) acc[tb][i] = low[tb][i] = 0.f;
 #pragma unroll
   for (int j = 0; j < N && !HALF; ++j) {
     const cq_v4u rh = __builtin_bit_cast(cq_v4u, ring[j % D][0]), rl = __builtin_bit_cast(cq_v4u, ring[j % D][1]);
@@ -468,24 +481,21 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
       ring[j % D][0] = frag[(size_t)(j + D) * 128];
       ring[j % D][1] = frag[(size_t)(j + D) * 128 + 64];
     }
-    const cq_v4u rs = times_2048(rh);
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
-      acc[tb] = mfma_f16(rs, xh[tb][j % NX], acc[tb]);
-      acc[tb] = mfma_f16(rl, xh[tb][j % NX], acc[tb]);
-      acc[tb] = mfma_f16(rh, xl[tb][j % NX], acc[tb]);
+      acc[tb] = mfma_f16(rh, xh[tb][j % NX], acc[tb]);
+      low[tb] = mfma_f16(rl, xh[tb][j % NX], low[tb]);
+      low[tb] = mfma_f16(rh, xl[tb][j % NX], low[tb]);
     }
   }
   // MFMA 32x32 output: register v of a lane holds column (of R) 8*(v/4) + 4*(lane/32) + v%4, token lane%32
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb) {
     const bool bad = __float_as_uint(pow2[tb]) == 0x7f800000u;   // (an infinite entry: an infinite row, as in fp32)
-    const float sc = pow2[tb] * kLoUnscale;
-    auto val = [&](float a) { return bad ? pow2[tb] : sc * a; };
+    auto val = [&](int i) { return bad ? pow2[tb] : pow2[tb] * fmaf(low[tb][i], kLoUnscale, acc[tb][i]); };
 #pragma unroll
     for (int vb = 0; vb < 4; ++vb)
-      lds[((wave * TB + tb) * 4 + vb) * 64 + lane] =
-          make_float4(val(acc[tb][4 * vb]), val(acc[tb][4 * vb + 1]), val(acc[tb][4 * vb + 2]), val(acc[tb][4 * vb + 3]));
+      lds[((wave * TB + tb) * 4 + vb) * 64 + lane] = make_float4(val(4 * vb), val(4 * vb + 1), val(4 * vb + 2), val(4 * vb + 3));
   }
   __syncthreads();
 #pragma unroll
@@ -493,14 +503,9 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
     const int i = i0 + tid;
     if (i >= TB * 256) break;
     const int tok = (i >> 8) * 32 + r32, vb = (i >> 6) & 3;
-    float4 s = lds[i];
-#pragma unroll
-    for (int w = 1; w < kFewWaves; ++w) {
-      const float4 o = lds[w * TB * 256 + i];
-      s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
-    }
     if (tok < p.T)
-      *reinterpret_cast<float4*>(p.out + ((size_t)kz * p.T + tok) * p.H + nb * 32 + vb * 8 + g2 * 4) = s;
+      *reinterpret_cast<float4*>(p.out + ((size_t)kz * p.T + tok) * p.H + nb * 32 + vb * 8 + g2 * 4) =
+          few_sum(lds + i, TB * 256);
   }
 }
 
@@ -518,9 +523,7 @@ template <int N>
 cq_status launch_few_tokens(const RotFewArgs& a, hipStream_t s) {
   if (a.T <= 16) return launch_few<N, 0>(a, s);
   if (a.T <= 32) return launch_few<N, 1>(a, s);
-  if constexpr (N <= 8) {
-    if (a.T <= 64) return launch_few<N, 2>(a, s);
-  }
+  if constexpr (N == 4) return launch_few<N, 2>(a, s);   // (more tokens: few_steps gives 4)
   return CQ_ERR_UNSUPPORTED;
 }
 
@@ -532,14 +535,16 @@ cq_status launch_few_tokens(const RotFewArgs& a, hipStream_t s) {
 // 33 and 64 tokens: H = 1024 31.1 / 32.2, 34.1 / 35.2; 1536 35.5 / 34.2, 40.2 / 36.8; 2560 51.4 / 48.4, 59.6 / 54.6; 4096
 // 170.8 / 171.2 at 40 tokens of the Mixtral shape.  Whole layers at 1 and 16 tokens: Mixtral shape 72.8 / 67.5, 149.7 / 144.0; DeepSeek-V2-Lite shape
 // 46.9 / 42.9, 85.3 / 80.0.
-// Error of X_R against float64 over those widths and batches, 2-norm (and largest, of the row's maximum): fp32 kernel 1.5e-7
-// .. 5.0e-7 (2.9e-7 .. 1.6e-6), this one 1.4e-7 .. 2.3e-7 (2.5e-7 .. 5.9e-7), and smaller at each of them.
+// Error of X_R against float64, 2-norm (and largest, of the row's maximum), fp32 kernel / this one: H = 1024 1.6e-7 / 1.2e-7
+// (6.4e-7 / 4.0e-7), 2048 2.2e-7 .. 2.9e-7 / 1.2e-7 (1.1e-6 / 4.3e-7), 3072 2.5e-7 .. 3.2e-7 / 1.3e-7 (1.6e-6 / 4.0e-7), 4096
+// 2.9e-7 .. 4.2e-7 / 1.5e-7 (1.5e-6 / 5.0e-7), and smaller at every width and batch.  8-bit codes that lie on the other side
+// of a rounding tie than float64's, over 49 million of them at all widths: 445 / 213.  Which code of which call that is
+// depends on the inputs: a single call can be further from float64 on either path.
 static int few_steps(int T, int H) {
   if (H % 512 != 0 || H < 1024 || H > 4096 || T > 64) return 0;
-  if (T > 32 && (H < 1536 || H >= 3072)) return 0;
+  if (T > 32) return H >= 1536 && H < 3072 ? 4 : 0;   // (a wavefront holds the activations of T tokens x 16 n values)
   const int blocks = H / 32;
-  const int most = T <= 32 ? 16 : 8;   // (registers: activations of T tokens x 16 n values)
-  for (int n = most; n > 4; n /= 2)
+  for (int n = 16; n > 4; n /= 2)
     if (H % (16 * kFewWaves * n) == 0 && blocks * (H / (16 * kFewWaves * n)) >= 192) return n;
   return 4;
 }

@@ -185,6 +185,39 @@ def test_rotation_of_few_tokens(B, H, batches):
         assert not torch.isfinite(XR[~ok]).any()
 
 
+@pytest.mark.parametrize("H,batches", [(1024, [1, 32]), (1536, [16, 64]), (2048, [1, 16, 33]), (3072, [16, 32]),
+                                       (4096, [1, 16, 17, 32])])
+def test_rotation_of_few_tokens_is_no_less_accurate(B, H, batches):
+    """X_R from the split copy of R at decode-sized batches against float64, in the 2-norm over eight draws: no further off
+    than the fp32 kernel on the same rows, and within 1.7e-7.  The bound: with u = 2^-24 and roundings that are independent
+    (u / sqrt(3) each, of the partial sum they round), a wavefront's at most 16 accumulations of the large product give
+    u sqrt(17 / 2 / 3), three levels of pairs and at most 7 parts of K together u sqrt(3 + 4) / sqrt(3), and the two operands
+    in two planes 2^-23 / sqrt(3) / sqrt(2): 1.0e-7, 0.9e-7 and 0.5e-7, 1.4e-7 in all; a fifth is left for the draw."""
+    import torch
+    rng = np.random.default_rng(H + 1)
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], H=H, I=64, T=1, outlier_channels=())
+    R = torch.linalg.qr(torch.from_numpy(rng.standard_normal((H, H))).cuda())[0].float().contiguous()
+    cb = [B.DeviceCodebook(*_rand_weights(rng, cfg.E, N, K), prepack=True) for N, K in ((128, H), (H, 64))]
+    layer = B.DeviceLayer(cfg, R, torch.from_numpy(rng.standard_normal((cfg.E, H)).astype(np.float32)) / H ** 0.5, None, *cb)
+    split = layer.R_split
+    for T in batches:
+        err = {True: [], False: []}
+        for _ in range(8):
+            X = rng.standard_normal((T, H)).astype(np.float32)
+            X[:, rng.permutation(H)[:8]] *= 100.0
+            X = _dev(X)
+            ref = X.double() @ R.double()
+            for use in (True, False):
+                layer.R_split, layer._ws = (split if use else None), None
+                B.cq_moe_forward(layer, X)
+                torch.cuda.synchronize()
+                XR = B.moe_intermediates(layer, T)["XR"].double()
+                err[use].append(((XR - ref).norm() / ref.norm()).item())
+        got, fp32 = np.mean(err[True]), np.mean(err[False])
+        _say(f"rotation of few tokens H={H} T={T}: {got:.2e}, fp32 kernel {fp32:.2e}")
+        assert got <= min(1.7e-7, fp32)
+
+
 @pytest.mark.parametrize("H", [64, 1024, 1088, 2048, 4096, 4160, 8192, 8256])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_quantize_rows_in_registers(B, H, bits):
