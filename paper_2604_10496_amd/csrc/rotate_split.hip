@@ -363,6 +363,21 @@ __device__ __forceinline__ float4 few_sum(const float4* lds, int apart) {
   return v[0];
 }
 
+// x . R[:, column] over a wavefront's slice (k from 16 j0 on), from the planes of R in plain fp32: what a slice with an
+// infinite entry gives.  Its planes are no numbers (inf - inf); the sum is +-Inf by the sign of x R, or NaN where infinities
+// of both signs meet, a NaN is among them, or R is 0, as in an fp32 product.
+__device__ __forceinline__ float few_fp32(const RotFewArgs& p, int nb, int j0, int count, int tok, int col) {
+  const float* x = p.X + (size_t)tok * p.H + (size_t)j0 * 16;
+  const _Float16* r = reinterpret_cast<const _Float16*>(p.Rs) + ((size_t)nb * (p.H / 16) + j0) * 1024 + col * 8;
+  float s = 0.f;
+#pragma unroll 1
+  for (int k = 0; k < count; ++k) {
+    const _Float16* e = r + (k >> 4) * 1024 + ((k >> 3) & 1) * 256 + (k & 7);
+    s = fmaf(x[k], fmaf((float)e[512], kLoUnscale, (float)e[0]), s);
+  }
+  return s;
+}
+
 template <int N, int TB_>
 __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFewArgs p) {
   constexpr bool HALF = TB_ == 0;
@@ -456,12 +471,16 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
       }
     }
     // MFMA 16x16 output: register v of a lane holds column (of R) 4*(lane/16) + v, token lane%16
-    const bool bad = __float_as_uint(pow2[0]) == 0x7f800000u;   // (an infinite entry: an infinite row, as in fp32)
-    auto val = [&](float a, float l) { return bad ? pow2[0] : pow2[0] * fmaf(l, kLoUnscale, a); };
+    auto val = [&](float a, float l) { return pow2[0] * fmaf(l, kLoUnscale, a); };
 #pragma unroll
     for (int h = 0; h < 2; ++h)
       lds[(wave * 2 + h) * 64 + lane] = make_float4(val(acc[h][0], low[h][0]), val(acc[h][1], low[h][1]),
                                                     val(acc[h][2], low[h][2]), val(acc[h][3], low[h][3]));
+    if (__float_as_uint(pow2[0]) == 0x7f800000u)
+#pragma unroll 1
+      for (int i = 0; i < 8; ++i)
+        few_lds[((wave * 2 + (i >> 2)) * 64 + lane) * 4 + (i & 3)] =
+            few_fp32(p, nb, j0, N * 16, min(tcol, p.T - 1), (i >> 2) * 16 + (lane >> 4) * 4 + (i & 3));
     __syncthreads();
     if (tid >= 128) return;
     if (tcol < p.T)
@@ -491,11 +510,15 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
   // MFMA 32x32 output: register v of a lane holds column (of R) 8*(v/4) + 4*(lane/32) + v%4, token lane%32
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb) {
-    const bool bad = __float_as_uint(pow2[tb]) == 0x7f800000u;   // (an infinite entry: an infinite row, as in fp32)
-    auto val = [&](int i) { return bad ? pow2[tb] : pow2[tb] * fmaf(low[tb][i], kLoUnscale, acc[tb][i]); };
+    auto val = [&](int i) { return pow2[tb] * fmaf(low[tb][i], kLoUnscale, acc[tb][i]); };
 #pragma unroll
     for (int vb = 0; vb < 4; ++vb)
       lds[((wave * TB + tb) * 4 + vb) * 64 + lane] = make_float4(val(4 * vb), val(4 * vb + 1), val(4 * vb + 2), val(4 * vb + 3));
+    if (__float_as_uint(pow2[tb]) == 0x7f800000u)
+#pragma unroll 1
+      for (int i = 0; i < 16; ++i)
+        few_lds[(((wave * TB + tb) * 4 + (i >> 2)) * 64 + lane) * 4 + (i & 3)] =
+            few_fp32(p, nb, j0, N * 16, min(tb * 32 + r32, p.T - 1), (i >> 2) * 8 + g2 * 4 + (i & 3));
   }
   __syncthreads();
 #pragma unroll

@@ -153,7 +153,8 @@ def test_rotate_quant_identity_and_grid(B):
 
 
 @pytest.mark.parametrize("H,batches", [(1024, [1, 16, 17, 32, 33]), (1536, [5, 16, 31, 64]), (2048, [1, 17, 40, 65, 128]),
-                                       (3584, [16, 32]), (4096, [1, 15, 17, 32, 33])])
+                                       (3584, [16, 32]), (4096, [1, 15, 17, 32, 33]),
+                                       (2560, [16, 32, 64]), (3072, [1, 16, 17, 32, 33])])
 def test_rotation_of_few_tokens(B, H, batches):
     """The layer's rotation from the split copy of R at decode-sized batches, around the numbers of tokens and the widths
     where its kernels change: every row within 4e-6 of its maximum (two f16 planes: 2^-22 of a product, and fp32 sums),
@@ -183,6 +184,52 @@ def test_rotation_of_few_tokens(B, H, batches):
         _say(f"rotation of few tokens H={H} T={T}: {err:.2e}")
         assert err <= 4e-6
         assert not torch.isfinite(XR[~ok]).any()
+
+
+def _class(v):
+    """0 finite, 1 +Inf, 2 -Inf, 3 NaN"""
+    return np.where(np.isnan(v), 3, np.where(np.isposinf(v), 1, np.where(np.isneginf(v), 2, 0)))
+
+
+@pytest.mark.parametrize("H,T", [(1024, 13), (1024, 32), (2048, 16), (2048, 40), (3072, 9), (3072, 19), (4096, 12), (4096, 31)])
+def test_rotation_of_few_tokens_non_finite(B, H, T):
+    """Rows with infinite and NaN entries through the rotation from the split copy of R: every entry of X_R is +Inf, -Inf or
+    NaN as in an fp32 product -- by the signs of the terms x R, NaN where infinities of both signs meet or an entry is NaN --
+    and the fp32 kernel says the same; the other rows are not touched."""
+    import torch
+    rng = np.random.default_rng(H + T)
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], H=H, I=64, T=T, outlier_channels=())
+    R = np.linalg.qr(rng.standard_normal((H, H)))[0].astype(np.float32)
+    R[R == 0] = 1e-3
+    cb = [B.DeviceCodebook(*_rand_weights(rng, cfg.E, N, K), prepack=True) for N, K in ((128, H), (H, 64))]
+    layer = B.DeviceLayer(cfg, R, rng.standard_normal((cfg.E, H)).astype(np.float32) / np.float32(H ** 0.5), None, *cb)
+    X = rng.standard_normal((T, H)).astype(np.float32)
+    clean = X.copy()
+    inf, nan, far = np.float32(np.inf), np.float32(np.nan), H // 2 + 5
+    special = {0: {7: inf}, 1: {far: -inf}, 2: {3: inf, far: -inf}, 3: {16: inf, 17: -inf}, 4: {1: nan, 2: inf},
+               5: {9: nan}, 6: {5: -inf, 6: -inf, far: -inf}, T - 1: {H - 1: inf}}
+    want = np.zeros((T, H), dtype=np.int64)
+    for t, entries in special.items():
+        pos, neg, bad = (np.zeros(H, dtype=bool) for _ in range(3))
+        for k, v in entries.items():
+            X[t, k] = v
+            bad |= np.isnan(v)
+            if np.isinf(v):
+                pos |= (R[k] > 0) == (v > 0)
+                neg |= (R[k] > 0) != (v > 0)
+        want[t] = np.where(bad | (pos & neg), 3, np.where(pos, 1, np.where(neg, 2, 0)))
+    split = layer.R_split
+    for use in (split, None):
+        layer.R_split, layer._ws = use, None
+        B.cq_moe_forward(layer, _dev(X))
+        torch.cuda.synchronize()
+        XR = B.moe_intermediates(layer, T)["XR"].cpu().numpy()
+        _say(f"non-finite rows H={H} T={T} split={use is not None}")
+        assert np.array_equal(_class(XR), want)
+        B.cq_moe_forward(layer, _dev(clean))
+        torch.cuda.synchronize()
+        ok = [t for t in range(T) if t not in special]
+        assert np.array_equal(XR[ok], B.moe_intermediates(layer, T)["XR"].cpu().numpy()[ok])
 
 
 @pytest.mark.parametrize("H,batches", [(1024, [1, 32]), (1536, [16, 64]), (2048, [1, 16, 33]), (3072, [16, 32]),
