@@ -421,8 +421,9 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
         amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v[j][h].x), fabsf(v[j][h].y))), fmaxf(fabsf(v[j][h].z), fabsf(v[j][h].w)));
     amax = fmaxf(amax, __shfl_xor(amax, 32));
     if constexpr (HALF) amax = fmaxf(amax, __shfl_xor(amax, 16));
-    const uint32_t ebits = __float_as_uint(amax) & 0x7f800000u;
-    pow2[tb] = ebits == 0u ? 1.f : __uint_as_float(ebits);
+    // (a slice of subnormal numbers is divided by the smallest normal one: undivided, its planes would all be zero)
+    const uint32_t ebits = max(__float_as_uint(amax) & 0x7f800000u, 0x00800000u);
+    pow2[tb] = __uint_as_float(ebits);
     const float inv = ebits == 0x7f800000u ? 1.f : 1.f / pow2[tb];   // exact: a power of two
 #pragma unroll
     for (int j = 0; j < NX; ++j) {

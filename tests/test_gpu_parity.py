@@ -186,6 +186,32 @@ def test_rotation_of_few_tokens(B, H, batches):
         assert not torch.isfinite(XR[~ok]).any()
 
 
+@pytest.mark.parametrize("H,T", [(1024, 3), (2048, 20), (2048, 34), (3072, 2), (4096, 16), (4096, 17)])
+def test_rotation_of_few_tokens_at_the_ends_of_the_range(B, H, T):
+    """Rows of subnormal numbers and of the largest ones through the rotation from the split copy of R.  Bound: 4e-6 of the
+    row's maximum as everywhere, and half a step of the subnormal grid, 2^-149, for each wavefront's and each part's sum."""
+    import torch
+    rng = np.random.default_rng(H * T)
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], H=H, I=64, T=T, outlier_channels=())
+    R = torch.linalg.qr(torch.from_numpy(rng.standard_normal((H, H))).cuda())[0].float().contiguous()
+    cb = [B.DeviceCodebook(*_rand_weights(rng, cfg.E, N, K), prepack=True) for N, K in ((128, H), (H, 64))]
+    layer = B.DeviceLayer(cfg, R, rng.standard_normal((cfg.E, H)).astype(np.float32) / np.float32(H ** 0.5), None, *cb)
+    X = rng.standard_normal((T, H))
+    X[0] *= 1e-40                  # (subnormal throughout)
+    X[1] *= 2e-38                  # (some entries subnormal, slices of both kinds)
+    X[1, :H // 2] *= 1e-3
+    X[T - 1] *= 3e37
+    X = _dev(X.astype(np.float32))
+    B.cq_moe_forward(layer, X)
+    torch.cuda.synchronize()
+    XR = B.moe_intermediates(layer, T)["XR"].double()
+    ref = X.double() @ R.double()
+    top = ref.abs().amax(dim=1)
+    err = (XR - ref).abs().amax(dim=1)
+    _say(f"ends of the range H={H} T={T}: error / row maximum {(err / top)[[0, 1, T - 1]].tolist()}")
+    assert (err <= 4e-6 * top + 0.5 * (8 + 1) * 8 * 2.0 ** -149).all()
+
+
 def _class(v):
     """0 finite, 1 +Inf, 2 -Inf, 3 NaN"""
     return np.where(np.isnan(v), 3, np.where(np.isposinf(v), 1, np.where(np.isneginf(v), 2, 0)))
