@@ -46,11 +46,21 @@ int row_bound(int M_total, int max_group_rows) {
 // Short K (2048 and less), where the large tiles took the small groups as well: 8 rows cost a tile what 64 do, so a group that
 // fits one pass is cheaper streamed (66 groups x 2816 x 2048: 8 rows 60 / 46 us, 32 rows 62 / 58; two passes 110), whole
 // layers of the DeepSeek-V2-Lite shape on tiles and in passes: 33 tokens 126 / 106, 64 tokens 140 / 123, 128 tokens
-// 151 / 144 (256: 167 / 178); Qwen3 shape, whose rows are very uneven, 33 tokens 88 / 79, 96 tokens 118 / 116, 128 tokens
-// 124.3 / 123.5 (192: 132 / 149).
+// 151 / 144 (256: 167 / 178).
+// But a unit of 64 weight rows costs a workgroup about 1.2 us + 0.5 us per 1024 of K (its table, and eight wavefronts' sums
+// to add up), a tile of 256 of them 2 us + 9.5 us per 1024 of K in a round of 512: the shorter K, the fewer units may come
+// one after the other on a workgroup.  Up to K / 256 of them it is still the cheaper (tiles / passes, us: K = 256 4 groups x
+// 1024 8.8 / 6.5, 8 x 8192 7.0 / 10.4; K = 512 8 x 4096 of 66 rows 12.6 / 11.4, 64 x 2048 of 384 rows 17.7 / 23.3, uneven 16.9 /
+// 23.7; K = 768 16 x 2048 15.6 / 10.3, 128 x 2048 of 264 uneven rows 21.6 / 26.7; K = 1024 8 x 4096 16.5 / 13.1, 32 x 4096 of
+// 256 rows 26.8 / 27.5).  From K = 1408 on a batch of even rows always gains (45 / 41 .. 113 / 92); very uneven ones, whose
+// large groups need more passes than are counted here, lie between 32.2 / 31.9 and 37.4 / 45.0.
+bool short_k_in_passes(const cq_codebook_weights* W, int M_total) {
+  const long units = (long)((W->G < M_total ? W->G : M_total) + M_total / cq_route::kPassRows) * (W->N / 64);
+  return W->K >= 1408 || (W->K >= 256 && units <= W->K);
+}
 long rows_in_passes(const cq_codebook_weights* W) { return (cq_tables_per_row(W) > 1 ? 23L : 28L) * W->G; }
 bool streams_in_passes(const cq_codebook_weights* W, int M_total, int max_group_rows) {
-  if (W->K <= 2048 && cq_tables_per_row(W) > 1) return false;
+  if (W->K <= 2048 && (cq_tables_per_row(W) > 1 || !short_k_in_passes(W, M_total))) return false;
   return row_bound(M_total, max_group_rows) <= 128 && (long)M_total < rows_in_passes(W);
 }
 

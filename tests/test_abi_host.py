@@ -158,6 +158,27 @@ def test_a_workspace_serves_every_smaller_batch(name, over):
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("G,N,K,rows,passes", [
+    # K = 256 units of 64 weight rows are as many as a product of K = 256 may have: (groups + rows / 32) x N / 64
+    (4, 2048, 256, 100, True), (8, 4096, 256, 66, False), (4, 1024, 128, 66, False), (16, 16384, 256, 66, False),
+    (8, 4096, 512, 66, False), (8, 2048, 512, 66, True), (32, 1024, 512, 132, False), (64, 2048, 512, 198, False),
+    (8, 4096, 1024, 128, True), (128, 2048, 768, 264, False), (16, 1536, 1024, 200, True), (17, 2048, 1024, 480, False),
+    (66, 2816, 1408, 512, True), (128, 4096, 1408, 512, True), (128, 1536, 2048, 1024, True), (8, 2048, 2048, 224, False),
+])
+def test_short_k_streams_in_passes_where_its_units_are_few(G, N, K, rows, passes):
+    """Batches of 33 and more tokens with K <= 2048: the product streams in passes (and the layer keeps no second copy of
+    its codes) only where few units follow each other on a workgroup, otherwise it is on tiles."""
+    lib = B.load_library()
+    k = next(k for k in (8, 6, 5, 4, 3, 2, 1) if rows % k == 0 and rows // k > 32)
+    T = rows // k
+    gu = B.CodebookWeights(256, 256, 256, G, N, K)
+    dn = B.CodebookWeights(256, 256, 256, G, K, N // 2)
+    L = B.Layer(K, N // 2, G, k, 0, 8, 256, 256, None, gu, dn)
+    lay = B.MoeLayout()
+    assert lib.cq_moe_workspace_layout(ctypes.byref(L), T, ctypes.byref(lay)) == 0
+    assert lay.scale - lay.Q16 == (0 if passes else -(-T * K * 2 // 256) * 256)
+
+
 def test_prepack_layout_documented_in_header_matches_numpy_model():
     """The tile order and nibble grouping stated in cq.h keep every weight exactly once."""
     rng = np.random.default_rng(5)
