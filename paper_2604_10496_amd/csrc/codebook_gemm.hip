@@ -49,14 +49,17 @@ int row_bound(int M_total, int max_group_rows) {
 // 151 / 144 (256: 167 / 178).
 // But a unit of 64 weight rows costs a workgroup about 1.2 us + 0.5 us per 1024 of K (its table, and eight wavefronts' sums
 // to add up), a tile of 256 of them 2 us + 9.5 us per 1024 of K in a round of 512: the shorter K, the fewer units may come
-// one after the other on a workgroup.  Up to K / 256 of them it is still the cheaper (tiles / passes, us: K = 256 4 groups x
-// 1024 8.8 / 6.5, 8 x 8192 7.0 / 10.4; K = 512 8 x 4096 of 66 rows 12.6 / 11.4, 64 x 2048 of 384 rows 17.7 / 23.3, uneven 16.9 /
-// 23.7; K = 768 16 x 2048 15.6 / 10.3, 128 x 2048 of 264 uneven rows 21.6 / 26.7; K = 1024 8 x 4096 16.5 / 13.1, 32 x 4096 of
-// 256 rows 26.8 / 27.5).  From K = 1408 on a batch of even rows always gains (45 / 41 .. 113 / 92); very uneven ones, whose
-// large groups need more passes than are counted here, lie between 32.2 / 31.9 and 37.4 / 45.0.
+// one after the other on a workgroup.  Up to K / 256 of them passes are still the cheaper (tiles / passes, us: K = 256 4 groups
+// x 2048 of 56 rows 6.3 / 5.5, 53 of them in one group 6.9 / 7.3, 8 x 8192 of 112 rows 7.0 / 10.4; K = 512 8 x 2048 of 112
+// rows 8.6 / 5.9, 8 x 8192 9.7 / 11.1, 64 x 2048 of 384 rows 17.7 / 23.3; K = 768 16 x 2048 of 96 rows 10.9 / 8.3, 128 x 2048
+// of 264 uneven rows 21.6 / 26.7; K = 1024 8 x 4096 of 112 rows 13.3 / 9.7, 32 x 4096 of 256 rows 26.8 / 27.5).  K = 2048 always gains (DeepSeek-V2-Lite shape 33 and 128 tokens 55.6 / 45.6 and 61.2 / 58.8,
+// Qwen3 shape 64 and 128 tokens 37.8 / 30.0 and 41.5 / 37.3), from 1408 on where the tiles make more than a round even if
+// some groups are empty (64 x 4096 x 1408 of 256 even and uneven rows 60.7 / 50.0 and 47.6 / 48.4), not where they make one:
+// 66 x 2048 x 1408, DeepSeek-V2-Lite shape, 33, 64 and 128 tokens 30.2 / 32.0, 32.8 / 40.0 and 36.1 / 41.8.
 bool short_k_in_passes(const cq_codebook_weights* W, int M_total) {
-  const long units = (long)((W->G < M_total ? W->G : M_total) + M_total / cq_route::kPassRows) * (W->N / 64);
-  return W->K >= 1408 || (W->K >= 256 && units <= W->K);
+  const long groups = W->G < M_total ? W->G : M_total;
+  if (W->K >= 2048 || (W->K >= 1408 && groups * (W->N / 256) > 640)) return true;
+  return W->K >= 256 && (groups + M_total / cq_route::kPassRows) * (W->N / 64) <= W->K;
 }
 long rows_in_passes(const cq_codebook_weights* W) { return (cq_tables_per_row(W) > 1 ? 23L : 28L) * W->G; }
 bool streams_in_passes(const cq_codebook_weights* W, int M_total, int max_group_rows) {

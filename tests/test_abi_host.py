@@ -163,7 +163,8 @@ def test_a_workspace_serves_every_smaller_batch(name, over):
     (4, 2048, 256, 100, True), (8, 4096, 256, 66, False), (4, 1024, 128, 66, False), (16, 16384, 256, 66, False),
     (8, 4096, 512, 66, False), (8, 2048, 512, 66, True), (32, 1024, 512, 132, False), (64, 2048, 512, 198, False),
     (8, 4096, 1024, 128, True), (128, 2048, 768, 264, False), (16, 1536, 1024, 200, True), (17, 2048, 1024, 480, False),
-    (66, 2816, 1408, 512, True), (128, 4096, 1408, 512, True), (128, 1536, 2048, 1024, True), (8, 2048, 2048, 224, False),
+    (66, 2816, 1408, 512, True), (128, 4096, 1408, 512, True), (66, 2048, 1408, 512, False), (80, 2048, 1408, 480, False),
+    (82, 2048, 1408, 480, True), (8, 2048, 1408, 200, True), (128, 1536, 2048, 1024, True), (8, 2048, 2048, 224, False),
 ])
 def test_short_k_streams_in_passes_where_its_units_are_few(G, N, K, rows, passes):
     """Batches of 33 and more tokens with K <= 2048: the product streams in passes (and the layer keeps no second copy of
