@@ -275,22 +275,24 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
 
 // The same for more assignments and up to 128 experts, still in one launch: workgroup b ranks assignments 1024 b .. + 1023,
 // and finds out by itself what precedes them -- it counts the ids of all assignments, those in front of its own in the upper
-// half word (a token selects an expert at most once: counts stay below 2^16 for fewer tokens than that).  Four copies of the
-// counters keep the additions to a popular expert apart.  Counting everything again in every workgroup costs it about a
-// microsecond per 16384 assignments and saves two launches and their waits: 16384 assignments to 128 experts 8 us
-// against 19 in the counting sort's three launches, 8192 to 8 experts 6 against 12 in one workgroup.
+// half word (a token selects an expert at most once: counts stay below 2^16 for fewer tokens than that).  Sixteen copies of
+// the counters, for every sixteenth lane, keep the additions to a popular expert apart.  Counting everything again in every
+// workgroup saves two launches and their waits.  Top-k and grouping, with the counting sort (up to 8192 assignments one
+// workgroup) / so: 16384 assignments to 128 experts 19.8 / 10.7 us, 8192 to 8 experts 15.3 / 9.4, 65535 to 2 experts 53 / 36, all
+// of 65535 to one expert 52 / 35 (with four copies of the counters 84: the 64 lanes of an addition met in one of them).
 constexpr int kGroupChunk = 1024;
 constexpr int kGroupMostAssign = 65535;   // (one expert may have them all)
 __global__ __launch_bounds__(1024) void group_chunks_kernel(const int32_t* __restrict__ ids, int T, int E, int k, int S,
                                                             int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
                                                             int32_t* __restrict__ inv_perm,
                                                             int32_t* __restrict__ src_token) {
-  __shared__ uint32_t s_cnt[4][kFusedMaxE];
+  constexpr int kCopies = 16;
+  __shared__ uint32_t s_cnt[kCopies][kFusedMaxE + 1];   // (+ 1: copies of a counter on different banks)
   __shared__ int s_wave[16][kFusedMaxE];
   __shared__ int s_off[kFusedMaxE + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int A = T * k, start = blockIdx.x * kGroupChunk;
-  for (int i = tid; i < 4 * kFusedMaxE; i += 1024) (&s_cnt[0][0])[i] = 0u;
+  for (int i = tid; i < kCopies * (kFusedMaxE + 1); i += 1024) (&s_cnt[0][0])[i] = 0u;
   for (int i = tid; i < 16 * kFusedMaxE; i += 1024) (&s_wave[0][0])[i] = 0;
   const int a = start + tid;
   const bool valid = a < A;
@@ -313,7 +315,7 @@ __global__ __launch_bounds__(1024) void group_chunks_kernel(const int32_t* __res
         for (int m = 0; m < A - i; ++m) e[m] = ids[i + m];
 #pragma unroll
       for (int m = 0; m < 4; ++m)
-        if (e[m] >= 0) atomicAdd(&s_cnt[m][e[m]], one);
+        if (e[m] >= 0) atomicAdd(&s_cnt[lane % kCopies][e[m]], one);
     }
   }
   // ---- this workgroup's: rank among the wavefront's assignments to the same expert ----
@@ -330,7 +332,7 @@ __global__ __launch_bounds__(1024) void group_chunks_kernel(const int32_t* __res
   if (tid < kFusedMaxE) {
     uint32_t all = 0u;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) all += s_cnt[c][tid];
+    for (int c = 0; c < kCopies; ++c) all += s_cnt[c][tid];
     int before = (int)(all >> 16);
     for (int c = 0; c < 16; ++c) {   // positions of the wavefronts' first assignments, relative to the expert's first row
       const int v = s_wave[c][tid];

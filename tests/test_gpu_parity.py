@@ -385,6 +385,7 @@ def test_route_limits(B, T, E, k):
     (512, 128, 8),                                  # 4096 assignments: the largest grouping in one workgroup
     (4097, 8, 1), (2049, 100, 3), (1024, 128, 8), (4096, 4, 2), (2048, 128, 8),   # in several, the last one ragged or full
     (65535, 3, 1), (65536, 3, 1),                   # the most of them, and the counting sort
+    (65535, 1, 1), (4097, 1, 1), (8192, 2, 2),      # all of them to one expert, and to both of two
     (1025, 128, 8), (1367, 33, 6),
 ])
 def test_route_selection_and_grouping_forms(B, T, E, k):
