@@ -320,7 +320,12 @@ bool spans_columns(int T, int N) { return N <= 16 || (N <= 64 && T >= 64 && T <=
 // Rotation of so few values that tiles of 128 x 128 leave most of the chip idle: tiles of 16 x 256 also from 64 tokens on
 // (layer of width 256 at 64, 128, 256 and 512 tokens 36.3 -> 32.2, 40.2 -> 36.3, 43.5 -> 39.8 and 49.1 -> 45.1 us; of width
 // 2048 at 64 and 128 tokens 122.5 -> 117.4 and 143.9 -> 140.6).
-bool few_rows(int T, int N, int K) { return N == K && (long)T * N <= (1L << 18); }
+// Wider than 2048 the row tiles' reads of R meet in an XCD's L2 only if their number of column tiles is even: 2304 (9 column
+// tiles), 80 and 112 tokens 26.0 -> 26.6 and 27.0 -> 31.9 us; 2816, 90 tokens 32.0 -> 38.1; 3328, 72 tokens 40.3 -> 42.3; but
+// 2560, 80 and 100 tokens 27 -> 24 and 29.5 -> 30.5; 3072, 64 and 80 tokens 32.8 -> 25.3 and 35.8 -> 28.6; 4096, 64 tokens 45.7 -> 34.6.
+bool few_rows(int T, int N, int K) {
+  return N == K && (long)T * N <= (1L << 18) && (N <= 2048 || (N % 512 == 0 && T <= 96));
+}
 }  // namespace
 
 cq_gemm_f32_plan cq_gemm_f32_make_plan(int T, int N, int K, bool wide_tiles) {

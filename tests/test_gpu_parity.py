@@ -1402,6 +1402,23 @@ def test_layer_rotation_rule(B, H, T, f16):
         assert (np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)).max() <= 4e-6
 
 
+@pytest.mark.parametrize("H,T,narrow", [(2304, 100, False), (2816, 90, False), (3328, 72, False), (2560, 102, False),
+                                        (2560, 96, True), (1856, 129, True), (3072, 80, True), (1088, 129, True)])
+def test_rotate_quant_rule(B, H, T, narrow):
+    """Which batches of few values rotate on tiles of 16 rows in the fp32 kernel: on the others a row's X_R is bit for bit
+    what it is in a batch just too large for them, whose K parts are as many."""
+    rng = np.random.default_rng(H + T)
+    more = (1 << 18) // H + 1
+    assert -(-more // 128) == -(-T // 128)
+    X = rng.standard_normal((more, H)).astype(np.float32)
+    R = _dev(rng.standard_normal((H, H)).astype(np.float32) / np.float32(np.sqrt(H)))
+    a = B.cq_rotate_quant(_dev(X[:T]), R, 8)["XR"].cpu().numpy()
+    b = B.cq_rotate_quant(_dev(X), R, 8)["XR"].cpu().numpy()[:T]
+    assert np.array_equal(a, b) == (not narrow)
+    ref = X[:T].astype(np.float64) @ R.cpu().numpy().astype(np.float64)
+    assert (np.abs(a - ref).max(axis=1) / np.abs(ref).max(axis=1)).max() <= 4e-6
+
+
 @pytest.mark.parametrize("name,over", [
     ("mixtral_decode", dict(H=4096, I=256, T=16)),                         # the decode shape's front end and gate/up K
     ("mixtral_decode", dict(H=4096, I=128, T=1)),                          # one token: six experts without rows
