@@ -78,8 +78,9 @@ cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H,
                                 const float* bias, int E, float* XR, int8_t* Q, uint16_t* Q16, float* scale,
                                 float* logits, int top_k, int32_t* topk_ids, float* topk_w, hipStream_t s);
 
-// Quantization, router logits and top-k in one launch for any batch (Q NULL: the rows are quantized already).
-bool cq_front_rows_supported(int T, int H, int E, int top_k);
+// Quantization, router logits and top-k in one launch for 32 to 512 tokens, up to 128 experts and H <= 4096 (quantized, and
+// Q NULL: the rows are quantized already).
+bool cq_front_rows_supported(int T, int H, int E, int top_k, bool quantized);
 cq_status cq_front_rows_launch(const float* partials, int ksplit, int T, int H, int act_bits, const float* Wr,
                                const float* bias, int E, float* XR, int8_t* Q, uint16_t* Q16, float* scale,
                                float* logits, int top_k, int32_t* topk_ids, float* topk_w, hipStream_t s);

@@ -187,8 +187,15 @@ cq_status launch_front_rows(const FrontRowsArgs& a, hipStream_t s) {
 // tokens 60.8 / 64.8, 64 tokens 92.5 / 84.9, 128 tokens 116.8 / 106.7, 300 tokens (two) 140.9 / 137.3, 600 tokens 184 / 196;
 // Mixtral shape (8 experts), 512 tokens 526 / 522.  Not where the router matrix is so small that its product is not what the
 // launches wait for (4 experts of width 256, 512 tokens 41.8 / 43.8).
-bool cq_front_rows_supported(int T, int H, int E, int top_k) {
-  return T >= 32 && T <= 512 && H % 64 == 0 && H <= 4 * kRowsThreads && E <= kRowsMaxE && top_k <= 64 && (long)E * H >= (1L << 15);
+// With fewer than 64 tokens not where a workgroup has a router matrix of more than 1 MiB to read for its one token: 128
+// experts of width 4096 32 and 63 tokens 104.5 / 109.0 and 119.7 / 121.9 (64 tokens 137.2 / 121.6), of width 3072 33 tokens
+// 93.4 / 98.8; 128 of width 2048 75.4 / 71.0, 64 of width 4096 90.3 / 88.2 (48 tokens).  Behind the Hadamard rotation, whose
+// rows are quantized already, not with more than 64 experts either: 128 of width 2048, 33 tokens 61.7 / 62.7 (64 tokens 71.5 /
+// 65.7), 64 of width 4096 48 tokens 2 % less.
+bool cq_front_rows_supported(int T, int H, int E, int top_k, bool quantized) {
+  if (T < 32 || T > 512 || H % 64 != 0 || H > 4 * kRowsThreads || E > kRowsMaxE || top_k > 64) return false;
+  if (T < 64 && ((long)E * H > (1L << 18) || (quantized && (T == 32 || E > 64)))) return false;
+  return (long)E * H >= (1L << 15);
 }
 
 cq_status cq_front_rows_launch(const float* partials, int ksplit, int T, int H, int act_bits, const float* Wr, const float* bias,

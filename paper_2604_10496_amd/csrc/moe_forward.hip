@@ -227,7 +227,7 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
     if (!mark(1)) return CQ_ERR_HIP;
     // (the rows are quantized: logits and top-k in one launch; 32 tokens 68.4 us per layer of the Qwen3 shape without, 70.8
     // with it, 64 tokens 84.4 / 80.2, 512 tokens 144.2 / 142.8)
-    if (T > 32 && cq_front_rows_supported(T, L->H, L->E, L->top_k)) {
+    if (cq_front_rows_supported(T, L->H, L->E, L->top_k, true)) {
       st = cq_front_rows_launch(XR, 1, T, L->H, L->act_bits, L->Wr, L->bias, L->E, XR, nullptr, nullptr, nullptr, logits,
                                 L->top_k, ids, tw, hs);
       if (st == CQ_OK) st = cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
@@ -257,7 +257,7 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
       if (st != CQ_OK) return st;
     }
     if (!mark(2)) return CQ_ERR_HIP;
-  } else if (cq_front_rows_supported(T, L->H, L->E, L->top_k)) {
+  } else if (cq_front_rows_supported(T, L->H, L->E, L->top_k, false)) {
     // larger batches: the rotation; quantization, logits and top-k in one launch; the grouping (stage boundary as above)
     int parts;
     float* part;

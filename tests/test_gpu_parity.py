@@ -1402,6 +1402,26 @@ def test_layer_rotation_rule(B, H, T, f16):
         assert (np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)).max() <= 4e-6
 
 
+@pytest.mark.parametrize("E,H,T,had,one", [
+    (128, 4096, 40, False, False), (128, 4096, 64, False, True), (128, 3072, 63, False, False), (128, 2048, 32, False, True),
+    (128, 2048, 40, True, False), (128, 2048, 64, True, True), (64, 4096, 33, True, True), (64, 4096, 32, True, False),
+])
+def test_layer_front_rows_rule(B, E, H, T, had, one):
+    """Which batches quantize, form logits and select in one launch: elsewhere the logits are bit for bit those of the
+    routing step on its own on the layer's X_R (one launch per step), and in the one launch their sums have another order."""
+    rng = np.random.default_rng(E + H + T)
+    cfg = synth.small_variant(synth.CONFIGS["qwen3_zipf"], H=H, I=64, E=E, S=0, top_k=4, T=T, r_hadamard=had)
+    W = [B.DeviceCodebook(*_rand_weights(rng, E, n, k)) for n, k in ((128, H), (H, 64))]
+    R = None if had else rng.standard_normal((H, H)).astype(np.float32) / np.float32(np.sqrt(H))
+    layer = B.DeviceLayer(cfg, R, rng.standard_normal((E, H)).astype(np.float32), None, *W)
+    B.cq_moe_forward(layer, _dev(rng.standard_normal((T, H)).astype(np.float32)))
+    mid = B.moe_intermediates(layer, T)
+    step = B.cq_route_permute(mid["XR"].contiguous(), layer.Wr, None, 4)["logits"].cpu().numpy()
+    got = mid["logits"].cpu().numpy()
+    assert np.allclose(got, step, rtol=1e-4, atol=1e-3)
+    assert np.array_equal(got, step) == (not one)
+
+
 @pytest.mark.parametrize("H,T,narrow", [(2304, 100, False), (2816, 90, False), (3328, 72, False), (2560, 102, False),
                                         (2560, 96, True), (1856, 129, True), (3072, 80, True), (1088, 129, True)])
 def test_rotate_quant_rule(B, H, T, narrow):
