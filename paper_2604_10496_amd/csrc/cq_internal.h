@@ -18,6 +18,14 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float cq_v16f;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float cq_v4f;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t cq_v4u;
 
+// Between one wavefront's LDS stores and its other lanes' loads of them.  It is no instruction: a wavefront's LDS operations
+// complete in order.  The fences hold the compiler to that order, which the barrier alone does not.
+__device__ __forceinline__ static void cq_wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 static inline cq_status cq_check_launch() {
   return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
 }

@@ -128,8 +128,7 @@ __device__ __forceinline__ void wave_topk_regs(float val, int E, int k, int lane
 }
 
 // The same for up to 128 experts, two per lane (val[s]: the logit of expert 64 s + lane): still one wavefront on its own,
-// no workgroup barrier; the selected pairs are sorted through 64 entries of LDS of this wavefront's own (LDS operations
-// of one wavefront complete in order).  Called by all 64 lanes.
+// no workgroup barrier; the selected pairs are sorted through 64 entries of LDS of this wavefront's own.  Called by all 64 lanes.
 __device__ __forceinline__ void wave_topk_regs2(const float (&val)[2], int E, int k, int lane, int* lds_id, float* lds_val,
                                                 int32_t* ids_out, float* w_out, int* lds_ids = nullptr) {
   const uint64_t lt = lanemask_lt(lane);
@@ -165,7 +164,7 @@ __device__ __forceinline__ void wave_topk_regs2(const float (&val)[2], int E, in
       lds_id[rank[s]] = s * 64 + lane;
       lds_val[rank[s]] = val[s];
     }
-  __builtin_amdgcn_wave_barrier();
+  cq_wave_lds_fence();
   const int id_sorted = lds_id[lane < k ? lane : 0];
   const float v_sorted = lds_val[lane < k ? lane : 0];
   const float top = lds_val[0];
@@ -178,7 +177,7 @@ __device__ __forceinline__ void wave_topk_regs2(const float (&val)[2], int E, in
     if (lds_ids) lds_ids[lane] = id_sorted;
     w_out[lane] = ex / sum;
   }
-  __builtin_amdgcn_wave_barrier();   // (the entries may be reused by the caller's next token)
+  cq_wave_lds_fence();   // (the entries may be reused by the caller's next token)
 }
 
 // inclusive sum over the lanes of a wavefront (data-parallel moves inside rows of 16 lanes, then across them)

@@ -278,7 +278,7 @@ __global__ __launch_bounds__(NT * ROWS) void hadamard_rows_kernel(const float* _
     for (int a = 0; a < A; ++a) lds[a * kStride + tid] = v[a];
   }
   if constexpr (NT > 64) __syncthreads();
-  else __builtin_amdgcn_wave_barrier();   // (a row is one wavefront's: its LDS operations complete in order)
+  else cq_wave_lds_fence();   // (a row is one wavefront's)
 
   // ---- step 2 ----
   const int l = tid & (L - 1);

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
     id[c] = c < chunks && a < A ? ids[a] : -1;
   }
   for (int i = lane; i < kFusedMaxE; i += 64) s_cnt[wave][i] = 0;
-  __builtin_amdgcn_wave_barrier();   // (a wavefront's own row: its LDS operations complete in order)
+  cq_wave_lds_fence();   // (a wavefront's own row)
   const uint64_t lt = lanemask_lt(lane);
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
@@ -229,9 +229,9 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
       const int before = valid ? s_cnt[wave][id[c]] : 0;
       const int in_chunk = __popcll(mask & lt);
       rank[c] = before + in_chunk;
-      __builtin_amdgcn_wave_barrier();
+      cq_wave_lds_fence();
       if (valid && in_chunk == 0) s_cnt[wave][id[c]] = before + __popcll(mask);
-      __builtin_amdgcn_wave_barrier();
+      cq_wave_lds_fence();
     }
   }
   __syncthreads();

@@ -200,6 +200,17 @@ def test_prepack_layout_documented_in_header_matches_numpy_model():
         sorted(np.concatenate([idx.reshape(-1) & 15, idx.reshape(-1) >> 4]).tolist())
 
 
+def test_exchanges_within_a_wavefront_are_fenced():
+    """Lanes that hand values to each other through LDS without a workgroup barrier use the helper that orders memory: the
+    wavefront barrier alone lets the compiler move a load in front of another lane's store."""
+    import os
+    from paper_2604_10496_amd import build
+    for name in sorted(os.listdir(build.CSRC)):
+        with open(os.path.join(build.CSRC, name)) as f:
+            bare = f.read().count("__builtin_amdgcn_wave_barrier()")
+        assert bare == (1 if name == "cq_internal.h" else 0), name
+
+
 def test_build_reads_spill_counts_from_the_compiler_remarks():
     """build.py refuses kernels with asynchronous register loads that spill; its reader of hipcc's resource
     remarks is checked on a sample of that output."""
