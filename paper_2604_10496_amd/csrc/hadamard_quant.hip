@@ -151,8 +151,8 @@ __global__ __launch_bounds__(kHadThreads) void hadamard_quant_kernel(const float
   }
 }
 
-// ---- the sizes of the configured layers, in registers ----
-// H_I = H_A (x) H_P with P = 32 .. 512: A is the Paley order, or for a power of two 16 of its factors of 2.
+// ---- in registers ----
+// H_I = H_A (x) H_P with P = 32 .. 512: A is the Paley order, or for a power of two 16 or 32 of its factors of 2.
 // Bound by memory (4 bytes in, 1 to 7 out per value); one pass through LDS is what is left of the exchanges:
 //   1. thread b of a row loads its A values (whole cache lines per wavefront), combines them with H_A in registers and
 //      writes them to LDS;
@@ -160,7 +160,10 @@ __global__ __launch_bounds__(kHadThreads) void hadamard_quant_kernel(const float
 //      butterflies in registers, those of l are data-parallel moves inside a row of 16 lanes.
 // The general kernel above (an LDS pass per two bits, every value combined from LDS) against this one, back-to-back calls
 // that also store the fp32 rows: 4096 rows of 14336 174 / 103 us (5.1 TB/s of what it reads and writes), of 4096 47.5 / 24.4,
-// of 2048 29.9 / 18.0, of 1408 56 / 15.5, of 768 16.4 / 14.7 (a call alone takes 14); 1001 rows of 14336 47.6 / 25.9.
+// of 2048 29.9 / 18.0, of 1408 56 / 15.5, of 768 16.4 / 14.7 (a call alone takes 14); 1001 rows of 14336 47.6 / 25.9.  In
+// a graph, 16 and 4096 rows: 1024 3.9 / 3.5 and 18.5 / 8.4, 1536 4.3 / 3.8 and 21.9 / 12.1, 1792 5.2 / 4.8 and 29.7 / 13.3, 3072
+// 5.0 / 3.8 and 33.8 / 19.2, 3584 6.7 / 5.6 and 45.6 / 23.9, 5632 9.7 / 8.6 and 86.5 / 39.4, 6144 7.3 / 5.3 and 63.4 / 40.3, 7168
+// 8.3 / 5.7 and 70.9 / 42.4, 8192 9.7 / 5.2 and 92.5 / 52.8, 11264 12.6 / 8.8 and 153.7 / 85.9, 16384 16.0 / 6.1 and 202.9 / 112.7.
 //
 // Step 2 across lanes.  With s_j the sign of bit j of the lane and P_j the exchange of lanes that differ in it, a stage is
 // v <- s_j v + P_j v.  On x = (product of all s_j) v it becomes x <- x - s_j P_j x, one multiply-add on a moved operand, and
@@ -176,11 +179,11 @@ __device__ __forceinline__ float lane_move(float x) {
 // v <- H_A v (rows of the sign tables: inputs, columns: outputs)
 template <int A>
 __device__ __forceinline__ void combine(float (&v)[A]) {
-  if constexpr (A == 16) {
+  if constexpr ((A & (A - 1)) == 0) {
 #pragma unroll
-    for (int d = 1; d < 16; d <<= 1)
+    for (int d = 1; d < A; d <<= 1)
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
+      for (int i = 0; i < A; ++i)
         if (!(i & d)) {
           const float a = v[i], b = v[i | d];
           v[i] = a + b;
@@ -223,7 +226,7 @@ __device__ __forceinline__ void combine(float (&v)[A]) {
   }
 }
 
-// NT threads per row (P of them, or 64 where P = 32), ROWS rows per workgroup
+// NT threads per row, ROWS rows per workgroup
 template <int A, int LOGP, int NT, int ROWS>
 __global__ __launch_bounds__(NT * ROWS) void hadamard_rows_kernel(const float* __restrict__ Hin, int M, float qmax,
                                                                   int8_t* __restrict__ Q, uint16_t* __restrict__ Q16,
@@ -367,8 +370,10 @@ __global__ __launch_bounds__(NT * ROWS) void hadamard_rows_kernel(const float* _
   else codes(std::false_type{});
 }
 
-template <int A, int LOGP, int NT, int ROWS>
+// P threads take a row, a wavefront where P = 32; rows of one wavefront share a workgroup by four, of two by two
+template <int A, int LOGP>
 cq_status launch_rows(const float* Hin, int M, float qmax, int8_t* Q, uint16_t* Q16, float* scale, float* HR, hipStream_t s) {
+  constexpr int NT = LOGP > 6 ? 1 << LOGP : 64, ROWS = NT == 64 ? 4 : NT == 128 ? 2 : 1;
   constexpr int lds = ROWS * A * ((1 << LOGP) + 16) * 4;
   auto kern = hadamard_rows_kernel<A, LOGP, NT, ROWS>;
   static std::atomic<bool> configured{false};
@@ -376,6 +381,31 @@ cq_status launch_rows(const float* Hin, int M, float qmax, int8_t* Q, uint16_t* 
   if (st != CQ_OK) return st;
   hipLaunchKernelGGL(kern, dim3((M + ROWS - 1) / ROWS), dim3(NT * ROWS), lds, s, Hin, M, qmax, Q, Q16, scale, HR);
   return cq_check_launch();
+}
+
+// Blocks of 2^logp values, A of them: in registers from 64 on (32 where 44 blocks make up for it) as far as a thread's values
+// fit, which for a power of two takes 32 blocks from 8192 on; CQ_ERR_UNSUPPORTED: the general kernel.  Narrower rows leave
+// a wavefront's lanes without work, 12288 would need 1024 threads for 12 blocks.  44 blocks of 64, a wavefront's work for
+// each row, pay from 256 rows on (2816: 64 rows 7.8 / 8.2 us, 300 rows 9.3 / 8.7).
+template <int A>
+cq_status rows_by_block(int logp, const float* Hin, int M, float qmax, int8_t* Q, uint16_t* Q16, float* scale, float* HR,
+                        hipStream_t s) {
+  switch (logp) {
+    case 5:
+      if constexpr (A == 44) return launch_rows<A, 5>(Hin, M, qmax, Q, Q16, scale, HR, s);
+      return CQ_ERR_UNSUPPORTED;
+    case 6: return A == 44 && M < 256 ? CQ_ERR_UNSUPPORTED : launch_rows<A, 6>(Hin, M, qmax, Q, Q16, scale, HR, s);
+    case 7: return launch_rows<A, 7>(Hin, M, qmax, Q, Q16, scale, HR, s);
+    case 8: return launch_rows<A, 8>(Hin, M, qmax, Q, Q16, scale, HR, s);
+    case 9:
+      if constexpr (A == 16) return launch_rows<32, 8>(Hin, M, qmax, Q, Q16, scale, HR, s);
+      else if constexpr (A * 512 <= kHadMaxI) return launch_rows<A, 9>(Hin, M, qmax, Q, Q16, scale, HR, s);
+      return CQ_ERR_UNSUPPORTED;
+    case 10:
+      if constexpr (A == 16) return launch_rows<32, 9>(Hin, M, qmax, Q, Q16, scale, HR, s);
+      return CQ_ERR_UNSUPPORTED;
+    default: return CQ_ERR_UNSUPPORTED;
+  }
 }
 
 // I = m * 2^k with m in {1, 12, 28, 44}; false if I has no such form
@@ -414,15 +444,11 @@ cq_status cq_hadamard_quant_launch(const float* Hin, int M, int I, int bits, int
       return CQ_ERR_HIP;
   }
   const float qmax = (float)((1 << (bits - 1)) - 1);
-  // sizes with an instantiation in registers
-  switch (I) {
-    case 14336: return launch_rows<28, 9, 512, 1>(Hin, M, qmax, Q, Q16, scale, HR, s);
-    case 4096: return launch_rows<16, 8, 256, 1>(Hin, M, qmax, Q, Q16, scale, HR, s);
-    case 2048: return launch_rows<16, 7, 128, 2>(Hin, M, qmax, Q, Q16, scale, HR, s);
-    case 1408: return launch_rows<44, 5, 64, 4>(Hin, M, qmax, Q, Q16, scale, HR, s);
-    case 768: return launch_rows<12, 6, 64, 4>(Hin, M, qmax, Q, Q16, scale, HR, s);
-    default: break;
-  }
+  const cq_status in_registers = m == 1    ? rows_by_block<16>(k - 4, Hin, M, qmax, Q, Q16, scale, HR, s)
+                                 : m == 12 ? rows_by_block<12>(k, Hin, M, qmax, Q, Q16, scale, HR, s)
+                                 : m == 28 ? rows_by_block<28>(k, Hin, M, qmax, Q, Q16, scale, HR, s)
+                                           : rows_by_block<44>(k, Hin, M, qmax, Q, Q16, scale, HR, s);
+  if (in_registers != CQ_ERR_UNSUPPORTED) return in_registers;
   const size_t lds = (size_t)I * 4;
   switch (m) {
     case 1:

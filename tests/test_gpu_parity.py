@@ -1575,10 +1575,11 @@ def test_hadamard_quant(B, M, I, bits):
     assert n_tie <= max(2, M * I // 500)
 
 
-@pytest.mark.parametrize("I", [14336, 4096, 2048, 1408, 768])
-@pytest.mark.parametrize("M", [1, 5])
+@pytest.mark.parametrize("M,I", [(M, I) for M in (1, 5) for I in (14336, 4096, 2048, 1408, 768, 1024, 1536, 1792, 3072, 3584,
+                                                                  5632, 6144, 7168, 8192, 11264, 16384)] +
+                         [(255, 2816), (258, 2816)])
 def test_hadamard_quant_in_registers(B, M, I):
-    """The sizes with a kernel of their own: one row and a number that its workgroups' rows do not divide; rows at both
+    """Every order and block of the transform in registers (2816 only from 256 rows on): one row and a number that its workgroups' rows do not divide; rows at both
     ends of the exponent range take the division instead of the reciprocal.  Bound: an output is a sum of I terms in at
     most 15 + 41 roundings of 2^-24 (14 stages, 42 terms of H_44 one after the other), each relative to a partial sum that is
     no larger than the row's 2-norm times a few: 4e-6 of the row's maximum, as for the other sizes."""
