@@ -35,8 +35,9 @@ struct FrontRowsArgs {
   float* w;
 };
 
-// EB: experts of a wavefront at a time
-template <int TPW, int EB>
+constexpr int EB = 2;   // experts of a wavefront at a time
+
+template <int TPW>
 __global__ __launch_bounds__(kRowsThreads) void front_rows_kernel(const FrontRowsArgs p) {
   extern __shared__ float4 rows[];          // [TPW][H / 4]
   __shared__ float red[TPW][kRowsWaves];
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(kRowsThreads) void front_rows_kernel(const FrontRow
 
 template <int TPW>
 cq_status launch_front_rows(const FrontRowsArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((front_rows_kernel<TPW, 2>), dim3((a.T + TPW - 1) / TPW), dim3(kRowsThreads), (size_t)TPW * a.H * 4, s, a);
+  hipLaunchKernelGGL((front_rows_kernel<TPW>), dim3((a.T + TPW - 1) / TPW), dim3(kRowsThreads), (size_t)TPW * a.H * 4, s, a);
   return cq_check_launch();
 }
 

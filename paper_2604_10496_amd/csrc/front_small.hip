@@ -140,9 +140,10 @@ cq_status cq_front_small_launch(const float* partials, int ksplit, int T, int H,
                                 float* logits, int top_k, int32_t* topk_ids, float* topk_w, hipStream_t s) {
   const float qmax = (float)((1 << (act_bits - 1)) - 1);
   const int in_place = (partials == XR && ksplit == 1) ? 1 : 0;
-  const bool few = ksplit <= 4;   // (the rotation of few tokens: 2 or 4 parts; a part past the end costs a load)
-  auto kern = H <= 4 * kFrontThreads ? (few ? front_small_kernel<1, 3> : front_small_kernel<1, 15>)
-                                     : (few ? front_small_kernel<2, 3> : front_small_kernel<2, 15>);
+  // (a part past the end costs a load; the rotation of few tokens leaves 2 to 5 or 7 parts)
+  auto kern = H <= 4 * kFrontThreads
+                  ? (ksplit <= 4 ? front_small_kernel<1, 3> : ksplit <= 8 ? front_small_kernel<1, 7> : front_small_kernel<1, 15>)
+                  : (ksplit <= 4 ? front_small_kernel<2, 3> : front_small_kernel<2, 15>);
   hipLaunchKernelGGL(kern, dim3(T), dim3(kFrontThreads), 0, s, partials, ksplit, in_place, T, H, qmax, Wr, bias, E, XR, Q,
                      Q16, scale, logits, top_k, topk_ids, topk_w);
   return cq_check_launch();

@@ -188,7 +188,7 @@ __global__ __launch_bounds__(1024) void route_fused_kernel(const float* logits_i
     for (int i = tid; i < S * T; i += 1024) src_token[A + i] = i % T;
 }
 
-// The stable grouping alone, in one workgroup, for up to 16 * 64 * CH assignments and 128 experts: wavefront w takes a
+// The stable grouping alone, in one workgroup, for up to 16 * 64 * kGroupMaxChunks assignments and 128 experts: wavefront w takes a
 // contiguous run of them, 64 at a time; a running count per (wavefront, expert) in LDS and the ballot match masks give
 // every assignment its rank among the wavefront's assignments to the same expert, and the counts' exclusive prefix over
 // the wavefronts and over the experts gives the position.  One launch instead of the counting sort's three (histogram,
@@ -196,7 +196,6 @@ __global__ __launch_bounds__(1024) void route_fused_kernel(const float* logits_i
 // (One workgroup stores from one compute unit: 5 us at 4096 assignments, 12 us at 8192, 24 us at 16384; more than 4096 go to
 // group_chunks_kernel.)
 constexpr int kGroupMaxChunks = 4;
-template <int CH>
 __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__ ids, int T, int E, int k, int S,
                                                      int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
                                                      int32_t* __restrict__ inv_perm, int32_t* __restrict__ src_token) {
@@ -206,9 +205,9 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
   const int A = T * k;
   const int chunks = (A + 1023) / 1024;   // of 64 assignments, per wavefront
   const int a0 = wave * chunks * 64 + lane;
-  int id[CH], rank[CH];
+  int id[kGroupMaxChunks], rank[kGroupMaxChunks];
 #pragma unroll
-  for (int c = 0; c < CH; ++c) {
+  for (int c = 0; c < kGroupMaxChunks; ++c) {
     const int a = a0 + c * 64;
     id[c] = c < chunks && a < A ? ids[a] : -1;
   }
@@ -216,7 +215,7 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
   cq_wave_lds_fence();   // (a wavefront's own row)
   const uint64_t lt = lanemask_lt(lane);
 #pragma unroll
-  for (int c = 0; c < CH; ++c) {
+  for (int c = 0; c < kGroupMaxChunks; ++c) {
     if (c < chunks) {
       const bool valid = id[c] >= 0;
       uint64_t mask = __ballot(valid);
@@ -260,7 +259,7 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
   if (tid <= E) offsets[tid] = s_off[tid];
   for (int s = tid; s < S; s += 1024) offsets[E + s + 1] = A + (s + 1) * T;
 #pragma unroll
-  for (int c = 0; c < CH; ++c) {
+  for (int c = 0; c < kGroupMaxChunks; ++c) {
     const int a = a0 + c * 64;
     if (id[c] >= 0) {
       const int pos = s_off[id[c]] + s_cnt[wave][id[c]] + rank[c];
@@ -482,7 +481,7 @@ cq_status cq_permute_launch(const int32_t* topk_ids, int T, int E, int top_k, in
   const int n_assign = T * top_k;
   if (n_assign <= kGroupMostAssign && E <= kFusedMaxE) {
     if (n_assign <= 1024 * kGroupMaxChunks)
-      hipLaunchKernelGGL(group_kernel<kGroupMaxChunks>, dim3(1), dim3(1024), 0, s, topk_ids, T, E, top_k, n_shared,
+      hipLaunchKernelGGL(group_kernel, dim3(1), dim3(1024), 0, s, topk_ids, T, E, top_k, n_shared,
                          expert_offsets, perm, inv_perm, src_token);
     else
       hipLaunchKernelGGL(group_chunks_kernel, dim3((n_assign + kGroupChunk - 1) / kGroupChunk), dim3(1024), 0, s, topk_ids, T,
