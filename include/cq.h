@@ -107,7 +107,7 @@ typedef struct {
   const float* bias;  /* [E] or NULL                                                    */
   cq_codebook_weights gate_up; /* G = E+S, N = 2I (gate/up interleaved), K = H          */
   cq_codebook_weights down;    /* G = E+S, N = H, K = I                                 */
-  const void* R_split; /* optional: copy of R written by cq_rotation_split(); NULL if absent */
+  const void* R_split; /* optional: copy of R written by cq_rotation_split(); NULL: the rotation reads R in fp32 */
   int h_bits;          /* 0, or 4 / 8: online-Hadamard variant -- the intermediate h is multiplied by
                           H_I / sqrt(I) and quantized per row to h_bits before the down projection,
                           whose weights are then clustered in that rotated basis (cq_hadamard_quant) */
@@ -131,12 +131,13 @@ cq_status cq_rotate_quant(const float* X, const float* R, int T, int H, int act_
                           void* workspace, size_t workspace_bytes, cq_stream stream);
 
 /*
- * a1 for many tokens: a copy of R (AOS section) as two f16 planes, R = Rh + 2^-11 Rl, in the order the
- * matrix-core fragments are loaded in.  With it cq_moe_forward computes X R (for H % 256 == 0 and enough
- * tokens: from 64 at H = 4096, 129 at H = 2048, 513 at H = 1024) as Xh Rh + 2^-11 (Xh Rl + Xl Rh) on the f16
- * matrix cores with fp32 accumulation: every operand is represented to 2^-23 of its size and only the 2^-22
- * Xl Rl term is dropped, so the result is as accurate as the fp32 product and the codes still differ from an
- * exact evaluation only at rounding ties.
+ * a1 from a copy of R (AOS section) as two f16 planes, R = Rh + 2^-11 Rl, in the order the matrix-core fragments
+ * are loaded in.  With it cq_moe_forward computes X R as Xh Rh + 2^-11 (Xh Rl + Xl Rh) on the f16 matrix cores
+ * with fp32 accumulation where that is the faster: for up to 32 tokens at H = 1024, 1536, ... 4096 (64 at H = 1536 ..
+ * 2560), and with H % 256 == 0 for enough tokens (from 64 at H = 4096, 129 at H = 2048, 513 at H = 1024).  Every
+ * operand is represented to 2^-23 of its size and only the 2^-22 Xl Rl term is dropped; the sums are shorter than the
+ * fp32 kernel's, so that the result is no less accurate and the codes still differ from an exact evaluation only at
+ * rounding ties, though not at the same ones.  A layer whose R_split is NULL rotates in fp32 at every batch size.
  *   R [H,H] f32 device, H % 32 == 0; out: cq_rotation_split_bytes(H) bytes of device memory, owned by
  *   the caller, read by every later cq_moe_forward on a layer whose R_split points to it.
  */
@@ -179,7 +180,8 @@ cq_status cq_route_permute(const float* XR, const float* Wr, const float* bias, 
  *     out[m, n] = (row_scale ? row_scale[src(m)] : 1) * acc[m, n]          (CQ_EPI_NONE, N outputs)
  *     out[m, i] = SiLU(sc*acc[m,2i]) * (sc*acc[m,2i+1])                    (CQ_EPI_SWIGLU, N/2 outputs)
  *   Weights are never materialised: packed indices stream from HBM, are turned into centroid
- *   values through a table staged in LDS (the streaming kernel: small groups, and medium batches with a long K) or
+ *   values through a table staged in LDS (the streaming kernel: small groups, and batches of medium size where it
+ *   is the cheaper) or
  *   held in registers (the large-tile kernel: the others), and feed the matrix cores directly.  Integer codes and
  *   bf16 centroids are exact operands (bf16 MFMA, fp32 accumulation); CQ_A_F16 / CQ_A_F32 rows
  *   use f16 MFMA with centroids converted bf16 -> f16.

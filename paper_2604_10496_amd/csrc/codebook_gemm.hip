@@ -212,9 +212,10 @@ cq_status cq_gemm_codebook_launch(const cq_codebook_weights* W, const void* A, i
   const bool converts = a_kind == CQ_A_INT8_CODES || a_kind == CQ_A_F32;
   const bool half = large && cq_gemm_uses_half_tiles(W, M_total, converts || !row_gather ? M_total : a_rows);
   // Where large tiles run anyway, they take the small groups as well and the streaming launch falls away if that is the
-  // cheaper: with a short K always where it has not gone to passes above (DeepSeek-V2-Lite shape, gate/up + down at 40 tokens: 92 us against 105 us in two
-  // launches, Qwen3 shape 46 against 78), with a long one from 28 rows per group on (Mixtral shape at 64 tokens 245
-  // against 172 us, at 96 tokens 241 against 246, at 128 tokens the whole layer 290 against 302).
+  // cheaper: with a short K always where the batch does not stream in passes (gate/up + down at 40 tokens, before they did:
+  // DeepSeek-V2-Lite shape 92 us against 105 us in two launches, Qwen3 shape 46 against 78), with a long one from 28 rows per
+  // group on (Mixtral shape at 64 tokens 245 against 172 us, at 96 tokens 241 against 246, at 128 tokens the whole layer 290
+  // against 302).
   const bool no_small = blockwise || (half && (W->K <= 2048 || (long)M_total >= 28L * W->G)) ||
                         (large && !half && (long)M_total >= 384L * W->G);
   const int small_max = no_small ? 0 : kSmallMaxRows;

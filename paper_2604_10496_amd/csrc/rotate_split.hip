@@ -555,7 +555,9 @@ cq_status launch_few_tokens(const RotFewArgs& a, hipStream_t s) {
 
 // Sub-steps of 16 k per wavefront of the kernel for few tokens, 0: not taken.  Layer of 8 small experts, fp32 kernel / this
 // one, us at 1, 16 and 32 tokens: H = 1024 26.4 / 25.7, 27.4 / 26.9, 29.9 / 29.7; 2048 30.0 / 28.0, 32.3 / 30.0, 35.0 / 32.5;
-// 3072 38.7 / 36.0, 43.4 / 42.0, 50.0 / 47.4; 4096 45.6 / 41.1, 49.7 / 46.0, 53.8 / 51.2; 8192 86 / 86, 91 / 95, 116 / 123.
+// 3072 38.7 / 36.0, 43.4 / 42.0, 50.0 / 47.4; 4096 45.6 / 41.1, 49.7 / 46.0, 53.8 / 51.2.  Wider ones keep the fp32 operands: from
+// 6144 on they lose (61.9 / 64.0, 67.5 / 71.8, 80.3 / 86.7; 8192 86 / 86, 91 / 95, 116 / 123), and between them the gain is 3 % and
+// not at every width (4608 50.0 / 47.7, 55.7 / 53.4, 69.2 / 69.1; 5120 52.5 / 52.1, 58.4 / 59.7; 5632 56.4 / 54.6, 63.2 / 60.5).
 // 33 and 64 tokens: H = 1024 31.1 / 32.2, 34.1 / 35.2; 1536 35.5 / 34.2, 40.2 / 36.8; 2560 51.4 / 48.4, 59.6 / 54.6; 4096
 // 170.8 / 171.2 at 40 tokens of the Mixtral shape.  Whole layers at 1 and 16 tokens: Mixtral shape 72.8 / 67.5, 149.7 / 144.0; DeepSeek-V2-Lite shape
 // 46.9 / 42.9, 85.3 / 80.0.

@@ -1345,7 +1345,8 @@ def test_layer_reduced_shapes(B, name, over):
 @pytest.mark.parametrize("name,over", [
     ("mixtral_decode", dict(H=4096, I=64, T=64, E=4)),              # one token tile, 16 K parts, decode front end
     ("mixtral_decode", dict(H=4096, I=64, T=129, E=4)),             # a second tile of one token
-    ("dsv2lite", dict(H=2048, I=64, T=130, E=32)),                  # quantization in a launch of its own, 8 parts
+    ("dsv2lite", dict(H=2048, I=64, T=130, E=32)),                  # 8 parts, added in front of logits and top-k
+    ("dsv2lite", dict(H=2048, I=64, T=130, E=130)),                 # ... in a launch that only quantizes (more than 128 experts)
     ("dsv2lite", dict(H=1024, I=64, T=520, E=32)),                  # ... 4 parts
 ])
 def test_layer_rotation_in_k_parts(B, name, over):
