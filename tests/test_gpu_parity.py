@@ -314,6 +314,31 @@ def test_quantize_rows_in_registers(B, H, bits):
     assert np.array_equal(out["Q"].cpu().numpy().astype(np.float32), np.clip(np.rint(X / s[:, None]), -qmax, qmax))
 
 
+@pytest.mark.parametrize("bits", [4, 8])
+def test_quantize_scales_with_significands_of_ones(B, bits):
+    """Rows whose scale has a significand of 24 ones, or one next to it: one Newton step does not round that reciprocal
+    correctly.  Their entries lie within two units in the last place of the rounding ties; the codes are those of the IEEE
+    quotient."""
+    qmax, T, H = np.float32(2 ** (bits - 1) - 1), 300, 256
+    rng = np.random.default_rng(bits)
+    X = np.zeros((T, H), dtype=np.float32)
+    ones = 0
+    for t in range(T):
+        want = ((np.uint32(100 + t % 40) << np.uint32(23)) | np.uint32(0x7fffff - (t // 40) % 3)).view(np.float32)
+        top = np.float32(want * qmax)
+        top = next((c for c in (top, np.nextafter(top, np.float32(0)), np.nextafter(top, np.float32(np.inf)))
+                    if np.float32(c / qmax) == want), top)
+        ones += (np.float32(top / qmax).view(np.uint32) & 0x7fffff) == 0x7fffff
+        tie = ((rng.integers(-int(qmax), int(qmax), H) + 0.5) * np.float64(want)).astype(np.float32)
+        X[t] = (tie.view(np.int32) + rng.integers(-2, 3, H).astype(np.int32)).view(np.float32)
+        X[t, t % H] = top
+    assert ones >= 40
+    out = B.cq_rotate_quant(_dev(X), _dev(np.eye(H, dtype=np.float32)), bits)
+    s = np.abs(X).max(axis=1) / qmax
+    assert np.array_equal(out["scale"].cpu().numpy(), s)
+    assert np.array_equal(out["Q"].cpu().numpy().astype(np.float32), np.clip(np.rint(X / s[:, None]), -qmax, qmax))
+
+
 # ---------------------------------------------------------------------------------------------
 # routing and permutation: bit-exact
 # ---------------------------------------------------------------------------------------------
