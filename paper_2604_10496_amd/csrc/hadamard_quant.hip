@@ -164,6 +164,9 @@ __global__ __launch_bounds__(kHadThreads) void hadamard_quant_kernel(const float
 // a graph, 16 and 4096 rows: 1024 3.9 / 3.5 and 18.5 / 8.4, 1536 4.3 / 3.8 and 21.9 / 12.1, 1792 5.2 / 4.8 and 29.7 / 13.3, 3072
 // 5.0 / 3.8 and 33.8 / 19.2, 3584 6.7 / 5.6 and 45.6 / 23.9, 5632 9.7 / 8.6 and 86.5 / 39.4, 6144 7.3 / 5.3 and 63.4 / 40.3, 7168
 // 8.3 / 5.7 and 70.9 / 42.4, 8192 9.7 / 5.2 and 92.5 / 52.8, 11264 12.6 / 8.8 and 153.7 / 85.9, 16384 16.0 / 6.1 and 202.9 / 112.7.
+// Error against float64 over 17 of the widths, 1024 rows and six draws each, general kernel / this one: 0.85e-7 .. 1.48e-7 /
+// 0.85e-7 .. 1.47e-7 in the 2-norm and no larger at any width; largest, of a row's maximum, 1.8e-7 .. 5.4e-7 / 1.9e-7 .. 2.8e-7;
+// codes on the other side of a rounding tie than float64's, of 561 million, 119 / 108 (4 bits) and 2080 / 1954 (8 bits).
 //
 // Step 2 across lanes.  With s_j the sign of bit j of the lane and P_j the exchange of lanes that differ in it, a stage is
 // v <- s_j v + P_j v.  On x = (product of all s_j) v it becomes x <- x - s_j P_j x, one multiply-add on a moved operand, and

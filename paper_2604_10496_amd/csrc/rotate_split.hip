@@ -564,7 +564,7 @@ cq_status launch_few_tokens(const RotFewArgs& a, hipStream_t s) {
 // Error of X_R against float64, 2-norm (and largest, of the row's maximum), fp32 kernel / this one: H = 1024 1.6e-7 / 1.2e-7
 // (6.4e-7 / 4.0e-7), 2048 2.2e-7 .. 2.9e-7 / 1.2e-7 (1.1e-6 / 4.3e-7), 3072 2.5e-7 .. 3.2e-7 / 1.3e-7 (1.6e-6 / 4.0e-7), 4096
 // 2.9e-7 .. 4.2e-7 / 1.5e-7 (1.5e-6 / 5.0e-7), and smaller at every width and batch.  8-bit codes that lie on the other side
-// of a rounding tie than float64's, over 49 million of them at all widths: 445 / 213.  Which code of which call that is
+// of a rounding tie than float64's, over 49 million of them at all widths: 452 / 213.  Which code of which call that is
 // depends on the inputs: a single call can be further from float64 on either path.
 static int few_steps(int T, int H) {
   if (H % 512 != 0 || H < 1024 || H > 4096 || T > 64) return 0;
