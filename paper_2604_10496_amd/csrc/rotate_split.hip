@@ -473,15 +473,17 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
     }
     // MFMA 16x16 output: register v of a lane holds column (of R) 4*(lane/16) + v, token lane%16
     auto val = [&](float a, float l) { return pow2[0] * fmaf(l, kLoUnscale, a); };
+    if (__float_as_uint(pow2[0]) != 0x7f800000u) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      lds[(wave * 2 + h) * 64 + lane] = make_float4(val(acc[h][0], low[h][0]), val(acc[h][1], low[h][1]),
-                                                    val(acc[h][2], low[h][2]), val(acc[h][3], low[h][3]));
-    if (__float_as_uint(pow2[0]) == 0x7f800000u)
+      for (int h = 0; h < 2; ++h)
+        lds[(wave * 2 + h) * 64 + lane] = make_float4(val(acc[h][0], low[h][0]), val(acc[h][1], low[h][1]),
+                                                      val(acc[h][2], low[h][2]), val(acc[h][3], low[h][3]));
+    } else {
 #pragma unroll 1
       for (int i = 0; i < 8; ++i)
         few_lds[((wave * 2 + (i >> 2)) * 64 + lane) * 4 + (i & 3)] =
             few_fp32(p, nb, j0, N * 16, min(tcol, p.T - 1), (i >> 2) * 16 + (lane >> 4) * 4 + (i & 3));
+    }
     __syncthreads();
     if (tid >= 128) return;
     if (tcol < p.T)
@@ -512,14 +514,16 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb) {
     auto val = [&](int i) { return pow2[tb] * fmaf(low[tb][i], kLoUnscale, acc[tb][i]); };
+    if (__float_as_uint(pow2[tb]) != 0x7f800000u) {
 #pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
-      lds[((wave * TB + tb) * 4 + vb) * 64 + lane] = make_float4(val(4 * vb), val(4 * vb + 1), val(4 * vb + 2), val(4 * vb + 3));
-    if (__float_as_uint(pow2[tb]) == 0x7f800000u)
+      for (int vb = 0; vb < 4; ++vb)
+        lds[((wave * TB + tb) * 4 + vb) * 64 + lane] = make_float4(val(4 * vb), val(4 * vb + 1), val(4 * vb + 2), val(4 * vb + 3));
+    } else {
 #pragma unroll 1
       for (int i = 0; i < 16; ++i)
         few_lds[(((wave * TB + tb) * 4 + (i >> 2)) * 64 + lane) * 4 + (i & 3)] =
             few_fp32(p, nb, j0, N * 16, min(tb * 32 + r32, p.T - 1), (i >> 2) * 8 + g2 * 4 + (i & 3));
+    }
   }
   __syncthreads();
 #pragma unroll
