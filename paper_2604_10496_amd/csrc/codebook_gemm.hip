@@ -49,7 +49,7 @@ int row_bound(int M_total, int max_group_rows) {
 // 151 / 144 (256: 167 / 178).
 // But a unit of 64 weight rows costs a workgroup about 1.2 us + 0.5 us per 1024 of K (its table, and eight wavefronts' sums
 // to add up), a tile of 256 of them 2 us + 9.5 us per 1024 of K in a round of 512: the shorter K, the fewer units may come
-// one after the other on a workgroup.  Up to K / 256 of them passes are still the cheaper (tiles / passes, us: K = 256 4 groups
+// one after the other on a workgroup.  Up to (K + 64) / 256 of them passes are still the cheaper (tiles / passes, us: K = 256 4 groups
 // x 2048 of 56 rows 6.3 / 5.5, 53 of them in one group 6.9 / 7.3, 8 x 8192 of 112 rows 7.0 / 10.4; K = 512 8 x 2048 of 112
 // rows 8.6 / 5.9, 8 x 8192 9.7 / 11.1, 64 x 2048 of 384 rows 17.7 / 23.3; K = 768 16 x 2048 of 96 rows 10.9 / 8.3, 128 x 2048
 // of 264 uneven rows 21.6 / 26.7; K = 1024 8 x 4096 of 112 rows 13.3 / 9.7, 32 x 4096 of 256 rows 26.8 / 27.5).  K = 2048 always gains (DeepSeek-V2-Lite shape 33 and 128 tokens 55.6 / 45.6 and 61.2 / 58.8,
@@ -59,7 +59,7 @@ int row_bound(int M_total, int max_group_rows) {
 bool short_k_in_passes(const cq_codebook_weights* W, int M_total) {
   const long groups = W->G < M_total ? W->G : M_total;
   if (W->K >= 2048 || (W->K >= 1408 && groups * (W->N / 256) > 640)) return true;
-  return W->K >= 256 && (groups + M_total / cq_route::kPassRows) * (W->N / 64) <= W->K;
+  return W->K >= 256 && (groups + M_total / cq_route::kPassRows) * (W->N / 64) <= W->K + 64;
 }
 long rows_in_passes(const cq_codebook_weights* W) { return (cq_tables_per_row(W) > 1 ? 23L : 28L) * W->G; }
 bool streams_in_passes(const cq_codebook_weights* W, int M_total, int max_group_rows) {

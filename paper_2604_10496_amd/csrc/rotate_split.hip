@@ -383,8 +383,7 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
   constexpr bool HALF = TB_ == 0;
   constexpr int TB = HALF ? 1 : TB_;
   constexpr int NX = HALF ? N / 2 : N;  // activation fragments of a lane
-  constexpr int kMost = HALF ? 16 : 8;
-  constexpr int D = N < kMost ? N : kMost;   // sub-steps of R in flight (2 KiB each)
+  constexpr int D = N < 8 ? N : 8;      // sub-steps of R in flight (2 KiB each)
   extern __shared__ float few_lds[];   // [wavefront][token block][quad of columns][lane] float4
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r32 = lane & 31, g2 = lane >> 5;
@@ -397,6 +396,9 @@ __global__ __launch_bounds__(64 * kFewWaves, 1) void rot_few_kernel(const RotFew
     ring[d][0] = frag[(size_t)d * 128];
     ring[d][1] = frag[(size_t)d * 128 + 64];
   }
+  // (the loads of R stay in front of the conversion of X, where the compiler leaves 4 of them otherwise: H = 4096, 8 and 16
+  // tokens 44.5 -> 43.6 and 46.5 -> 45.5 us per layer, with sixteen in flight 45.3 and 47.6; the shorter slices gain nothing)
+  if constexpr (HALF && N == 16) __builtin_amdgcn_sched_barrier(0);
   // this lane's activations: token r32 of every block, values 8 g2 .. + 7 of every sub-step, as f16 planes
   // (HALF: token lane%16, of every pair of sub-steps the values 8 (lane/32) .. + 7 of sub-step lane/16%2)
   cq_v4u xh[TB][NX], xl[TB][NX];

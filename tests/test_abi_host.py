@@ -159,9 +159,9 @@ def test_a_workspace_serves_every_smaller_batch(name, over):
 
 
 @pytest.mark.parametrize("G,N,K,rows,passes", [
-    # K = 256 units of 64 weight rows are as many as a product of K = 256 may have: (groups + rows / 32) x N / 64
-    (4, 2048, 256, 100, True), (8, 4096, 256, 66, False), (4, 1024, 128, 66, False), (16, 16384, 256, 66, False),
-    (8, 4096, 512, 66, False), (8, 2048, 512, 66, True), (32, 1024, 512, 132, False), (64, 2048, 512, 198, False),
+    # a product of K = 256 may have 320 units of 64 weight rows: (groups + rows / 32) x N / 64
+    (4, 2048, 256, 100, True), (8, 2048, 256, 66, True), (8, 2048, 256, 128, False), (8, 4096, 256, 66, False), (4, 1024, 128, 66, False), (16, 16384, 256, 66, False),
+    (8, 4096, 512, 66, False), (8, 2048, 512, 66, True), (32, 1024, 512, 132, True), (32, 1024, 512, 256, False), (64, 2048, 512, 198, False),
     (8, 4096, 1024, 128, True), (128, 2048, 768, 264, False), (16, 1536, 1024, 200, True), (17, 2048, 1024, 480, False),
     (66, 2816, 1408, 512, True), (128, 4096, 1408, 512, True), (66, 2048, 1408, 512, False), (80, 2048, 1408, 480, False),
     (82, 2048, 1408, 480, True), (8, 2048, 1408, 200, True), (128, 1536, 2048, 1024, True), (8, 2048, 2048, 224, False),
