@@ -7,11 +7,13 @@
 //   * a lane owns one row of each of its two 32-row blocks for the whole K loop, so the two 16-entry
 //     centroid tables it needs are loop invariant and live in registers.  Decoding is pure vector ALU:
 //     nibbles become byte selectors, v_perm_b32 picks the low and the high bytes of the centroids out
-//     of register-resident byte tables (two 8-entry halves; a third perm, steered by bit 3 of the
-//     index, picks between them), one or two more perm levels interleave the bytes into bf16/f16 pairs.
-//     About 1.4 ALU operations per MFMA at 256 tokens, mostly hidden behind the matrix pipe (with two wavefronts on a
-//     SIMD v_perm_b32 and the other three-operand operations take 4.6 clocks, two-operand ones 4.1, an MFMA about 10 of the
-//     issue beside them: 184 operations per step and wavefront are what half tiles of up to 64 tokens wait for);
+//     of register-resident byte tables (two 8-entry halves, xored: cq_decode.h), one or two more perm levels
+//     interleave the bytes into bf16/f16 pairs.
+//     About 1.3 ALU operations per MFMA at 256 tokens, mostly hidden behind the matrix pipe (with two wavefronts on a
+//     SIMD v_perm_b32 and the other three-operand operations take 4.4 clocks, two-operand ones 2.7, an MFMA about 8 of the
+//     issue beside six or more of them: 168 operations per step and wavefront).  What the launches wait for is power: the
+//     clock falls from 2.3 GHz for 64 workgroups to 1.5..1.9 for 512, four wavefronts per SIMD instead of two (32 rows
+//     each) take fewer clocks and the same time, and activations of zero 10 to 21 % less of it;
 //     With block-wise tables (one per group of g weights along K, g a multiple of 512) the two tables are
 //     replaced every g/64 steps; the raw tables of the next group are requested one group ahead;
 //   * LDS holds only the activation tiles.  They arrive by direct global->LDS loads (no staging
@@ -279,10 +281,8 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   constexpr int kValu = !A32 || C >= 8 ? 4 : C == 4 ? 6 : 12;
   cq_v4u af[2][2];
   cq_v4u bfr[C];
-  uint32_t ident = 0x03020100u;   // kept in a vector register (see decode8)
-  asm volatile("" : "+v"(ident));
-  af[0][0] = decode8<PRE>(wq[0][0][0], t0, ident);
-  af[0][1] = decode8<PRE>(wq[0][1][0], t1, ident);
+  af[0][0] = decode8<PRE>(wq[0][0][0], t0);
+  af[0][1] = decode8<PRE>(wq[0][1][0], t1);
 #pragma unroll
   for (int cb = 0; cb < C; ++cb) bfr[cb] = read_b(0, 0, cb);
 
@@ -327,8 +327,8 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
         else if (jj < C) fetch_tile(s3, (par + D - 1) & (D - 1), jj, 1);
         // next sub-step: jj + 1 of this step, or the first one of the next step
         const int nbuf = jj < 3 ? par : (par + 1) & (D - 1), njj = (jj + 1) & 3;
-        af[nxt][0] = decode8<PRE>(wq[nbuf][0][njj], t0, ident);
-        af[nxt][1] = decode8<PRE>(wq[nbuf][1][njj], t1, ident);
+        af[nxt][0] = decode8<PRE>(wq[nbuf][0][njj], t0);
+        af[nxt][1] = decode8<PRE>(wq[nbuf][1][njj], t1);
 #pragma unroll
         for (int cb = 0; cb < C; ++cb) {
           const cq_v4u b = bfr[cb];

@@ -730,6 +730,37 @@ def test_gemm_streaming_workgroups_by_active_groups(B, G, N, K, rows, prepacked)
                 assert np.array_equal(out[at].astype(np.float64), ref), f"group {g}"
 
 
+@pytest.mark.parametrize("blockwise", [False, True])
+@pytest.mark.parametrize("prepacked", [True, False])
+@pytest.mark.parametrize("a_kind", ["bf16", "f16"])
+def test_gemm_tiles_decode_any_table(B, a_kind, prepacked, blockwise):
+    """The large-tile kernel's register decoding: rows of a unit matrix as activations read single centroids out of tables of
+    random bit patterns (every sign of either byte of an entry, all 16 indices), which must come back bit for bit.
+    (Finite, and normal numbers in f16, which the f16 rows' tables are converted to.)"""
+    import torch
+    rng = np.random.default_rng(31 + 2 * blockwise)
+    G, N, K, g = 3, 256, 1024 if blockwise else 128, 512 if blockwise else 0
+    nblk = K // g if g else 1
+    exp = rng.integers(115, 140, (G, N, nblk, 16))
+    cent = ((rng.integers(0, 2, exp.shape) << 15) | (exp << 7) | rng.integers(0, 128, exp.shape)).astype(np.uint16)
+    idx = rng.integers(0, 256, (G, N, K // 2), dtype=np.uint8)
+    W = B.DeviceCodebook(idx, cent if blockwise else cent[:, :, 0], prepack=prepacked, group_k=g)
+    rows = 128
+    ks = np.concatenate([rng.permutation(K)[:rows] for _ in range(G)])
+    A = np.zeros((G * rows, K), dtype=np.float32)
+    A[np.arange(G * rows), ks] = 1.0
+    A = _dev(A).to(torch.bfloat16 if a_kind == "bf16" else torch.float16)
+    off = _dev(_group_offsets([rows] * G))
+    out = B.cq_codebook_grouped_gemm(W, A, B.CQ_A_BF16 if a_kind == "bf16" else B.CQ_A_F16, None, None, off, G * rows,
+                                     B.CQ_EPI_NONE, B.CQ_OUT_F32, use_prepacked=prepacked).cpu().numpy()
+    n = np.arange(N)
+    for m in range(G * rows):
+        grp, k = m // rows, ks[m]
+        nib = (idx[grp, :, k // 2] >> (4 * (k % 2))) & 15
+        want = (cent[grp, n, k // g if g else 0, nib].astype(np.uint32) << 16).view(np.float32)
+        assert np.array_equal(out[m], want), (grp, k)
+
+
 @pytest.mark.parametrize("gathered", [False, True])
 @pytest.mark.parametrize("N,K,counts", [
     (512, 256, [1, 32, 33, 64, 65, 96, 97, 128, 129, 0, 192, 193, 225, 257]),   # half tiles: edges of the three widths
