@@ -278,7 +278,7 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   // vector ALU operations per MFMA that the scheduler is asked for: in half tiles two decode8 calls per 2 C MFMAs.  (Whole
   // tiles have no second workgroup on the compute unit whose products could run under the decoding: four per MFMA also
   // where the tile is narrow; block-wise tables, gate/up + down at 96 tokens 350 -> 344 us, at 200 tokens 400 -> 396.)
-  constexpr int kValu = !A32 || C >= 8 ? 4 : C == 4 ? 6 : 12;
+  constexpr int kValu = !A32 || C >= 8 ? 4 : C == 4 ? 6 : C == 1 ? 21 : 12;
   cq_v4u af[2][2];
   cq_v4u bfr[C];
   af[0][0] = decode8<PRE>(wq[0][0][0], t0);
@@ -532,9 +532,8 @@ struct tile_map {
 // leave most of the chip idle.  Two forms:
 //   * whole tiles, 256 / 128 / 64 tokens, one workgroup per compute unit (all 512 registers of a lane, four or eight
 //     activation tiles in LDS): a decoded weight serves up to 256 tokens.  Bound by the matrix cores and by power;
-//   * half tiles, 128 / 96 / 64 tokens (HALF), 256 registers and at most half the LDS, so that TWO workgroups share a
-//     compute unit and one's barriers, waits, decoding and epilogue run under the other's matrix work.  (A tile of 32
-//     would cost what one of 64 does: decoding its weights takes longer than either's products.)
+//   * half tiles, 128 / 96 / 64 (or 32) tokens (HALF), 256 registers and at most half the LDS, so that TWO workgroups share a
+//     compute unit and one's barriers, waits, decoding and epilogue run under the other's matrix work.
 //     gate/up + down of the Mixtral shape at 128 rows per group 314 + 172 -> 275 + 148 us, of DeepSeek-V2-Lite's at
 //     48 rows per group (two launches before, of the streaming kernel and of whole tiles) 203 -> 134 us.
 // cq_gemm_uses_half_tiles has the rule between the two.
@@ -578,9 +577,18 @@ __global__ __launch_bounds__(256, HALF ? 2 : 1) void gemm_large_kernel(const Lar
     return;
   }
   slot -= s1;
-  if (slot < s2 && item(2, map.kS1))
-    large_tile<F16, EPI, OUTK, W::w2 / 32, kDeep, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS1,
-                                                                  p.tail_abs ? row0 : p.tail_rows1 + tile * W::w2);
+  if (slot >= s2 || !item(2, map.kS1)) return;
+  const int tail_row = p.tail_abs ? row0 : p.tail_rows1 + tile * W::w2;
+  if constexpr (HALF) {
+    // (up to 32 rows: decoding a tile's weights takes longer than the products of 64 tokens, but those cost power, which is
+    // what a full launch is bound by; 66 groups of 20 rows x 2816 x 2048 60.5 -> 57.0 us, x 2048 x 1408 42.8 -> 41.1.  Rows
+    // of zeros in place of the missing ones, in wider tiles, gained 2 % at 33 of 64 rows and lost 1 % at 46 and 64)
+    if (cnt <= 32) {
+      large_tile<F16, EPI, OUTK, 1, kDeep, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS1, tail_row);
+      return;
+    }
+  }
+  large_tile<F16, EPI, OUTK, W::w2 / 32, kDeep, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS1, tail_row);
 }
 
 // out[row] += slice 0 + slice 1 + ... of the tiles' K parts, in that order (see LargeArgs::tail_part).
