@@ -110,14 +110,15 @@ constexpr int epilogue_row_stride(int epi, int outk) {
   return row + (quad == 16 ? 16 : 8);
 }
 
-// One tile: 256 weight rows (row tile rt) x up to 32*C tokens (rows mrow0 .. mrow0+mcnt-1 of group grp).
+// One tile: 128 * RB weight rows (row tile rt of that height) x up to 32*C tokens (rows mrow0 .. mrow0+mcnt-1 of group
+// grp); each wavefront owns RB blocks of 32 rows.
 // F16: the activations are f16 (else bf16); C = CT/32 token blocks (8, 4, 3, 2 or 1); D = depth of the load
 // pipeline in K steps (a power of two; narrow tiles spend less matrix time per step and need more).
 // BLK: block-wise centroid tables (p.nblk per row, each serving p.gsteps K steps).  PRE: the indices are the
 // prepacked copy (whose nibble arrangement decodes with four operations fewer per 8 weights).
 // kz / kS: this workgroup takes part kz of kS equal parts of K (narrow tiles of a plain fp32 product; 0 / 1
 // otherwise) and, for kz > 0, stores at row tail_row0 of slice kz-1 of p.tail_part instead of p.out.
-template <bool F16, int EPI, int OUTK, int C, int D, bool BLK, bool PRE, bool A32 = false>
+template <bool F16, int EPI, int OUTK, int C, int D, bool BLK, bool PRE, bool A32 = false, int RB = 2>
 __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, const int mrow0_, const int mcnt_,
                                            const int rt_, const int kz_ = 0, const int kS_ = 1, const int tail_row0 = 0) {
   // (uniform, but derived per work item: kept in scalar registers from here on)
@@ -126,6 +127,8 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   const int kz = __builtin_amdgcn_readfirstlane(kz_), kS = __builtin_amdgcn_readfirstlane(kS_);
   constexpr bool kTail = !BLK && EPI == CQ_EPI_NONE && OUTK == CQ_OUT_F32;
   constexpr int CT = 32 * C;
+  constexpr int kRows = 128 * RB;
+  static_assert(RB == 2 || (RB == 1 && !BLK), "tiles of 128 rows have one table per row");
   constexpr uint32_t kBufBytes = CT * kStepBytes;  // one activation tile: CT tokens x 128 bytes
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -133,7 +136,7 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   const int r32 = lane & 31, g2 = lane >> 5;
   const int N = p.N, K = p.K;
   const size_t rowbytes = (size_t)K >> 1;
-  const int n0 = rt * kLargeRows + wave * 64;  // this wavefront's 64 rows
+  const int n0 = rt * kRows + wave * (32 * RB);  // this wavefront's rows
   // index loads: a uniform base per row block and step, plus this lane's offset of its 16 bytes (of row r32 of the block)
   const uint8_t* wp0 = p.idx + ((size_t)grp * N + n0) * rowbytes;
   const uint8_t* wp1 = wp0 + 32 * rowbytes;
@@ -159,9 +162,11 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   const int blk0 = BLK ? sb / p.gsteps : 0;                                     // first table group of the K range
   const uint32_t crow_off = ((uint32_t)(n0 + r32) * nblk + blk0) * (CQ_N_CENTROIDS * 2);  // row r32's first table, bytes
   const uint32_t crow_skip = 32u * nblk * (CQ_N_CENTROIDS * 2);                // from row r32 to row 32 + r32
-  RowTable t0 = make_row_table<F16>(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(cgrp) + crow_off));
-  RowTable t1 = make_row_table<F16>(
-      reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(cgrp) + crow_off + crow_skip));
+  RowTable tab[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+    tab[rb] = make_row_table<F16>(
+        reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(cgrp) + crow_off + rb * crow_skip));
   // Block-wise tables: the raw centroids of the next group of weights wait in LDS above the activation
   // tiles, 2 KiB per wavefront and parity of the group (two direct-to-LDS loads: lane (r32, g2) moves half
   // g2 of the 32-byte table of row r32, then of row 32 + r32), and become register tables when that group
@@ -212,10 +217,10 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
         else load_global_to_lds(buf * kBufBytes + lds_wave + i * 1024, ap[i] + o);
       }
   };
-  auto fetch_weights = [&](cq_v4u (&w)[2], int s) {
+  auto fetch_weights = [&](cq_v4u (&w)[RB], int s) {
     const size_t o = (size_t)s * sstride;
     load_global_async_s<0>(w[0], wp0 + o, woff);
-    load_global_async_s<0>(w[1], wp1 + o, woff);
+    if constexpr (RB == 2) load_global_async_s<0>(w[1], wp1 + o, woff);
   };
   // fragment read: lane (token r32 of block cb, k group g2) wants chunk g2*4 + jj of sub-step jj
   const uint32_t boff = (uint32_t)r32 * kStepBytes + ((uint32_t)((g2 * 4) ^ ((r32 >> 1) & 7)) << 4);
@@ -235,9 +240,9 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
     return lds_read_u128(bx[buf / kSetBufs][jj] + (uint32_t)(buf % kSetBufs) * kBufBytes + cb * 32 * kStepBytes);
   };
 
-  cq_v16f acc[2][C];
+  cq_v16f acc[RB][C];
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int cb = 0; cb < C; ++cb)
 #pragma unroll
@@ -250,12 +255,12 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   // of step s+1 already reads from it.  The barrier also retires tile s, which the requests of step
   // s+1 overwrite.  Loads thus have D-2 full steps to arrive (two steps = about 2 us for 256 tokens).
   // vector-memory loads a wavefront issues per step: the wait counts below depend on it
-  constexpr int kPerStep = C + 2;  // C tile loads + 2 weight loads
+  constexpr int kPerStep = C + RB;  // C tile loads + RB weight loads
   constexpr int kInFlight = (D - 3) * kPerStep;
   static_assert(D >= 4 && (D & (D - 1)) == 0 && kInFlight < 64, "ring depth / vmcnt range");
   static_assert(2 * kPerStep > 2 && kInFlight + kPerStep + 2 < 64,
                 "the waits of D - 1 steps retire the table loads before they are used");
-  cq_v4u wq[D][2];
+  cq_v4u wq[D][RB];
 #pragma unroll
   for (int i = 0; i < D - 1; ++i) {
     // (block-wise tables: the first request for tables sits where the loop's requests will sit, in front
@@ -266,7 +271,8 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
     fetch_weights(wq[i], min(i, nS - 1));
     fetch_tile(min(i, nS - 1), i, 0, C);
   }
-  vm_wait<kInFlight>(wq[0][0], wq[0][1], wq[1][0], wq[1][1]);
+  if constexpr (RB == 2) vm_wait<kInFlight>(wq[0][0], wq[0][1], wq[1][0], wq[1][1]);
+  else vm_wait<kInFlight>(wq[0][0], wq[1][0]);
   __syncthreads();
 
   // Software pipeline over the 16-wide K sub-steps.  While the matrix cores work through the 2*C MFMAs
@@ -279,10 +285,10 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   // tiles have no second workgroup on the compute unit whose products could run under the decoding: four per MFMA also
   // where the tile is narrow; block-wise tables, gate/up + down at 96 tokens 350 -> 344 us, at 200 tokens 400 -> 396.)
   constexpr int kValu = !A32 || C >= 8 ? 4 : C == 4 ? 6 : C == 1 ? 21 : 12;
-  cq_v4u af[2][2];
+  cq_v4u af[2][RB];
   cq_v4u bfr[C];
-  af[0][0] = decode8<PRE>(wq[0][0][0], t0);
-  af[0][1] = decode8<PRE>(wq[0][1][0], t1);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) af[0][rb] = decode8<PRE>(wq[0][rb][0], tab[rb]);
 #pragma unroll
   for (int cb = 0; cb < C; ++cb) bfr[cb] = read_b(0, 0, cb);
 
@@ -311,8 +317,8 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
               const cq_v4u b0 = lds_read_u128(at + 1024), b1 = lds_read_u128(at + 1536);
               uint32_t r0[8] = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
               uint32_t r1[8] = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
-              t0 = make_row_table<F16>(r0);
-              t1 = make_row_table<F16>(r1);
+              tab[0] = make_row_table<F16>(r0);
+              tab[1] = make_row_table<F16>(r1);
               ++blk_next;
               switch_at += p.gsteps;
             }
@@ -327,27 +333,29 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
         else if (jj < C) fetch_tile(s3, (par + D - 1) & (D - 1), jj, 1);
         // next sub-step: jj + 1 of this step, or the first one of the next step
         const int nbuf = jj < 3 ? par : (par + 1) & (D - 1), njj = (jj + 1) & 3;
-        af[nxt][0] = decode8<PRE>(wq[nbuf][0][njj], t0);
-        af[nxt][1] = decode8<PRE>(wq[nbuf][1][njj], t1);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) af[nxt][rb] = decode8<PRE>(wq[nbuf][rb][njj], tab[rb]);
 #pragma unroll
         for (int cb = 0; cb < C; ++cb) {
           const cq_v4u b = bfr[cb];
-          acc[0][cb] = mfma_large<F16>(af[cur][0], b, acc[0][cb]);
-          acc[1][cb] = mfma_large<F16>(af[cur][1], b, acc[1][cb]);
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) acc[rb][cb] = mfma_large<F16>(af[cur][rb], b, acc[rb][cb]);
           bfr[cb] = read_b(nbuf, njj, cb);
         }
 #pragma unroll
-        for (int i = 0; i < 2 * C; ++i) {
+        for (int i = 0; i < RB * C; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                   // one MFMA
           __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);               // vector ALU operations
-          if (i % 2 == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+          if (i % RB == RB - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
         }
         __builtin_amdgcn_sched_barrier(0);
       }
       // (block-wise tables: the two table requests of a pass's last step are younger than what the waits
       // of that step and of the next D - 4 steps are for, and may stay in flight as well)
       // (par is a constant once the loop is unrolled: no branch is left here)
-      if (BLK && (par == D - 1 || par <= D - 5))
+      if constexpr (RB == 1)
+        vm_wait<kInFlight>(wq[(par + 2) & (D - 1)][0]);
+      else if (BLK && (par == D - 1 || par <= D - 5))
         vm_wait<kInFlight + 2>(wq[(par + 2) & (D - 1)][0], wq[(par + 2) & (D - 1)][1]);
       else
         vm_wait<kInFlight>(wq[(par + 2) & (D - 1)][0], wq[(par + 2) & (D - 1)][1]);
@@ -364,14 +372,14 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   // now) 64 tokens at a time: row-major [token][this workgroup's columns] with a padded row stride
   // (conflict-free writes), then the workgroup streams whole rows out, neighbouring lanes writing
   // neighbouring bytes.
-  constexpr int kOutCols = EPI == CQ_EPI_SWIGLU ? kLargeRows / 2 : kLargeRows;
+  constexpr int kOutCols = EPI == CQ_EPI_SWIGLU ? kRows / 2 : kRows;
   constexpr int kEsize = OUTK == CQ_OUT_F16 ? 2 : 4;
   constexpr int kRowBytes = kOutCols * kEsize;                    // 256 .. 1024
   constexpr int kQuadBytes = (EPI == CQ_EPI_SWIGLU ? 2 : 4) * kEsize;  // what one accumulator quad becomes
   constexpr int kRowStride = kRowBytes + (kQuadBytes == 16 ? 16 : 8);
   constexpr int kPiece = kRowStride % 16 == 0 ? 16 : 8;           // bytes per lane when streaming out
   constexpr int kPiecesPerRow = kRowBytes / kPiece;
-  static_assert(kRowStride == epilogue_row_stride(EPI, OUTK), "the launcher sizes LDS with the same formula");
+  static_assert(kRowStride <= epilogue_row_stride(EPI, OUTK), "the launcher sizes LDS for tiles of 256 rows");
   const size_t out_col0 = (size_t)rt * kOutCols;
   typedef __attribute__((address_space(3))) uint32_t lds_u32;
   typedef __attribute__((address_space(3))) cq_v4u lds_v4u;
@@ -391,11 +399,11 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
         sc = p.row_scale[p.scale_gather ? p.scale_gather[m] : m];
       }
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
+      for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
         for (int vb = 0; vb < 4; ++vb) {
           // MFMA 32x32 output: register v holds row 8*(v/4) + 4*(lane/32) + v%4, column lane%32
-          const int quad = (wave * 64 + rb * 32 + vb * 8 + g2 * 4) >> 2;  // which 4 weight rows of the tile
+          const int quad = (wave * (32 * RB) + rb * 32 + vb * 8 + g2 * 4) >> 2;  // which 4 weight rows of the tile
           const uint32_t at = (uint32_t)tl * kRowStride + (uint32_t)quad * kQuadBytes;
           const float x0 = sc * acc[rb][cb][4 * vb], x1 = sc * acc[rb][cb][4 * vb + 1];
           const float x2 = sc * acc[rb][cb][4 * vb + 2], x3 = sc * acc[rb][cb][4 * vb + 3];
@@ -528,12 +536,28 @@ struct tile_map {
   }
 };
 
+// How many of an XCD's last tiles are cut into two of 128 rows (all: its tiles of the launch, last: those of list 2).
+// An XCD has 32 compute units, and one that runs a single workgroup does 0.84 of the work of two: what counts is how many
+// tiles the busiest unit gets, all / 32 rounded up.  Up to half a round too many, 16 tiles in halves save half a tile's time
+// (groups x 2048 x 2048 of 60 rows, us, whole / halves: 36 groups, i.e. tiles per XCD, 39.1 / 32.4, 48 41.1 / 35.3, 66
+// 58.9 / 51.4, 80 62.2 / 55.2, 112 83.8 / 76.5); any more, and the halves themselves begin another round (52: 41.5 / 48.4,
+// 64: 45.2 / 52.0, 96: 64.9 / 69.9).  A launch that leaves units idle takes all of them in halves, while none gets a half
+// besides a whole tile (8 23.0 / 16.7, 16 25.0 / 18.5, 24 26.0 / 24.9, 32 28.7 / 27.4).  With 8, 24 or 32 halves instead of
+// 16 the launches of more than a round take the same or longer.
+constexpr int kHalvedMax = 32;
+__device__ __forceinline__ int halved_tiles(int all, int last) {
+  if (all <= 32) return all + last <= 32 || last == all ? last : 0;
+  const int over = all & 31;
+  return over > 0 && over <= 16 && last >= over ? min(16, last) : 0;
+}
+
 // Work items = (token tile, row tile, K part); tiles of the three widths in ONE launch so that the short lists do not
 // leave most of the chip idle.  Two forms:
 //   * whole tiles, 256 / 128 / 64 tokens, one workgroup per compute unit (all 512 registers of a lane, four or eight
 //     activation tiles in LDS): a decoded weight serves up to 256 tokens.  Bound by the matrix cores and by power;
 //   * half tiles, 128 / 96 / 64 (or 32) tokens (HALF), 256 registers and at most half the LDS, so that TWO workgroups share a
 //     compute unit and one's barriers, waits, decoding and epilogue run under the other's matrix work.
+//     The last tiles of list 2 may come in two halves of 128 weight rows (halved_tiles).
 //     gate/up + down of the Mixtral shape at 128 rows per group 314 + 172 -> 275 + 148 us, of DeepSeek-V2-Lite's at
 //     48 rows per group (two launches before, of the streaming kernel and of whole tiles) 203 -> 134 us.
 // cq_gemm_uses_half_tiles has the rule between the two.
@@ -577,12 +601,22 @@ __global__ __launch_bounds__(256, HALF ? 2 : 1) void gemm_large_kernel(const Lar
     return;
   }
   slot -= s1;
+  // the last tiles of the launch, cut into halves
+  const int halves = HALF ? halved_tiles(s0 + s1 + s2, s2) : 0;
+  const bool cut = slot >= s2 - halves;
+  const int part = cut ? (slot - (s2 - halves)) & 1 : 0;
+  if (cut) slot = s2 - halves + ((slot - (s2 - halves)) >> 1);
   if (slot >= s2 || !item(2, map.kS1)) return;
   const int tail_row = p.tail_abs ? row0 : p.tail_rows1 + tile * W::w2;
   if constexpr (HALF) {
     // (up to 32 rows: decoding a tile's weights takes longer than the products of 64 tokens, but those cost power, which is
     // what a full launch is bound by; 66 groups of 20 rows x 2816 x 2048 60.5 -> 57.0 us, x 2048 x 1408 42.8 -> 41.1.  Rows
     // of zeros in place of the missing ones, in wider tiles, gained 2 % at 33 of 64 rows and lost 1 % at 46 and 64)
+    if (cut) {
+      if (cnt <= 32) large_tile<F16, EPI, OUTK, 1, kDeep, BLK, PRE, HALF, 1>(p, grp, row0, cnt, 2 * rt + part, kz, map.kS1, tail_row);
+      else large_tile<F16, EPI, OUTK, 2, kDeep, BLK, PRE, HALF, 1>(p, grp, row0, cnt, 2 * rt + part, kz, map.kS1, tail_row);
+      return;
+    }
     if (cnt <= 32) {
       large_tile<F16, EPI, OUTK, 1, kDeep, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS1, tail_row);
       return;
@@ -724,7 +758,7 @@ cq_status launch_tiles(LargeArgs a, int max0, int max1, hipStream_t s) {
   // two lists round up separately): ceil(n0/8) + ceil(n1/8) + ceil(n2/8) slots on each of 8 XCDs
   const long w0 = (long)max0 * a.row_tiles * (a.tail_part && a.tail_abs ? kTailSplitMax : 1),
              w1 = (long)max1 * a.row_tiles * (a.tail_part ? kTailSplitMax : 1);   // (narrow tiles may come in K parts)
-  const long grid = ((w0 + 7) / 8 + (w1 + 7) / 8 + 1) * 8;
+  const long grid = ((w0 + 7) / 8 + (w1 + 7) / 8 + 1 + (HALF ? kHalvedMax : 0)) * 8;
   if (grid <= 0) return CQ_OK;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, s, a);
   return cq_check_launch();

@@ -36,6 +36,10 @@ static __device__ __forceinline__ void load_global_to_lds_s(uint32_t lds_base, c
 // wait until at most N of this wavefront's vector-memory loads are outstanding; the registers passed
 // through become usable only after it
 template <int N>
+static __device__ __forceinline__ void vm_wait(cq_v4u& a) {
+  asm volatile("s_waitcnt vmcnt(%1)" : "+v"(a) : "n"(N) : "memory");
+}
+template <int N>
 static __device__ __forceinline__ void vm_wait(cq_v4u& a, cq_v4u& b) {
   asm volatile("s_waitcnt vmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N) : "memory");
 }

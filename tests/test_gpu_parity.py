@@ -761,6 +761,38 @@ def test_gemm_tiles_decode_any_table(B, a_kind, prepacked, blockwise):
         assert np.array_equal(out[m], want), (grp, k)
 
 
+@pytest.mark.parametrize("wide", [0, 1])
+@pytest.mark.parametrize("tiles", [1, 16, 17, 31, 32, 33, 48, 49, 64, 65, 80, 81])
+def test_gemm_last_tiles_in_halves(B, tiles, wide):
+    """Launches around the numbers of tiles per XCD (8 row tiles, one group each) at which the large-tile kernel cuts its last
+    tiles into two of 128 rows, alone and behind a tile of the widest kind.  Exact: integer centroids and codes, sums below
+    2^24; SiLU within the error of exp(x) = 2^(x log2 e) at the |x| < 70 that keep it above 1e-30: 70 * 2^-24 and a few ulp."""
+    import torch
+    rng = np.random.default_rng(tiles + 100 * wide)
+    N, K = 2048, 128
+    counts = [97] * wide + [int(c) for c in rng.integers(1, 65, tiles - wide)]
+    counts = counts or [40]
+    G, M = len(counts), sum(counts)
+    idx, cent = _rand_weights(rng, G, N, K, cent=synth.f32_to_bf16_bits(np.tile(np.arange(-8, 8, dtype=np.float32), (G, N, 1))))
+    W = B.DeviceCodebook(idx, cent)
+    off = _dev(_group_offsets(counts))
+    A = torch.from_numpy(rng.integers(-9, 10, (M, K)).astype(np.float32)).cuda()
+    dense = (torch.stack((W.idx & 15, W.idx >> 4), dim=-1).view(G, N, K).float() - 8.0)
+    for kind, epi in ((B.CQ_A_BF16, B.CQ_EPI_NONE), (B.CQ_A_F16, B.CQ_EPI_NONE), (B.CQ_A_BF16, B.CQ_EPI_SWIGLU)):
+        rows = A.bfloat16() if kind == B.CQ_A_BF16 else A.half()
+        out = B.cq_codebook_grouped_gemm(W, rows, kind, None, None, off, M, epi, B.CQ_OUT_F32)
+        at = 0
+        for g, c in enumerate(counts):
+            want = A[at:at + c].double() @ dense[g].double().T
+            if epi == B.CQ_EPI_SWIGLU:
+                x = want[:, 0::2]
+                want = x * torch.sigmoid(x) * want[:, 1::2]
+                assert ((out[at:at + c].double() - want).abs() <= 1e-5 * want.abs() + 1e-30).all(), (g, c)
+            else:
+                assert torch.equal(out[at:at + c].double(), want), (g, c)
+            at += c
+
+
 @pytest.mark.parametrize("gathered", [False, True])
 @pytest.mark.parametrize("N,K,counts", [
     (512, 256, [1, 32, 33, 64, 65, 96, 97, 128, 129, 0, 192, 193, 225, 257]),   # half tiles: edges of the three widths
