@@ -93,6 +93,14 @@ cq_status cq_front_rows_launch(const float* partials, int ksplit, int T, int H, 
                                const float* bias, int E, float* XR, int8_t* Q, uint16_t* Q16, float* scale,
                                float* logits, int top_k, int32_t* topk_ids, float* topk_w, hipStream_t s);
 
+// The same in two launches for batches of many tokens (from 64 on, H % 256 == 0, up to 128 experts); workspace: bytes of
+// device memory of its own.
+bool cq_front_tiles_supported(int T, int H, int E, int top_k);
+size_t cq_front_tiles_bytes(int T, int H, int E);
+cq_status cq_front_tiles_launch(const float* partials, int ksplit, int T, int H, int act_bits, const float* Wr, const float* bias,
+                                int E, float* XR, int8_t* Q, uint16_t* Q16, float* scale, float* logits, int top_k,
+                                int32_t* topk_ids, float* topk_w, void* workspace, hipStream_t s);
+
 // X_R = X R on f16 matrix cores from a split copy of R (cq_rotation_split), accurate to about fp32
 bool cq_rotate_split_supported(int T, int H);
 // K parts of the layer's rotation where it takes this kernel and has `available` bytes of device memory, 0: the fp32 kernel

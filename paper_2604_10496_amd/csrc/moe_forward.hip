@@ -61,12 +61,18 @@ struct layer_plan {
   size_t rot_at;   // partial sums of the rotation
   int rot_parts;   // K parts of the rotation on the f16 matrix cores; 0: the fp32 kernel
   bool rot_few;    // ... by the kernel for few tokens
+  size_t front_at; // partial logits of the front end for many tokens, 0: not taken
 };
 
 // Batches large enough for the large-tile product get the codes a second time as bf16, so that staging
 // them into LDS is a plain copy.
 bool use_bf16_codes(const cq_layer* L, int T) {
   return cq_gemm_uses_large_tiles(&L->gate_up, (int)((long)T * (L->top_k + L->S)), CQ_EPI_SWIGLU, T);
+}
+
+bool front_in_tiles(const cq_layer* L, int T) {
+  return !cq_front_small_supported(T, L->H, L->E, L->top_k) && !cq_front_rows_supported(T, L->H, L->E, L->top_k, false) &&
+         cq_front_tiles_supported(T, L->H, L->E, L->top_k);
 }
 
 // The size that the query reports (lay.total) is a function of the layer and the batch only, and never falls as the batch
@@ -147,6 +153,15 @@ void make_plan(const cq_layer* L, int T, layer_plan* plan) {
   plan->rot_at = off + rotation <= o->total && off + rotation <= CQ_STATIC_SCRATCH_BYTES ? o->scratch : o->Hbuf;
   plan->used = off + scratch;
   raise(plan->used, plan->rot_at + rotation);
+  // The front end for many tokens keeps its partial logits where nothing is kept before the down product writes o, and behind
+  // the rotation's partial sums where these reach there, if that is memory that the call touches anyway.
+  plan->front_at = 0;
+  if (!L->r_hadamard && front_in_tiles(L, T)) {
+    const size_t rot_end = plan->rot_at + (plan->rot_parts > 1 || !plan->rot_parts ? rotation : 0);
+    size_t at = o->Obuf;
+    if (plan->rot_at < o->scratch && rot_end > at) at = cq_align_up(rot_end, 256);
+    if (at + cq_front_tiles_bytes(T, L->H, L->E) <= (at < off ? off : plan->used)) plan->front_at = at;
+  }
 }
 
 }  // namespace
@@ -256,6 +271,18 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
       st = cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
       if (st != CQ_OK) return st;
     }
+    if (!mark(2)) return CQ_ERR_HIP;
+  } else if (plan.front_at) {
+    // many tokens: the rotation; logits of the rows; quantization and top-k; the grouping (stage boundary as above)
+    int parts;
+    float* part;
+    st = rotate(&parts, &part);
+    if (st != CQ_OK) return st;
+    if (!mark(1)) return CQ_ERR_HIP;
+    st = cq_front_tiles_launch(part, parts, T, L->H, L->act_bits, L->Wr, L->bias, L->E, XR, Q, Q16, scale, logits, L->top_k,
+                               ids, tw, ws + plan.front_at, hs);
+    if (st == CQ_OK) st = cq_permute_launch(ids, T, L->E, L->top_k, L->S, offsets, perm, inv_perm, src_token, scratch, hs);
+    if (st != CQ_OK) return st;
     if (!mark(2)) return CQ_ERR_HIP;
   } else if (cq_front_rows_supported(T, L->H, L->E, L->top_k, false)) {
     // larger batches: the rotation; quantization, logits and top-k in one launch; the grouping (stage boundary as above)

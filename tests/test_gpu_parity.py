@@ -1567,6 +1567,48 @@ def test_layer_front_rows(B, over):
     _check_layer(B, synth.small_variant(synth.CONFIGS["mixtral_decode"], **over), label="front rows")
 
 
+@pytest.mark.parametrize("E,k,H,T,bits", [(5, 4, 256, 600, 8), (16, 4, 512, 513, 4), (17, 6, 256, 641, 8), (32, 4, 1024, 530, 4),
+                                          (33, 4, 768, 64, 8), (33, 4, 768, 95, 4), (64, 6, 512, 1000, 8), (65, 8, 256, 545, 4),
+                                          (100, 8, 2048, 577, 8), (128, 8, 256, 2049, 4), (20, 8, 8192, 66, 8)])
+def test_front_of_many_tokens(B, E, k, H, T, bits):
+    """Rows, codes, logits and selection from the two launches for batches of many tokens, at the edges of their tiles (32
+    tokens, blocks of 16 experts, one to eight of them, one to 32 blocks of columns): codes and scales are those of the stored
+    X_R to the bit, logits those of the stored X_R to the rounding of an fp32 sum, ids and weights those of the stored logits."""
+    import torch
+    rng = np.random.default_rng(E * 7 + T)
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], E=E, top_k=k, H=H, I=512, T=T, act_bits=bits, outlier_channels=())
+    R = torch.linalg.qr(torch.from_numpy(rng.standard_normal((H, H))).cuda())[0].float().contiguous()
+    cb = []
+    for N, K in ((1024, H), (H, 512)):
+        idx = torch.randint(0, 256, (E, N, K // 2), dtype=torch.uint8, device="cuda")
+        cent = torch.randn((E, N, 16), device="cuda").mul_(0.02).bfloat16().view(torch.int16)
+        cb.append(B.DeviceCodebook(idx, cent, keep_canonical=False))
+    Wr = torch.from_numpy(rng.standard_normal((E, H)).astype(np.float32)) / H ** 0.5
+    bias = torch.from_numpy(rng.standard_normal(E).astype(np.float32))
+    layer = B.DeviceLayer(cfg, R, Wr, bias, *cb)
+    X = torch.from_numpy(rng.standard_normal((T, H)).astype(np.float32)).cuda()
+    X[3] = 0.0
+    X[T - 1] *= 1e4
+    B.cq_moe_forward(layer, X)
+    torch.cuda.synchronize()
+    im = B.moe_intermediates(layer, T)
+    XR, ref = im["XR"], X.double() @ R.double()
+    assert ((XR.double() - ref).norm(dim=1) <= 1e-6 * ref.norm(dim=1)).all()
+    rows = XR.cpu().numpy()               # (torch divides by a number through its reciprocal on the GPU)
+    s = np.abs(rows).max(axis=1) / np.float32(2 ** (bits - 1) - 1)
+    s[s == 0] = 1.0
+    assert np.array_equal(im["scale"].cpu().numpy(), s)
+    assert np.array_equal(im["Q"].cpu().numpy().astype(np.float32), np.rint(rows / s[:, None]))
+    # (at most H / 4 additions of partial sums that Cauchy's inequality bounds, each to 2^-24, and the bias)
+    want = XR.double() @ layer.Wr.double().T + layer.bias.double()
+    bound = 2.0 ** -24 * (H / 4 * XR.double().norm(dim=1)[:, None] * layer.Wr.double().norm(dim=1)[None] + want.abs())
+    assert ((im["logits"].double() - want).abs() <= bound).all()
+    top, ids = torch.sort(im["logits"], dim=1, descending=True, stable=True)
+    assert torch.equal(im["ids"], ids[:, :k].int())
+    w = torch.softmax(top[:, :k].double(), dim=1)
+    assert ((im["w"].double() - w).abs() <= 1e-6).all()
+
+
 @pytest.mark.parametrize("over,rows", [
     # gate/up in passes of 32 rows (gathered rows, row scales, the gated epilogue)
     (dict(H=4096, I=128, T=45, zipf_s=2.0), 33), (dict(H=4096, I=128, T=77, zipf_s=1.5), 65),   # (from 64 tokens: split rotation)
