@@ -821,11 +821,13 @@ bool cq_gemm_large_tail_split(const cq_codebook_weights* W, int epilogue, int ou
 // count) and several 256-token tiles per group, whole tiles save more than two workgroups per compute unit gain
 // (Mixtral shape, K = 4096 and 14336: 1645 us per layer on half tiles against 1604 at 512 rows per group, 961 against
 // 983 at 256, 622 against 691 at 128; K = 2048 / 1408 and 2048 / 768: 823 against 888 at 496 rows per group, 618 against
-// 674 at 256).  Half tiles address the rows of A with 32-bit byte offsets.
+// 674 at 256).  Launches of less than three quarters of a round of whole tiles leave compute units idle that twice as many half
+// tiles use (one group of 400 rows x 4096 x 4096 80 against 50 us, of 2000 94 / 68; 2 groups x 700 x 2560 x 2560 57 / 37).
+// Half tiles address the rows of A with 32-bit byte offsets.
 // a_rows: number of rows of A, 0 if unknown.
 bool cq_gemm_uses_half_tiles(const cq_codebook_weights* W, int M_total, long a_rows) {
   if (cq_tables_per_row(W) > 1 || a_rows <= 0 || a_rows * W->K * 2 >= (1L << 32)) return false;
-  return W->K <= 2048 || M_total < 384L * W->G;
+  return W->K <= 2048 || M_total < 384L * W->G || M_total / 256L * (W->N / 256) < 192;
 }
 
 namespace {

@@ -188,14 +188,13 @@ __global__ __launch_bounds__(1024) void route_fused_kernel(const float* logits_i
     for (int i = tid; i < S * T; i += 1024) src_token[A + i] = i % T;
 }
 
-// The stable grouping alone, in one workgroup, for up to 16 * 64 * kGroupMaxChunks assignments and 128 experts: wavefront w takes a
-// contiguous run of them, 64 at a time; a running count per (wavefront, expert) in LDS and the ballot match masks give
-// every assignment its rank among the wavefront's assignments to the same expert, and the counts' exclusive prefix over
-// the wavefronts and over the experts gives the position.  One launch instead of the counting sort's three (histogram,
-// one-workgroup scan over its blocks, scatter: 15 us at 3072 assignments, 6.5 us so).
-// (One workgroup stores from one compute unit: 5 us at 4096 assignments, 12 us at 8192, 24 us at 16384; more than 4096 go to
-// group_chunks_kernel.)
-constexpr int kGroupMaxChunks = 4;
+// The stable grouping alone, in one workgroup, for up to 1024 assignments and 128 experts: wavefront w takes 64 of them in a
+// row; ballot match masks give every assignment its rank among the wavefront's assignments to the same expert, and the
+// exclusive prefix of the counts per (wavefront, expert) over the wavefronts and over the experts gives the position.
+// (More go to group_chunks_kernel, whose workgroups each do the same for 1024.  Up to 4096 here, a wavefront ranking four
+// times 64 one after the other, and all stores from one compute unit, was the slower: top-k and grouping of 3000 assignments
+// to 8 experts 8.9 us against 7.7 there, of 3072 to 64 9.7 / 8.0, of 4088 to 128 12.6 / 9.5; of 1024 6.7 / 7.0, 1200 equal.)
+constexpr int kGroupOne = 1024;
 __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__ ids, int T, int E, int k, int S,
                                                      int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
                                                      int32_t* __restrict__ inv_perm, int32_t* __restrict__ src_token) {
@@ -203,36 +202,19 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
   __shared__ int s_off[kFusedMaxE + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int A = T * k;
-  const int chunks = (A + 1023) / 1024;   // of 64 assignments, per wavefront
-  const int a0 = wave * chunks * 64 + lane;
-  int id[kGroupMaxChunks], rank[kGroupMaxChunks];
-#pragma unroll
-  for (int c = 0; c < kGroupMaxChunks; ++c) {
-    const int a = a0 + c * 64;
-    id[c] = c < chunks && a < A ? ids[a] : -1;
-  }
+  const bool valid = tid < A;
+  const int id = valid ? ids[tid] : -1;
   for (int i = lane; i < kFusedMaxE; i += 64) s_cnt[wave][i] = 0;
   cq_wave_lds_fence();   // (a wavefront's own row)
-  const uint64_t lt = lanemask_lt(lane);
+  uint64_t mask = __ballot(valid);
 #pragma unroll
-  for (int c = 0; c < kGroupMaxChunks; ++c) {
-    if (c < chunks) {
-      const bool valid = id[c] >= 0;
-      uint64_t mask = __ballot(valid);
-#pragma unroll
-      for (int bit = 0; bit < 7; ++bit) {
-        const bool set = (id[c] >> bit) & 1;
-        const uint64_t bal = __ballot(valid && set);
-        mask &= set ? bal : ~bal;
-      }
-      const int before = valid ? s_cnt[wave][id[c]] : 0;
-      const int in_chunk = __popcll(mask & lt);
-      rank[c] = before + in_chunk;
-      cq_wave_lds_fence();
-      if (valid && in_chunk == 0) s_cnt[wave][id[c]] = before + __popcll(mask);
-      cq_wave_lds_fence();
-    }
+  for (int bit = 0; bit < 7; ++bit) {
+    const bool set = (id >> bit) & 1;
+    const uint64_t bal = __ballot(valid && set);
+    mask &= set ? bal : ~bal;
   }
+  const int rank = __popcll(mask & lanemask_lt(lane));
+  if (valid && rank == 0) s_cnt[wave][id] = __popcll(mask);
   __syncthreads();
   if (tid < kFusedMaxE) {
     int tot = 0;
@@ -258,15 +240,11 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
   __syncthreads();
   if (tid <= E) offsets[tid] = s_off[tid];
   for (int s = tid; s < S; s += 1024) offsets[E + s + 1] = A + (s + 1) * T;
-#pragma unroll
-  for (int c = 0; c < kGroupMaxChunks; ++c) {
-    const int a = a0 + c * 64;
-    if (id[c] >= 0) {
-      const int pos = s_off[id[c]] + s_cnt[wave][id[c]] + rank[c];
-      perm[pos] = a;
-      inv_perm[a] = pos;
-      if (src_token) src_token[pos] = a / k;
-    }
+  if (valid) {
+    const int pos = s_off[id] + s_cnt[wave][id] + rank;
+    perm[pos] = tid;
+    inv_perm[tid] = pos;
+    if (src_token) src_token[pos] = tid / k;
   }
   if (src_token)
     for (int i = tid; i < S * T; i += 1024) src_token[A + i] = i % T;
@@ -276,7 +254,7 @@ __global__ __launch_bounds__(1024) void group_kernel(const int32_t* __restrict__
 // and finds out by itself what precedes them -- it counts the ids of all assignments, those in front of its own in the upper
 // half word (a token selects an expert at most once: counts stay below 2^16 for fewer tokens than that).  Sixteen copies of
 // the counters, for every sixteenth lane, keep the additions to a popular expert apart.  Counting everything again in every
-// workgroup saves two launches and their waits.  Top-k and grouping, with the counting sort (up to 8192 assignments one
+// workgroup saves two launches and their waits.  Top-k and grouping, with the counting sort (8192 assignments: in one
 // workgroup) / so: 16384 assignments to 128 experts 19.8 / 10.7 us, 8192 to 8 experts 15.3 / 9.4, 65535 to 2 experts 53 / 36, all
 // of 65535 to one expert 52 / 35 (with four copies of the counters 84: the 64 lanes of an addition met in one of them).
 constexpr int kGroupChunk = 1024;
@@ -480,7 +458,7 @@ cq_status cq_permute_launch(const int32_t* topk_ids, int T, int E, int top_k, in
                             int32_t* perm, int32_t* inv_perm, int32_t* src_token, void* workspace, hipStream_t s) {
   const int n_assign = T * top_k;
   if (n_assign <= kGroupMostAssign && E <= kFusedMaxE) {
-    if (n_assign <= 1024 * kGroupMaxChunks)
+    if (n_assign <= kGroupOne)
       hipLaunchKernelGGL(group_kernel, dim3(1), dim3(1024), 0, s, topk_ids, T, E, top_k, n_shared,
                          expert_offsets, perm, inv_perm, src_token);
     else

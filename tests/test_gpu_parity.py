@@ -793,6 +793,27 @@ def test_gemm_last_tiles_in_halves(B, tiles, wide):
             at += c
 
 
+@pytest.mark.parametrize("N,counts", [(4096, [3072]), (4096, [3071]), (4096, [1000, 1072, 0, 1000]), (256, [400]), (12288, [1030])])
+def test_gemm_whole_tile_rule(B, N, counts):
+    """Either side of the rule for whole tiles in launches of few tiles (from 384 rows per group and 192 tiles on).  Exact:
+    integer centroids and codes, sums below 2^24."""
+    import torch
+    rng = np.random.default_rng(N + counts[0])
+    G, K, M = len(counts), 4096, sum(counts)
+    idx = torch.randint(0, 256, (G, N, K // 2), dtype=torch.uint8, device="cuda")
+    cent = np.tile(np.arange(-8, 8, dtype=np.float32), (G, N, 1))
+    W = B.DeviceCodebook(idx, torch.from_numpy(synth.f32_to_bf16_bits(cent).view(np.int16)))
+    A = torch.randint(-9, 10, (M, K), device="cuda").bfloat16()
+    out = B.cq_codebook_grouped_gemm(W, A, B.CQ_A_BF16, None, None, _dev(_group_offsets(counts)), M, B.CQ_EPI_NONE, B.CQ_OUT_F32)
+    at = 0
+    for g, c in enumerate(counts):
+        rows = np.unique(rng.integers(0, c, 40)) if c else []
+        dense = torch.stack((idx[g] & 15, idx[g] >> 4), dim=-1).view(N, K).float() - 8.0
+        for r in rows:   # (a few rows of every group against all of its columns)
+            assert torch.equal(out[at + int(r)], dense @ A[at + int(r)].float()), (g, int(r))
+        at += c
+
+
 @pytest.mark.parametrize("gathered", [False, True])
 @pytest.mark.parametrize("N,K,counts", [
     (512, 256, [1, 32, 33, 64, 65, 96, 97, 128, 129, 0, 192, 193, 225, 257]),   # half tiles: edges of the three widths
