@@ -104,12 +104,13 @@ cq_status cq_front_tiles_launch(const float* partials, int ksplit, int T, int H,
 // X_R = X R on f16 matrix cores from a split copy of R (cq_rotation_split), accurate to about fp32
 bool cq_rotate_split_supported(int T, int H);
 // K parts of the layer's rotation where it takes this kernel and has `available` bytes of device memory, 0: the fp32 kernel
-int cq_rotate_split_parts(int T, int H, size_t available);
+// (narrow: in tiles of 64 tokens)
+int cq_rotate_split_parts(int T, int H, size_t available, bool* narrow);
 bool cq_rotate_split_always(int T, int H);   // ... takes this kernel also uncut
 size_t cq_rotate_split_bytes_upto(int T, int H);   // the most device memory that it takes for any batch of up to T tokens
 size_t cq_rotate_split_partials_bytes(int parts, int T, int H);   // its partial sums (0: one part, written to X_R)
 size_t cq_rotate_split_workspace_bytes(int T, int H);   // of the launch, without partial sums
-cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, float* XR_out,
+cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, bool narrow, float* XR_out,
                                  void* workspace, hipStream_t s);
 
 // the same for few tokens: parts (1: `out` is X_R) of the partial sums [parts][T][H] that the launch leaves, 0: not taken

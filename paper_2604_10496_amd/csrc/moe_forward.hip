@@ -61,6 +61,7 @@ struct layer_plan {
   size_t rot_at;   // partial sums of the rotation
   int rot_parts;   // K parts of the rotation on the f16 matrix cores; 0: the fp32 kernel
   bool rot_few;    // ... by the kernel for few tokens
+  bool rot_narrow; // ... in tiles of 64 tokens
   size_t front_at; // partial logits of the front end for many tokens, 0: not taken
 };
 
@@ -130,7 +131,7 @@ void make_plan(const cq_layer* L, int T, layer_plan* plan) {
   if (L->R_split && !L->r_hadamard) raise(o->total, o->Hbuf + cq_align_up(cq_rotate_split_bytes_upto(T, L->H), 256));
   size_t rotation = 0;   // (the Hadamard variant transforms in LDS)
   plan->rot_parts = 0;
-  plan->rot_few = false;
+  plan->rot_few = plan->rot_narrow = false;
   if (!L->r_hadamard) {
     if (L->R_split) {
       // (a batch that fits the library's own array with the fp32 rotation also fits it with this one, in fewer parts)
@@ -138,7 +139,7 @@ void make_plan(const cq_layer* L, int T, layer_plan* plan) {
       raise(fp32_used, o->Hbuf + fp32_rotation);
       const size_t room = fp32_used <= CQ_STATIC_SCRATCH_BYTES && o->total > CQ_STATIC_SCRATCH_BYTES
                               ? (size_t)CQ_STATIC_SCRATCH_BYTES : o->total;
-      plan->rot_parts = cq_rotate_split_parts(T, L->H, room - o->Hbuf);
+      plan->rot_parts = cq_rotate_split_parts(T, L->H, room - o->Hbuf, &plan->rot_narrow);
       const int few = cq_rotate_few_parts(T, L->H);
       // (its partial sums are never more than the fp32 kernel's, which every size holds)
       if (few && cq_rotate_split_partials_bytes(few, T, L->H) <= fp32_rotation) {
@@ -222,7 +223,7 @@ cq_status run_layer(const cq_layer* L, const float* X, int T, float* Y, void* wo
       *parts = plan.rot_parts;
       *part = *parts > 1 ? (float*)rot_ws : XR;
       if (plan.rot_few) return cq_rotate_few_launch(X, L->R_split, T, L->H, *part, hs);
-      return cq_rotate_split_launch(X, L->R_split, T, L->H, *parts, *part,
+      return cq_rotate_split_launch(X, L->R_split, T, L->H, *parts, plan.rot_narrow, *part,
                                     rot_ws + cq_rotate_split_partials_bytes(*parts, T, L->H), hs);
     }
     const cq_gemm_f32_plan p = cq_gemm_f32_make_plan(T, L->H, L->H);

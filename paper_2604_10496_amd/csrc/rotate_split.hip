@@ -12,8 +12,8 @@
 // scale of the activations.  R is split once, when the layer is set up, into the order the MFMA
 // fragments are loaded in.
 //
-// Kernel: workgroup tile 256 output columns x 128 tokens, four wavefronts, each owning 64 columns (as
-// MFMA "A" rows, two blocks of 32) and all 128 tokens (2 x 4 accumulator blocks of 32x32).  R fragments
+// Kernel: workgroup tile 256 output columns x 128 tokens (or 64), four wavefronts, each owning 64 columns (as
+// MFMA "A" rows, two blocks of 32) and all the tokens (2 x 4 accumulator blocks of 32x32, or 2 x 2).  R fragments
 // go from global memory (L2) straight into registers, one step (64 k) ahead
 // (two steps ahead, with 64 more registers, was measured: no faster, so it is not their latency that bounds the loop); token tiles (both halves)
 // arrive by direct global->LDS loads, four steps deep.
@@ -25,15 +25,15 @@ namespace {
 using namespace cq_async;
 
 constexpr int kCols = 256;             // output columns per workgroup
-constexpr int kTok = 128;              // tokens per workgroup
-constexpr int kC = kTok / 32;          // token blocks
+constexpr int kTok = 128;              // tokens per workgroup (or, C = 2, 64)
 constexpr int kStepK = 64;             // K per pipeline step (four MFMA sub-steps of 16)
 constexpr int kStepBytes = kStepK * 2; // one token's share of a step and plane, in LDS and in memory
-constexpr int kPlaneBytes = kTok * kStepBytes;   // 16 KiB
-constexpr int kStageBytes = 2 * kPlaneBytes;     // hi and lo tile of one step
 constexpr int kDepth = 4;                        // token tiles in LDS
-constexpr int kRotLdsBytes = kDepth * kStageBytes;  // 128 KiB
 constexpr int kOutStride = kCols * 4 + 16;       // epilogue staging row (64 tokens at a time)
+constexpr int rot_lds_bytes(int C) {             // hi and lo tile of a step, kDepth of them: 128 KiB, or (C = 2) 64 KiB
+  const int ring = kDepth * 2 * 32 * C * kStepBytes, out = 64 * kOutStride;
+  return ring > out ? ring : out;
+}
 constexpr float kLoScale = 2048.f, kLoUnscale = 1.f / 2048.f;
 
 __device__ __forceinline__ uint32_t f16_bits(float x) {
@@ -136,7 +136,12 @@ __device__ __forceinline__ cq_v4f mfma_f16_16(const cq_v4u a, const cq_v4u b, cq
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(cq_v8f16, a), __builtin_bit_cast(cq_v8f16, b), c, 0, 0, 0);
 }
 
+// C: token blocks of 32.  TWICE: the two halves of the K range are summed apart and added at the end (an accumulator rounds
+// at the size of its own partial sum: the result is as accurate as two parts').
+template <int C, bool TWICE>
 __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
+  constexpr int kC = C, kTok = 32 * C;
+  constexpr int kPlaneBytes = kTok * kStepBytes, kStageBytes = 2 * kPlaneBytes;
   // XCD-aware remap of the linear workgroup id (ids go round-robin over the 8 XCDs): XCD x takes a
   // contiguous share of the work, so that neighbours in its L2 share token tiles and columns of R
   const int per = (p.n_work + 7) >> 3;
@@ -160,23 +165,25 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
 
   // ---- token tiles: as in the codebook product's large-tile kernel (token-major rows of 128 bytes,
   // chunk c of token t at position c ^ ((t >> 1) & 7); one direct-to-LDS load moves 8 tokens x 128 bytes;
-  // the swizzle is applied on the global side).  Wavefront w moves tokens [32w, 32w + 32) of both planes:
-  // 2 x 4 loads per step, one of each plane per sub-step. ----
-  uint32_t aoff[4];  // byte offset of this lane's 16 bytes of step 0 within a plane (T*K*2 < 2^32)
+  // the swizzle is applied on the global side).  Wavefront w moves tokens [8Cw, 8Cw + 8C) of both planes:
+  // 2 x C loads per step, C/2 of them per sub-step. ----
+  uint32_t aoff[C];  // byte offset of this lane's 16 bytes of step 0 within a plane (T*K*2 < 2^32)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int tok = wave * 32 + i * 8 + (lane >> 3);
+  for (int i = 0; i < C; ++i) {
+    const int tok = wave * (8 * C) + i * 8 + (lane >> 3);
     const uint32_t row = (uint32_t)(mrow0 + min(tok, mcnt - 1));  // tokens past the end repeat the last row
     const int chunk = (lane & 7) ^ ((tok >> 1) & 7);
     aoff[i] = (row * (uint32_t)K + (uint32_t)chunk * 8) * 2;
   }
   const uint8_t* xh = reinterpret_cast<const uint8_t*>(p.Xh) + (size_t)sb * kStepBytes;
   const uint8_t* xl = reinterpret_cast<const uint8_t*>(p.Xl) + (size_t)sb * kStepBytes;
-  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(wave * 32 * kStepBytes);
-  auto fetch_tile_part = [&](int s, int buf, int i) {  // tokens 32w + 8i .. +7 of step s, both planes
+  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(wave * (8 * C) * kStepBytes);
+  // a quarter of the wavefront's loads of step s: tokens 8Cw + 8jj .. +7 of both planes, or (C = 2) 8 tokens of one
+  auto fetch_tile_part = [&](int s, int buf, int jj) {
     const size_t o = (size_t)s * kStepBytes;
-    load_global_to_lds_s<0>(buf * kStageBytes + lds_wave + i * 1024, xh + o, aoff[i]);
-    load_global_to_lds_s<0>(buf * kStageBytes + kPlaneBytes + lds_wave + i * 1024, xl + o, aoff[i]);
+    const int i = C == 4 ? jj : jj >> 1;
+    if (C == 4 || (jj & 1) == 0) load_global_to_lds_s<0>(buf * kStageBytes + lds_wave + i * 1024, xh + o, aoff[i]);
+    if (C == 4 || (jj & 1) == 1) load_global_to_lds_s<0>(buf * kStageBytes + kPlaneBytes + lds_wave + i * 1024, xl + o, aoff[i]);
   };
   // R fragments of sub-step jj of step s: [rb][plane]
   auto fetch_R = [&](cq_v4u (&w)[2][2], int s, int jj) {
@@ -212,11 +219,11 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
       for (int i = 0; i < 16; ++i) acc[rb][cb][i] = 0.f;
 
   // Vector-memory operations per sub-step, in this order: 4 R fragment loads (sub-step jj of the NEXT
-  // step, into the registers just consumed), then 2 tile loads (part jj of the tile three steps ahead).
-  // A fragment is therefore followed by 2 + 3*6 = 20 younger operations when its sub-step comes round,
-  // and the last part of the tile two steps ahead by the 24 operations of the current step: those are
-  // the two wait counts.  (A count is safe as long as at least that many younger operations exist.)
-  constexpr int kPerSub = 6, kWaitR = 2 + 3 * kPerSub, kWaitTile = 4 * kPerSub;
+  // step, into the registers just consumed), then C/2 tile loads (part jj of the tile three steps ahead).
+  // A fragment is therefore followed by C/2 + 3*(4 + C/2) younger operations when its sub-step comes round
+  // (20 or 16), and the last part of the tile two steps ahead by the operations of the current step (24 or 20): those
+  // are the two wait counts.  (A count is safe as long as at least that many younger operations exist.)
+  constexpr int kPerSub = 4 + C / 2, kWaitR = C / 2 + 3 * kPerSub, kWaitTile = 4 * kPerSub;
   cq_v4u wq[4][2][2];
   // prologue, oldest first: tiles 0 and 1, the R fragments of step 0, tile 2
 #pragma unroll
@@ -237,6 +244,7 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
     bl[cb] = read_b(0, 1, 0, cb);
   }
 
+  cq_v16f first[TWICE ? 2 : 1][TWICE ? kC : 1];   // the first half's sums
   int s0 = 0;
   do {  // K is a multiple of 256: steps come in fours (no zero-trip path, accumulators stay in place)
 #pragma unroll
@@ -278,7 +286,25 @@ __global__ __launch_bounds__(256, 1) void rot_split_kernel(const RotArgs p) {
       __syncthreads();
     }
     s0 += kDepth;
+    if constexpr (TWICE) {
+      if (s0 * 2 == nS)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int cb = 0; cb < kC; ++cb) {
+            first[rb][cb] = acc[rb][cb];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[rb][cb][i] = 0.f;
+          }
+    }
   } while (s0 < nS);
+  if constexpr (TWICE)
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < kC; ++cb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[rb][cb][i] += first[rb][cb][i];
   // Nothing of this workgroup may still be on its way into LDS when the tile buffers are reused, nor into
   // registers: the last (clamped, unused) fragment loads still target the ring, which therefore has to
   // stay allocated up to this wait -- it is named here so that the compiler cannot reuse it earlier.
@@ -605,6 +631,13 @@ bool cq_rotate_split_supported(int T, int H) {
 // took 124 us, in four parts 52 us; T = 77: 43 us on the fp32 matrix cores, 23 us in 16 parts.)  The sum over K in parts
 // is also the more accurate one: an accumulator rounds at the size of its own partial sum.  The partial sums lie where the
 // layer keeps other things later.
+// What a launch in parts waits for is less its products than the fill of its pipelines and the partial sums, written once
+// and read again by the next launch.  It therefore takes tiles of 64 tokens in half as many parts (narrow_parts), each of
+// which sums the halves of its K range apart, so that the result is as accurate: the same products per workgroup, half the
+// partial sums, less padding.  Whole layers with narrow experts, us, tiles of 128 / 64 tokens (with the other changes to
+// those layers' products): H = 4096, 64 tokens 65.6 / 60.1, 128 97.0 / 82.9, 192 107.3 / 83.8, 400 156.0 / 134.3; H = 2048,
+// 129 80.7 / 72.4, 512 111.5 / 105.9, 1024 155.8 / 140.9; H = 3072, 100 tokens 102.1 / 79.2; error of X_R against float64 over
+// 37 sizes the same or smaller (H = 4096, 128 tokens, where the parts did not all fit, 2.7e-7 / 2.0e-7, 77 tokens 2.09e-7 / 2.04e-7).
 //
 // Whether the layer's rotation takes this path: uncut from 48 tiles on, cut into parts where these make at least 44
 // workgroups -- from 64 tokens on, or, narrower than 3072 columns, from a second tile of tokens, and narrower than 2048 from
@@ -630,6 +663,10 @@ int full_parts(int T, int H) {
   while (tiles(T, H) * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0) parts *= 2;
   return parts;
 }
+// Launches in parts take tiles of 64 tokens, in half as many parts if these still fill the chip (they are never more).
+int narrow_parts(int T, int H, int parts) {
+  return (long)((T + 63) / 64) * (H / kCols) * parts > 256 || (long)((T + 63) / 64) * (H / kCols) * (parts / 2) >= 192 ? parts / 2 : parts;
+}
 bool preferred(int T, int H) {
   if (cq_rotate_split_always(T, H)) return true;
   if (H % kCols != 0 || H < 1024 || (long)T * H < (1L << 18) || (long)T * H * 2 >= (1L << 32)) return false;
@@ -652,13 +689,17 @@ size_t cq_rotate_split_bytes_upto(int T, int H) {
   return most;
 }
 
-int cq_rotate_split_parts(int T, int H, size_t available) {
+int cq_rotate_split_parts(int T, int H, size_t available, bool* narrow) {
+  *narrow = false;
   if (!preferred(T, H)) return 0;
   const size_t fixed = cq_rotate_split_workspace_bytes(T, H);
   if (fixed > available) return 0;
   int parts = full_parts(T, H);
   while (parts > 1 && fixed + cq_rotate_split_partials_bytes(parts, T, H) > available) parts /= 2;
-  return cq_rotate_split_always(T, H) || tiles(T, H) * parts >= kFewest ? parts : 0;
+  if (!cq_rotate_split_always(T, H) && tiles(T, H) * parts < kFewest) return 0;
+  if (parts == 1) return 1;
+  *narrow = true;
+  return narrow_parts(T, H, parts);
 }
 
 bool cq_rotate_split_always(int T, int H) {
@@ -677,7 +718,7 @@ extern "C" cq_status cq_rotate_quant_split(const float* X, const void* R_split, 
   if (!cq_rotate_split_supported(T, H)) return CQ_ERR_SHAPE;
   if (act_bits != 4 && act_bits != 8) return CQ_ERR_UNSUPPORTED;
   if (!workspace || workspace_bytes < cq_rotate_split_workspace_bytes(T, H)) return CQ_ERR_WORKSPACE;
-  const cq_status st = cq_rotate_split_launch(X, R_split, T, H, 1, XR_out, workspace, (hipStream_t)stream);
+  const cq_status st = cq_rotate_split_launch(X, R_split, T, H, 1, false, XR_out, workspace, (hipStream_t)stream);
   if (st != CQ_OK) return st;
   return cq_quantize_launch(XR_out, 1, T, H, act_bits, XR_out, Q_out, nullptr, scale_out, nullptr, (hipStream_t)stream);
 }
@@ -701,11 +742,15 @@ size_t cq_rotate_split_workspace_bytes(int T, int H) {
 }
 
 // X_R = X R from the split R; XR_out [T, H] fp32.  workspace: cq_rotate_split_workspace_bytes(T, H).
-// parts > 1: XR_out receives partial sums [parts][T][H].
-cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, float* XR_out,
+// parts > 1: XR_out receives partial sums [parts][T][H].  narrow: tiles of 64 tokens.
+cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int H, int parts, bool narrow, float* XR_out,
                                  void* workspace, hipStream_t s) {
-  static std::atomic<bool> configured{false};
-  const cq_status cst = cq_configure_lds(rot_split_kernel, kRotLdsBytes, configured, true);
+  const int tok = narrow ? 64 : kTok;
+  const bool twice = narrow && H / kStepK / parts % (2 * kDepth) == 0;
+  auto kern = !narrow ? rot_split_kernel<4, false> : twice ? rot_split_kernel<2, true> : rot_split_kernel<2, false>;
+  static std::atomic<bool> configured[3] = {{false}, {false}, {false}};
+  const int lds = rot_lds_bytes(narrow ? 2 : 4);
+  const cq_status cst = cq_configure_lds(kern, lds, configured[narrow + twice], true);
   if (cst != CQ_OK) return cst;
   char* ws = (char*)workspace;
   float* row_pow2 = (float*)ws;
@@ -722,10 +767,10 @@ cq_status cq_rotate_split_launch(const float* X, const void* R_split, int T, int
   a.N = H;
   a.K = H;
   a.row_tiles = H / kCols;
-  a.tok_tiles = (T + kTok - 1) / kTok;
+  a.tok_tiles = (T + tok - 1) / tok;
   a.ksteps = H / kStepK / parts;
   a.n_work = a.tok_tiles * a.row_tiles * parts;
   const int per = (a.n_work + 7) / 8;
-  hipLaunchKernelGGL(rot_split_kernel, dim3(per * 8), dim3(256), kRotLdsBytes, s, a);
+  hipLaunchKernelGGL(kern, dim3(per * 8), dim3(256), lds, s, a);
   return cq_check_launch();
 }

@@ -1486,6 +1486,28 @@ def test_layer_rotation_in_k_parts(B, name, over):
         assert forward(n) == 4   # CQ_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("H,T", [(4096, 64), (4096, 65), (4096, 77), (4096, 129), (2048, 129), (2048, 192), (2048, 193), (3072, 100),
+                                 (1024, 513), (1024, 1985), (2560, 300), (2048, 2048)])
+def test_layer_rotation_in_narrow_tiles(B, H, T):
+    """X_R from the split copy of R in tiles of 64 tokens, around their edges, in one part and in several, against float64 row
+    by row.  The bound: 2^-23 of either operand in two planes, and accumulations each to 2^-24 of a partial sum that grows
+    like the root of their number, at most 128 of 16 products in a half of K and 16 parts: 2^-24 sqrt(128) over the row, less
+    by independent signs than that, 6.7e-7."""
+    import torch
+    rng = np.random.default_rng(H + T)
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], H=H, I=512, T=T, outlier_channels=())
+    R = torch.linalg.qr(torch.from_numpy(rng.standard_normal((H, H))).cuda())[0].float().contiguous()
+    cb = [B.DeviceCodebook(*_rand_weights(rng, cfg.E, N, K)) for N, K in ((1024, H), (H, 512))]
+    Wr = torch.from_numpy(rng.standard_normal((cfg.E, H)).astype(np.float32)) / H ** 0.5
+    layer = B.DeviceLayer(cfg, R, Wr, None, *cb)
+    X = torch.from_numpy((rng.standard_normal((T, H)) * 10.0 ** rng.integers(-3, 4, (T, 1))).astype(np.float32)).cuda()
+    B.cq_moe_forward(layer, X)
+    torch.cuda.synchronize()
+    ref = X.double() @ R.double()
+    err = (B.moe_intermediates(layer, T)["XR"].double() - ref).norm(dim=1) / ref.norm(dim=1)
+    assert err.max().item() <= 6.7e-7
+
+
 @pytest.mark.parametrize("H,T,f16", [
     (1280, 256, False), (1792, 300, False), (2304, 256, False), (3840, 100, False),   # K cannot be cut, too few tiles
     (2304, 700, True), (3840, 300, True),                                             # ... and enough of them
