@@ -276,7 +276,7 @@ __global__ __launch_bounds__(1024) void group_chunks_kernel(const int32_t* __res
   const int id = valid ? ids[a] : 0;
   __syncthreads();
   // ---- all assignments: how many to every expert, and how many of them in front of this workgroup's ----
-  for (int i0 = tid * 4; i0 < A; i0 += 4 * 4096) {   // (four loads of four ids requested together)
+  for (int i0 = tid * 4; i0 < A; i0 += 4 * 4096) {   // (four loads of four ids requested together; 4-byte alignment is enough)
     int4 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
