@@ -551,10 +551,21 @@ __device__ __forceinline__ int halved_tiles(int all, int last) {
   return over > 0 && over <= 16 && last >= over ? min(16, last) : 0;
 }
 
+// The same for whole tiles, one workgroup per compute unit: where up to half a round of the widest ones is too many (s0 on an
+// XCD), these come in halves, which all run at once.  Groups of 512 rows x 2048 x 4096, us, whole / halves: s0 = 34 198.5 /
+// 171.0, 40 198.5 / 174.0, 48 215.7 / 196.6, 66 319.5 / 292.5, 80 337.7 / 317.7, 112 454 / 439; one group of 8448 to 9216 rows x
+// 4096 x 14336 (66 to 72) 1001..1007 / 914..922.  Beyond ten rounds no difference (28672 x 4096, 462 to 504: 1624..1745 / 1608..1749).
+constexpr int kHalvedWholeMax = 16;
+__device__ __forceinline__ int halved_whole_tiles(int s0) {
+  const int over = s0 & 31;
+  return s0 > 32 && over <= kHalvedWholeMax ? over : 0;
+}
+
 // Work items = (token tile, row tile, K part); tiles of the three widths in ONE launch so that the short lists do not
 // leave most of the chip idle.  Two forms:
 //   * whole tiles, 256 / 128 / 64 tokens, one workgroup per compute unit (all 512 registers of a lane, four or eight
-//     activation tiles in LDS): a decoded weight serves up to 256 tokens.  Bound by the matrix cores and by power;
+//     activation tiles in LDS): a decoded weight serves up to 256 tokens.  Bound by the matrix cores and by power; the
+//     last ones of 256 tokens may come in two halves of 128 weight rows (halved_whole_tiles);
 //   * half tiles, 128 / 96 / 64 (or 32) tokens (HALF), 256 registers and at most half the LDS, so that TWO workgroups share a
 //     compute unit and one's barriers, waits, decoding and epilogue run under the other's matrix work.
 //     The last tiles of list 2 may come in two halves of 128 weight rows (halved_tiles).
@@ -589,11 +600,20 @@ __global__ __launch_bounds__(256, HALF ? 2 : 1) void gemm_large_kernel(const Lar
   };
   const int s0 = (map.n0 * row_tiles * map.kS0 + 7) >> 3, s1 = (map.n1 * row_tiles * map.kS1 + 7) >> 3,
             s2 = (map.n2 * row_tiles * map.kS1 + 7) >> 3;
-  if (slot < s0) {
+  const int over = !HALF && !BLK && map.kS0 == 1 ? halved_whole_tiles(s0) : 0;
+  if (slot < s0 - over) {
     if (item(0, map.kS0)) large_tile<F16, EPI, OUTK, W::w0 / 32, 4, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS0, row0);
     return;
   }
-  slot -= s0;
+  if (slot < s0 + over) {
+    if constexpr (!HALF && !BLK) {
+      const int part0 = (slot - (s0 - over)) & 1;
+      slot = s0 - over + ((slot - (s0 - over)) >> 1);
+      if (item(0, 1)) large_tile<F16, EPI, OUTK, W::w0 / 32, 4, BLK, PRE, HALF, 1>(p, grp, row0, cnt, 2 * rt + part0, 0, 1, row0);
+    }
+    return;
+  }
+  slot -= s0 + over;
   if (slot < s1) {
     if (item(1, map.kS1))
       large_tile<F16, EPI, OUTK, W::w1 / 32, kDeep, BLK, PRE, HALF>(p, grp, row0, cnt, rt, kz, map.kS1,
@@ -758,7 +778,7 @@ cq_status launch_tiles(LargeArgs a, int max0, int max1, hipStream_t s) {
   // two lists round up separately): ceil(n0/8) + ceil(n1/8) + ceil(n2/8) slots on each of 8 XCDs
   const long w0 = (long)max0 * a.row_tiles * (a.tail_part && a.tail_abs ? kTailSplitMax : 1),
              w1 = (long)max1 * a.row_tiles * (a.tail_part ? kTailSplitMax : 1);   // (narrow tiles may come in K parts)
-  const long grid = ((w0 + 7) / 8 + (w1 + 7) / 8 + 1 + (HALF ? kHalvedMax : 0)) * 8;
+  const long grid = ((w0 + 7) / 8 + (w1 + 7) / 8 + 1 + (HALF ? kHalvedMax : BLK ? 0 : kHalvedWholeMax)) * 8;
   if (grid <= 0) return CQ_OK;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, s, a);
   return cq_check_launch();

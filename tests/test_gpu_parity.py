@@ -793,6 +793,42 @@ def test_gemm_last_tiles_in_halves(B, tiles, wide):
             at += c
 
 
+@pytest.mark.parametrize("groups,extra", [(16, 0), (16, 1), (17, 64), (23, 0), (24, 0), (24, 1), (25, 100), (33, 0)])
+def test_gemm_last_whole_tiles_in_halves(B, groups, extra):
+    """Launches of whole tiles around the numbers of them per XCD (8 row tiles, two tiles of tokens per group) at which the last
+    ones are cut into two of 128 rows, alone and in front of narrower tiles.  Exact: integer centroids and codes, sums below
+    2^24; SiLU within the error of exp(x) = 2^(x log2 e) at the |x| < 70 that keep it above 1e-30: 70 * 2^-24 and a few ulp."""
+    import torch
+    rng = np.random.default_rng(groups + extra)
+    N, K = 2048, 2176
+    counts = [512] * groups
+    counts[-1] += extra
+    counts[groups // 2] -= 3
+    counts[0] += 3                        # (three rows more than two tiles: a narrow one)
+    G, M = groups, sum(counts)
+    idx = torch.randint(0, 256, (G, N, K // 2), dtype=torch.uint8, device="cuda")
+    cent = np.tile(np.arange(-8, 8, dtype=np.float32), (G, N, 1))
+    W = B.DeviceCodebook(idx, torch.from_numpy(synth.f32_to_bf16_bits(cent).view(np.int16)))
+    A = torch.randint(-9, 10, (M, K), device="cuda").float()
+    off = _dev(_group_offsets(counts))
+    for kind, epi, out_kind in ((B.CQ_A_BF16, B.CQ_EPI_NONE, B.CQ_OUT_F32), (B.CQ_A_F16, B.CQ_EPI_NONE, B.CQ_OUT_F32),
+                                (B.CQ_A_BF16, B.CQ_EPI_SWIGLU, B.CQ_OUT_F32)):
+        rows = A.bfloat16() if kind == B.CQ_A_BF16 else A.half()
+        out = B.cq_codebook_grouped_gemm(W, rows, kind, None, None, off, M, epi, out_kind)
+        at = 0
+        for g, c in enumerate(counts):
+            dense = torch.stack((idx[g] & 15, idx[g] >> 4), dim=-1).view(N, K).float() - 8.0
+            want = A[at:at + c] @ dense.T                # (fp32: exact)
+            got = out[at:at + c].double()
+            if epi == B.CQ_EPI_SWIGLU:
+                x, u = want[:, 0::2].double(), want[:, 1::2].double()
+                want = x * torch.sigmoid(x) * u
+                assert ((got - want).abs() <= 1e-5 * want.abs() + 1e-30).all(), (g, c)
+            else:
+                assert torch.equal(got, want.double()), (g, c)
+            at += c
+
+
 @pytest.mark.parametrize("N,counts", [(4096, [3072]), (4096, [3071]), (4096, [1000, 1072, 0, 1000]), (256, [400]), (12288, [1030])])
 def test_gemm_whole_tile_rule(B, N, counts):
     """Either side of the rule for whole tiles in launches of few tiles (from 384 rows per group and 192 tiles on).  Exact:
