@@ -363,8 +363,15 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
     }
     s0 += D;
   } while (s0 < nS);
-  // nothing of this workgroup may still be on its way into LDS when the loop is left
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // Nothing of this workgroup may still be on its way into LDS when the loop is left, nor into registers: the last (clamped,
+  // unused) loads of weights still target the ring, which therefore has to stay allocated up to this wait -- its entries are
+  // named here and behind it, so that the compiler cannot reuse them earlier.  (What is on its way after the last step, an odd
+  // one of the ring, was requested in the last D - 3 steps: with four entries, an even one.)
+  asm volatile("s_waitcnt vmcnt(0)" : "+v"(wq[0][0])::"memory");
+#pragma unroll
+  for (int i = 0; i < D; i += D == 4 ? 2 : 1)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) asm volatile("" : "+v"(wq[i][rb]));
 
   // ---- epilogue: per-token scale, optional SiLU(gate)*up, store ----
   // A lane holds 4 consecutive outputs of ONE token per accumulator quad, so storing from registers

@@ -211,6 +211,26 @@ def test_exchanges_within_a_wavefront_are_fenced():
         assert bare == (1 if name == "cq_internal.h" else 0), name
 
 
+def test_closing_waits_name_the_registers_that_loads_still_target():
+    """The last loads of a pipeline from inline assembly are not used by anybody.  Their registers must be operands of what
+    waits for them: to the compiler they are free otherwise, and what it keeps in them a late load overwrites."""
+    import os
+    import re
+    from paper_2604_10496_amd import build
+    loads = 0
+    for name in sorted(os.listdir(build.CSRC)):
+        with open(os.path.join(build.CSRC, name)) as f:
+            text = f.read()
+        calls = name != "cq_async.h" and "load_global_async_s<" in text
+        loads += calls
+        if not calls and name != "cq_async.h":
+            continue
+        assert not re.search(r's_waitcnt vmcnt\(0\)"\s*::', text), f"{name}: a closing wait without registers"
+        if calls:   # (one closing wait per kernel body that has a ring)
+            assert re.search(r's_waitcnt vmcnt\(0\)"\s*:\s*"\+v"', text), f"{name}: no closing wait"
+    assert loads >= 2
+
+
 def test_build_reads_spill_counts_from_the_compiler_remarks():
     """build.py refuses kernels with asynchronous register loads that spill; its reader of hipcc's resource
     remarks is checked on a sample of that output."""
