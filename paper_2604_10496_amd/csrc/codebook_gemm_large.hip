@@ -848,13 +848,19 @@ bool cq_gemm_large_tail_split(const cq_codebook_weights* W, int epilogue, int ou
 // count) and several 256-token tiles per group, whole tiles save more than two workgroups per compute unit gain
 // (Mixtral shape, K = 4096 and 14336: 1645 us per layer on half tiles against 1604 at 512 rows per group, 961 against
 // 983 at 256, 622 against 691 at 128; K = 2048 / 1408 and 2048 / 768: 823 against 888 at 496 rows per group, 618 against
-// 674 at 256).  Launches of less than three quarters of a round of whole tiles leave compute units idle that twice as many half
-// tiles use (one group of 400 rows x 4096 x 4096 80 against 50 us, of 2000 94 / 68; 2 groups x 700 x 2560 x 2560 57 / 37).
+// 674 at 256).  Launches whose half tiles all run at once, one per compute unit, take these: whole tiles would leave half of the
+// units idle.  Beyond, some units get two, while the whole tiles still have one each.  us, whole / half tiles, rows x N x K:
+// one group of 1124 x 4096 x 4096 83 / 53, 1892 83 / 64, 2148 84 / 94, 2660 90 / 97, 3140 100 / 100; four of 921 x 2048 x 7168
+// 133 / 104, 1177 141 / 158; 8 uneven ones, mean 460 x 2048 x 7168 134 / 112, 524 136 / 151; 16, mean 518 x 1024 x 2560 58 / 60.
+// A group leaves up to a tile of fewer rows, which costs less: of 504 launches of 2 to 32 groups, even and uneven, all were
+// faster on half tiles up to 122 * 256 rows x row tiles (by 13 % and more), of 144 from 125 to 128 * 256 29 were slower, by up to 12 %.
 // Half tiles address the rows of A with 32-bit byte offsets.
 // a_rows: number of rows of A, 0 if unknown.
 bool cq_gemm_uses_half_tiles(const cq_codebook_weights* W, int M_total, long a_rows) {
   if (cq_tables_per_row(W) > 1 || a_rows <= 0 || a_rows * W->K * 2 >= (1L << 32)) return false;
-  return W->K <= 2048 || M_total < 384L * W->G || M_total / 256L * (W->N / 256) < 192;
+  if (W->K <= 2048 || M_total < 384L * W->G) return true;
+  const long row_tiles = W->N / kLargeRows;
+  return W->G == 1 ? (M_total + 127L) / 128 * row_tiles <= 256 : M_total * row_tiles <= 122L * 256;
 }
 
 namespace {

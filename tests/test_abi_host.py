@@ -231,6 +231,20 @@ def test_closing_waits_name_the_registers_that_loads_still_target():
     assert loads >= 2
 
 
+@pytest.mark.parametrize("G,M,N,K,half", [
+    (1, 2048, 4096, 4096, True), (1, 2049, 4096, 4096, False), (1, 384, 28672, 4096, False), (1, 383, 28672, 4096, True),
+    (2, 2755, 4096, 4096, False), (8, 5112, 2048, 7168, False), (8, 3904, 2048, 7168, True), (8, 3905, 2048, 7168, False),
+    (16, 6144, 1024, 2560, True), (8, 5112, 2048, 2048, True), (8, 3071, 28672, 4096, True), (8, 8192, 28672, 4096, False)])
+def test_rule_between_whole_and_half_tiles(G, M, N, K, half):
+    """Half tiles for a short K, for fewer than 384 rows per group, and for launches whose half tiles all run at once: one
+    that gives some of the 256 compute units two of them is faster on whole tiles, of which they have one each."""
+    lib = B.load_library()
+    rule = lib._Z23cq_gemm_uses_half_tilesPK19cq_codebook_weightsil
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_int, ctypes.c_long]
+    W = B.CodebookWeights(256, 256, None, G, N, K)
+    assert rule(ctypes.byref(W), M, M) is half
+
+
 def test_build_reads_spill_counts_from_the_compiler_remarks():
     """build.py refuses kernels with asynchronous register loads that spill; its reader of hipcc's resource
     remarks is checked on a sample of that output."""

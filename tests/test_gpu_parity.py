@@ -829,10 +829,11 @@ def test_gemm_last_whole_tiles_in_halves(B, groups, extra):
             at += c
 
 
-@pytest.mark.parametrize("N,counts", [(4096, [3072]), (4096, [3071]), (4096, [1000, 1072, 0, 1000]), (256, [400]), (12288, [1030])])
+@pytest.mark.parametrize("N,counts", [(4096, [3072]), (4096, [3071]), (4096, [1000, 1072, 0, 1000]), (256, [400]), (12288, [1030]),
+                                      (4096, [2048]), (4096, [2049]), (2048, [2000, 0, 1904]), (2048, [2000, 0, 1905])])
 def test_gemm_whole_tile_rule(B, N, counts):
-    """Either side of the rule for whole tiles in launches of few tiles (from 384 rows per group and 192 tiles on).  Exact:
-    integer centroids and codes, sums below 2^24."""
+    """Either side of the rule for whole tiles in launches of few tiles (from 384 rows per group on, where half tiles would not
+    all run at once).  Exact: integer centroids and codes, sums below 2^24."""
     import torch
     rng = np.random.default_rng(N + counts[0])
     G, K, M = len(counts), 4096, sum(counts)
