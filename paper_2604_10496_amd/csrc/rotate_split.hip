@@ -30,7 +30,7 @@ constexpr int kStepK = 64;             // K per pipeline step (four MFMA sub-ste
 constexpr int kStepBytes = kStepK * 2; // one token's share of a step and plane, in LDS and in memory
 constexpr int kDepth = 4;                        // token tiles in LDS
 constexpr int kOutStride = kCols * 4 + 16;       // epilogue staging row (64 tokens at a time)
-constexpr int rot_lds_bytes(int C) {             // hi and lo tile of a step, kDepth of them: 128 KiB, or (C = 2) 64 KiB
+constexpr int rot_lds_bytes(int C) {             // hi and lo tile of a step, kDepth of them: 128 KiB, or (C = 2) 65 KiB, what the epilogue takes
   const int ring = kDepth * 2 * 32 * C * kStepBytes, out = 64 * kOutStride;
   return ring > out ? ring : out;
 }
@@ -108,7 +108,7 @@ struct RotArgs {
   float* XR;               // [T, N] fp32, or (K parts) partial sums [parts][T][N]
   int T, N, K;
   int row_tiles;           // N / 256
-  int tok_tiles;           // ceil(T / 128)
+  int tok_tiles;           // ceil(T / 128), or of 64
   int ksteps;              // K steps (of 64) per K part, a multiple of four
   int n_work;              // token tiles x row tiles x K parts
 };
@@ -631,13 +631,16 @@ bool cq_rotate_split_supported(int T, int H) {
 // took 124 us, in four parts 52 us; T = 77: 43 us on the fp32 matrix cores, 23 us in 16 parts.)  The sum over K in parts
 // is also the more accurate one: an accumulator rounds at the size of its own partial sum.  The partial sums lie where the
 // layer keeps other things later.
-// What a launch in parts waits for is less its products than the fill of its pipelines and the partial sums, written once
-// and read again by the next launch.  It therefore takes tiles of 64 tokens in half as many parts (narrow_parts), each of
-// which sums the halves of its K range apart, so that the result is as accurate: the same products per workgroup, half the
-// partial sums, less padding.  Whole layers with narrow experts, us, tiles of 128 / 64 tokens (with the other changes to
-// those layers' products): H = 4096, 64 tokens 65.6 / 60.1, 128 97.0 / 82.9, 192 107.3 / 83.8, 400 156.0 / 134.3; H = 2048,
-// 129 80.7 / 72.4, 512 111.5 / 105.9, 1024 155.8 / 140.9; H = 3072, 100 tokens 102.1 / 79.2; error of X_R against float64 over
-// 37 sizes the same or smaller (H = 4096, 128 tokens, where the parts did not all fit, 2.7e-7 / 2.0e-7, 77 tokens 2.09e-7 / 2.04e-7).
+// A launch in parts takes tiles of 64 tokens in half as many parts (narrow_parts), each of which sums the halves of its K
+// range apart, so that the result is as accurate: the same products per workgroup, half the partial sums, which are written
+// once and read again by the next launch, and less padding.  The launch alone is shorter only where its padding or its
+// number of workgroups was worse (a workgroup's fragments of R serve half the tokens, and the second sum leaves a
+// compute unit's registers to one workgroup), what is always shorter is the next launch, which reads half the sums.  This
+// launch + the next one, us, tiles of 128 / 64 tokens, everything else the same: H = 4096, 128 tokens 25.2 + 9.6 / 19.2 + 9.5,
+// 192 37.5 + 9.2 / 25.0 + 9.1, 384 61.4 + 11.3 / 40.0 + 11.3, 600 68.3 + 19.3 / 71.6 + 13.8, 1024 84.5 + 22.1 / 90.2 + 16.9;
+// H = 2048, 129 16.4 + 12.5 / 11.1 + 12.9, 512 19.8 + 17.5 / 17.9 + 15.1, 1024 28.9 + 18.9 / 28.6 + 16.6, 2048 49.8 + 28.1 /
+// 51.3 + 23.3; H = 1024, 1024 20.1 + 12.2 / 16.0 + 12.9, 4096 30.8 + 22.8 / 28.7 + 18.1.  Error of X_R against float64 over 37
+// sizes the same or smaller (H = 4096, 128 tokens, where the parts did not all fit, 2.7e-7 / 2.0e-7, 77 tokens 2.09e-7 / 2.04e-7).
 //
 // Whether the layer's rotation takes this path: uncut from 48 tiles on, cut into parts where these make at least 44
 // workgroups -- from 64 tokens on, or, narrower than 3072 columns, from a second tile of tokens, and narrower than 2048 from
@@ -663,9 +666,18 @@ int full_parts(int T, int H) {
   while (tiles(T, H) * parts * 2 <= 256 && (H / kStepK) % (parts * 2 * kDepth) == 0) parts *= 2;
   return parts;
 }
-// Launches in parts take tiles of 64 tokens, in half as many parts if these still fill the chip (they are never more).
+// Launches in parts take tiles of 64 tokens, in half as many parts if these still fill the chip (they are never more).  0:
+// tiles of 128 are faster.  Half as many parts of twice the tiles read R twice as often, which a wide R, far larger than the
+// caches, does not give back beyond a few tiles of tokens.  Layers of 8 experts with I = 512, us, tiles of 128 / 64: H = 5120,
+// 128 tokens 138 / 122, 320 172 / 168, 384 179 / 179, 512 233 / 245, 700 274 / 281; 6144, 128 157 / 141, 192 175 / 175, 256 187 /
+// 193, 448 270 / 282; 7168, 128 186 / 173, 140 200 / 207, 384 300 / 321; 8192, 100 213 / 203, 140 233 / 242, 384 345 / 365;
+// 4096, 256 tokens 124 / 122, 512 163 / 162, 700 216 / 215, 960 255 / 257, 1024 253 / 256 (two of the 8 experts per token: 900
+// 189 / 186, 960 191 / 187, 1024 194 / 195); narrower always less.
+// Where the parts stay as many the tiles only lose padding: 6144, 270 tokens 232 / 199.
 int narrow_parts(int T, int H, int parts) {
-  return (long)((T + 63) / 64) * (H / kCols) * parts > 256 || (long)((T + 63) / 64) * (H / kCols) * (parts / 2) >= 192 ? parts / 2 : parts;
+  const long all = (long)((T + 63) / 64) * (H / kCols);
+  if (all * parts <= 256 && all * (parts / 2) < 192) return parts;
+  return H <= 3072 || T <= (H <= 4096 ? 960 : H <= 5120 ? 384 : 128) ? parts / 2 : 0;
 }
 bool preferred(int T, int H) {
   if (cq_rotate_split_always(T, H)) return true;
@@ -697,9 +709,9 @@ int cq_rotate_split_parts(int T, int H, size_t available, bool* narrow) {
   int parts = full_parts(T, H);
   while (parts > 1 && fixed + cq_rotate_split_partials_bytes(parts, T, H) > available) parts /= 2;
   if (!cq_rotate_split_always(T, H) && tiles(T, H) * parts < kFewest) return 0;
-  if (parts == 1) return 1;
-  *narrow = true;
-  return narrow_parts(T, H, parts);
+  const int halved = parts > 1 ? narrow_parts(T, H, parts) : 0;
+  *narrow = halved > 0;
+  return *narrow ? halved : parts;
 }
 
 bool cq_rotate_split_always(int T, int H) {

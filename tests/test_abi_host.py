@@ -245,6 +245,19 @@ def test_rule_between_whole_and_half_tiles(G, M, N, K, half):
     assert rule(ctypes.byref(W), M, M) is half
 
 
+@pytest.mark.parametrize("T,H,parts,narrow", [
+    (128, 8192, 4, True), (129, 8192, 4, False), (384, 8192, 2, False), (512, 7168, 2, False), (128, 6144, 4, True),
+    (256, 6144, 4, False), (270, 6144, 2, True), (384, 5120, 2, True), (385, 5120, 2, False), (512, 4096, 2, True),
+    (960, 4096, 1, True), (961, 4096, 2, False), (2048, 2048, 1, True), (64, 4096, 16, True), (1025, 4096, 1, False)])
+def test_rule_for_the_rotation_in_narrow_tiles(T, H, parts, narrow):
+    """Tiles of 64 tokens in half as many parts of K read R twice as often: not where R is wide and the batch has several."""
+    lib = B.load_library()
+    rule = lib._Z21cq_rotate_split_partsiimPb
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.POINTER(ctypes.c_bool)]
+    got = ctypes.c_bool()
+    assert (rule(T, H, 1 << 32, ctypes.byref(got)), got.value) == (parts, narrow)
+
+
 def test_build_reads_spill_counts_from_the_compiler_remarks():
     """build.py refuses kernels with asynchronous register loads that spill; its reader of hipcc's resource
     remarks is checked on a sample of that output."""

@@ -1545,6 +1545,26 @@ def test_layer_rotation_in_narrow_tiles(B, H, T):
     assert err.max().item() <= 6.7e-7
 
 
+@pytest.mark.parametrize("H,T,sums", [(8192, 128, 8), (8192, 129, 4), (6144, 270, 4), (5120, 384, 4), (5120, 385, 2), (4096, 960, 2),
+                                      (4096, 961, 2)])
+def test_layer_rotation_of_wide_rows(B, H, T, sums):
+    """X_R on either side of the sizes from which tiles of 128 tokens are taken instead of 64.  The bound as above: 2^-24 of a
+    partial sum that grows like the root of the H / 16 / sums products of 16 in each.  (Every expert is selected: a layer's
+    partial sums lie where it keeps the rows of the down product later.)"""
+    import torch
+    rng = np.random.default_rng(H + T)
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], H=H, I=512, T=T, E=4, top_k=4, outlier_channels=())
+    R = torch.from_numpy(rng.standard_normal((H, H)).astype(np.float32)).cuda() / H ** 0.5
+    cb = [B.DeviceCodebook(*_rand_weights(rng, cfg.E, N, K)) for N, K in ((1024, H), (H, 512))]
+    layer = B.DeviceLayer(cfg, R, torch.from_numpy(rng.standard_normal((cfg.E, H)).astype(np.float32)) / H ** 0.5, None, *cb)
+    X = torch.from_numpy((rng.standard_normal((T, H)) * 10.0 ** rng.integers(-3, 4, (T, 1))).astype(np.float32)).cuda()
+    B.cq_moe_forward(layer, X)
+    torch.cuda.synchronize()
+    ref = X.double() @ R.double()
+    err = (B.moe_intermediates(layer, T)["XR"].double() - ref).norm(dim=1) / ref.norm(dim=1)
+    assert err.max().item() <= 2.0 ** -24 * (H / 16 / sums) ** 0.5
+
+
 @pytest.mark.parametrize("H,T,f16", [
     (1280, 256, False), (1792, 300, False), (2304, 256, False), (3840, 100, False),   # K cannot be cut, too few tiles
     (2304, 700, True), (3840, 300, True),                                             # ... and enough of them
