@@ -406,9 +406,10 @@ def test_route_limits(B, T, E, k):
 
 @pytest.mark.parametrize("T,E,k", [
     (64, 65, 3), (50, 128, 8), (7, 128, 64),        # one workgroup: two experts per lane
-    (65, 64, 6), (65, 128, 64), (200, 100, 5),      # top-k over workgroups, then the grouping in one
-    (512, 128, 8),                                  # 4096 assignments: the largest grouping in one workgroup
-    (4097, 8, 1), (2049, 100, 3), (1024, 128, 8), (4096, 4, 2), (2048, 128, 8),   # in several, the last one ragged or full
+    (65, 64, 6), (200, 100, 5), (128, 16, 8),       # top-k over workgroups, then the grouping in one, up to 1024 assignments
+    (1025, 8, 1), (205, 100, 5), (1023, 33, 3),     # in several: one assignment more, and counts that no load of four divides
+    (65, 128, 64), (512, 128, 8),                   # ... 4160 and 4096 assignments
+    (4097, 8, 1), (2049, 100, 3), (1024, 128, 8), (4096, 4, 2), (2048, 128, 8),   # ... the last one ragged or full
     (65535, 3, 1), (65536, 3, 1),                   # the most of them, and the counting sort
     (65535, 1, 1), (4097, 1, 1), (8192, 2, 2),      # all of them to one expert, and to both of two
     (1025, 128, 8), (1367, 33, 6),
@@ -827,6 +828,38 @@ def test_gemm_last_whole_tiles_in_halves(B, groups, extra):
             else:
                 assert torch.equal(got, want.double()), (g, c)
             at += c
+
+
+@pytest.mark.parametrize("prepacked", [True, False])
+@pytest.mark.parametrize("gathered,K,counts", [(True, 2176, [512] * 16 + [515]), (True, 128, [512] * 20), (False, 128, [61] * 36),
+                                               (False, 2048, [64, 17, 1, 33, 64, 48])])
+def test_gemm_tiles_in_halves_gated_f16(B, gathered, K, counts, prepacked):
+    """The form that a layer's gate/up product takes, on launches whose last tiles (whole ones where the rows are gathered from
+    a matrix of unknown length, else half tiles) come in two of 128 weight rows: bf16 codes, row scales, the gated epilogue, f16
+    results, either copy of the indices.  Integer centroids and codes, scales that are powers of two: the gate and the linear
+    part are exact, SiLU is within 1e-5 of its value at these |x| < 70, the result rounds at 2^-11 (2^-25 where it is subnormal)."""
+    import torch
+    rng = np.random.default_rng(K + len(counts))
+    N, G, M = 2048, len(counts), sum(counts)
+    rows = 700 if gathered else M
+    idx = torch.from_numpy(rng.integers(0, 256, (G, N, K // 2), dtype=np.uint8)).cuda()
+    cent = np.tile(np.arange(-8, 8, dtype=np.float32), (G, N, 1))
+    W = B.DeviceCodebook(idx, torch.from_numpy(synth.f32_to_bf16_bits(cent).view(np.int16)), prepack=prepacked)
+    A = torch.from_numpy(rng.integers(-9, 10, (rows, K)).astype(np.float32)).cuda()
+    scale = torch.from_numpy(2.0 ** rng.integers(-12, -8, rows).astype(np.float32)).cuda()
+    gather = torch.from_numpy(rng.integers(0, rows, M).astype(np.int32)).cuda() if gathered else None
+    out = B.cq_codebook_grouped_gemm(W, A.bfloat16(), B.CQ_A_BF16, scale, gather, _dev(_group_offsets(counts)), M,
+                                     B.CQ_EPI_SWIGLU, B.CQ_OUT_F16, use_prepacked=prepacked)
+    at = 0
+    for g, c in enumerate(counts):
+        src = gather[at:at + c].long() if gathered else torch.arange(at, at + c, device="cuda")
+        dense = torch.stack((idx[g] & 15, idx[g] >> 4), dim=-1).view(N, K).float() - 8.0
+        y = (A[src] @ dense.T).double() * scale[src].double()[:, None]   # (fp32: exact)
+        x, u = y[:, 0::2], y[:, 1::2]
+        assert x.abs().max() < 70
+        want = x * torch.sigmoid(x) * u
+        assert ((out[at:at + c].double() - want).abs() <= (2.0 ** -11 + 1e-5) * want.abs() + 2.0 ** -25).all(), (g, c)
+        at += c
 
 
 @pytest.mark.parametrize("N,counts", [(4096, [3072]), (4096, [3071]), (4096, [1000, 1072, 0, 1000]), (256, [400]), (12288, [1030]),
@@ -1707,6 +1740,71 @@ def test_front_of_many_tokens(B, E, k, H, T, bits):
     assert torch.equal(im["ids"], ids[:, :k].int())
     w = torch.softmax(top[:, :k].double(), dim=1)
     assert ((im["w"].double() - w).abs() <= 1e-6).all()
+
+
+@pytest.mark.parametrize("E,k,bits", [(20, 8, 8), (40, 6, 4), (100, 8, 8)])
+def test_front_of_many_tokens_special_rows(B, E, k, bits):
+    """Rows with infinite and NaN entries and experts of equal logits through the two launches: codes and scales are those of
+    the stored X_R (NaN counts as nothing for the maximum, and a quotient that is NaN becomes the lowest code), a NaN logit is
+    never preferred, equal ones go to the lower expert, and the other rows of a tile are as without the special ones."""
+    import torch
+    rng = np.random.default_rng(E)
+    H, T = 512, 600
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], E=E, top_k=k, H=H, I=512, T=T, act_bits=bits, outlier_channels=())
+    R = np.linalg.qr(rng.standard_normal((H, H)))[0].astype(np.float32)
+    R[R == 0] = 1e-3
+    Wr = rng.standard_normal((E, H)).astype(np.float32) / np.float32(H ** 0.5)
+    Wr[0], Wr[2] = R[5], -R[5]            # infinite entries of channel 5 give logits of +Inf and -Inf
+    Wr[3] = Wr[E - 1] = Wr[1]
+    layer = B.DeviceLayer(cfg, R, Wr, None, *[B.DeviceCodebook(*_rand_weights(rng, E, N, K)) for N, K in ((1024, H), (H, 512))])
+    X = rng.standard_normal((T, H)).astype(np.float32)
+    X[7] = 0.0
+    clean = X.copy()
+    X[1, 5], X[40, 9], X[T - 1, 5], X[33, 5], X[33, 6] = np.inf, np.nan, -np.inf, np.inf, -np.inf
+    special = [1, 33, 40, T - 1]
+    clean[special] = 0.0
+
+    def forward(x):
+        B.cq_moe_forward(layer, _dev(x))
+        torch.cuda.synchronize()
+        return {n: v.cpu().numpy().copy() for n, v in B.moe_intermediates(layer, T).items() if n in ("XR", "Q", "scale", "logits", "ids")}
+    got, plain = forward(X), forward(clean)
+    rest = np.setdiff1d(np.arange(T), special)
+    for n in got:
+        assert np.array_equal(got[n][rest], plain[n][rest]), n
+    xr, logits, qmax = got["XR"], got["logits"], np.float32(2 ** (bits - 1) - 1)
+    assert np.isinf(xr[[1, T - 1]]).all() and np.isnan(xr[40]).all()
+    with np.errstate(invalid="ignore"):
+        s = np.fmax.reduce(np.abs(xr), axis=1, initial=np.float32(0)) / qmax
+        s[s == 0] = 1.0
+        q = np.rint(xr / s[:, None])
+    assert np.array_equal(got["scale"], s)
+    assert np.array_equal(got["Q"].astype(np.float32), np.where(np.isnan(q), -qmax, np.clip(q, -qmax, qmax)))
+    assert np.isposinf(logits[[1, T - 1], [0, 2]]).all() and np.isneginf(logits[[1, T - 1], [2, 0]]).all()
+    assert np.isnan(logits[40]).all() and not np.isnan(logits[rest]).any()
+    assert np.array_equal(logits[rest, 3], logits[rest, 1]) and np.array_equal(logits[rest, E - 1], logits[rest, 1])
+    for t in range(T):
+        row = logits[t]
+        want = sorted(range(E), key=lambda e: (True, 0.0) if np.isnan(row[e]) else (False, -row[e]))[:k]
+        assert np.array_equal(got["ids"][t], want), t
+
+
+@pytest.mark.parametrize("over,tiles", [
+    (dict(E=33, top_k=1, H=1024, I=64, T=600), True), (dict(E=8, top_k=2, H=512, I=512, T=1000), True),
+    (dict(E=33, top_k=1, H=1024, I=64, T=1024), False), (dict(E=8, top_k=2, H=512, I=512, T=2048), False)])
+def test_front_of_many_tokens_where_it_finds_room(B, over, tiles):
+    """The two launches keep their partial logits in memory that the call touches anyway; where the rotation's partial sums
+    leave none, the separate launches run, whose logits are those of cq_route_permute to the bit."""
+    import torch
+    cfg = synth.small_variant(synth.CONFIGS["mixtral_decode"], **over)
+    _check_layer(B, cfg, label="front of many tokens")
+    L = Hp.make_inputs(cfg)
+    layer = B.device_layer_from_inputs(L)
+    B.cq_moe_forward(layer, _dev(L.X))
+    torch.cuda.synchronize()
+    im = B.moe_intermediates(layer, cfg.T)
+    separate = B.cq_route_permute(im["XR"].clone(), layer.Wr, layer.bias, cfg.top_k)["logits"]
+    assert torch.equal(im["logits"], separate) is not tiles
 
 
 @pytest.mark.parametrize("over,rows", [
