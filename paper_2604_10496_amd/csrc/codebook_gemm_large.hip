@@ -281,7 +281,7 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   // the group barriers below ask the scheduler for exactly that).
   // The B fragments live in one register set: as soon as the two MFMAs of a token block are issued,
   // its registers take the block's fragment of the next sub-step (a full sub-step of slack).
-  // vector ALU operations per MFMA that the scheduler is asked for: in half tiles two decode8 calls per 2 C MFMAs.  (Whole
+  // vector ALU operations per MFMA that the scheduler is asked for: in half tiles a decode8 call per C MFMAs and row block.  (Whole
   // tiles have no second workgroup on the compute unit whose products could run under the decoding: four per MFMA also
   // where the tile is narrow; block-wise tables, gate/up + down at 96 tokens 350 -> 344 us, at 200 tokens 400 -> 396.)
   constexpr int kValu = !A32 || C >= 8 ? 4 : C == 4 ? 6 : C == 1 ? 21 : 12;
@@ -381,7 +381,7 @@ __device__ __forceinline__ void large_tile(const LargeArgs& p, const int grp_, c
   // neighbouring bytes.
   constexpr int kOutCols = EPI == CQ_EPI_SWIGLU ? kRows / 2 : kRows;
   constexpr int kEsize = OUTK == CQ_OUT_F16 ? 2 : 4;
-  constexpr int kRowBytes = kOutCols * kEsize;                    // 256 .. 1024
+  constexpr int kRowBytes = kOutCols * kEsize;                    // 128 .. 1024
   constexpr int kQuadBytes = (EPI == CQ_EPI_SWIGLU ? 2 : 4) * kEsize;  // what one accumulator quad becomes
   constexpr int kRowStride = kRowBytes + (kQuadBytes == 16 ? 16 : 8);
   constexpr int kPiece = kRowStride % 16 == 0 ? 16 : 8;           // bytes per lane when streaming out

@@ -6,9 +6,10 @@
 // nothing but the rows, the partial logits of 256 columns each and their maxima crosses it.
 // A workgroup of the first launch has 32 tokens x 256 columns, so that the router matrix, which all of them read from L2, is
 // read once per 32 tokens (a workgroup of front_rows.hip per 1 or 2).  fp32 MFMA of 16 tokens x 16 experts; a lane's four k of
-// a 16-byte load go to four MFMAs, the same ones for both operands.  2048 tokens of width 2048, 128 experts: 14.2 + 22.1 + 9.3
-// us in separate launches, 24 + 13 so; the product's share is 7.5 of the 24, the rest loads that wait for one another.
-// (Four wavefronts with 16 columns' loads each in flight and both blocks of experts in turn: 28.7 us.)
+// a 16-byte load go to four MFMAs, the same ones for both operands.  2048 tokens of width 2048, 128 experts, from a rotation in
+// one part: 36.0 us in the three separate launches, 29.9 in these two (on another card 19.2 + 12.2); the product's share is 7.5
+// of the first one, the rest loads that wait for one another.  (With two parts of the rotation to add up, when the first one
+// took 24 us: four wavefronts with 16 columns' loads each in flight and both blocks of experts in turn 28.7.)
 // All sums have a fixed order: parts ascending; a partial logit in the order of the MFMAs (of up to 32 experts: in eighths of
 // the columns, added in pairs); 256-column blocks ascending.
 #include "cq_internal.h"
@@ -250,13 +251,18 @@ void launch_second(const FrontTilesArgs& a, hipStream_t s) {
 }  // namespace
 
 // From 64 tokens on where front_rows.hip does not take the batch: more than 512 tokens, H > 4096 or small router matrices.  us
-// per layer in separate launches / so: Qwen3 shape (128 experts) 600 tokens 190.8 / 181.0, 1024 227.9 / 215.6, 2048 346.5 /
-// 338.3, 4096 582.3 / 581.6; DeepSeek-V2-Lite shape (64 experts) 600 202.3 / 198.2, 2048 442.9 / 434.6, 4096 761.7 / 756.9;
-// 33 experts of width 768 64 tokens 45.5 / 41.2, 1500 98.0 / 92.3; 20 of width 8192 200 tokens 256.3 / 240.0; 8 of width 4096 2048
-// and 4096 tokens equal.  Up to 512 tokens front_rows.hip is as fast or faster: 64 experts of width 2048 200 tokens 150.4 /
+// per layer (I = 512, everything else the same) in separate launches / so: 128 experts of width 2048, 600 tokens 149.0 / 137.7,
+// 1024 179.6 / 167.2, 2048 282.5 / 276.8; 64 of 2048, 600 112.1 / 106.4, 2048 228.4 / 220.4; 33 of 768, 64 50.2 / 46.0, 1500
+// 87.6 / 82.2; 32 of 2048, 600 97.9 / 91.9, 2048 179.3 / 171.5; 32 of 4096, 2048 407.4 / 394.3; 20 of 8192, 200 221.0 / 206.0, 1000
+// 567.1 / 560.2; 16 of 1024, 600 69.7 / 65.8, 4096 153.7 / 152.7; 16 of 4096, 600 178.3 / 176.5, 2048 369.3 / 368.2.  Up to 8 experts,
+// whose separate product is the cheapest: 8 of 1024, 600 67.7 / 64.2, 1024 75.6 / 76.2, 4096 112.2 / 111.1; 8 of 2048, 600
+// 93.1 / 93.3, 1500 120.3 / 118.6, 3000 182.1 / 180.3, 4096 222.0 / 225.4; 8 of 4096, 600 163.0 / 161.2, 1024 196.4 / 195.2, 2048
+// 307.1 / 309.3, 4096 567.3 / 567.8.  From 2^21 values on these are within 1.5 % of each other either way, and come here for the
+// logits' accuracy (below).  Up to 512 tokens front_rows.hip is as fast or faster: 64 experts of width 2048 200 tokens 150.4 /
 // 153.2, 400 tokens 171.7 / 171.2.
 // The logits' error against float64 (2-norm, with that of X_R) is smaller than the separate product's: 3.4e-7 / 3.1e-7 at 600
-// tokens of 64 and 128 experts, 8.2e-7 / 7.1e-7 at 2048 tokens of width 4096, 2.5e-7 / 2.2e-7 at 600 of width 1024.
+// tokens of 64 and 128 experts; 8 experts, 6.5e-7 / 5.2e-7 at 4096 tokens of width 2048, 8.3e-7 / 7.3e-7 at 2048 and 9.1e-7 / 7.2e-7 at
+// 4096 tokens of width 4096; 2.5e-7 / 2.2e-7 at 600 of width 1024.
 bool cq_front_tiles_supported(int T, int H, int E, int top_k) {
   return T >= 64 && H % kColumns == 0 && H <= 32 * kColumns && E <= kMaxE && top_k <= 64;
 }

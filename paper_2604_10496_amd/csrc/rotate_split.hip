@@ -30,7 +30,8 @@ constexpr int kStepK = 64;             // K per pipeline step (four MFMA sub-ste
 constexpr int kStepBytes = kStepK * 2; // one token's share of a step and plane, in LDS and in memory
 constexpr int kDepth = 4;                        // token tiles in LDS
 constexpr int kOutStride = kCols * 4 + 16;       // epilogue staging row (64 tokens at a time)
-constexpr int rot_lds_bytes(int C) {             // hi and lo tile of a step, kDepth of them: 128 KiB, or (C = 2) 65 KiB, what the epilogue takes
+// hi and lo tile of a step, kDepth of them: 128 KiB, or (C = 2) 64 KiB, of which the epilogue takes one more
+constexpr int rot_lds_bytes(int C) {
   const int ring = kDepth * 2 * 32 * C * kStepBytes, out = 64 * kOutStride;
   return ring > out ? ring : out;
 }
